@@ -61,12 +61,12 @@ _lib = None
 
 def load():
     """Loads the built library; raises if it has not been built (no fallback exists)."""
-    global _lib
+    global _lib, _torch
     if _lib is not None:
         return _lib
     # PyTorch ships its own HIP runtime: it must be in the process before libpre3.so is
     # loaded, so that both resolve to the same runtime (two runtimes cannot share the GPU).
-    import torch  # noqa: F401
+    import torch
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: build it with paper_2506_03887_amd.build.build()")
     lib = ctypes.CDLL(LIB_PATH)
@@ -110,26 +110,29 @@ def load():
     for name in EXPORTS:
         if name != "pre3_last_error":
             getattr(lib, name).restype = i32
-    _lib = lib
+    _KINDS.update(i32=(torch.int32,), u16=(torch.bfloat16, torch.uint16, torch.int16), u32=(torch.int32, torch.uint32),
+                  u8=(torch.uint8,))
+    _torch, _lib = torch, lib
     return lib
 
 
+_torch = None          # set by load(), with the dtypes each kind of buffer may have
+_KINDS = {}
+
+
 def _stream_ptr(stream):
+    """Handle of `stream` (a torch stream or a plain handle), by default the current stream of the current device.
+    The handle is asked for directly: building a torch.cuda.Stream object for it took 3.0 of the 13 us of a call."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _dev(t, dtype_name):
     """Device pointer of a contiguous torch tensor of the expected dtype."""
-    import torch
-    want = {"i32": torch.int32, "u16": (torch.bfloat16, torch.uint16, torch.int16), "u32": (torch.int32, torch.uint32),
-            "u8": torch.uint8}[dtype_name]
-    ok = t.dtype in want if isinstance(want, tuple) else t.dtype == want
-    if not (t.is_cuda and ok):
+    if not (t.is_cuda and t.dtype in _KINDS[dtype_name]):
         raise TypeError(f"expected a CUDA tensor of kind {dtype_name}, got {t.dtype} on {t.device}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 class Pre3:
@@ -309,12 +312,12 @@ class Pre3:
         self._bound = (states, data, length, err)          # keep the tensors alive
 
     def fill_mask(self, states, data, length, bitmask, stream=None):
-        assert bitmask.is_contiguous() and tuple(bitmask.shape) == (data.shape[0], self.words)
+        assert bitmask.is_contiguous() and bitmask.shape == (data.shape[0], self.words)
         self._check(self._lib.pre3_fill_mask(self._h, _dev(states, "i32"), self._stacks(data, length),
                                              _dev(bitmask, "u32"), _stream_ptr(stream)))
 
     def fill_apply_mask(self, states, data, length, bitmask, logits, stream=None):
-        assert bitmask.is_contiguous() and tuple(bitmask.shape) == (data.shape[0], self.words)
+        assert bitmask.is_contiguous() and bitmask.shape == (data.shape[0], self.words)
         assert logits.dim() == 2 and logits.stride(1) == 1 and logits.shape[0] == data.shape[0]
         self._check(self._lib.pre3_fill_apply_mask(self._h, _dev(states, "i32"), self._stacks(data, length),
                                                    _dev(bitmask, "u32"), _dev(logits, "u16"), logits.stride(0),
