@@ -283,9 +283,8 @@ int32_t pre3_step_is_one_kernel(const pre3_handle *h, const uint16_t *logits_bf1
  *   chosen; -1 if no token is both allowed and not NaN.
  * This is the arg max of what pre3_apply_mask would leave in the row, but the logits are only
  * read (groups of 8 masked tokens are not even read) and nothing is written back.
- * logits_bf16: device, [batch, row_stride] bf16 bit patterns, row_stride >= n_tokens (16-byte
- * aligned rows take the vector path, any other layout a slower one); bitmask: device, [batch,
- * ceil(n_tokens/32)] as pre3_fill_mask writes it; out_tokens: device [batch], ready to be
+ * logits_bf16: device, [batch, row_stride] bf16 bit patterns, row_stride >= n_tokens (rows may
+ * start at any logit); bitmask: device, [batch, ceil(n_tokens/32)] as pre3_fill_mask writes it; out_tokens: device [batch], ready to be
  * passed to pre3_advance.  batch is that of the bound buffers (pre3_bind_state), which also
  * sized the call's workspace inside the handle: calls on one handle must not overlap.
  * Errors: BADARG (nothing bound, null pointer, row_stride < n_tokens). */

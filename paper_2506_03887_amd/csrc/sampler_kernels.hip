@@ -35,7 +35,7 @@ constexpr int kArgUnroll = 4;
 // the next pass are fetched while the logits of the current one are in flight.
 __global__ __launch_bounds__(kArgBlock) void masked_argmax_kernel(
     const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
-    int n_words, int groups_per_seg, int vec_ok, unsigned long long *__restrict__ partial, int32_t *__restrict__ out) {
+    int n_words, int groups_per_seg, unsigned long long *__restrict__ partial, int32_t *__restrict__ out) {
     __shared__ unsigned long long s_part[kArgBlock / 64 + 1];
     __shared__ uint2 s_expand[16];                      // half a mask byte -> AND masks of two of the group's registers
     const int b = blockIdx.x, seg = blockIdx.y, n_seg = gridDim.y, tid = threadIdx.x;
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kArgBlock) void masked_argmax_kernel(
 #pragma unroll
         for (int u = 0; u < kArgUnroll; ++u) {
             const int g = g0 + u * kArgBlock;
-            if (m[u] != 0u && vec_ok && g * 8 + 8 <= vocab) v[u] = stream_load(lrow + (size_t)g * 8);
+            if (m[u] != 0u && g * 8 + 8 <= vocab) v[u] = stream_load(lrow + (size_t)g * 8);
         }
 #pragma unroll
         for (int u = 0; u < kArgUnroll; ++u) {
@@ -71,9 +71,9 @@ __global__ __launch_bounds__(kArgBlock) void masked_argmax_kernel(
             uint32_t mu = m[u];
             if (mu == 0u) continue;
             const int g = g0 + u * kArgBlock, t0 = g * 8;
-            if (!(vec_ok && t0 + 8 <= vocab)) {        // ragged tail or unaligned rows: one logit at a time
+            if (t0 + 8 > vocab) {                      // ragged tail: one logit at a time
                 uint32_t x[4] = {0u, 0u, 0u, 0u};
-                if (t0 + 8 > vocab) mu &= (1u << (vocab - t0)) - 1u;
+                mu &= (1u << (vocab - t0)) - 1u;
                 for (int k = 0; k < 8 && t0 + k < vocab; ++k) x[k >> 1] |= (uint32_t)lrow[t0 + k] << (16 * (k & 1));
                 v[u] = make_uint4(x[0], x[1], x[2], x[3]);
                 if (mu == 0u) continue;
@@ -247,10 +247,10 @@ constexpr int kTopkPerThread = 32;
 constexpr int kTopkChunk = kTopkPerThread * kTopkBlock;   // tokens per chunk (twice as many for the wide block)
 constexpr int kTopkRegion = 256;
 
-// Eight logits from t0 on, one 2-byte load each (rows that are not 16-byte aligned, and the group
-// that straddles the end of the vocabulary); tokens beyond the vocabulary read as NaN.  A loop that
+// Eight logits from t0 on, one 2-byte load each (the group that straddles the end of the vocabulary);
+// tokens beyond the vocabulary read as NaN.  A loop that
 // is not unrolled: the path is rare and must not cost the kernel registers.
-__device__ __forceinline__ uint4 topk_load_group_unaligned(const uint16_t *__restrict__ lrow, int t0, int vocab) {
+__device__ __forceinline__ uint4 topk_load_last_group(const uint16_t *__restrict__ lrow, int t0, int vocab) {
     unsigned long long lo = 0x7FC07FC07FC07FC0ull, hi = lo;
 #pragma unroll 1
     for (int j = 0; j < 8; ++j) {
@@ -288,7 +288,7 @@ __device__ __noinline__ uint32_t topk_cut_list(unsigned long long *list, int n, 
 template <int kBlock>
 __device__ __forceinline__ void masked_topk_chunked(
     const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
-    int n_words, int vec_ok, int k, int chunks_per_seg, unsigned long long *__restrict__ out,
+    int n_words, int k, int chunks_per_seg, unsigned long long *__restrict__ out,
     int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_vals, int b, int seg, int n_seg) {
     constexpr int kWaves = kBlock / 64, kChunk = kTopkPerThread * kBlock;
     __shared__ unsigned long long s_list[kWaves * kTopkRegion];
@@ -339,7 +339,7 @@ __device__ __forceinline__ void masked_topk_chunked(
     };
     auto load_logits = [&](int chunk, const uint32_t (&m)[kTopkPerThread / 8], uint4 (&v)[kTopkPerThread / 8]) {
         const uint16_t *p = lrow + (size_t)chunk * kChunk + (size_t)tid * 8;
-        if (vec_ok && (chunk + 1) * kChunk <= vocab) {       // a whole chunk of an aligned row
+        if ((chunk + 1) * kChunk <= vocab) {                 // a whole chunk
 #pragma unroll
             for (int g = 0; g < kTopkPerThread / 8; ++g) {
                 v[g] = make_uint4(0u, 0u, 0u, 0u);               // its mask zeroes the keys anyway
@@ -352,8 +352,8 @@ __device__ __forceinline__ void masked_topk_chunked(
             const int t0 = chunk * kChunk + (tid + g * kBlock) * 8;
             v[g] = make_uint4(0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u);   // NaN: no candidate
             if (m[g] != 0u) {
-                if (vec_ok && t0 + 8 <= vocab) v[g] = stream_load(lrow + (size_t)t0);
-                else v[g] = topk_load_group_unaligned(lrow, t0, vocab);
+                if (t0 + 8 <= vocab) v[g] = stream_load(lrow + (size_t)t0);
+                else v[g] = topk_load_last_group(lrow, t0, vocab);
             }
         }
     };
@@ -624,9 +624,9 @@ __device__ __forceinline__ void masked_topk_chunked(
 template <int kBlock>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void masked_topk_kernel(
     const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
-    int n_words, int vec_ok, int k, int chunks_per_seg, unsigned long long *__restrict__ out,
+    int n_words, int k, int chunks_per_seg, unsigned long long *__restrict__ out,
     int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_vals) {
-    masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, vec_ok, k, chunks_per_seg, out, out_ids, out_vals,
+    masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, chunks_per_seg, out, out_ids, out_vals,
                                 blockIdx.x, blockIdx.y, gridDim.y);
 }
 
@@ -638,7 +638,7 @@ __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
 }
 
 // The k best of a whole row by one block of 1,024 threads that keeps the row in registers: rows of at
-// most kTopkRowGroups * 1,024 groups of 8 tokens (131,072 tokens), 16-byte aligned.  Every thread
+// most kTopkRowGroups * 1,024 groups of 8 tokens (131,072 tokens).  Every thread
 // issues the loads of its mask bytes and of its up to 16 groups of logits at once (a group is read
 // whatever its mask byte says: no load waits for another one) and turns them into 64 registers of
 // packed 16-bit keys (0 = masked, NaN or beyond the vocabulary), with the packed maximum of every
@@ -689,7 +689,7 @@ __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(
         const int g = tid + u * kBlock;
         v[u] = make_uint4(0u, 0u, 0u, 0u);
         if (g * 8 + 8 <= vocab) v[u] = stream_load(lrow + (size_t)g * 8);
-        else if (g < groups) v[u] = topk_load_group_unaligned(lrow, g * 8, vocab);   // the group the vocabulary ends in
+        else if (g < groups) v[u] = topk_load_last_group(lrow, g * 8, vocab);   // the group the vocabulary ends in
     }
     lds_barrier();                                            // s_expand, s_rank, s_count
     uint32_t kp[kG * 4], gmax2[kG];
@@ -776,7 +776,7 @@ __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(
     __syncthreads();
     const int n = s_count;
     if (n > kTopkRowList) {                                   // same in every thread
-        masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, 1, k,
+        masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, k,
                                     (vocab + kTopkPerThread * kBlock - 1) / (kTopkPerThread * kBlock), workspace, out_ids, out_vals,
                                     b, 0, 1);
         return;
@@ -910,9 +910,8 @@ hipError_t launch_masked_argmax(const uint16_t *logits, const uint32_t *bitmask,
     const int n_words = (vocab + 31) / 32, groups = (vocab + 7) / 8;
     const int n_seg = masked_argmax_segments(batch, vocab, n_compute_units);
     const int groups_per_seg = (groups + n_seg - 1) / n_seg;
-    const int vec_ok = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && (row_stride % 8 == 0);
     hipLaunchKernelGGL(masked_argmax_kernel, dim3(batch, n_seg), dim3(kArgBlock), 0, stream, logits, bitmask, vocab,
-                       row_stride, n_words, groups_per_seg, vec_ok, workspace, out);
+                       row_stride, n_words, groups_per_seg, workspace, out);
     if (n_seg > 1)
         hipLaunchKernelGGL(masked_argmax_finish_kernel, dim3((batch + kArgFinishRows - 1) / kArgFinishRows),
                            dim3(64 * kArgFinishRows), 0, stream, batch, n_seg, workspace, out);
@@ -947,8 +946,7 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     if (batch == 0) return hipSuccess;
     if (!masked_topk_fits(vocab, k)) return hipErrorInvalidValue;
     const int n_words = (vocab + 31) / 32;
-    const int vec_ok = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && (row_stride % 8 == 0);
-    if (batch >= n_compute_units && vec_ok && (vocab + 7) / 8 <= kTopkRowGroups * kTopkBlockWide) {
+    if (batch >= n_compute_units && (vocab + 7) / 8 <= kTopkRowGroups * kTopkBlockWide) {
         // a block per row that keeps the whole row in registers
         hipLaunchKernelGGL(masked_topk_row_kernel, dim3(batch), dim3(kTopkBlockWide), 0, stream, logits, bitmask, vocab,
                            row_stride, n_words, k, workspace, out_ids, out_vals);
@@ -957,7 +955,7 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     if (batch >= n_compute_units && batch < 2 * n_compute_units) {
         // a row per compute unit and no second block beside it: sixteen waves take the row
         hipLaunchKernelGGL(masked_topk_kernel<kTopkBlockWide>, dim3(batch, 1), dim3(kTopkBlockWide), 0, stream, logits, bitmask,
-                           vocab, row_stride, n_words, vec_ok, k, masked_topk_chunks(vocab, kTopkPerThread * kTopkBlockWide),
+                           vocab, row_stride, n_words, k, masked_topk_chunks(vocab, kTopkPerThread * kTopkBlockWide),
                            workspace, out_ids, out_vals);
         return hipGetLastError();
     }
@@ -965,11 +963,11 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     const int n_seg = (masked_topk_chunks(vocab) + per - 1) / per;
     if (n_seg == 1) {
         hipLaunchKernelGGL(masked_topk_kernel<kTopkBlock>, dim3(batch, 1), dim3(kTopkBlock), 0, stream, logits, bitmask, vocab,
-                           row_stride, n_words, vec_ok, k, per, workspace, out_ids, out_vals);
+                           row_stride, n_words, k, per, workspace, out_ids, out_vals);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(masked_topk_kernel<kTopkBlock>, dim3(batch, n_seg), dim3(kTopkBlock), 0, stream, logits, bitmask, vocab,
-                       row_stride, n_words, vec_ok, k, per, workspace, (int32_t *)nullptr, (uint16_t *)nullptr);
+                       row_stride, n_words, k, per, workspace, (int32_t *)nullptr, (uint16_t *)nullptr);
     hipLaunchKernelGGL(masked_topk_finish_kernel, dim3(batch), dim3(64), 0, stream, workspace, n_seg * k, k, logits, row_stride,
                        out_ids, out_vals);
     return hipGetLastError();

@@ -9,8 +9,12 @@ namespace pre3 {
 // 16-byte accesses marked non-temporal: the logits pass through once, and lines marked this way
 // are the first to leave L2, so the automaton's tables survive the pass for the next kernel.
 typedef unsigned int NativeUint4 __attribute__((ext_vector_type(4)));
+// Loads may start at any logit (rows of an odd vocabulary do): the memory system takes 16-byte loads at any
+// address, and a wave's loads stay one contiguous 1 KiB (8 top-20 steps on 300 x 100,003: 393 us against 948 us
+// with one load per logit; 8 greedy steps on 100 x 100,003: 170 against 254 us).
+typedef NativeUint4 __attribute__((aligned(2))) NativeUint4AtLogit;
 __device__ __forceinline__ uint4 stream_load(const uint16_t *p) {
-    const NativeUint4 x = __builtin_nontemporal_load(reinterpret_cast<const NativeUint4 *>(p));
+    const NativeUint4 x = __builtin_nontemporal_load(reinterpret_cast<const NativeUint4AtLogit *>(p));
     return make_uint4(x.x, x.y, x.z, x.w);
 }
 __device__ __forceinline__ void stream_store(uint4 v, uint16_t *p) {

@@ -36,3 +36,37 @@ def test_masked_rows_at_every_offset(V, pad, offset):
     oracle_apply_mask(want, mask, V)
     assert (view.cpu().numpy().view(np.uint16) == want).all()
     assert (flat[:offset] == 0x2345).all() and (flat[offset + B * stride:] == 0x2345).all()
+
+
+@pytest.mark.parametrize("V,B", [(65, 3), (1003, 70), (40_005, 9), (20_011, 256), (131_071, 257)])
+@pytest.mark.parametrize("pad,offset", [(0, 1), (3, 0), (16, 5)])
+def test_sampled_rows_at_every_offset(V, B, pad, offset):
+    """The greedy choice and the k best of rows that start off a 16-byte boundary: rows split over blocks, one block
+    per row, and the row kept in registers (257 rows), special rows among them."""
+    from test_gpu_argmax import _bound_lib, _special_logits, _special_masks
+    from oracle import masked_argmax, masked_topk
+    from workloads.vocab import Vocab
+    torch, dev = _torch()
+    rng = np.random.default_rng(V + B + pad)
+    lib = _bound_lib(Vocab([bytes([97 + i % 5]) for i in range(V - 1)] + [b""], V - 1), B)
+    stride = V + pad
+    host = np.zeros((B, stride), dtype=np.uint16)
+    host[:, :V] = bf16_logits(rng, B, V)
+    W = (V + 31) // 32
+    mask = rng.integers(0, 2 ** 32, size=(B, W), dtype=np.uint64).astype(np.uint32)
+    head = min(B, 16)
+    special, special_mask = _special_logits(rng, 16, V), _special_masks(rng, 16, V)
+    host[:head, :V], mask[:head] = special[:head], special_mask[:head]
+    mask[:, -1] &= np.uint32(0xFFFFFFFF >> (W * 32 - V))
+    flat = torch.zeros(B * stride + offset + 16, dtype=torch.int16, device=dev)
+    view = flat[offset: offset + B * stride].view(B, stride)
+    view.copy_(torch.from_numpy(host.view(np.int16)).to(dev))
+    logits, mask_d = view.view(torch.bfloat16), torch.from_numpy(mask.view(np.int32)).to(dev)
+    tok = torch.empty(B, dtype=torch.int32, device=dev)
+    lib.apply_mask_argmax(logits, mask_d, tok)
+    assert tok.cpu().numpy().tolist() == masked_argmax(host, mask, V).tolist()
+    for k in (1, 33, 64):
+        ids, vals = torch.empty((B, k), dtype=torch.int32, device=dev), torch.empty((B, k), dtype=torch.int16, device=dev)
+        lib.apply_mask_topk(logits, mask_d, ids, vals)
+        want_ids, want_vals = masked_topk(host, mask, V, k)
+        assert (ids.cpu().numpy() == want_ids).all() and (vals.cpu().numpy().view(np.uint16) == want_vals).all(), k
