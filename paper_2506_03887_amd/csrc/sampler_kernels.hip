@@ -637,102 +637,177 @@ __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
     return (folded & 0x8000u) ? (int)(folded & 0x7FFFu) : (int)((0x10000u - folded) & 0xFFFFu);
 }
 
-// The k best of a whole row by one block of 1,024 threads that keeps the row in registers: rows of at
-// most kTopkRowGroups * 1,024 groups of 8 tokens (131,072 tokens).  Every thread
-// issues the loads of its mask bytes and of its up to 16 groups of logits at once (a group is read
-// whatever its mask byte says: no load waits for another one) and turns them into 64 registers of
-// packed 16-bit keys (0 = masked, NaN or beyond the vocabulary), with the packed maximum of every
-// group and the thread's maximum.  What follows the stream is short:
-//   (1) a lower bound M of the k-th largest key: every wave takes the q-th largest of its 64 thread
-//       maxima (q = ceil(k / 16); a wave with fewer holders its smallest); if these quotas add up to
-//       k, at least k keys reach the smallest of the waves' values (one barrier);
-//   (2) the few threads whose maximum reaches M look through the groups whose maximum does and
-//       append those keys, as words, to one list in LDS;
-//   (3) the list (little more than k words) is ranked by all threads together -- a word's rank is the
-//       number of larger words, counted in slices by several threads and added up in LDS -- and the
-//       k best write their id and pattern (rebuilt from the key, read back only for a zero) in order.
-// A list that would pass kTopkRowList words (thousands of ties with the bound, or quotas that do not
-// add up to k on a dense row) is given up: the block then takes the row chunk by chunk with
-// masked_topk_chunked, which has no such limit.
-// (Measured and dropped: taking the bound from half of the row while the other half is still in
+// The k best of a whole row by one block of 1,024 threads that keeps the row in registers: rows of 8 to
+// kTopkRowGroups * 1,024 * 8 tokens (131,072).  The mask row goes to LDS with a few loads per thread, and every
+// thread loads its 16 groups of logits, kAhead of them in flight, whatever their mask bytes say and without a branch
+// (groups beyond the row's end load the last one), and works on a group as it arrives.  The block is then bound by what
+// its sixteen waves do after the stream, so what is done to every token is two packed instructions under the stream: its half is
+// set to 0xFFFF if it is masked, and the maximum of the patterns as signed 16-bit numbers is taken.  For
+// patterns above zero that order is the order of the values, and the k best of most rows are such.  Then
+//   (1) a lower bound M of the k-th largest value: the k-th largest of the 128 maxima of eight threads each, ranked
+//       by all threads together between two barriers: 64 of 128,256 random values reach the bound for k = 50;
+//   (2) the few groups whose maximum reaches M are copied to a list in LDS (one atomic per wave), and behind a barrier
+//       eight threads per listed group pick the tokens that reach M out of it, as words;
+//   (3) the words (little more than k) are ranked by all threads together -- a word's rank is the
+//       number of larger words -- and the k best write their id and pattern (rebuilt from the key, read back only
+//       for a zero) in order.
+// A row where fewer than k of the 128 hold a value (few tokens allowed, or few above zero) or an allowed NaN of
+// positive sign takes the maxima and (1) again on the keys of bf16_key (0xFFFF, the pattern of a negative NaN, becomes
+// 0 = no candidate) of the groups that have an allowed token; the registers keep the patterns.
+// Lists that would run full (hundreds of ties with the bound, or a dense row where the threads' maxima do not
+// say enough) are given up: the block then takes the row chunk by chunk with masked_topk_chunked, which has no
+// such limit.
+// (15.3 us per launch at 256 x 128,256, k = 50, 4.6 TB/s: 9.4 us until the row has arrived and is worked on, 0.8 for
+// the bound, 1.4 for the list, 0.7 for the ranks.  24.9 us before, with keys computed for every token, all sixteen
+// loads issued first -- behind branches, so that nothing was worked on before the last had arrived: a wave that wants
+// to issue its sixteenth load waits for it until 8 us --, a bound from quotas per wave (147 words listed) and one
+// returning atomic per listed token.  Copying all sixteen groups of a thread to the list without a branch per group
+// costs 1 us more: a 16-byte LDS store takes its time whatever the number of lanes.
+// Measured and dropped: taking the bound from half of the row while the other half is still in
 // flight, with the second half filtered as it arrives -- the waves of a block finish their halves
 // microseconds apart, so the barrier gains nothing, and the looser bound doubles the list.)
+__device__ __forceinline__ uint32_t packed_max_i16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(PackedI16, a), __builtin_bit_cast(PackedI16, b)));
+}
+// The row chunk by chunk, as a call (its registers stay apart from the row kernel's).
+__device__ __noinline__ void topk_row_in_chunks(const uint16_t *logits, const uint32_t *bitmask, int vocab, int64_t row_stride,
+                                                int n_words, int k, unsigned long long *workspace, int32_t *out_ids,
+                                                uint16_t *out_vals, int b) {
+    masked_topk_chunked<kTopkBlockWide>(logits, bitmask, vocab, row_stride, n_words, k,
+                                        (vocab + kTopkPerThread * kTopkBlockWide - 1) / (kTopkPerThread * kTopkBlockWide),
+                                        workspace, out_ids, out_vals, b, 0, 1);
+}
 constexpr int kTopkRowGroups = 16;
-constexpr int kTopkRowList = 512;
+constexpr int kAhead = 8;                          // groups a thread has in flight
+constexpr int kTopkRowList = 512, kTopkRowGroupList = 256;
 __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(4))) void masked_topk_row_kernel(
     const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
     int n_words, int k, unsigned long long *__restrict__ workspace, int32_t *__restrict__ out_ids,
     uint16_t *__restrict__ out_vals) {
     constexpr int kBlock = kTopkBlockWide, kWaves = kBlock / 64, kG = kTopkRowGroups;
+    static_assert(kWaves * 8 == 128 && kTopkMax <= 128, "step (1) ranks 128 maxima");
+    __shared__ uint32_t s_mask[kBlock * kG / 4];              // the mask row, for every wave the bytes of its groups
     __shared__ uint2 s_expand[16];                            // half a mask byte -> AND masks of two of the group's registers
+    __shared__ __align__(16) uint32_t s_pub[2][kBlock / 8];
+    __shared__ uint32_t s_first[2], s_kth[2];
+    __shared__ uint4 s_group[kTopkRowGroupList];
+    __shared__ int s_group_at[kTopkRowGroupList];
     __shared__ unsigned long long s_cand[kTopkRowList];
     __shared__ int s_rank[kTopkRowList];
-    __shared__ int s_nz[kWaves];
-    __shared__ uint32_t s_wbound[kWaves];
-    __shared__ int s_count;
+    __shared__ int s_count, s_groups;
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const unsigned long long lanes_below = (1ull << lane) - 1ull;
+    const uint32_t *mrow = bitmask + (size_t)b * n_words;
+    const uint16_t *lrow = logits + (size_t)b * row_stride;
+    const int whole = vocab >> 3;
+    const uint32_t last_group = (uint32_t)(whole - 1) * 16u;
+    // the mask words of the wave's own groups: its 64 groups of round u are the words u * 256 + wave * 16 + (0 .. 15)
+    uint32_t mw[kG / 4];
+    auto mask_word = [&](int i) { return (i * 4 + (lane >> 4)) * (kBlock / 4) + wave * 16 + (lane & 15); };
+#pragma unroll
+    for (int i = 0; i < kG / 4; ++i) mw[i] = mrow[min(mask_word(i), n_words - 1)];
+    uint4 v[kG];
+    auto load_group = [&](int u) { v[u] = stream_load_at(lrow, min((uint32_t)tid * 16u + (uint32_t)(u * kBlock * 16), last_group)); };
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) load_group(u);
     mask_nibble_table_init(s_expand, tid);
     if (tid < kTopkRowList) s_rank[tid] = 0;                  // (the list has fewer entries than the block has threads)
-    if (tid == 0) s_count = 0;
-    const uint8_t *mrow = reinterpret_cast<const uint8_t *>(bitmask + (size_t)b * n_words);
-    const uint16_t *lrow = logits + (size_t)b * row_stride;
-    const int groups = (vocab + 7) >> 3, n_mask_bytes = n_words * 4;
-    uint32_t m[kG];
-    uint4 v[kG];
+    if (tid == 0) { s_count = 0; s_groups = 0; }
+    lds_barrier();                                            // s_expand and what starts at zero (the loads are on their way)
+#pragma unroll
+    for (int i = 0; i < kG / 4; ++i) {
+        const int w = mask_word(i);
+        // bits of groups that are not whole count as masked: their tokens are taken one by one below
+        uint32_t x = w * 4 + 4 <= whole ? mw[i] : 0u;
+        if (w * 4 < whole && w * 4 + 4 > whole) x = mw[i] & ((1u << ((whole & 3) * 8)) - 1u);
+        s_mask[wave * (kG * 16) + i * 64 + lane] = x;
+    }
+    __builtin_amdgcn_wave_barrier();                          // (written and read by the same wave)
+    const uint8_t *mask_bytes = reinterpret_cast<const uint8_t *>(s_mask) + wave * (kG * 64);
+    uint32_t kp[kG * 4], mu[kG];
+    int gmax[kG], best_i = 0;                                 // the largest pattern of a group, of the thread (as signed numbers)
+#pragma unroll
+    for (int u = 0; u < kG; ++u) mu[u] = mask_bytes[u * 64 + lane];
 #pragma unroll
     for (int u = 0; u < kG; ++u) {
-        const int g = tid + u * kBlock;
-        m[u] = (g < groups && g < n_mask_bytes) ? mrow[g] : 0u;
+        if (u + kAhead < kG) load_group(u + kAhead);
+        __builtin_amdgcn_sched_barrier(0);
+        const uint4 allow = expand_mask_byte(s_expand, mu[u]);
+        kp[u * 4] = v[u].x | ~allow.x;
+        kp[u * 4 + 1] = v[u].y | ~allow.y;
+        kp[u * 4 + 2] = v[u].z | ~allow.z;
+        kp[u * 4 + 3] = v[u].w | ~allow.w;
+        const uint32_t top2 = packed_max_i16(packed_max_i16(kp[u * 4], kp[u * 4 + 1]), packed_max_i16(kp[u * 4 + 2], kp[u * 4 + 3]));
+        gmax[u] = max((int)(int16_t)(top2 & 0xFFFFu), (int)top2 >> 16);
+        best_i = max(best_i, gmax[u]);
+        // (worked on here, as it arrives: the compiler would otherwise read the table for all groups first, which does
+        // not fit the registers, and do the rest behind the barrier below)
+        asm volatile("" : "+v"(kp[u * 4]), "+v"(kp[u * 4 + 1]), "+v"(kp[u * 4 + 2]), "+v"(kp[u * 4 + 3]), "+v"(gmax[u]), "+v"(best_i));
     }
+    // the tokens behind the last whole group, one thread each
+    uint32_t tail = 0xFFFFu;
+    const int tail_t = whole * 8 + tid;
+    if (tail_t < vocab && ((mrow[tail_t >> 5] >> (tail_t & 31)) & 1u)) tail = lrow[tail_t];
+    // (1) the bound
+    bool nan = false;
+    uint32_t bound = 0u, kth = 0u;
+    auto find_bound = [&](int round, uint32_t best) {
+        uint32_t top = best;                                  // of eight lanes
+        top = max(top, (uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0xB1, 0xF, 0xF, true));    // lane ^ 1
+        top = max(top, (uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0x4E, 0xF, 0xF, true));    // lane ^ 2
+        top = max(top, (uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0x141, 0xF, 0xF, true));   // the other four of eight
+        if ((lane & 7) == 0) s_pub[round][tid >> 3] = top << 7 | (uint32_t)(127 - (tid >> 3));   // distinct
+        lds_barrier();
+        // eight lanes rank one of the 128: each counts the larger ones among sixteen
+        const uint32_t mine = s_pub[round][tid >> 3];
+        int larger = 0;
 #pragma unroll
-    for (int u = 0; u < kG; ++u) {
-        const int g = tid + u * kBlock;
-        v[u] = make_uint4(0u, 0u, 0u, 0u);
-        if (g * 8 + 8 <= vocab) v[u] = stream_load(lrow + (size_t)g * 8);
-        else if (g < groups) v[u] = topk_load_last_group(lrow, g * 8, vocab);   // the group the vocabulary ends in
-    }
-    lds_barrier();                                            // s_expand, s_rank, s_count
-    uint32_t kp[kG * 4], gmax2[kG];
-    uint32_t best2 = 0u;
-#pragma unroll
-    for (int u = 0; u < kG; ++u) {
-        const uint4 allow = expand_mask_byte(s_expand, m[u]);
-        const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w}, a[4] = {allow.x, allow.y, allow.z, allow.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) kp[u * 4 + j] = bf16_key_pair(x[j]) & a[j];
-        gmax2[u] = packed_max_u16(packed_max_u16(kp[u * 4], kp[u * 4 + 1]), packed_max_u16(kp[u * 4 + 2], kp[u * 4 + 3]));
-        best2 = packed_max_u16(best2, gmax2[u]);
-    }
-    if ((best2 & 0xFFFFu) > kTopkKeyMax || (best2 >> 16) > kTopkKeyMax) {          // an allowed NaN: its key goes
-        best2 = 0u;
+        for (int i = 0; i < 4; ++i) {
+            const uint4 x = reinterpret_cast<const uint4 *>(s_pub[round])[(lane & 7) * 4 + i];
+            larger += (x.x > mine ? 1 : 0) + (x.y > mine ? 1 : 0) + (x.z > mine ? 1 : 0) + (x.w > mine ? 1 : 0);
+        }
+        larger += __builtin_amdgcn_mov_dpp(larger, 0xB1, 0xF, 0xF, true);
+        larger += __builtin_amdgcn_mov_dpp(larger, 0x4E, 0xF, 0xF, true);
+        larger += __builtin_amdgcn_mov_dpp(larger, 0x141, 0xF, 0xF, true);
+        if ((lane & 7) == 0) {
+            if (larger == 0) s_first[round] = mine >> 7;
+            if (larger == k - 1) s_kth[round] = mine >> 7;
+        }
+        lds_barrier();
+        nan = s_first[round] > 0x7F80u;
+        kth = s_kth[round];
+        bound = kth != 0u ? kth : s_first[round] != 0u ? 1u : 0u;      // fewer than k: every candidate
+    };
+    uint32_t best = (uint32_t)max(best_i, (int)(int16_t)tail);
+    find_bound(0, best);
+    const bool positive = !nan && kth != 0u;                  // the same in every thread
+    if (!positive) {
+        const bool drop_nan = nan;
+        best = 0u;
 #pragma unroll
         for (int u = 0; u < kG; ++u) {
+            const bool empty = (kp[u * 4] & kp[u * 4 + 1] & kp[u * 4 + 2] & kp[u * 4 + 3]) == 0xFFFFFFFFu;
+            gmax[u] = 0;
+            if (!__any(!empty)) continue;
+            uint32_t top2 = 0u;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t lo = kp[u * 4 + j] & 0xFFFFu, hi = kp[u * 4 + j] >> 16;
-                kp[u * 4 + j] = (lo > kTopkKeyMax ? 0u : lo) | ((hi > kTopkKeyMax ? 0u : hi) << 16);
+                uint32_t key = bf16_key_pair(kp[u * 4 + j]);
+                if (drop_nan) {                               // a positive NaN's key goes
+                    const uint32_t lo = key & 0xFFFFu, hi = key >> 16;
+                    key = (lo > kTopkKeyMax ? 0u : lo) | ((hi > kTopkKeyMax ? 0u : hi) << 16);
+                }
+                top2 = packed_max_u16(top2, key);
             }
-            gmax2[u] = packed_max_u16(packed_max_u16(kp[u * 4], kp[u * 4 + 1]), packed_max_u16(kp[u * 4 + 2], kp[u * 4 + 3]));
-            best2 = packed_max_u16(best2, gmax2[u]);
+            gmax[u] = (int)max(top2 & 0xFFFFu, top2 >> 16);
+            best = max(best, (uint32_t)gmax[u]);
         }
-    }
-    const uint32_t best = (best2 & 0xFFFFu) > (best2 >> 16) ? (best2 & 0xFFFFu) : (best2 >> 16);
-    // (1) the bound
-    const int quota = (k + kWaves - 1) / kWaves;
-    const int nz_wave = __popcll(__ballot(best != 0u));
-    uint32_t wave_m = 0x10000u;                                // no candidate in this wave
-    if (nz_wave > 0) {
-        int reached;
-        wave_m = wave_key_threshold<1>([&](int) { return best; }, nz_wave, nz_wave < quota ? nz_wave : quota, &reached);
-    }
-    if (lane == 0) { s_nz[wave] = nz_wave; s_wbound[wave] = wave_m; }
-    lds_barrier();
-    uint32_t bound = 0x10000u;
-    int reach_bound = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        bound = s_wbound[w] < bound ? s_wbound[w] : bound;
-        reach_bound += s_nz[w] < quota ? s_nz[w] : quota;
+        tail = bf16_key(tail);
+        if (tail > kTopkKeyMax) tail = 0u;
+        best = max(best, tail);
+        find_bound(1, best);
+    } else {
+        if ((int)(int16_t)tail < 0) tail = 0u;
     }
     auto emit = [&](int rank, unsigned long long word) {
         if (word != 0ull) {
@@ -747,43 +822,81 @@ __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(
             if (out_vals) out_vals[(size_t)b * k + rank] = 0xFF80u;
         }
     };
-    if (bound == 0x10000u) {                                  // nothing is allowed (or only NaN)
+    if (bound == 0u) {                                        // nothing is allowed (or only NaN)
         if (tid < k) emit(tid, 0ull);
         return;
     }
-    if (reach_bound < k) bound = 1u;                          // the quotas do not add up: every candidate
-    // (2) the list
+    // (2) the groups that hold a value of at least `bound`, then the tokens
+    const uint32_t to_key = positive ? bf16_key(0u) : 0u;     // a positive pattern's key is the pattern plus that of zero
     if (__any(best >= bound)) {
-        const uint32_t below = (bound - 1u) * 0x10001u;
+        unsigned long long reach[kG];
+        int total = 0;
 #pragma unroll
         for (int u = 0; u < kG; ++u) {
-            if (packed_sub_sat_u16(gmax2[u], below) == 0u) continue;
+            reach[u] = __ballot(gmax[u] >= (int)bound);
+            total += __popcll(reach[u]);
+        }
+        int slot0 = 0;
+        if (lane == 0) slot0 = atomicAdd(&s_groups, total);
+        slot0 = __builtin_amdgcn_readfirstlane(slot0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t reach = packed_sub_sat_u16(kp[u * 4 + j], below);
-                const uint32_t t0 = (uint32_t)(tid + u * kBlock) * 8u + (uint32_t)j * 2u;
-                if (reach & 0xFFFFu) {
-                    const int slot = atomicAdd(&s_count, 1);
-                    if (slot < kTopkRowList) s_cand[slot] = topk_word(kp[u * 4 + j] & 0xFFFFu, t0);
-                }
-                if (reach >> 16) {
-                    const int slot = atomicAdd(&s_count, 1);
-                    if (slot < kTopkRowList) s_cand[slot] = topk_word(kp[u * 4 + j] >> 16, t0 + 1u);
-                }
+        for (int u = 0; u < kG; ++u) {
+            if (reach[u] == 0ull) continue;
+            const int slot = slot0 + __popcll(reach[u] & lanes_below);
+            if (gmax[u] >= (int)bound && slot < kTopkRowGroupList) {
+                s_group[slot] = make_uint4(kp[u * 4], kp[u * 4 + 1], kp[u * 4 + 2], kp[u * 4 + 3]);
+                s_group_at[slot] = tid + u * kBlock;
             }
+            slot0 += __popcll(reach[u]);
+        }
+        if (tail >= bound) {                                  // at most seven tokens, all in the first wave
+            const int slot = atomicAdd(&s_count, 1);
+            s_cand[slot] = topk_word(tail + to_key, (uint32_t)tail_t);
         }
     }
-    __syncthreads();
+    lds_barrier();
+    const int n_groups = s_groups;                            // the same in every thread
+    if (n_groups <= kTopkRowGroupList) {
+        const uint16_t *halves = reinterpret_cast<const uint16_t *>(s_group);
+        for (int at0 = wave * 64; at0 < n_groups * 8; at0 += kBlock) {
+            const int at = at0 + lane;
+            uint32_t x = at < n_groups * 8 ? halves[at] : 0xFFFFu;
+            if (positive) {
+                if (x & 0x8000u) x = 0u;
+            } else {
+                x = bf16_key(x);
+                if (x > kTopkKeyMax) x = 0u;                  // a positive NaN
+            }
+            const bool take = x >= bound;
+            const unsigned long long mm = __ballot(take);
+            if (mm == 0ull) continue;
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&s_count, __popcll(mm));
+            const int slot = __builtin_amdgcn_readfirstlane(base) + __popcll(mm & lanes_below);
+            if (take && slot < kTopkRowList) s_cand[slot] = topk_word(x + to_key, (uint32_t)(s_group_at[at >> 3] * 8 + (at & 7)));
+        }
+    }
+    lds_barrier();
     const int n = s_count;
-    if (n > kTopkRowList) {                                   // same in every thread
-        masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, k,
-                                    (vocab + kTopkPerThread * kBlock - 1) / (kTopkPerThread * kBlock), workspace, out_ids, out_vals,
-                                    b, 0, 1);
+    if (n > kTopkRowList || n_groups > kTopkRowGroupList) {   // same in every thread
+        topk_row_in_chunks(logits, bitmask, vocab, row_stride, n_words, k, workspace, out_ids, out_vals, b);
         return;
     }
-    // (3) ranks: thread (slice, word) counts the larger words of its slice of the list
+    // (3) ranks: up to 128 words, as usual, are ranked by eight lanes each, which count the larger ones in turn
     if (tid >= n && tid < k) emit(tid, 0ull);
-    if (n == 0) return;
+    if (n <= kBlock / 8) {
+        const int at = tid >> 3;
+        const unsigned long long mine = at < n ? s_cand[at] : ~0ull;
+        int larger = 0;
+#pragma unroll 4
+        for (int j = tid & 7; j < n; j += 8) larger += s_cand[j] > mine ? 1 : 0;
+        larger += __builtin_amdgcn_mov_dpp(larger, 0xB1, 0xF, 0xF, true);
+        larger += __builtin_amdgcn_mov_dpp(larger, 0x4E, 0xF, 0xF, true);
+        larger += __builtin_amdgcn_mov_dpp(larger, 0x141, 0xF, 0xF, true);
+        if ((tid & 7) == 0 && at < n && larger < k) emit(larger, mine);
+        return;
+    }
+    // more: thread (slice, word) counts the larger words of its slice of the list
     const int slices = kBlock / n > 0 ? kBlock / n : 1, per = (n + slices - 1) / slices;
     const int word_at = tid % n, slice = tid / n;
     if (slice < slices) {
@@ -946,7 +1059,7 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     if (batch == 0) return hipSuccess;
     if (!masked_topk_fits(vocab, k)) return hipErrorInvalidValue;
     const int n_words = (vocab + 31) / 32;
-    if (batch >= n_compute_units && (vocab + 7) / 8 <= kTopkRowGroups * kTopkBlockWide) {
+    if (batch >= n_compute_units && vocab >= 8 && vocab / 8 <= kTopkRowGroups * kTopkBlockWide) {
         // a block per row that keeps the whole row in registers
         hipLaunchKernelGGL(masked_topk_row_kernel, dim3(batch), dim3(kTopkBlockWide), 0, stream, logits, bitmask, vocab,
                            row_stride, n_words, k, workspace, out_ids, out_vals);

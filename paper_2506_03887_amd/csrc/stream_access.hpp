@@ -17,6 +17,10 @@ __device__ __forceinline__ uint4 stream_load(const uint16_t *p) {
     const NativeUint4 x = __builtin_nontemporal_load(reinterpret_cast<const NativeUint4AtLogit *>(p));
     return make_uint4(x.x, x.y, x.z, x.w);
 }
+// The same at a wave-uniform row plus a 32-bit byte offset per lane (no 64-bit address register per load).
+__device__ __forceinline__ uint4 stream_load_at(const uint16_t *row, uint32_t byte_offset) {
+    return stream_load(reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(row) + byte_offset));
+}
 __device__ __forceinline__ void stream_store(uint4 v, uint16_t *p) {
     const NativeUint4 x = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(x, reinterpret_cast<NativeUint4 *>(p));

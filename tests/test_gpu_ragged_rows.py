@@ -70,3 +70,42 @@ def test_sampled_rows_at_every_offset(V, B, pad, offset):
         lib.apply_mask_topk(logits, mask_d, ids, vals)
         want_ids, want_vals = masked_topk(host, mask, V, k)
         assert (ids.cpu().numpy() == want_ids).all() and (vals.cpu().numpy().view(np.uint16) == want_vals).all(), k
+
+
+@pytest.mark.parametrize("V", [8, 9, 15, 64, 8191, 8192, 8205, 65_535, 131_072])
+def test_topk_of_rows_kept_in_registers(V):
+    """256 rows (a block per row): rows with values of one sign only, few allowed tokens, hundreds of ties (the lists
+    of the kernel run full), zeros of both signs, infinities, allowed NaN of both signs, and nothing allowed."""
+    from test_gpu_argmax import _bound_lib
+    from oracle import masked_topk
+    from workloads.vocab import Vocab
+    torch, dev = _torch()
+    rng = np.random.default_rng(V)
+    B, W = 256, (V + 31) // 32
+    lib = _bound_lib(Vocab([bytes([97 + i % 5]) for i in range(V - 1)] + [b""], V - 1), B)
+    host = bf16_logits(rng, B, V)
+    mask = rng.integers(0, 2 ** 32, size=(B, W), dtype=np.uint64).astype(np.uint32)
+    host[1::16] |= 0x8000                                                   # below zero only
+    host[2::16] = rng.choice([0x3F80, 0xBF80, 0x0000, 0x8000], size=host[2::16].shape)
+    host[3::16, ::3] = 0x7FC1                                               # NaN of both signs, -inf, +inf
+    host[3::16, 1::7] = 0xFFC1
+    host[4::16, ::2] = 0xFF80
+    host[5::16, 1::9] = 0x7F80
+    host[6::16] = 0x3F80                                                    # one value everywhere
+    for step, rows in ((2, slice(7, None, 16)), (8, slice(8, None, 16)), (12, slice(9, None, 16))):
+        for _ in range(step):                                               # 1 in 4, in 256, in 4,096 of the tokens
+            mask[rows] &= rng.integers(0, 2 ** 32, size=mask[rows].shape, dtype=np.uint64).astype(np.uint32)
+    mask[10::16], mask[11::16] = 0, 0xFFFFFFFF
+    mask[12::16] = 0
+    mask[12::16, 0], mask[12::16, -1] = 0x00000101, 1 << ((V - 1) & 31)     # first tokens and the last
+    mask[13::16] = 0
+    mask[13::16, : max(1, W // 100)] = 0xFFFFFFFF                           # one run of ids
+    host[14::16, : V // 2] |= 0x8000
+    mask[:, -1] &= np.uint32(0xFFFFFFFF >> (W * 32 - V))
+    logits, mask_d = torch.from_numpy(host.view(np.int16)).to(dev).view(torch.bfloat16), torch.from_numpy(mask.view(np.int32)).to(dev)
+    for k in (1, 17, 64):
+        ids, vals = torch.empty((B, k), dtype=torch.int32, device=dev), torch.empty((B, k), dtype=torch.int16, device=dev)
+        lib.apply_mask_topk(logits, mask_d, ids, vals)
+        want_ids, want_vals = masked_topk(host, mask, V, k)
+        bad = np.argwhere((ids.cpu().numpy() != want_ids) | (vals.cpu().numpy().view(np.uint16) != want_vals))
+        assert len(bad) == 0, (k, bad[:4].tolist())
