@@ -249,6 +249,9 @@ int pre3_advance_fill_mask(pre3_handle *h, const int32_t *tokens, uint32_t *bitm
  * be read (JSON, 512 x 128,256: 47.2 against 51.6 us) and loses where they are sparse (a fixed
  * schema, 512 x 152,064: 55.4 against 53.7 us), since it fetches a row before its mask is known
  * and pre3_apply_mask does not read what is masked as a whole.
+ * A batch whose rows, in blocks of 8,192 tokens, fill the GPU at most four blocks to a compute unit (64
+ * sequences of 128,256 tokens on 256 units) is neither: it runs as one launch in which every row is
+ * spread over its blocks, whatever the layout of the logits, unless PRE3_STEP_ONE_KERNEL is given.
  * flags: PRE3_ADVANCE_RESTART_ON_EOS as for pre3_advance_fill_mask, PRE3_STEP_ONE_KERNEL.
  * Errors: BADARG (nothing bound, null pointer, unknown flag, row_stride < n_tokens, logits not
  * 2-byte aligned), HIP. */
@@ -264,7 +267,9 @@ int pre3_advance_fill_apply_mask(pre3_handle *h, const int32_t *tokens, uint32_t
  * The call takes its one-kernel form -- the logits are fetched while the token is walked and the
  * arg max is taken from the registers that hold them -- under the conditions and for the batch
  * sizes of pre3_advance_fill_apply_mask, except that the vocabulary may have at most 153,600 tokens
- * (the fold needs registers of its own), and is the two calls otherwise; flags as there.
+ * (the fold needs registers of its own), spreads the rows of the smaller batches over blocks as there
+ * (up to half a row per compute unit where the one kernel could serve the logits), and is the two
+ * calls otherwise; flags as there.
  * Errors: BADARG (nothing bound, null pointer, unknown flag, row_stride < n_tokens, logits not
  * 2-byte aligned), HIP. */
 int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bitmask, const uint16_t *logits_bf16,
@@ -272,7 +277,8 @@ int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bi
 
 /* Which form pre3_advance_fill_apply_mask takes for the bound batch and these logits: 0 = the two
  * calls, n >= 1 = the one kernel, launched n times on equal shares of the batch (n = 1 up to one
- * sequence per compute unit); BADARG if nothing is bound.  pre3_advance_fill_argmax takes the same
+ * sequence per compute unit); a small batch that is spread over blocks (one launch) answers as if it
+ * were not; BADARG if nothing is bound.  pre3_advance_fill_argmax takes the same
  * form for vocabularies of at most 153,600 tokens.  Host call, launches nothing. */
 int32_t pre3_step_is_one_kernel(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride, int32_t flags);
 

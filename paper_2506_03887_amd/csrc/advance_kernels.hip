@@ -395,27 +395,28 @@ __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
     if (d > 0) commit_overlay(row, priv, s_base[wave], d, lane);
 }
 
+// What an advance leaves to be stored: the new stack is  row[0 .. base) ++ priv[0 .. d)  (or, compacted, the first
+// nl entries staged in LDS, of which those from `from` on changed).
+struct Advanced {
+    int base, d, nl, from, n, token, out_err, out_state;
+};
+
 // The work of the wave that advances one sequence (all 64 lanes with identical values): walks the
-// sampled token (or applies its stack-effect record), commits the new stack, stages the new top of
+// sampled token (or applies its stack-effect record), stages the new top of
 // the stack in s_new and descends the condition tree of the token-level edges with it; the result is
-// `plan`.  kCompact: the new stack is put together at after_row (LDS, cap entries), folded and only
-// then written back and looked up; stage_cycles: the block's other waves copy the cycle tables to
+// `plan`.  Nothing is stored: commit_advance does that.  kCompact: the new stack is put together at after_row (LDS, cap
+// entries), folded and only then looked up; stage_cycles: the block's other waves copy the cycle tables to
 // after_row + cap meanwhile and meet this wave at one block barrier.
 template <bool kCompact, bool kScalar = false>
-__device__ __forceinline__ void advance_and_plan(const DevTables &T, const DevTokenEdges &E, const int32_t *__restrict__ tokens,
-                                                 int32_t *__restrict__ states, int32_t *row, int32_t *__restrict__ len,
-                                                 int cap, int batch, int32_t *__restrict__ err, int restart_on_eos,
-                                                 int32_t *adv_scratch, const int32_t *cycle_head, const int32_t *cycle_pool,
+__device__ __forceinline__ Advanced advance_and_plan(const DevTables &T, const DevTokenEdges &E, const int32_t *__restrict__ tokens,
+                                                 const int32_t *states, const int32_t *row, const int32_t *len,
+                                                 int cap, int restart_on_eos,
+                                                 PrivateStack &priv, const int32_t *cycle_head, const int32_t *cycle_pool,
                                                  int stage_cycles, int32_t *after_row, int32_t *s_win, int32_t *s_new,
-                                                 int32_t *s_info, int32_t *s_adv_stack, RowPlan &plan, int b, int lane) {
-    PrivateStack priv;
-    priv.lds = s_adv_stack;
-    priv.lds_stride = 1;
-    priv.spill = adv_scratch + b;
-    priv.spill_stride = (size_t)batch;
+                                                 int32_t *s_info, RowPlan &plan, int b, int lane) {
     const int t = kScalar ? table<true>(tokens, b) : tokens[b];
-    const int n = kScalar ? table<true>(const_cast<const int32_t *>(len), b) : len[b];
-    const int st = kScalar ? table<true>(const_cast<const int32_t *>(states), b) : states[b];
+    const int n = kScalar ? table<true>(len, b) : len[b];
+    const int st = kScalar ? table<true>(states, b) : states[b];
     const bool shape_ok = n >= 1 && n <= cap;
     const bool live = t >= 0 && t < T.n_tokens && st >= 0 && shape_ok;
     StagedToken tok{0, 0};
@@ -509,61 +510,70 @@ __device__ __forceinline__ void advance_and_plan(const DevTables &T, const DevTo
     // Its top is staged and the condition tree descended BEFORE anything is stored: a wave that has
     // stores in flight waits for them wherever it next waits for a load, and in the one-launch step
     // kernel they complete only behind the row loads of the block's other waves.
+    Advanced r;
+    r.base = base; r.d = d; r.nl = out_len; r.from = 0; r.n = n; r.token = t; r.out_err = out_err; r.out_state = out_state;
     int nl = out_len;
+    int32_t *stack = after_row;                         // kCompact
     if (kCompact && shape_ok) {
-        // put it together in LDS, compact it, write back what changed
-        int32_t *stack = after_row;
+        // put it together in LDS and compact it
         for (int i = lane; i < nl; i += 64)
             stack[i] = i < base ? StackView{row, s_win, n}.at(i) : priv.get(i - base);
         __builtin_amdgcn_wave_barrier();
         int first_moved = nl;
         if (nl >= 2) nl = fold_cycles(stack, nl, cycle_head, cycle_pool, T.n_states, lane, &first_moved);
-        auto new_at = [&](int k) -> int32_t { return k < nl ? stack[nl - 1 - k] : -1; };
+        r.from = restarted ? nl : (first_moved < base ? first_moved : base);
+        r.nl = nl;
         s_new[lane] = lane < nl ? stack[nl - 1 - lane] : -1;
-        __builtin_amdgcn_wave_barrier();
-        const int top = s_new[0];
-        if (out_state < 0) {
-            if (lane == 0) plan.mode = kRowDone;
-        } else if ((unsigned)top >= (unsigned)T.n_states) {
-            if (lane == 0) plan.mode = kRowEmpty;
-        } else {
-            if (kScalar) plan_row_scalar(E, scalar_node(E.root_nodes + __builtin_amdgcn_readfirstlane(top)), s_new, nl, new_at, &plan, lane);
-            else plan_row(E, E.root_nodes[top], s_new, nl, new_at, &plan, lane);
-        }
-        if (lane == 0) { plan.top = top; plan.len = nl; }
-        const int from = restarted ? nl : (first_moved < base ? first_moved : base);
-        for (int i = from + lane; i < nl; i += 64) row[i] = stack[i];
+    }
+    auto new_at = [&](int k) -> int32_t {               // entry k below the new top
+        if (kCompact && shape_ok) return k < nl ? stack[nl - 1 - k] : -1;
+        if (restarted) return k == 0 ? (kScalar ? table<true>(row, 0) : row[0]) : -1;
+        if (k < d) return priv.get(d - 1 - k);
+        const int idx = base - 1 - (k - d);
+        return idx >= 0 ? StackView{row, s_win, n}.at(idx) : -1;
+    };
+    if (!(kCompact && shape_ok)) s_new[lane] = (shape_ok && lane < nl) ? new_at(lane) : -1;
+    __builtin_amdgcn_wave_barrier();
+    // ---- descent of the condition tree with the new stack
+    const int top = s_new[0];
+    if (out_state < 0) {
+        if (lane == 0) plan.mode = kRowDone;
+    } else if (!shape_ok || (unsigned)top >= (unsigned)T.n_states) {
+        if (lane == 0) plan.mode = kRowEmpty;
+    } else {
+        if (kScalar) plan_row_scalar(E, scalar_node(E.root_nodes + __builtin_amdgcn_readfirstlane(top)), s_new, nl, new_at, &plan, lane);
+        else plan_row(E, E.root_nodes[top], s_new, nl, new_at, &plan, lane);
+    }
+    if (lane == 0) { plan.top = top; plan.len = nl; }
+    return r;
+}
+
+// Stores what advance_and_plan found: the entries of the new stack that changed, states, len and err.
+template <bool kCompact>
+__device__ __forceinline__ void commit_advance(const Advanced &r, const PrivateStack &priv, const int32_t *after_row, int32_t *states,
+                                               int32_t *row, int32_t *len, int32_t *err, int cap, int b, int lane) {
+    if (kCompact && r.n >= 1 && r.n <= cap) {
+        for (int i = r.from + lane; i < r.nl; i += 64) row[i] = after_row[i];
         if (lane == 0) {
-            err[b] = out_err;
-            if ((out_err == 0 && t >= 0) || nl != n) { states[b] = out_state; len[b] = nl; }
+            err[b] = r.out_err;
+            if ((r.out_err == 0 && r.token >= 0) || r.nl != r.n) { states[b] = r.out_state; len[b] = r.nl; }
         }
     } else {
-        auto new_at = [&](int k) -> int32_t {           // entry k below the new top
-            if (restarted) return k == 0 ? (kScalar ? table<true>(const_cast<const int32_t *>(row), 0) : row[0]) : -1;
-            if (k < d) return priv.get(d - 1 - k);
-            const int idx = base - 1 - (k - d);
-            return idx >= 0 ? StackView{row, s_win, n}.at(idx) : -1;
-        };
-        s_new[lane] = (shape_ok && lane < nl) ? new_at(lane) : -1;
-        __builtin_amdgcn_wave_barrier();
-        // ---- descent of the condition tree with the new stack
-        const int top = s_new[0];
-        if (out_state < 0) {
-            if (lane == 0) plan.mode = kRowDone;
-        } else if (!shape_ok || (unsigned)top >= (unsigned)T.n_states) {
-            if (lane == 0) plan.mode = kRowEmpty;
-        } else {
-            if (kScalar) plan_row_scalar(E, scalar_node(E.root_nodes + __builtin_amdgcn_readfirstlane(top)), s_new, nl, new_at, &plan, lane);
-            else plan_row(E, E.root_nodes[top], s_new, nl, new_at, &plan, lane);
-        }
-        if (lane == 0) { plan.top = top; plan.len = nl; }
-        // ---- commit the private part
-        commit_overlay(row, priv, base, d, lane);
+        commit_overlay(row, priv, r.base, r.d, lane);
         if (lane == 0) {
-            err[b] = out_err;
-            if (out_err == 0 && t >= 0) { states[b] = out_state; len[b] = out_len; }
+            err[b] = r.out_err;
+            if (r.out_err == 0 && r.token >= 0) { states[b] = r.out_state; len[b] = r.nl; }
         }
     }
+}
+
+__device__ __forceinline__ PrivateStack wave_stack(int32_t *s_adv_stack, int32_t *spill, size_t spill_stride) {
+    PrivateStack priv;
+    priv.lds = s_adv_stack;
+    priv.lds_stride = 1;
+    priv.spill = spill;
+    priv.spill_stride = spill_stride;
+    return priv;
 }
 
 // Advance and next mask in one launch: one block per sequence.  Wave 0 walks the sampled token
@@ -613,9 +623,11 @@ __global__ __launch_bounds__(kAfBlock) void advance_fill_kernel(
         }
     }
     if (tid < 64) {
-        advance_and_plan<kCompact>(T, E, tokens, states, row, len, cap, batch, err, restart_on_eos, adv_scratch, cycle_head,
-                                   cycle_pool, stage_cycles, reinterpret_cast<int32_t *>(bits4 + ((T.n_words + 3) >> 2)), s_win,
-                                   s_new, s_info, s_adv_stack, plan, b, lane);
+        PrivateStack priv = wave_stack(s_adv_stack, adv_scratch + b, (size_t)batch);
+        int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
+        const Advanced r = advance_and_plan<kCompact>(T, E, tokens, states, row, len, cap, restart_on_eos, priv, cycle_head, cycle_pool,
+                                                      stage_cycles, after_row, s_win, s_new, s_info, plan, b, lane);
+        commit_advance<kCompact>(r, priv, after_row, states, row, len, err, cap, b, lane);
     }
     __syncthreads();
     // ---- the next mask row, by the whole block
@@ -650,6 +662,18 @@ __device__ __forceinline__ void plan_only_scalar(const DevTables &T, const DevTo
                         [&](int k) { return global_read(row + (n - 1 - k)); }, &plan, lane);
     }
     if (lane == 0) { plan.top = top; plan.len = n; }
+}
+
+// All ones in the halves of a register whose mask bits (the lowest two of `bits`) are set.
+__device__ __forceinline__ uint32_t allow_pair(uint32_t bits) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 0, 1), hi = (uint32_t)__builtin_amdgcn_sbfe((int)bits, 1, 1);
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+// A group of 8 logits with -inf where its mask byte has a zero.
+__device__ __forceinline__ uint4 mask_group(uint4 v, uint32_t mu) {
+    const uint4 a = make_uint4(allow_pair(mu), allow_pair(mu >> 2), allow_pair(mu >> 4), allow_pair(mu >> 6));
+    return make_uint4((v.x & a.x) | (~a.x & kNegInfPair), (v.y & a.y) | (~a.y & kNegInfPair), (v.z & a.z) | (~a.z & kNegInfPair),
+                      (v.w & a.w) | (~a.w & kNegInfPair));
 }
 
 // The whole decode step in one launch: advance, next mask row, and that row applied to the
@@ -701,11 +725,13 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
     __shared__ unsigned long long s_part[kArgmax ? kStepBlock / 64 + 1 : 1];
 
     if (tid < 64) {
-        if (tokens)
-            advance_and_plan<kCompact, true>(T, E, tokens, states, row, len, cap, batch, err, restart_on_eos, adv_scratch,
-                                             cycle_head, cycle_pool, stage_cycles, reinterpret_cast<int32_t *>(bits4 + n_vec),
-                                             s_win, s_new, s_info, s_adv_stack, plan, b, lane);
-        else
+        if (tokens) {
+            PrivateStack priv = wave_stack(s_adv_stack, adv_scratch + b, (size_t)batch);
+            int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
+            const Advanced r = advance_and_plan<kCompact, true>(T, E, tokens, states, row, len, cap, restart_on_eos, priv, cycle_head,
+                                                                cycle_pool, stage_cycles, after_row, s_win, s_new, s_info, plan, b, lane);
+            commit_advance<kCompact>(r, priv, after_row, states, row, len, err, cap, b, lane);
+        } else
             plan_only_scalar(T, E, states, row, len, cap, s_new, plan, b, lane);
         // (barriers that order LDS only: this wave's stores of the new stack are still on their way, and
         // nothing in this block reads them before the launch ends -- except the walks below, which wait)
@@ -896,6 +922,200 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
             mine = argmax_block_max(argmax_segment_by_compare_inline(lrow, reinterpret_cast<const uint8_t *>(bits4), 0,
                                                                      (T.n_tokens + 7) >> 3, T.n_tokens, tid), s_part, tid);
             if (tid == 0) out_tokens[b] = mine != 0ull ? (int32_t)(0xFFFFFFFFu - (uint32_t)mine) : -1;
+        }
+    }
+}
+
+// The whole decode step of a small batch in one launch: every row of logits is spread over n_seg blocks, so that a few
+// sequences fill the chip.  Each block of a row advances the sequence for itself (wave 0, as in advance_fill_kernel, on
+// private stacks of its own) while its other four waves load the block's kSpreadGroups groups of 8 logits; the plan
+// of the new row is the same in all of them, so each masks its groups and stores its part of the mask row by itself.
+// Only one may store the advance, and none before all have read what it overwrites: the blocks of a row count
+// themselves in when their plan is done, and the last to arrive stores (and sets the count back to zero for the next
+// launch).  No block waits for another.  Rows that the condition tree leaves open (tokens to be walked on the
+// stored stack) are left to that last block as a whole.
+// kArgmax: the greedy step; the blocks' best words meet in best[row] through an atomic maximum, and the last block to
+// count itself in on a second counter takes the result (words that the keys cannot decide are redone on the whole row).
+// A launch is bound by the chain of dependent loads of the advance (about 5 us) where the two-launch form pays for a
+// second launch and for reading the mask row back.  us per step inside a graph, against the form used before: 1 x 128,256
+// 7.4 (9.0), 16 x 128,256 9.1, 60 x 128,256 12.3 (15.6), 4 x 513 8.3 (9.9), 64 x 32,000 9.6 (11.6); greedy
+// 1 x 128,256 9.3 (13.7), 16 x 128,256 11.3 (15.0).  Four groups per lane and 256 lanes: with eight groups 8.2 and 10.0 us
+// at 1 and 16 x 128,256, with 512 lanes 7.8 and 9.6; with the advance through scalar loads (as in the kernel above,
+// where vector loads wait behind a whole row's) 8.8 and 10.5.
+constexpr int kSpreadLanes = 256, kSpreadBlock = kSpreadLanes + 64, kSpreadHeld = 4;
+constexpr int kSpreadGroups = kSpreadLanes * kSpreadHeld;
+template <bool kCompact, bool kArgmax>
+__global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
+    DevTables T, DevTokenEdges E, const int32_t *tokens, int32_t *states, int32_t *data, int32_t *len, int cap,
+    int32_t *__restrict__ err, uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_spill, int32_t *walk_spill,
+    size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
+    uint16_t *__restrict__ logits, int64_t row_stride, int32_t *out_tokens, int n_seg, StepArrivals *arrivals) {
+    extern __shared__ uint4 bits4[];                   // an open row's mask; kCompact: then cap stack entries [+ cycle tables]
+    __shared__ int32_t s_win[kWindow], s_new[kWindow], s_info[64];
+    __shared__ int32_t s_adv_stack[kLdsDepth], s_walk_stack[kLdsDepth * 64];
+    __shared__ RowPlan plan;
+    __shared__ unsigned long long s_part[kArgmax ? kSpreadBlock / 64 + 1 : 1];
+    __shared__ int s_last;
+    const int tid = threadIdx.x, lane = tid & 63, j = tid - 64;
+    const int b = blockIdx.x / n_seg, seg = blockIdx.x - b * n_seg;
+    const int n_vec = (T.n_words + 3) >> 2, g0 = seg * kSpreadGroups;
+    const int whole = T.n_tokens >> 3, tail = T.n_tokens & 7, groups = (T.n_tokens + 7) >> 3;
+    int32_t *row = data + (size_t)b * cap;
+    uint32_t *dst_row = bitmask + (size_t)b * T.n_words;
+    uint16_t *lrow = logits + (size_t)b * row_stride;
+    StepArrivals *mine = arrivals + b;
+    int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
+    PrivateStack priv = wave_stack(s_adv_stack, adv_spill + blockIdx.x, (size_t)gridDim.x);
+    Advanced r{};
+    uint4 held[kSpreadHeld];
+    if (tid < 64) {
+        r = advance_and_plan<kCompact>(T, E, tokens, states, row, len, cap, restart_on_eos, priv, cycle_head, cycle_pool,
+                                       stage_cycles, after_row, s_win, s_new, s_info, plan, b, lane);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kSpreadHeld; ++i) {
+            const int g = g0 + i * kSpreadLanes + j;
+            held[i] = make_uint4(0u, 0u, 0u, 0u);
+            if (g < whole) held[i] = stream_load(lrow + (size_t)g * 8);
+        }
+        if (kCompact && stage_cycles) {
+            int32_t *cycle_lds = after_row + cap;
+            copy_cycle_tables(cycle_lds, T.n_states, T.cycle_pool_n, cycle_head, cycle_pool, j, kSpreadLanes);
+            __syncthreads();
+        }
+    }
+    lds_barrier();                                     // the plan is there
+    const int mode = plan.mode;
+    const bool open = mode == kRowWalkAll || (mode == kRowFast && (plan.walk_count > 0 || plan.nseg > 0));
+    if (tid < 64) {
+        uint32_t before = 0;
+        if (lane == 0) before = atomicAdd(&mine->planned, 1u);
+        const bool last = (uint32_t)__builtin_amdgcn_readfirstlane((int)before) == (uint32_t)(n_seg - 1);
+        if (last) {
+            commit_advance<kCompact>(r, priv, after_row, states, row, len, err, cap, b, lane);
+            if (lane == 0) atomicExch(&mine->planned, 0u);
+        }
+        if (lane == 0) s_last = last;
+    }
+    if (open) {                                        // the same in every block of the row
+        __syncthreads();                               // s_last; the walks read the stored stack
+        if (!s_last) return;
+        PrivateStack wp;
+        wp.lds = s_walk_stack + lane;
+        wp.lds_stride = 64;
+        wp.spill = walk_spill + (size_t)b * 64 + lane;
+        wp.spill_stride = walk_spill_stride;
+        const bool vector_ok = (T.n_words & 3) == 0 && (reinterpret_cast<uintptr_t>(bitmask) & 15) == 0;
+        build_and_store_row<kSpreadBlock, true>(T, E, plan, bits4, 0, n_vec, row, wp, dst_row, vector_ok, tid);
+        const uint8_t *mask_bytes = reinterpret_cast<const uint8_t *>(bits4);
+        if (kArgmax) {
+            const unsigned long long w = argmax_block_max<kSpreadBlock>(
+                argmax_by_compare<kSpreadBlock>(lrow, [&](int g) { return (uint32_t)mask_bytes[g]; }, 0, groups, T.n_tokens, tid), s_part, tid);
+            if (tid == 0) out_tokens[b] = w != 0ull ? (int32_t)(0xFFFFFFFFu - (uint32_t)w) : -1;
+        } else {
+            for (int g = tid; g < groups; g += kSpreadBlock) {
+                const uint32_t mu = mask_bytes[g];
+                if (mu == 0xFFu) continue;
+                if (g < whole) {
+                    stream_store(mask_group(stream_load(lrow + (size_t)g * 8), mu), lrow + (size_t)g * 8);
+                } else {
+                    for (int k = 0; k < tail; ++k)
+                        if (!((mu >> k) & 1u)) lrow[whole * 8 + k] = 0xFF80;
+                }
+            }
+        }
+        return;
+    }
+    // the mask byte of a group: from the materialised row, else nothing (a finished sequence: the EOS bit) is allowed
+    const uint32_t *dense = mode == kRowFast && plan.dense >= 0 ? E.dense_rows + (size_t)plan.dense * n_vec * 4 : nullptr;
+    const int eos_group = mode == kRowDone ? T.eos_id >> 3 : -1;
+    auto mask_byte = [&](int g) {
+        uint32_t mu = g == eos_group ? 1u << (T.eos_id & 7) : 0u;
+        if (dense) mu = reinterpret_cast<const uint8_t *>(dense)[g];
+        return mu;
+    };
+    unsigned long long word = 0ull;                    // kArgmax: this lane's candidate
+    if (tid >= 64) {
+        uint32_t m[kSpreadHeld];
+#pragma unroll
+        for (int i = 0; i < kSpreadHeld; ++i) {
+            const int g = g0 + i * kSpreadLanes + j;
+            m[i] = g < groups ? mask_byte(g) : 0u;
+        }
+        const int w = seg * (kSpreadGroups / 4) + j;   // this block's part of the mask row: a word per lane
+        static_assert(kSpreadGroups / 4 == kSpreadLanes, "a mask word per lane");
+        if (w < T.n_words) dst_row[w] = dense ? dense[w] : (w == (eos_group >> 2) && eos_group >= 0) ? 1u << (T.eos_id & 31) : 0u;
+        uint32_t tail_x[4] = {0u, 0u, 0u, 0u};         // the last, partial group: in the lane whose group it is
+        if (kArgmax) {
+            int best = kOrderNegInf - 1, best_g = -1;
+            uint4 best_x = make_uint4(0, 0, 0, 0);
+            uint32_t best_m = 0u;
+#pragma unroll
+            for (int i = 0; i < kSpreadHeld; ++i) {
+                const int g = g0 + i * kSpreadLanes + j;
+                if (g >= groups) continue;
+                uint32_t mu = m[i];
+                if (g == whole) {
+                    for (int k = 0; k < tail; ++k) tail_x[k >> 1] |= (uint32_t)lrow[whole * 8 + k] << (16 * (k & 1));
+                    held[i] = make_uint4(tail_x[0], tail_x[1], tail_x[2], tail_x[3]);
+                    mu &= (1u << tail) - 1u;
+                }
+                if (mu == 0u) continue;
+                const uint4 allow = make_uint4(allow_pair(mu), allow_pair(mu >> 2), allow_pair(mu >> 4), allow_pair(mu >> 6));
+                const uint32_t k01 = packed_max_s16(bf16_order_pair(held[i].x, allow.x), bf16_order_pair(held[i].y, allow.y));
+                const uint32_t k23 = packed_max_s16(bf16_order_pair(held[i].z, allow.z), bf16_order_pair(held[i].w, allow.w));
+                const uint32_t k = packed_max_s16(k01, k23);
+                const int group_best = max((int)(int16_t)(k & 0xFFFFu), (int)k >> 16);
+                if (group_best > best) { best = group_best; best_g = g; best_x = held[i]; best_m = mu; }
+            }
+            if (best_g >= 0) {
+                const uint32_t x[4] = {best_x.x, best_x.y, best_x.z, best_x.w};
+                int first = 0;
+#pragma unroll
+                for (int k = 7; k >= 0; --k) {          // descending: the smallest k is assigned last
+                    const uint32_t h = (k & 1) ? (x[k >> 1] >> 16) : (x[k >> 1] & 0xFFFFu);
+                    if (((best_m >> k) & 1u) && bf16_order(h) == best) first = k;
+                }
+                word = argmax_word(best, best_g * 8 + first);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < kSpreadHeld; ++i) {
+                const int g = g0 + i * kSpreadLanes + j;
+                const uint32_t mu = g < whole ? m[i] : 0xFFu;
+                // (groups of a 128-byte line are written together or not at all, as in the other masking kernels)
+                const unsigned long long changed = __ballot(mu != 0xFFu);
+                if (g < whole && ((changed >> (lane & 56)) & 0xFFull)) stream_store(mask_group(held[i], mu), lrow + (size_t)g * 8);
+                if (g == whole) {
+                    for (int k = 0; k < tail; ++k)
+                        if (!((m[i] >> k) & 1u)) lrow[whole * 8 + k] = 0xFF80;
+                }
+            }
+        }
+    }
+    if (kArgmax) {
+        word = argmax_block_max<kSpreadBlock>(word, s_part, tid);
+        if (tid == 0) {
+            bool last = true;
+            if (n_seg > 1) {
+                // the count comes after the maximum has been taken (its result is waited for), so the last block finds all of them
+                unsigned long long old = atomicMax(&mine->best, word);
+                asm volatile("" : "+v"(old) : : "memory");
+                last = atomicAdd(&mine->sampled, 1u + (uint32_t)(old & 0ull)) == (uint32_t)(n_seg - 1);
+                if (last) {
+                    word = atomicExch(&mine->best, 0ull);
+                    atomicExch(&mine->sampled, 0u);
+                }
+            }
+            const int top = (int)(uint32_t)(word >> 32) - 32768;
+            const bool redo = last && word != 0ull && (top > kOrderPosInf || top == 0);
+            if (last && !redo) out_tokens[b] = word != 0ull ? (int32_t)(0xFFFFFFFFu - (uint32_t)word) : -1;
+            s_last = redo;
+        }
+        __syncthreads();
+        if (s_last) {                                  // a NaN pattern or a zero on top: compared as numbers, on the whole row
+            word = argmax_block_max<kSpreadBlock>(argmax_by_compare<kSpreadBlock>(lrow, mask_byte, 0, groups, T.n_tokens, tid), s_part, tid);
+            if (tid == 0) out_tokens[b] = word != 0ull ? (int32_t)(0xFFFFFFFFu - (uint32_t)word) : -1;
         }
     }
 }
@@ -1231,6 +1451,40 @@ hipError_t launch_fill_apply_rows(const DevTables &T, const DevTokenEdges &E, co
                                           row_stride, nullptr, first);
     return hipGetLastError();
 }
+
+int step_spread_segments(int n_tokens) { return ((n_tokens + 7) / 8 + kSpreadGroups - 1) / kSpreadGroups; }
+
+hipError_t launch_step_spread(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states, int32_t *data,
+                              int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask, int restart_on_eos,
+                              int32_t *adv_spill, int32_t *walk_spill, const int32_t *cycle_head, const int32_t *cycle_pool,
+                              uint16_t *logits, int64_t row_stride, int32_t *out_tokens, StepArrivals *arrivals, hipStream_t stream) {
+    if (batch == 0) return hipSuccess;
+    size_t lds = (size_t)edge_row_stride_words(T.n_words) * sizeof(uint32_t);
+    int stage = 0;
+    if (cycle_head) {
+        lds += (size_t)cap * sizeof(int32_t);
+        const size_t tables = (size_t)(T.n_states + T.cycle_pool_n) * sizeof(int32_t);
+        stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) && lds + tables <= kAfDynamicLdsMax;
+        if (stage) lds += tables;
+    }
+    if (lds > kAfDynamicLdsMax) return hipErrorInvalidValue;
+    const int n_seg = step_spread_segments(T.n_tokens);
+#define PRE3_SPREAD(C, A)                                                                                                   \
+    hipLaunchKernelGGL((step_spread_kernel<C, A>), dim3(batch * n_seg), dim3(kSpreadBlock), lds, stream, T, E, tokens, states, data, \
+                       len, cap, err, bitmask, restart_on_eos, adv_spill, walk_spill, (size_t)batch * 64, cycle_head, cycle_pool,   \
+                       stage, logits, row_stride, out_tokens, n_seg, arrivals)
+    if (cycle_head) {
+        if (out_tokens) PRE3_SPREAD(true, true);
+        else PRE3_SPREAD(true, false);
+    } else {
+        if (out_tokens) PRE3_SPREAD(false, true);
+        else PRE3_SPREAD(false, false);
+    }
+#undef PRE3_SPREAD
+    return hipGetLastError();
+}
+
+bool advance_fill_fits(int n_words) { return (size_t)edge_row_stride_words(n_words) * sizeof(uint32_t) <= kAfDynamicLdsMax; }
 
 bool advance_fill_fits_compact(int n_words, int cap) {
     return cap <= kCompactMaxLen &&

@@ -47,8 +47,9 @@ struct pre3_handle {
     pre3_stacks b_stacks{};
     // per-batch workspaces (pre3_bind_state): device allocations of their own, outside the arena
     struct Workspace { void *p = nullptr; size_t bytes = 0; };
-    Workspace ws_adv, ws_argmax, ws_topk, ws_af_spill;
+    Workspace ws_adv, ws_argmax, ws_topk, ws_af_spill, ws_arrivals;
     int32_t *adv_scratch = nullptr;              // private-stack spill of the advance
+    StepArrivals *arrivals = nullptr;            // per-row counters of the spread step, zero between launches
     int32_t *af_walk_spill = nullptr;            // ... of per-lane walks beside an advance
     unsigned long long *argmax_best = nullptr;   // per-segment partial results of pre3_apply_mask_argmax
     unsigned long long *topk_cand = nullptr;     // per-segment candidates of pre3_apply_mask_topk
@@ -348,6 +349,19 @@ bool locate(const pre3_handle *h, int state, int *g, int *local) {
     return false;
 }
 
+// Blocks of the spread step for a batch, 0 where that form does not serve it.  It is chosen while all its blocks (four per
+// compute unit) are on the chip at once: 64 sequences x 128,256 tokens take 12.5 us against 14.5 us in the one-kernel form,
+// 256 x 32,000 12.7 against 13.3 us, 60 x 128,256 12.3 against 15.6 us as two launches; with twice as many blocks the
+// second half starts when the first ends and it loses (128 x 128,256: 24.5 against 15.2 us).  It needs tables without id
+// lists, rows that fit the kernel's LDS, and spill columns (one per block) of at most 64 MiB.
+int spread_step_blocks(const pre3_handle *h, int batch) {
+    const int64_t blocks = (int64_t)batch * step_spread_segments(h->V.n_tokens);
+    if (!h->use_edges || blocks > 4 * h->n_compute_units || !h->E.delta_ids.empty()) return 0;
+    const bool cycles = h->compact && h->T.n_cycles > 0;
+    if (cycles ? !advance_fill_fits_compact(h->V.n_words, h->stack_cap) : !advance_fill_fits(h->V.n_words)) return 0;
+    return advance_scratch_entries((int)blocks, h->max_depth) * sizeof(int32_t) <= ((size_t)64 << 20) ? (int)blocks : 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -424,7 +438,7 @@ int pre3_compile(const char *const *grammars, int32_t n_grammars, const pre3_voc
 int pre3_free(pre3_handle *h) {
     if (!h) return PRE3_OK;
     for (void *p : h->allocations) (void)hipFree(p);
-    for (pre3_handle::Workspace *w : {&h->ws_adv, &h->ws_argmax, &h->ws_topk, &h->ws_af_spill})
+    for (pre3_handle::Workspace *w : {&h->ws_adv, &h->ws_argmax, &h->ws_topk, &h->ws_af_spill, &h->ws_arrivals})
         if (w->p) (void)hipFree(w->p);
     delete h;
     return PRE3_OK;
@@ -451,9 +465,21 @@ int pre3_bind_state(pre3_handle *h, int32_t *states, pre3_stacks stacks, int32_t
     // so far; a superseded one is freed (hipFree waits until the device no longer uses it)
     hipError_t e;
     void *p = nullptr;
-    if ((e = grow_workspace(h->ws_adv, advance_scratch_entries(stacks.batch, h->max_depth) * sizeof(int32_t), &p)) != hipSuccess)
+    const int spread_blocks = spread_step_blocks(h, stacks.batch);
+    if ((e = grow_workspace(h->ws_adv, advance_scratch_entries(std::max(stacks.batch, spread_blocks), h->max_depth) * sizeof(int32_t), &p)) != hipSuccess)
         return hip_fail(h, e, "allocate advance scratch");
     h->adv_scratch = static_cast<int32_t *>(p);
+    if (spread_blocks > 0) {
+        const size_t held = h->ws_arrivals.bytes;
+        if ((e = grow_workspace(h->ws_arrivals, (size_t)stacks.batch * sizeof(StepArrivals), &p)) != hipSuccess)
+            return hip_fail(h, e, "allocate step counters");
+        if (h->ws_arrivals.bytes != held) {             // new: the counters start at zero, on whatever stream the steps run
+            e = hipMemset(p, 0, h->ws_arrivals.bytes);
+            if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+            if (e != hipSuccess) { (void)hipFree(p); h->ws_arrivals = {}; h->arrivals = nullptr; return hip_fail(h, e, "clear step counters"); }
+        }
+        h->arrivals = static_cast<StepArrivals *>(p);
+    }
     if ((e = grow_workspace(h->ws_argmax, masked_argmax_workspace_bytes(stacks.batch, h->V.n_tokens, h->n_compute_units), &p)) != hipSuccess)
         return hip_fail(h, e, "allocate argmax workspace");
     h->argmax_best = static_cast<unsigned long long *>(p);
@@ -626,6 +652,13 @@ int pre3_advance_fill_apply_mask(pre3_handle *h, const int32_t *tokens, uint32_t
     if (row_stride < h->V.n_tokens) return fail(h, PRE3_E_BADARG, "advance_fill_apply_mask: row stride below vocabulary size");
     if (reinterpret_cast<uintptr_t>(logits_bf16) % 2 != 0) return fail(h, PRE3_E_BADARG, "advance_fill_apply_mask: misaligned logits");
     const bool cycles = h->compact && h->T.n_cycles > 0;
+    if (!(flags & PRE3_STEP_ONE_KERNEL) && spread_step_blocks(h, h->b_stacks.batch) > 0) {
+        hipError_t e = launch_step_spread(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,
+                                          h->b_stacks.batch, h->b_err, bitmask, flags & PRE3_ADVANCE_RESTART_ON_EOS, h->adv_scratch,
+                                          h->af_walk_spill, cycles ? h->cycle_head : nullptr, cycles ? h->cycle_pool : nullptr,
+                                          logits_bf16, row_stride, nullptr, h->arrivals, static_cast<hipStream_t>(stream));
+        return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_fill_apply_mask");
+    }
     if (step_takes_one_kernel(h, logits_bf16, row_stride, flags, false)) {
         const int restart = (flags & PRE3_ADVANCE_RESTART_ON_EOS) ? 1 : 0;
         hipError_t e = launch_advance_fill_apply(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len,
@@ -651,7 +684,21 @@ int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bi
     if (flags & ~(PRE3_ADVANCE_RESTART_ON_EOS | PRE3_STEP_ONE_KERNEL)) return fail(h, PRE3_E_BADARG, "advance_fill_argmax: unknown flag");
     if (row_stride < h->V.n_tokens) return fail(h, PRE3_E_BADARG, "advance_fill_argmax: row stride below vocabulary size");
     if (reinterpret_cast<uintptr_t>(logits_bf16) % 2 != 0) return fail(h, PRE3_E_BADARG, "advance_fill_argmax: misaligned logits");
-    if (step_takes_one_kernel(h, logits_bf16, row_stride, flags, true)) {
+    // The blocks of a spread row meet through atomics to choose the token, which costs more the more of them there are: from
+    // half a row per compute unit on the one kernel is the better form where it serves the logits (250 x 32,000: 12.8
+    // against 14.3 us; 64 x 32,000: 13.1 against 11.6 us).
+    const bool one_kernel = step_takes_one_kernel(h, logits_bf16, row_stride, flags, true);
+    if (!(flags & PRE3_STEP_ONE_KERNEL) && spread_step_blocks(h, h->b_stacks.batch) > 0 &&
+        !(one_kernel && 2 * h->b_stacks.batch >= h->n_compute_units)) {
+        const bool cycles = h->compact && h->T.n_cycles > 0;
+        hipError_t e = launch_step_spread(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,
+                                          h->b_stacks.batch, h->b_err, bitmask, flags & PRE3_ADVANCE_RESTART_ON_EOS, h->adv_scratch,
+                                          h->af_walk_spill, cycles ? h->cycle_head : nullptr, cycles ? h->cycle_pool : nullptr,
+                                          const_cast<uint16_t *>(logits_bf16), row_stride, out_tokens, h->arrivals,
+                                          static_cast<hipStream_t>(stream));
+        return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_fill_argmax");
+    }
+    if (one_kernel) {
         const bool cycles = h->compact && h->T.n_cycles > 0;
         const int restart = (flags & PRE3_ADVANCE_RESTART_ON_EOS) ? 1 : 0;
         // the kernel only reads the logits in this form

@@ -73,17 +73,19 @@ __device__ __forceinline__ uint4 expand_mask_byte(const uint2 *table, uint32_t m
 
 constexpr int kArgBlock = 1024;
 
+// The largest word of a block of kThreads threads, in every thread (s_part: a word per wave and one more).
+template <int kThreads = kArgBlock>
 __device__ __forceinline__ unsigned long long argmax_block_max(unsigned long long mine, unsigned long long *s_part, int tid) {
     mine = wave_max_u64(mine);
     __syncthreads();                                    // s_part may still be read from an earlier round
     if ((tid & 63) == 0) s_part[tid >> 6] = mine;
     __syncthreads();
     if (tid < 64) {
-        mine = wave_max_u64(tid < kArgBlock / 64 ? s_part[tid] : 0ull);
-        if (tid == 0) s_part[kArgBlock / 64] = mine;
+        mine = wave_max_u64(tid < kThreads / 64 ? s_part[tid] : 0ull);
+        if (tid == 0) s_part[kThreads / 64] = mine;
     }
     __syncthreads();
-    return s_part[kArgBlock / 64];
+    return s_part[kThreads / 64];
 }
 
 // The segment's candidate with one float compare per token: a lane keeps the largest value it has
@@ -91,13 +93,13 @@ __device__ __forceinline__ unsigned long long argmax_block_max(unsigned long lon
 // values, -0 and +0 are equal, a NaN never compares greater); an allowed -inf, which can only win if
 // nothing else is allowed, is remembered separately by lanes that have seen nothing larger.  Used
 // for the rare rows on which the packed keys of masked_argmax_kernel cannot decide.
-__device__ __forceinline__ unsigned long long argmax_segment_by_compare_inline(const uint16_t *__restrict__ lrow,
-                                                                                const uint8_t *__restrict__ mrow, int g_lo,
-                                                                                int g_hi, int vocab, int tid) {
+template <int kThreads, class MaskByte>
+__device__ __forceinline__ unsigned long long argmax_by_compare(const uint16_t *__restrict__ lrow, MaskByte mask_byte, int g_lo,
+                                                                int g_hi, int vocab, int tid) {
     float best_v = -INFINITY;
     int best_t = -1, ninf_t = -1;
-    for (int g = g_lo + tid; g < g_hi; g += kArgBlock) {
-        const uint32_t mu = mrow[g];
+    for (int g = g_lo + tid; g < g_hi; g += kThreads) {
+        const uint32_t mu = mask_byte(g);
         if (mu == 0u) continue;
         for (int k = 0; k < 8 && g * 8 + k < vocab; ++k) {
             if (!((mu >> k) & 1u)) continue;
@@ -110,6 +112,11 @@ __device__ __forceinline__ unsigned long long argmax_segment_by_compare_inline(c
     if (best_t >= 0) return argmax_word(bf16_order(__float_as_uint(best_v) >> 16), best_t);
     if (ninf_t >= 0) return argmax_word(kOrderNegInf, ninf_t);
     return 0ull;
+}
+__device__ __forceinline__ unsigned long long argmax_segment_by_compare_inline(const uint16_t *__restrict__ lrow,
+                                                                                const uint8_t *__restrict__ mrow, int g_lo,
+                                                                                int g_hi, int vocab, int tid) {
+    return argmax_by_compare<kArgBlock>(lrow, [&](int g) { return (uint32_t)mrow[g]; }, g_lo, g_hi, vocab, tid);
 }
 // The same as a call (keeps the register count of a kernel's main loop apart from this pass's).
 __device__ __noinline__ unsigned long long argmax_segment_by_compare(const uint16_t *__restrict__ lrow,

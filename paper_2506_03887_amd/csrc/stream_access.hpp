@@ -9,7 +9,7 @@ namespace pre3 {
 // 16-byte accesses marked non-temporal: the logits pass through once, and lines marked this way
 // are the first to leave L2, so the automaton's tables survive the pass for the next kernel.
 typedef unsigned int NativeUint4 __attribute__((ext_vector_type(4)));
-// Loads may start at any logit (rows of an odd vocabulary do): the memory system takes 16-byte loads at any
+// Accesses may start at any logit (rows of an odd vocabulary do): the memory system takes 16-byte accesses at any
 // address, and a wave's loads stay one contiguous 1 KiB (8 top-20 steps on 300 x 100,003: 393 us against 948 us
 // with one load per logit; 8 greedy steps on 100 x 100,003: 170 against 254 us).
 typedef NativeUint4 __attribute__((aligned(2))) NativeUint4AtLogit;
@@ -23,7 +23,7 @@ __device__ __forceinline__ uint4 stream_load_at(const uint16_t *row, uint32_t by
 }
 __device__ __forceinline__ void stream_store(uint4 v, uint16_t *p) {
     const NativeUint4 x = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(x, reinterpret_cast<NativeUint4 *>(p));
+    __builtin_nontemporal_store(x, reinterpret_cast<NativeUint4AtLogit *>(p));
 }
 
 // The same store for a mask row: the row is read once, by the kernel that masks the logits, and
