@@ -241,8 +241,7 @@ __device__ __forceinline__ unsigned long long wave_kth_largest(const unsigned lo
 //   larger words in all lists) and the k best write themselves in order.
 // The k words are written to out[(row * n_seg + segment) * k ..], best first, 0-padded; with one
 // segment per row the kernel writes the row's ids and bf16 patterns itself (out_ids, out_vals).
-constexpr int kTopkBlock = 512;                    // threads per block; kTopkBlockWide when a row has a compute unit to itself
-constexpr int kTopkBlockWide = 1024;
+constexpr int kTopkBlock = 512, kTopkBlockWide = 1024;        // threads per block
 constexpr int kTopkPerThread = 32;
 constexpr int kTopkChunk = kTopkPerThread * kTopkBlock;   // tokens per chunk (twice as many for the wide block)
 constexpr int kTopkRegion = 256;
@@ -637,14 +636,14 @@ __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
     return (folded & 0x8000u) ? (int)(folded & 0x7FFFu) : (int)((0x10000u - folded) & 0xFFFFu);
 }
 
-// The k best of a whole row by one block of 1,024 threads that keeps the row in registers: rows of 8 to
-// kTopkRowGroups * 1,024 * 8 tokens (131,072).  The mask row goes to LDS with a few loads per thread, and every
-// thread loads its 16 groups of logits, kAhead of them in flight, whatever their mask bytes say and without a branch
+// The k best of a whole row (blockIdx.x), or of a segment of kBlock * kG * 8 tokens of a longer one (blockIdx.y), by one
+// block that keeps it in registers.  The mask row goes to LDS with a few loads per thread, and every
+// thread loads its kG groups of logits, kAhead of them in flight, whatever their mask bytes say and without a branch
 // (groups beyond the row's end load the last one), and works on a group as it arrives.  The block is then bound by what
-// its sixteen waves do after the stream, so what is done to every token is two packed instructions under the stream: its half is
+// its waves do after the stream, so what is done to every token is two packed instructions under the stream: its half is
 // set to 0xFFFF if it is masked, and the maximum of the patterns as signed 16-bit numbers is taken.  For
 // patterns above zero that order is the order of the values, and the k best of most rows are such.  Then
-//   (1) a lower bound M of the k-th largest value: the k-th largest of the 128 maxima of eight threads each, ranked
+//   (1) a lower bound M of the k-th largest value: the k-th largest of 128 maxima of neighbouring threads, ranked
 //       by all threads together between two barriers: 64 of 128,256 random values reach the bound for k = 50;
 //   (2) the few groups whose maximum reaches M are copied to a list in LDS (one atomic per wave), and behind a barrier
 //       eight threads per listed group pick the tokens that reach M out of it, as words;
@@ -669,50 +668,107 @@ __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
 __device__ __forceinline__ uint32_t packed_max_i16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(PackedI16, a), __builtin_bit_cast(PackedI16, b)));
 }
-// The row chunk by chunk, as a call (its registers stay apart from the row kernel's).
-__device__ __noinline__ void topk_row_in_chunks(const uint16_t *logits, const uint32_t *bitmask, int vocab, int64_t row_stride,
-                                                int n_words, int k, unsigned long long *workspace, int32_t *out_ids,
-                                                uint16_t *out_vals, int b) {
-    masked_topk_chunked<kTopkBlockWide>(logits, bitmask, vocab, row_stride, n_words, k,
-                                        (vocab + kTopkPerThread * kTopkBlockWide - 1) / (kTopkPerThread * kTopkBlockWide),
-                                        workspace, out_ids, out_vals, b, 0, 1);
+// The segment chunk by chunk, as a call (its registers stay apart from the row kernel's).
+template <int kBlock>
+__device__ __noinline__ void topk_in_chunks(const uint16_t *logits, const uint32_t *bitmask, int vocab, int64_t row_stride,
+                                            int n_words, int k, int chunks_per_seg, unsigned long long *workspace, int32_t *out_ids,
+                                            uint16_t *out_vals, int b, int seg, int n_seg) {
+    masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, chunks_per_seg, workspace, out_ids, out_vals, b, seg, n_seg);
 }
-constexpr int kTopkRowGroups = 16;
-constexpr int kAhead = 8;                          // groups a thread has in flight
+constexpr int kTopkRowTokens = 16 * 8 * kTopkBlockWide;        // longest row that one block keeps in registers
 constexpr int kTopkRowList = 512, kTopkRowGroupList = 256;
-__global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(4))) void masked_topk_row_kernel(
+constexpr int kTopkMaxima = 128;                   // thread maxima that give the bound
+static_assert(kTopkMax <= kTopkMaxima, "the k-th of them has to exist");
+
+// The sum, or the maximum, over kLanes (2, 4 or 8) neighbouring lanes.
+template <int kLanes, class Op>
+__device__ __forceinline__ int lanes_reduce(int x, Op op) {
+    x = op(x, __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true));                        // lane ^ 1
+    if (kLanes > 2) x = op(x, __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true));        // lane ^ 2
+    if (kLanes > 4) x = op(x, __builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true));       // the other four of eight
+    return x;
+}
+
+// Step (1): the k-th largest of the kTopkMaxima maxima of the block's threads (kLanes threads each) in *kth, the largest
+// in *first; 0 where there are fewer.  s_pub: a word per maximum, s_out: two words that start at zero; every
+// call of a block takes others.  Two barriers.
+template <int kBlock>
+__device__ __forceinline__ void topk_bound(uint32_t best, int k, uint32_t *s_pub, uint32_t *s_out, int tid, uint32_t *first, uint32_t *kth) {
+    constexpr int kLanes = kBlock / kTopkMaxima;
+    auto largest = [](int a, int b) { return max(a, b); };
+    auto sum = [](int a, int b) { return a + b; };
+    const uint32_t top = (uint32_t)lanes_reduce<kLanes>((int)best, largest);
+    const int at = tid / kLanes, part = tid % kLanes;
+    if (part == 0) s_pub[at] = top << 7 | (uint32_t)(kTopkMaxima - 1 - at);      // distinct
+    lds_barrier();
+    // the threads of one maximum count the larger ones
+    const uint32_t mine = s_pub[at];
+    int larger = 0;
+#pragma unroll
+    for (int i = 0; i < kTopkMaxima / kLanes / 4; ++i) {
+        const uint4 x = reinterpret_cast<const uint4 *>(s_pub)[i * kLanes + part];
+        larger += (x.x > mine ? 1 : 0) + (x.y > mine ? 1 : 0) + (x.z > mine ? 1 : 0) + (x.w > mine ? 1 : 0);
+    }
+    larger = lanes_reduce<kLanes>(larger, sum);
+    if (part == 0 && larger == 0) s_out[0] = mine >> 7;
+    if (part == 0 && larger == k - 1) s_out[1] = mine >> 7;
+    lds_barrier();
+    *first = s_out[0];
+    *kth = s_out[1];
+}
+
+// Step (3): ranks the n words of the list (kBlock / kTopkMaxima lanes to a word) and hands out those below k.
+template <int kBlock, class Emit>
+__device__ __forceinline__ void topk_rank(const unsigned long long *s_cand, int n, int k, int tid, Emit emit) {
+    constexpr int kLanes = kBlock / kTopkMaxima;
+    auto sum = [](int a, int b) { return a + b; };
+    for (int at0 = 0; at0 < n; at0 += kTopkMaxima) {
+        const int at = at0 + tid / kLanes;
+        const unsigned long long mine = at < n ? s_cand[at] : ~0ull;
+        int larger = 0;
+#pragma unroll 4
+        for (int j = tid % kLanes; j < n; j += kLanes) larger += s_cand[j] > mine ? 1 : 0;
+        larger = lanes_reduce<kLanes>(larger, sum);
+        if (tid % kLanes == 0 && at < n && larger < k) emit(larger, mine);
+    }
+}
+
+template <int kBlock, int kG>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void masked_topk_row_kernel(
     const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
     int n_words, int k, unsigned long long *__restrict__ workspace, int32_t *__restrict__ out_ids,
     uint16_t *__restrict__ out_vals) {
-    constexpr int kBlock = kTopkBlockWide, kWaves = kBlock / 64, kG = kTopkRowGroups;
-    static_assert(kWaves * 8 == 128 && kTopkMax <= 128, "step (1) ranks 128 maxima");
+    constexpr int kWaves = kBlock / 64, kSegTokens = kBlock * kG * 8;
+    constexpr int kAhead = kG < 8 ? kG : 8;                   // groups a thread has in flight
+    static_assert(kG % 4 == 0 && kSegTokens % (kTopkPerThread * kBlock) == 0, "mask words of four rounds at a time, whole chunks");
     __shared__ uint32_t s_mask[kBlock * kG / 4];              // the mask row, for every wave the bytes of its groups
     __shared__ uint2 s_expand[16];                            // half a mask byte -> AND masks of two of the group's registers
-    __shared__ __align__(16) uint32_t s_pub[2][kBlock / 8];
-    __shared__ uint32_t s_first[2], s_kth[2];
+    __shared__ __align__(16) uint32_t s_pub[2][kTopkMaxima];
+    __shared__ uint32_t s_bound[2][2];
     __shared__ uint4 s_group[kTopkRowGroupList];
     __shared__ int s_group_at[kTopkRowGroupList];
     __shared__ unsigned long long s_cand[kTopkRowList];
-    __shared__ int s_rank[kTopkRowList];
     __shared__ int s_count, s_groups;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int b = blockIdx.x, seg = blockIdx.y, n_seg = gridDim.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long lanes_below = (1ull << lane) - 1ull;
-    const uint32_t *mrow = bitmask + (size_t)b * n_words;
-    const uint16_t *lrow = logits + (size_t)b * row_stride;
-    const int whole = vocab >> 3;
-    const uint32_t last_group = (uint32_t)(whole - 1) * 16u;
-    // the mask words of the wave's own groups: its 64 groups of round u are the words u * 256 + wave * 16 + (0 .. 15)
+    const uint16_t *whole_row = logits + (size_t)b * row_stride;
+    const int first_token = seg * kSegTokens, n_tokens = min(vocab - first_token, kSegTokens);
+    const uint32_t *mrow = bitmask + (size_t)b * n_words + first_token / 32;
+    const int seg_words = (n_tokens + 31) / 32, whole = n_tokens >> 3;
+    // (a last segment of less than a group loads the eight tokens before it and looks at none)
+    const uint16_t *lrow = whole_row + (whole > 0 ? first_token : max(first_token - 8, 0));
+    const uint32_t last_group = (uint32_t)max(whole - 1, 0) * 16u;
+    // the mask words of the wave's own groups: its 64 groups of round u are the words u * kBlock / 4 + wave * 16 + (0 .. 15)
     uint32_t mw[kG / 4];
     auto mask_word = [&](int i) { return (i * 4 + (lane >> 4)) * (kBlock / 4) + wave * 16 + (lane & 15); };
 #pragma unroll
-    for (int i = 0; i < kG / 4; ++i) mw[i] = mrow[min(mask_word(i), n_words - 1)];
+    for (int i = 0; i < kG / 4; ++i) mw[i] = mrow[min(mask_word(i), seg_words - 1)];
     uint4 v[kG];
     auto load_group = [&](int u) { v[u] = stream_load_at(lrow, min((uint32_t)tid * 16u + (uint32_t)(u * kBlock * 16), last_group)); };
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) load_group(u);
     mask_nibble_table_init(s_expand, tid);
-    if (tid < kTopkRowList) s_rank[tid] = 0;                  // (the list has fewer entries than the block has threads)
-    if (tid == 0) { s_count = 0; s_groups = 0; }
+    if (tid == 0) { s_count = 0; s_groups = 0; s_bound[0][0] = s_bound[0][1] = s_bound[1][0] = s_bound[1][1] = 0u; }
     lds_barrier();                                            // s_expand and what starts at zero (the loads are on their way)
 #pragma unroll
     for (int i = 0; i < kG / 4; ++i) {
@@ -746,43 +802,15 @@ __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(
     }
     // the tokens behind the last whole group, one thread each
     uint32_t tail = 0xFFFFu;
-    const int tail_t = whole * 8 + tid;
-    if (tail_t < vocab && ((mrow[tail_t >> 5] >> (tail_t & 31)) & 1u)) tail = lrow[tail_t];
+    const int tail_t = whole * 8 + tid;                       // (within the segment)
+    if (tail_t < n_tokens && ((mrow[tail_t >> 5] >> (tail_t & 31)) & 1u)) tail = whole_row[first_token + tail_t];
     // (1) the bound
-    bool nan = false;
-    uint32_t bound = 0u, kth = 0u;
-    auto find_bound = [&](int round, uint32_t best) {
-        uint32_t top = best;                                  // of eight lanes
-        top = max(top, (uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0xB1, 0xF, 0xF, true));    // lane ^ 1
-        top = max(top, (uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0x4E, 0xF, 0xF, true));    // lane ^ 2
-        top = max(top, (uint32_t)__builtin_amdgcn_mov_dpp((int)top, 0x141, 0xF, 0xF, true));   // the other four of eight
-        if ((lane & 7) == 0) s_pub[round][tid >> 3] = top << 7 | (uint32_t)(127 - (tid >> 3));   // distinct
-        lds_barrier();
-        // eight lanes rank one of the 128: each counts the larger ones among sixteen
-        const uint32_t mine = s_pub[round][tid >> 3];
-        int larger = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint4 x = reinterpret_cast<const uint4 *>(s_pub[round])[(lane & 7) * 4 + i];
-            larger += (x.x > mine ? 1 : 0) + (x.y > mine ? 1 : 0) + (x.z > mine ? 1 : 0) + (x.w > mine ? 1 : 0);
-        }
-        larger += __builtin_amdgcn_mov_dpp(larger, 0xB1, 0xF, 0xF, true);
-        larger += __builtin_amdgcn_mov_dpp(larger, 0x4E, 0xF, 0xF, true);
-        larger += __builtin_amdgcn_mov_dpp(larger, 0x141, 0xF, 0xF, true);
-        if ((lane & 7) == 0) {
-            if (larger == 0) s_first[round] = mine >> 7;
-            if (larger == k - 1) s_kth[round] = mine >> 7;
-        }
-        lds_barrier();
-        nan = s_first[round] > 0x7F80u;
-        kth = s_kth[round];
-        bound = kth != 0u ? kth : s_first[round] != 0u ? 1u : 0u;      // fewer than k: every candidate
-    };
+    uint32_t first, kth;
     uint32_t best = (uint32_t)max(best_i, (int)(int16_t)tail);
-    find_bound(0, best);
+    topk_bound<kBlock>(best, k, s_pub[0], s_bound[0], tid, &first, &kth);
+    const bool nan = first > 0x7F80u;
     const bool positive = !nan && kth != 0u;                  // the same in every thread
     if (!positive) {
-        const bool drop_nan = nan;
         best = 0u;
 #pragma unroll
         for (int u = 0; u < kG; ++u) {
@@ -793,7 +821,7 @@ __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 uint32_t key = bf16_key_pair(kp[u * 4 + j]);
-                if (drop_nan) {                               // a positive NaN's key goes
+                if (nan) {                                    // a positive NaN's key goes
                     const uint32_t lo = key & 0xFFFFu, hi = key >> 16;
                     key = (lo > kTopkKeyMax ? 0u : lo) | ((hi > kTopkKeyMax ? 0u : hi) << 16);
                 }
@@ -805,17 +833,20 @@ __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(
         tail = bf16_key(tail);
         if (tail > kTopkKeyMax) tail = 0u;
         best = max(best, tail);
-        find_bound(1, best);
+        topk_bound<kBlock>(best, k, s_pub[1], s_bound[1], tid, &first, &kth);
     } else {
         if ((int)(int16_t)tail < 0) tail = 0u;
     }
+    const uint32_t bound = kth != 0u ? kth : first != 0u ? 1u : 0u;      // fewer than k: every candidate
     auto emit = [&](int rank, unsigned long long word) {
-        if (word != 0ull) {
+        if (n_seg > 1) {                                      // masked_topk_finish_kernel merges the segments
+            workspace[((size_t)b * n_seg + seg) * (size_t)k + rank] = word;
+        } else if (word != 0ull) {
             const uint32_t id = kTopkIdMask - ((uint32_t)word & kTopkIdMask);
             out_ids[(size_t)b * k + rank] = (int32_t)id;
             if (out_vals) {
                 const int pattern = bf16_pattern_of_key((uint32_t)(word >> kTopkIdBits));
-                out_vals[(size_t)b * k + rank] = pattern >= 0 ? (uint16_t)pattern : lrow[id];
+                out_vals[(size_t)b * k + rank] = pattern >= 0 ? (uint16_t)pattern : whole_row[id];
             }
         } else {
             out_ids[(size_t)b * k + rank] = -1;
@@ -851,7 +882,7 @@ __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(
         }
         if (tail >= bound) {                                  // at most seven tokens, all in the first wave
             const int slot = atomicAdd(&s_count, 1);
-            s_cand[slot] = topk_word(tail + to_key, (uint32_t)tail_t);
+            s_cand[slot] = topk_word(tail + to_key, (uint32_t)(first_token + tail_t));
         }
     }
     lds_barrier();
@@ -873,132 +904,68 @@ __global__ __launch_bounds__(kTopkBlockWide) __attribute__((amdgpu_waves_per_eu(
             int base = 0;
             if (lane == 0) base = atomicAdd(&s_count, __popcll(mm));
             const int slot = __builtin_amdgcn_readfirstlane(base) + __popcll(mm & lanes_below);
-            if (take && slot < kTopkRowList) s_cand[slot] = topk_word(x + to_key, (uint32_t)(s_group_at[at >> 3] * 8 + (at & 7)));
+            if (take && slot < kTopkRowList) s_cand[slot] = topk_word(x + to_key, (uint32_t)(first_token + s_group_at[at >> 3] * 8 + (at & 7)));
         }
     }
     lds_barrier();
     const int n = s_count;
     if (n > kTopkRowList || n_groups > kTopkRowGroupList) {   // same in every thread
-        topk_row_in_chunks(logits, bitmask, vocab, row_stride, n_words, k, workspace, out_ids, out_vals, b);
+        constexpr int kChunks = kSegTokens / (kTopkPerThread * kBlock);
+        topk_in_chunks<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, kChunks, workspace, n_seg > 1 ? nullptr : out_ids,
+                               out_vals, b, seg, n_seg);
         return;
     }
-    // (3) ranks: up to 128 words, as usual, are ranked by eight lanes each, which count the larger ones in turn
+    // (3) ranks
     if (tid >= n && tid < k) emit(tid, 0ull);
-    if (n <= kBlock / 8) {
-        const int at = tid >> 3;
-        const unsigned long long mine = at < n ? s_cand[at] : ~0ull;
-        int larger = 0;
-#pragma unroll 4
-        for (int j = tid & 7; j < n; j += 8) larger += s_cand[j] > mine ? 1 : 0;
-        larger += __builtin_amdgcn_mov_dpp(larger, 0xB1, 0xF, 0xF, true);
-        larger += __builtin_amdgcn_mov_dpp(larger, 0x4E, 0xF, 0xF, true);
-        larger += __builtin_amdgcn_mov_dpp(larger, 0x141, 0xF, 0xF, true);
-        if ((tid & 7) == 0 && at < n && larger < k) emit(larger, mine);
-        return;
-    }
-    // more: thread (slice, word) counts the larger words of its slice of the list
-    const int slices = kBlock / n > 0 ? kBlock / n : 1, per = (n + slices - 1) / slices;
-    const int word_at = tid % n, slice = tid / n;
-    if (slice < slices) {
-        const unsigned long long mine = s_cand[word_at];
-        const int j_end = (slice + 1) * per < n ? (slice + 1) * per : n;
-        int larger = 0;
-#pragma unroll 4
-        for (int j = slice * per; j < j_end; ++j) larger += s_cand[j] > mine ? 1 : 0;
-        if (larger) atomicAdd(&s_rank[word_at], larger);
-    }
-    __syncthreads();
-    if (tid < n && s_rank[tid] < k) emit(s_rank[tid], s_cand[tid]);
+    topk_rank<kBlock>(s_cand, n, k, tid, emit);
 }
 
-// Merges the segments' candidates of one row with one wave: n_cand words (0 = empty), at most
-// kTopkFinishPer per lane.  As above, the k-th largest of the 64 per-lane maxima bounds the k-th
-// largest word from below; the words that reach it go to an LDS list.  Up to 256 listed words are
-// ranked directly (a word's rank = number of larger words) and those ranked below k written in
-// order; a longer list is first cut to its k best bit by bit.
-constexpr int kTopkFinishPer = 16;
-__global__ __launch_bounds__(64) void masked_topk_finish_kernel(
+// Merges the segments' candidates of one row: n_cand words (0 = empty), at most kTopkFinishPer per thread.  As above, the
+// k-th largest of 128 thread maxima bounds the k-th largest key from below, and the words that reach it are ranked.
+constexpr int kTopkFinishBlock = 512, kTopkFinishPer = 2;
+__global__ __launch_bounds__(kTopkFinishBlock) void masked_topk_finish_kernel(
     const unsigned long long *__restrict__ cand, int n_cand, int k, const uint16_t *__restrict__ logits,
     int64_t row_stride, int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_vals) {
-    __shared__ unsigned long long s_list[64 * kTopkFinishPer];
-    __shared__ unsigned long long s_best[kTopkMax];
-    const int b = blockIdx.x, lane = threadIdx.x;
+    __shared__ __align__(16) uint32_t s_pub[kTopkMaxima];
+    __shared__ uint32_t s_bound[2];
+    __shared__ unsigned long long s_cand[kTopkFinishBlock * kTopkFinishPer];
+    __shared__ int s_count;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     unsigned long long c[kTopkFinishPer], top = 0ull;
 #pragma unroll
     for (int i = 0; i < kTopkFinishPer; ++i) {
-        const int at = i * 64 + lane;
+        const int at = i * kTopkFinishBlock + tid;
         c[i] = at < n_cand ? cand[(size_t)b * n_cand + at] : 0ull;
         top = c[i] > top ? c[i] : top;
     }
-    // lower bound: the min(k, lanes with a candidate)-th largest of the lanes' best words
-    const int nz = __popcll(__ballot(top != 0ull));
-    const int kq = nz < k ? nz : k;
-    unsigned long long bound = 1ull;
-    if (kq < nz) {
-        unsigned long long prefix = 0ull;
-        for (int bit = kTopkWordBits - 1; bit >= 0; --bit) {
-            const unsigned long long t = prefix | (1ull << bit);
-            const int n = __popcll(__ballot(top >= t));
-            if (n >= kq) {
-                prefix = t;
-                if (n == kq) break;
-            }
-        }
-        bound = prefix;
-    }
-    int S = 0;
+    if (tid == 0) { s_count = 0; s_bound[0] = s_bound[1] = 0u; }
+    uint32_t first, kth;
+    topk_bound<kTopkFinishBlock>((uint32_t)(top >> kTopkIdBits), k, s_pub, s_bound, tid, &first, &kth);
 #pragma unroll
     for (int i = 0; i < kTopkFinishPer; ++i) {
-        const bool keep = c[i] != 0ull && c[i] >= bound;
+        const bool keep = c[i] != 0ull && (uint32_t)(c[i] >> kTopkIdBits) >= kth;
         const unsigned long long m = __ballot(keep);
-        if (keep) s_list[S + __popcll(m & ((1ull << lane) - 1ull))] = c[i];
-        S += __popcll(m);
+        if (m == 0ull) continue;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&s_count, __popcll(m));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (keep) s_cand[base + __popcll(m & ((1ull << lane) - 1ull))] = c[i];
     }
-    __builtin_amdgcn_wave_barrier();
-    const int kk = S < k ? S : k;
-    auto emit = [&](unsigned long long w, int rank) {
+    lds_barrier();
+    const int n = s_count;
+    auto emit = [&](int rank, unsigned long long w) {
         const uint32_t id = kTopkIdMask - ((uint32_t)w & kTopkIdMask);
         out_ids[(size_t)b * k + rank] = (int32_t)id;
-        if (out_vals) out_vals[(size_t)b * k + rank] = logits[(size_t)b * row_stride + id];
+        if (out_vals) {
+            const int pattern = bf16_pattern_of_key((uint32_t)(w >> kTopkIdBits));
+            out_vals[(size_t)b * k + rank] = pattern >= 0 ? (uint16_t)pattern : logits[(size_t)b * row_stride + id];
+        }
     };
-    if (S <= 256) {
-        // the usual case: every listed word is ranked directly (rank = number of larger words; all
-        // lanes read the same LDS word at a time)
-        unsigned long long w[4];
-        int rank[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = i * 64 + lane < S ? s_list[i * 64 + lane] : ~0ull;
-#pragma unroll 8
-        for (int j = 0; j < S; ++j) {
-            const unsigned long long o = s_list[j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) rank[i] += o > w[i] ? 1 : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (i * 64 + lane < S && rank[i] < k) emit(w[i], rank[i]);
-    } else {
-        s_best[lane] = 0ull;
-        __builtin_amdgcn_wave_barrier();
-        const unsigned long long thr = kk > 0 ? wave_kth_largest(s_list, S, kk, lane) : ~0ull;
-        int base = 0;
-        for (int r0 = 0; r0 < S; r0 += 64) {
-            const unsigned long long w = r0 + lane < S ? s_list[r0 + lane] : 0ull;
-            const bool take = w >= thr && w != 0ull;
-            const unsigned long long m = __ballot(take);
-            if (take) s_best[base + __popcll(m & ((1ull << lane) - 1ull))] = w;
-            base += __popcll(m);
-        }
-        __builtin_amdgcn_wave_barrier();
-        const unsigned long long mine = s_best[lane];         // kk <= 64 selected words, one per lane
-        int rank = 0;
-        for (int j = 0; j < kk; ++j) rank += s_best[j] > mine ? 1 : 0;
-        if (mine != 0ull) emit(mine, rank);
+    if (tid >= n && tid < k) {
+        out_ids[(size_t)b * k + tid] = -1;
+        if (out_vals) out_vals[(size_t)b * k + tid] = 0xFF80u;
     }
-    if (lane >= kk && lane < k) {
-        out_ids[(size_t)b * k + lane] = -1;
-        if (out_vals) out_vals[(size_t)b * k + lane] = 0xFF80u;
-    }
+    topk_rank<kTopkFinishBlock>(s_cand, n, k, tid, emit);
 }
 
 }  // namespace
@@ -1033,20 +1000,9 @@ hipError_t launch_masked_argmax(const uint16_t *logits, const uint32_t *bitmask,
 
 static int masked_topk_chunks(int vocab, int chunk = kTopkChunk) { return (vocab + chunk - 1) / chunk; }
 
-// Chunks per block: the whole row once there is a row per compute unit (the block then writes the
-// result itself and no second kernel runs); below that as many as still leave two blocks per compute
-// unit, so that small batches are spread over the chip.
-static int masked_topk_chunks_per_segment(int batch, int vocab, int n_compute_units) {
-    const int n_chunks = masked_topk_chunks(vocab);
-    if (batch >= n_compute_units) return n_chunks;
-    int per = 1;
-    while (per < n_chunks && (int64_t)batch * ((n_chunks + 2 * per - 1) / (2 * per)) >= 2 * (int64_t)n_compute_units) per *= 2;
-    return per < n_chunks ? per : n_chunks;
-}
-
 bool masked_topk_fits(int vocab, int k) {
     return k >= 1 && k <= kTopkMax && vocab >= 1 && vocab <= (1 << kTopkIdBits) &&
-           masked_topk_chunks(vocab) * k <= 64 * kTopkFinishPer;
+           masked_topk_chunks(vocab) * k <= kTopkFinishBlock * kTopkFinishPer;
 }
 
 size_t masked_topk_workspace_bytes(int batch, int vocab) {
@@ -1059,30 +1015,29 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     if (batch == 0) return hipSuccess;
     if (!masked_topk_fits(vocab, k)) return hipErrorInvalidValue;
     const int n_words = (vocab + 31) / 32;
-    if (batch >= n_compute_units && vocab >= 8 && vocab / 8 <= kTopkRowGroups * kTopkBlockWide) {
-        // a block per row that keeps the whole row in registers
-        hipLaunchKernelGGL(masked_topk_row_kernel, dim3(batch), dim3(kTopkBlockWide), 0, stream, logits, bitmask, vocab,
-                           row_stride, n_words, k, workspace, out_ids, out_vals);
-        return hipGetLastError();
-    }
-    if (batch >= n_compute_units && batch < 2 * n_compute_units) {
-        // a row per compute unit and no second block beside it: sixteen waves take the row
-        hipLaunchKernelGGL(masked_topk_kernel<kTopkBlockWide>, dim3(batch, 1), dim3(kTopkBlockWide), 0, stream, logits, bitmask,
-                           vocab, row_stride, n_words, k, masked_topk_chunks(vocab, kTopkPerThread * kTopkBlockWide),
-                           workspace, out_ids, out_vals);
-        return hipGetLastError();
-    }
-    const int per = masked_topk_chunks_per_segment(batch, vocab, n_compute_units);
-    const int n_seg = (masked_topk_chunks(vocab) + per - 1) / per;
-    if (n_seg == 1) {
+    if (vocab < 8) {                                   // not one group of eight logits
         hipLaunchKernelGGL(masked_topk_kernel<kTopkBlock>, dim3(batch, 1), dim3(kTopkBlock), 0, stream, logits, bitmask, vocab,
-                           row_stride, n_words, k, per, workspace, out_ids, out_vals);
+                           row_stride, n_words, k, masked_topk_chunks(vocab), workspace, out_ids, out_vals);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(masked_topk_kernel<kTopkBlock>, dim3(batch, n_seg), dim3(kTopkBlock), 0, stream, logits, bitmask, vocab,
-                       row_stride, n_words, k, per, workspace, (int32_t *)nullptr, (uint16_t *)nullptr);
-    hipLaunchKernelGGL(masked_topk_finish_kernel, dim3(batch), dim3(64), 0, stream, workspace, n_seg * k, k, logits, row_stride,
-                       out_ids, out_vals);
+    // A row that fits the registers of a block is one block's, whatever the batch (128,256 tokens, k = 50: 8.0 us for one
+    // row, 10.7 for 64, 15.4 for 256, against 9.9 and 14.1 us for 1 and 64 rows in segments of 16,384 tokens and a second
+    // launch); the block and its groups per thread are the smallest that hold it.  A longer row is cut into such
+    // blocks of 98,304 or 131,072 tokens (152,064 tokens: 14.4 us for 100 rows, 49 for 512) unless the batch
+    // is too small to fill the chip with them (16 rows: 11.8 against 13.4 us in segments of 16,384).
+#define PRE3_TOPK_ROW(BLOCK, GROUPS)                                                                                         \
+    n_seg = masked_topk_chunks(vocab, BLOCK * GROUPS * 8);                                                                   \
+    hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, vocab, \
+                       row_stride, n_words, k, workspace, out_ids, out_vals)
+    int n_seg = 1;
+    if (vocab <= kTopkChunk || (vocab > kTopkRowTokens && batch * 8 < n_compute_units)) { PRE3_TOPK_ROW(kTopkBlock, 4); }
+    else if (vocab <= kTopkRowTokens / 2) { PRE3_TOPK_ROW(kTopkBlockWide, 8); }
+    else if (vocab <= kTopkRowTokens / 4 * 3 || (vocab > kTopkRowTokens && vocab <= kTopkRowTokens / 2 * 3)) { PRE3_TOPK_ROW(kTopkBlockWide, 12); }
+    else { PRE3_TOPK_ROW(kTopkBlockWide, 16); }
+#undef PRE3_TOPK_ROW
+    if (n_seg > 1)
+        hipLaunchKernelGGL(masked_topk_finish_kernel, dim3(batch), dim3(kTopkFinishBlock), 0, stream, workspace, n_seg * k, k, logits,
+                           row_stride, out_ids, out_vals);
     return hipGetLastError();
 }
 

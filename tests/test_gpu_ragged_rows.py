@@ -72,16 +72,18 @@ def test_sampled_rows_at_every_offset(V, B, pad, offset):
         assert (ids.cpu().numpy() == want_ids).all() and (vals.cpu().numpy().view(np.uint16) == want_vals).all(), k
 
 
-@pytest.mark.parametrize("V", [8, 9, 15, 64, 8191, 8192, 8205, 65_535, 131_072])
-def test_topk_of_rows_kept_in_registers(V):
-    """256 rows (a block per row): rows with values of one sign only, few allowed tokens, hundreds of ties (the lists
+@pytest.mark.parametrize("V,B", [(7, 20), (8, 256), (9, 256), (15, 256), (64, 256), (8191, 256), (8192, 256), (8205, 256),
+                                 (16_384, 17), (16_385, 17), (65_535, 256), (65_536, 17), (65_537, 17), (98_305, 17),
+                                 (131_072, 256), (131_073, 17), (131_079, 48), (147_460, 17), (196_608, 48), (196_611, 48)])
+def test_topk_of_rows_kept_in_registers(V, B):
+    """A block per row, or two (or segments of 16,384 tokens of 17 rows) beyond 131,072 tokens: rows with values of one sign only, few allowed tokens, hundreds of ties (the lists
     of the kernel run full), zeros of both signs, infinities, allowed NaN of both signs, and nothing allowed."""
     from test_gpu_argmax import _bound_lib
     from oracle import masked_topk
     from workloads.vocab import Vocab
     torch, dev = _torch()
     rng = np.random.default_rng(V)
-    B, W = 256, (V + 31) // 32
+    W = (V + 31) // 32
     lib = _bound_lib(Vocab([bytes([97 + i % 5]) for i in range(V - 1)] + [b""], V - 1), B)
     host = bf16_logits(rng, B, V)
     mask = rng.integers(0, 2 ** 32, size=(B, W), dtype=np.uint64).astype(np.uint32)
@@ -97,13 +99,16 @@ def test_topk_of_rows_kept_in_registers(V):
             mask[rows] &= rng.integers(0, 2 ** 32, size=mask[rows].shape, dtype=np.uint64).astype(np.uint32)
     mask[10::16], mask[11::16] = 0, 0xFFFFFFFF
     mask[12::16] = 0
-    mask[12::16, 0], mask[12::16, -1] = 0x00000101, 1 << ((V - 1) & 31)     # first tokens and the last
+    mask[12::16, 0] = 0x00000101                                            # first tokens and the last
+    mask[12::16, -1] |= np.uint32(1 << ((V - 1) & 31))
     mask[13::16] = 0
     mask[13::16, : max(1, W // 100)] = 0xFFFFFFFF                           # one run of ids
     host[14::16, : V // 2] |= 0x8000
     mask[:, -1] &= np.uint32(0xFFFFFFFF >> (W * 32 - V))
     logits, mask_d = torch.from_numpy(host.view(np.int16)).to(dev).view(torch.bfloat16), torch.from_numpy(mask.view(np.int32)).to(dev)
     for k in (1, 17, 64):
+        if -(-V // 16384) * k > 1024:
+            continue
         ids, vals = torch.empty((B, k), dtype=torch.int32, device=dev), torch.empty((B, k), dtype=torch.int16, device=dev)
         lib.apply_mask_topk(logits, mask_d, ids, vals)
         want_ids, want_vals = masked_topk(host, mask, V, k)
