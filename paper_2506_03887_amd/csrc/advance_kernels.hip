@@ -585,14 +585,19 @@ __device__ __forceinline__ PrivateStack wave_stack(int32_t *s_adv_stack, int32_t
 // kCompact (cycle-aware stacks): the new stack is put together in LDS, complete traversals of reduction
 // cycles are taken out of it (fold_cycles) and only then is it written back and looked up, so the call
 // leaves compacted stacks and the mask of exactly those stacks.
-constexpr int kAfBlock = 512;
+// Threads per block: 512 while two blocks of that size per compute unit hold the batch, half of that for larger ones (more
+// of their blocks are on the chip at once: 1,024 x 128,256 tokens 10.4 against 14.2 us, 2,048 16.2 against 20.0; 256 x 128,256
+// 8.8 against 8.6 us), and two waves for large batches of short rows (2,048 x 8,000: 10.3 us; 13.7 with 256 threads, 18.9
+// with 512).
+constexpr int kAfBlock = 512, kAfBlockMany = 256, kAfBlockShort = 128;
+constexpr int kAfShortWords = 1024;                    // mask words of a short row (32,768 tokens)
 // LDS the kernel declares statically (stack windows, token bytes, private stacks, the row plan),
 // rounded up: what is left of the 64 KB for the dynamic part (mask row, staged stack)
 constexpr size_t kAfStaticLdsBytes =
     ((sizeof(int32_t) * (2 * kWindow + 64 + kLdsDepth + kLdsDepth * 64) + sizeof(RowPlan)) + 1023) & ~(size_t)1023;
 constexpr size_t kAfDynamicLdsMax = 65536 - kAfStaticLdsBytes;
-template <bool kCompact>
-__global__ __launch_bounds__(kAfBlock) void advance_fill_kernel(
+template <bool kCompact, int kThreads>
+__global__ __launch_bounds__(kThreads) void advance_fill_kernel(
     DevTables T, DevTokenEdges E, const int32_t *__restrict__ tokens, int32_t *__restrict__ states,
     int32_t *__restrict__ data, int32_t *__restrict__ len, int cap, int batch, int32_t *__restrict__ err,
     uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
@@ -611,14 +616,14 @@ __global__ __launch_bounds__(kAfBlock) void advance_fill_kernel(
         // The waves that wait for the walk pull the small tables it reads into this XCD's L2 (a
         // streaming kernel that ran in between has evicted them): one 128-byte line per lane,
         // the lines dealt out over the blocks of the XCD (blocks go round-robin to the 8 XCDs).
-        const int64_t per_xcd = (gridDim.x + 7) >> 3, idle = kAfBlock - 64;
+        const int64_t per_xcd = (gridDim.x + 7) >> 3, idle = kThreads - 64;
         int acc = 0;
         for (int64_t off = ((int64_t)(blockIdx.x >> 3) * idle + (tid - 64)) * 128; off < T.hot_bytes; off += per_xcd * idle * 128)
             acc |= *(const volatile __attribute__((address_space(1))) int *)(T.hot_begin + off);
         if (acc == 0x7ff1234f && T.fault) atomicAdd(T.fault, 0);   // keeps the loads alive; no effect
         if (kCompact && stage_cycles) {                 // ... and copy the cycle tables into LDS for wave 0
             int32_t *cycle_lds = reinterpret_cast<int32_t *>(bits4 + ((T.n_words + 3) >> 2)) + cap;
-            copy_cycle_tables(cycle_lds, T.n_states, T.cycle_pool_n, cycle_head, cycle_pool, tid - 64, kAfBlock - 64);
+            copy_cycle_tables(cycle_lds, T.n_states, T.cycle_pool_n, cycle_head, cycle_pool, tid - 64, kThreads - 64);
             __syncthreads();
         }
     }
@@ -637,7 +642,7 @@ __global__ __launch_bounds__(kAfBlock) void advance_fill_kernel(
     wp.spill = walk_spill + (size_t)b * 64 + lane;
     wp.spill_stride = walk_spill_stride;
     const bool vector_ok = (T.n_words & 3) == 0 && (reinterpret_cast<uintptr_t>(bitmask) & 15) == 0;
-    build_and_store_row<kAfBlock, true, true>(T, E, plan, bits4, 0, n_vec, row, wp, bitmask + (size_t)b * T.n_words, vector_ok, tid);
+    build_and_store_row<kThreads, true, true>(T, E, plan, bits4, 0, n_vec, row, wp, bitmask + (size_t)b * T.n_words, vector_ok, tid);
 }
 
 // The part of advance_and_plan that is left when there is no token: the top of the stack as it stands is
@@ -1434,24 +1439,31 @@ size_t advance_fill_walk_spill_entries(int batch, int max_depth) {
 hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states,
                                int32_t *data, int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask,
                                int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
-                               const int32_t *cycle_head, const int32_t *cycle_pool, hipStream_t stream) {
+                               const int32_t *cycle_head, const int32_t *cycle_pool, int n_compute_units, hipStream_t stream) {
     if (batch == 0) return hipSuccess;
-    const size_t row_bytes = (size_t)edge_row_stride_words(T.n_words) * sizeof(uint32_t);
+    size_t lds = (size_t)edge_row_stride_words(T.n_words) * sizeof(uint32_t);
+    int stage = 0;
     if (cycle_head) {                                  // cycle-aware stacks: the new stack is staged in LDS too
-        size_t lds = row_bytes + (size_t)cap * sizeof(int32_t);
+        lds += (size_t)cap * sizeof(int32_t);
         if (cap > kCompactMaxLen || lds > kAfDynamicLdsMax) return hipErrorInvalidValue;
         const size_t tables = (size_t)(T.n_states + T.cycle_pool_n) * sizeof(int32_t);
-        const int stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) && lds + tables <= kAfDynamicLdsMax;
+        stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) && lds + tables <= kAfDynamicLdsMax;
         if (stage) lds += tables;
-        hipLaunchKernelGGL(advance_fill_kernel<true>, dim3(batch), dim3(kAfBlock), lds, stream, T, E, tokens, states, data,
-                           len, cap, batch, err, bitmask, restart_on_eos, adv_scratch, walk_spill, (size_t)batch * 64,
-                           cycle_head, cycle_pool, stage);
-    } else {
-        if (row_bytes > kAfDynamicLdsMax) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(advance_fill_kernel<false>, dim3(batch), dim3(kAfBlock), row_bytes, stream, T, E, tokens, states,
-                           data, len, cap, batch, err, bitmask, restart_on_eos, adv_scratch, walk_spill, (size_t)batch * 64,
-                           nullptr, nullptr, 0);
+    } else if (lds > kAfDynamicLdsMax) {
+        return hipErrorInvalidValue;
     }
+#define PRE3_AF(C, THREADS)                                                                                                 \
+    hipLaunchKernelGGL((advance_fill_kernel<C, THREADS>), dim3(batch), dim3(THREADS), lds, stream, T, E, tokens, states, data,   \
+                       len, cap, batch, err, bitmask, restart_on_eos, adv_scratch, walk_spill, (size_t)batch * 64, cycle_head,  \
+                       cycle_pool, stage)
+#define PRE3_AF_SIZES(C)                                                                    \
+    if (batch <= 2 * n_compute_units) PRE3_AF(C, kAfBlock);                                  \
+    else if (batch > 4 * n_compute_units && T.n_words <= kAfShortWords) PRE3_AF(C, kAfBlockShort); \
+    else PRE3_AF(C, kAfBlockMany)
+    if (cycle_head) { PRE3_AF_SIZES(true); }
+    else { PRE3_AF_SIZES(false); }
+#undef PRE3_AF_SIZES
+#undef PRE3_AF
     return hipGetLastError();
 }
 

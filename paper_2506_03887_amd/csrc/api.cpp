@@ -612,7 +612,8 @@ int pre3_advance_fill_mask(pre3_handle *h, const int32_t *tokens, uint32_t *bitm
     if (h->use_edges && (!cycles || advance_fill_fits_compact(h->V.n_words, h->b_stacks.cap))) {
         e = launch_advance_fill(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len,
                                 h->b_stacks.cap, h->b_stacks.batch, h->b_err, bitmask, restart, h->adv_scratch,
-                                h->af_walk_spill, cycles ? h->cycle_head : nullptr, cycles ? h->cycle_pool : nullptr, s);
+                                h->af_walk_spill, cycles ? h->cycle_head : nullptr, cycles ? h->cycle_pool : nullptr,
+                                h->n_compute_units, s);
         return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_fill_mask");
     }
     e = launch_advance(h->dev, effect_edges(h), tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,

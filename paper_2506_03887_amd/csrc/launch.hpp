@@ -58,7 +58,7 @@ size_t advance_fill_walk_spill_entries(int batch, int max_depth);   // int32 ent
 hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states,
                                int32_t *data, int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask,
                                int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
-                               const int32_t *cycle_head, const int32_t *cycle_pool, hipStream_t stream);
+                               const int32_t *cycle_head, const int32_t *cycle_pool, int n_compute_units, hipStream_t stream);
 bool advance_fill_fits(int n_words);                    // the row bitmap within 64 KB of LDS
 bool advance_fill_fits_compact(int n_words, int cap);   // row bitmap + staged stack within 64 KB of LDS
 // The same followed by the masking of the logits with the new rows, as one kernel that fetches a

@@ -135,3 +135,36 @@ def test_spread_step_after_rebinding_and_in_a_graph():
             torch.cuda.synchronize()
             assert (tok_d.cpu().numpy() == want).all(), (B, s)
             tokens = want
+
+
+@pytest.mark.parametrize("B,V,cycles", [(513, 2003, False), (700, 40_001, False), (1100, 2003, False), (1100, 2003, True), (1030, 33_000, False)])
+def test_advance_and_mask_of_large_batches(B, V, cycles):
+    """pre3_advance_fill_mask on batches whose kernel runs with fewer threads per sequence (more than two blocks of
+    512 to a compute unit; two waves for large batches of short rows): allowed, refused, skipped and EOS tokens."""
+    from paper_2506_03887_amd import Pre3
+    torch, dev = _torch()
+    v = _vocab(V)
+    grammar = G.JSON_RIGHT_RECURSIVE if cycles else G.JSON
+    o = Oracle(grammar, compact_cycles=cycles)
+    lib = Pre3(grammar, v.bytes, v.offsets, v.eos_id, max_token_len=max(1, v.max_len), stack_cap=48, compact_cycles=cycles)
+    rng = np.random.default_rng(B)
+    states, length, data = np.full(B, o.initial_state(0), np.int32), np.ones(B, np.int32), np.zeros((B, 48), np.int32)
+    data[:, 0] = states
+    s_d, l_d, d_d = (torch.from_numpy(x.copy()).to(dev) for x in (states, length, data))
+    err_d, tok_d = torch.zeros(B, dtype=torch.int32, device=dev), torch.zeros(B, dtype=torch.int32, device=dev)
+    mask_d = torch.zeros((B, v.words), dtype=torch.int32, device=dev)
+    lib.bind_state(s_d, d_d, l_d, err_d)
+    mask = o.fill_mask(states, data, length, v)
+    for s in range(4):
+        tokens = np.array([rng.choice(np.flatnonzero((m[np.arange(V) >> 5] >> (np.arange(V) & 31).astype(np.uint32)) & 1))
+                           if m.any() else v.eos_id for m in mask], dtype=np.int32)
+        odd = rng.random(B) < 0.2
+        tokens[odd] = rng.choice([-1, V + 5, v.eos_id, *range(V - 9, V - 1)], size=int(odd.sum()))
+        tok_d.copy_(torch.from_numpy(tokens))
+        err = o.advance_batch(states, data, length, tokens, v)
+        mask = o.fill_mask(states, data, length, v)
+        lib.advance_fill_mask(tok_d, mask_d)
+        assert (err_d.cpu().numpy() == err).all() and (s_d.cpu().numpy() == states).all() and (l_d.cpu().numpy() == length).all(), s
+        live = np.arange(48)[None, :] < length[:, None]
+        assert (d_d.cpu().numpy()[live] == data[live]).all(), s
+        assert (mask_d.cpu().numpy().view(np.uint32) == mask).all(), s
