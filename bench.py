@@ -417,6 +417,10 @@ def main(argv=None):
     # =========================== headline: the step, then the dominant kernel ===========================
     step_kind = {"two-call": "fill+apply", "fused": "fused", "advance-fill": "advance-fill", "one-call": "one-call"}[args.step]
     step_launches = lib.step_kernel_launches(logits[0]) if step_kind == "one-call" else 0
+    # a batch whose rows, in blocks of 8,192 tokens, fill the chip at most four to a compute unit is spread over blocks
+    spread = (step_kind == "one-call" and
+              B * -(-V // 8192) <= 4 * torch.cuda.get_device_properties(0).multi_processor_count)
+    step_launches = 1 if spread else step_launches
     if step_kind == "one-call" and step_launches == 0:
         # outside the batch sizes (or vocabulary) of the one kernel the call is pre3_advance_fill_mask + pre3_apply_mask:
         # time and label those
@@ -469,7 +473,7 @@ def main(argv=None):
     if step_kind == "one-call":
         # the one kernel of the step reads and writes the logits (4 B/pair) and writes the mask (one bit per pair)
         # (a batch beyond one sequence per compute unit goes as several launches of equal shares: the figures are per launch)
-        dom_name, dom_bytes, dom_us = "advance_fill_apply_kernel", APPLY_BYTES_PER_PAIR * pairs / step_launches, apply_us / step_launches
+        dom_name, dom_bytes, dom_us = "step_spread_kernel" if spread else "advance_fill_apply_kernel", APPLY_BYTES_PER_PAIR * pairs / step_launches, apply_us / step_launches
         dom_timing = ("HIP events around every launch of an eager pass over the timed steps" if args.eager else
                       "inside the K timed steps replayed as one HIP graph: device clock stamps (one-thread kernels) before and "
                       "after every launch, minus the cost of a stamp")
