@@ -145,7 +145,7 @@ int32_t pre3_initial_state(const pre3_handle *h, int32_t grammar_idx);
  * must outlive the binding): states [batch] (top state of each stack, or PRE3_STATE_DONE),
  * the stacks, and err [batch].  Rebinding replaces the previous binding.
  * This is the call that allocates the per-batch workspaces (private-stack spill areas, partial
- * results of the arg max and the top-k): one allocation of each kind per handle, sized for the
+ * results of the arg max and the top-k, the counters of the step that is spread over blocks): one allocation of each kind per handle, sized for the
  * largest batch bound so far.  Binding a batch that needs no more reuses them; binding a larger
  * one frees the superseded workspace (hipFree: waits for the device to go idle) and allocates the
  * larger one, so a server that resizes its batch does not accumulate device memory.  Work that was
