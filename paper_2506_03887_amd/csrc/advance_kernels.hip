@@ -808,7 +808,7 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
             // (the compiler would otherwise leave all of that to the fold behind the barriers).  With the fold below that keeps
             // one register per group and looks for the token only where the block's best key is: 16.4 against 18.5 us per
             // greedy step in a graph at 256 x 128,256, 13.4 against 15.6 us at 128.
-            const uint32_t last_group = (uint32_t)(whole > 0 ? whole - 1 : 0) * 16u;
+            const uint32_t last_group = (uint32_t)(whole - 1) * 16u;         // (advance_fill_apply_fits: a whole group at least)
             auto load_group = [&](int i) { held[i] = stream_load_at(lrow, min((uint32_t)j * 16u + (uint32_t)(i * kStepData * 16), last_group)); };
 #pragma unroll
             for (int i = 0; i < (kStepAhead < kHeld ? kStepAhead : kHeld); ++i) load_group(i);
@@ -1473,6 +1473,8 @@ constexpr int kStepHeldMax = 27, kStepHeldMaxGreedy = 20;
 // Largest vocabulary the fused step kernel can hold in registers, and the choice of its variant.
 bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bool greedy) {
     const size_t row_bytes = (size_t)edge_row_stride_words(n_words) * sizeof(uint32_t);
+    // (the greedy form loads without a branch, slots beyond the row load its last whole group: there has to be one)
+    if (greedy && n_tokens < 8) return false;
     if ((n_tokens >> 3) > (greedy ? kStepHeldMaxGreedy : kStepHeldMax) * kStepData) return false;
     if (cycles) return cap <= kCompactMaxLen && row_bytes + (size_t)cap * sizeof(int32_t) <= kAfDynamicLdsMax;
     return row_bytes <= kAfDynamicLdsMax;
