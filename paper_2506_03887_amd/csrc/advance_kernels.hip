@@ -1024,6 +1024,7 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
     const bool open = mode == kRowWalkAll || (mode == kRowFast && (plan.walk_count > 0 || plan.nseg > 0));
     if (tid < 64) {
         uint32_t before = 0;
+        loads_returned();                              // of the stack: the block that counts last overwrites it
         if (lane == 0) before = atomicAdd(&mine->planned, 1u);
         const bool last = (uint32_t)__builtin_amdgcn_readfirstlane((int)before) == (uint32_t)(n_seg - 1);
         if (last) {

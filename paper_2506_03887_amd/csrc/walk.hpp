@@ -36,6 +36,11 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Every load that the source has before this point has returned, none of those behind it has begun: what the loads
+// read may be overwritten by whoever learns that this point was passed.  (A relaxed atomic alone orders nothing, and
+// lds_barrier leaves global loads free to move.)
+__device__ __forceinline__ void loads_returned() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Private stack of one walk: the states pushed above the part of the sequence's stack that
 // is still untouched.  The first kLdsDepth entries live in LDS (one column per lane), deeper
 // ones in a global spill area (one column per resident lane), both indexed [depth][lane] so

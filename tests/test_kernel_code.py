@@ -1,0 +1,48 @@
+"""What the compiled kernels have to hold whatever the compiler makes of the source: read from the disassembly of the
+built library's own gfx950 code (no GPU needed)."""
+import glob
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """name -> instructions, in the order of the code."""
+    from paper_2506_03887_amd.binding import LIB_PATH
+    at = tmp_path_factory.mktemp("code")
+    shutil.copy(LIB_PATH, at / "lib.so")
+    subprocess.run([OBJDUMP, "--offloading", str(at / "lib.so")], check=True, capture_output=True)
+    out = {}
+    for f in glob.glob(str(at / "lib.so.*gfx950")):
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", f], check=True, capture_output=True, text=True).stdout
+        name = None
+        for line in text.splitlines():
+            m = re.match(r"^[0-9a-f]+ <(\S+)>:", line)
+            if m:
+                name = m.group(1)
+                out[name] = []
+            elif name and line.strip():
+                out[name].append(line.split("//")[0].strip())
+    assert out
+    return out
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+def test_a_block_of_the_spread_step_counts_itself_in_when_its_loads_have_returned(kernels):
+    """The blocks of a row read its stack, count themselves in, and the last to do so overwrites the stack: between the
+    last load before the count (the first atomic that returns a value) and the count, the wave has to wait for all loads."""
+    found = {n: code for n, code in kernels.items() if "step_spread_kernel" in n}
+    assert len(found) == 4
+    for name, code in found.items():
+        count = next(i for i, x in enumerate(code) if re.match(r"global_atomic_add\b.*\bsc0\b", x))
+        loads = [i for i, x in enumerate(code[:count]) if re.match(r"(global|flat|buffer|scratch)_load", x)]
+        waits = [i for i, x in enumerate(code[:count]) if re.match(r"s_waitcnt\b.*vmcnt\(0\)", x)]
+        assert waits and waits[-1] > loads[-1], name
+        between = [x for x in code[waits[-1]: count] if re.match(r"s_cbranch|s_branch", x)]
+        assert all(x.startswith("s_cbranch_execz") for x in between), (name, between)     # straight code, lanes switched off at most
