@@ -145,12 +145,13 @@ int32_t pre3_initial_state(const pre3_handle *h, int32_t grammar_idx);
  * must outlive the binding): states [batch] (top state of each stack, or PRE3_STATE_DONE),
  * the stacks, and err [batch].  Rebinding replaces the previous binding.
  * This is the call that allocates the per-batch workspaces (private-stack spill areas, partial
- * results of the arg max and the top-k, the counters of the step that is spread over blocks): one allocation of each kind per handle, sized for the
- * largest batch bound so far.  Binding a batch that needs no more reuses them; binding a larger
- * one frees the superseded workspace (hipFree: waits for the device to go idle) and allocates the
- * larger one, so a server that resizes its batch does not accumulate device memory.  Work that was
- * recorded into a HIP graph before such a growing rebind points at the freed workspace and must be
- * recorded again.  Errors: BADARG, HIP (allocation failed). */
+ * results of the arg max and the top-k, the counters of the step that is spread over blocks): one
+ * allocation of each kind per handle, sized for the largest batch bound so far and every smaller
+ * one.  Binding a batch that is no larger reuses them; binding a larger one frees the superseded
+ * workspace (hipFree: waits for the device to go idle) and allocates the larger one, so a server
+ * that resizes its batch does not accumulate device memory.  Work that was recorded into a HIP
+ * graph before such a growing rebind points at the freed workspace and must be recorded again.
+ * Errors: BADARG, HIP (allocation failed). */
 int pre3_bind_state(pre3_handle *h, int32_t *states, pre3_stacks stacks, int32_t *err);
 
 /* Token mask of one decode step (Sec. 1: every token whose bytes leave the language of
@@ -413,6 +414,11 @@ int32_t pre3_debug_token_effect(const pre3_handle *h, const int32_t *stack, int3
 /* Sizes of the merged reduction edges (Sec. 3.2.2; Alg. 1 step 3): out[0] built?, [1] condition
  * nodes, [2] deepest stack entry tested, [3] bytes of device memory. */
 int pre3_symbol_edge_stats(const pre3_handle *h, int64_t out[4]);
+/* Bytes of the per-batch workspaces that pre3_bind_state holds for a batch of `batch` sequences (tests
+ * and tools): out[0] private-stack spill of the advance, [1] counters of the spread step, [2] arg max,
+ * [3] top-k (0: beyond its limit), [4] spill of per-lane walks.  Host call; a host-only handle answers
+ * for 256 compute units.  Errors: BADARG. */
+int pre3_debug_workspace_bytes(const pre3_handle *h, int32_t batch, int64_t out[5]);
 /* Consistency check of the compiled tables on the host (tests and tools): every index that a
  * kernel follows (edge targets, goto rows, condition children, record offsets, token ids, dense
  * rows, vocabulary offsets) must stay inside its table.  Returns the number of violations (0 for

@@ -30,7 +30,7 @@ EXPORTS = [
     "pre3_fill_mask", "pre3_apply_mask", "pre3_fill_apply_mask", "pre3_advance", "pre3_advance_fill_mask", "pre3_advance_fill_apply_mask", "pre3_advance_fill_argmax", "pre3_step_is_one_kernel", "pre3_apply_mask_argmax", "pre3_apply_mask_topk", "pre3_jump_forward", "pre3_n_grammars", "pre3_n_states",
     "pre3_n_byte_classes", "pre3_byte_class", "pre3_edge", "pre3_goto_target", "pre3_walk_depth_bound",
     "pre3_token_edge_stats", "pre3_debug_resolve_row", "pre3_symbol_edge_stats", "pre3_debug_advance", "pre3_debug_validate_tables",
-    "pre3_forced_run", "pre3_n_reduction_cycles", "pre3_reduction_cycle", "pre3_debug_compact", "pre3_debug_fault_count", "pre3_debug_timestamp", "pre3_advance_static", "pre3_token_effect_stats", "pre3_debug_token_effect",
+    "pre3_forced_run", "pre3_n_reduction_cycles", "pre3_reduction_cycle", "pre3_debug_compact", "pre3_debug_fault_count", "pre3_debug_timestamp", "pre3_advance_static", "pre3_token_effect_stats", "pre3_debug_token_effect", "pre3_debug_workspace_bytes",
 ]
 
 
@@ -99,6 +99,7 @@ def load():
         getattr(lib, name).argtypes = [vp]
     lib.pre3_byte_class.argtypes = [vp, i32]
     lib.pre3_debug_validate_tables.argtypes = [vp]
+    lib.pre3_debug_workspace_bytes.argtypes = [vp, i32, vp]
     lib.pre3_edge.argtypes = [vp, i32, i32, c.POINTER(i32), c.POINTER(i32)]
     lib.pre3_goto_target.argtypes = [vp, i32, i32]
     lib.pre3_token_edge_stats.argtypes = [vp, vp]
@@ -278,6 +279,12 @@ class Pre3:
         n = ctypes.c_int64()
         self._check(self._lib.pre3_debug_fault_count(self._h, ctypes.byref(n)))
         return n.value
+
+    def workspace_bytes(self, batch: int) -> dict:
+        """Bytes of the workspaces that bind_state holds for `batch` sequences."""
+        out = (ctypes.c_int64 * 5)()
+        self._check(self._lib.pre3_debug_workspace_bytes(self._h, batch, out))
+        return dict(zip(["advance_spill", "step_counters", "argmax", "topk", "walk_spill"], list(out)))
 
     def validate_tables(self) -> int:
         """Number of out-of-range indices in the compiled tables (0 expected)."""

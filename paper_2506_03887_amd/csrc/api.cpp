@@ -54,7 +54,7 @@ struct pre3_handle {
     unsigned long long *argmax_best = nullptr;   // per-segment partial results of pre3_apply_mask_argmax
     unsigned long long *topk_cand = nullptr;     // per-segment candidates of pre3_apply_mask_topk
     bool topk_ready = false;
-    int n_compute_units = 0;
+    int n_compute_units = 256;                   // of the MI355X; pre3_compile asks the device
     bool bound_empty = false;
     // stack compaction over reduction cycles (PRE3_FLAG_COMPACT_CYCLES)
     bool compact = false;
@@ -349,17 +349,40 @@ bool locate(const pre3_handle *h, int state, int *g, int *local) {
     return false;
 }
 
-// Blocks of the spread step for a batch, 0 where that form does not serve it.  It is chosen while all its blocks (four per
-// compute unit) are on the chip at once: 64 sequences x 128,256 tokens take 12.5 us against 14.5 us in the one-kernel form,
-// 256 x 32,000 12.7 against 13.3 us, 60 x 128,256 12.3 against 15.6 us as two launches; with twice as many blocks the
-// second half starts when the first ends and it loses (128 x 128,256: 24.5 against 15.2 us).  It needs tables without id
-// lists, rows that fit the kernel's LDS, and spill columns (one per block) of at most 64 MiB.
-int spread_step_blocks(const pre3_handle *h, int batch) {
-    const int64_t blocks = (int64_t)batch * step_spread_segments(h->V.n_tokens);
-    if (!h->use_edges || blocks > 4 * h->n_compute_units || !h->E.delta_ids.empty()) return 0;
+// Most sequences of a batch that runs as the spread step, 0 if the tables do not allow that form.  It is chosen while all its
+// blocks (four per compute unit) are on the chip at once: 64 sequences x 128,256 tokens take 12.5 us against 14.5 us in the
+// one-kernel form, 256 x 32,000 12.7 against 13.3 us, 60 x 128,256 12.3 against 15.6 us as two launches; with twice as
+// many blocks the second half starts when the first ends and it loses (128 x 128,256: 24.5 against 15.2 us).  It needs
+// tables without id lists, rows that fit the kernel's LDS, and spill columns (one per block) of at most 64 MiB.
+int spread_step_rows(const pre3_handle *h) {
     const bool cycles = h->compact && h->T.n_cycles > 0;
+    if (!(h->use_edges || (h->host_only && h->E.enabled)) || !h->E.delta_ids.empty()) return 0;
     if (cycles ? !advance_fill_fits_compact(h->V.n_words, h->stack_cap) : !advance_fill_fits(h->V.n_words)) return 0;
-    return advance_scratch_entries((int)blocks, h->max_depth) * sizeof(int32_t) <= ((size_t)64 << 20) ? (int)blocks : 0;
+    const int segments = step_spread_segments(h->V.n_tokens);
+    const size_t per_row = advance_scratch_entries(segments, h->max_depth) * sizeof(int32_t);
+    int rows = 4 * h->n_compute_units / segments;
+    if (per_row > 0) rows = (int)std::min((size_t)rows, ((size_t)64 << 20) / per_row);
+    return rows;
+}
+// Blocks of the spread step for a batch, 0 where that form does not serve it.
+int spread_step_blocks(const pre3_handle *h, int batch) {
+    return batch <= spread_step_rows(h) ? batch * step_spread_segments(h->V.n_tokens) : 0;
+}
+
+// Bytes of the per-batch workspaces that serve `batch` AND every smaller batch (a smaller one may take a form that needs
+// more: one spill column per block of the spread step, partial results of more segments per row): rebinding to fewer
+// sequences never replaces a workspace.  topk 0: beyond 1 GiB, the call then reports PRE3_E_LIMIT.
+struct BatchWorkspaces { size_t adv, arrivals, argmax, topk, af_spill; };
+BatchWorkspaces batch_workspaces(const pre3_handle *h, int batch) {
+    const int spread_rows = std::min(batch, spread_step_rows(h));
+    BatchWorkspaces w;
+    w.adv = advance_scratch_entries(std::max(batch, spread_step_blocks(h, spread_rows)), h->max_depth) * sizeof(int32_t);
+    w.arrivals = (size_t)spread_rows * sizeof(StepArrivals);
+    w.argmax = masked_argmax_workspace_bytes(batch, h->V.n_tokens, h->n_compute_units);
+    w.topk = masked_topk_workspace_bytes(batch, h->V.n_tokens);
+    if (w.topk > (size_t)1 << 30) w.topk = 0;
+    w.af_spill = advance_fill_walk_spill_entries(batch, h->max_depth) * sizeof(int32_t);
+    return w;
 }
 
 }  // namespace
@@ -463,16 +486,14 @@ int pre3_bind_state(pre3_handle *h, int32_t *states, pre3_stacks stacks, int32_t
         return fail(h, PRE3_E_BADARG, "bind_state: null buffer, negative batch or cap outside 1..stack_cap");
     // per-batch workspaces: each is an allocation of its own that grows with the largest batch bound
     // so far; a superseded one is freed (hipFree waits until the device no longer uses it)
+    const BatchWorkspaces need = batch_workspaces(h, stacks.batch);
     hipError_t e;
     void *p = nullptr;
-    const int spread_blocks = spread_step_blocks(h, stacks.batch);
-    if ((e = grow_workspace(h->ws_adv, advance_scratch_entries(std::max(stacks.batch, spread_blocks), h->max_depth) * sizeof(int32_t), &p)) != hipSuccess)
-        return hip_fail(h, e, "allocate advance scratch");
+    if ((e = grow_workspace(h->ws_adv, need.adv, &p)) != hipSuccess) return hip_fail(h, e, "allocate advance scratch");
     h->adv_scratch = static_cast<int32_t *>(p);
-    if (spread_blocks > 0) {
+    if (need.arrivals > 0) {
         const size_t held = h->ws_arrivals.bytes;
-        if ((e = grow_workspace(h->ws_arrivals, (size_t)stacks.batch * sizeof(StepArrivals), &p)) != hipSuccess)
-            return hip_fail(h, e, "allocate step counters");
+        if ((e = grow_workspace(h->ws_arrivals, need.arrivals, &p)) != hipSuccess) return hip_fail(h, e, "allocate step counters");
         if (h->ws_arrivals.bytes != held) {             // new: the counters start at zero, on whatever stream the steps run
             e = hipMemset(p, 0, h->ws_arrivals.bytes);
             if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
@@ -480,20 +501,17 @@ int pre3_bind_state(pre3_handle *h, int32_t *states, pre3_stacks stacks, int32_t
         }
         h->arrivals = static_cast<StepArrivals *>(p);
     }
-    if ((e = grow_workspace(h->ws_argmax, masked_argmax_workspace_bytes(stacks.batch, h->V.n_tokens, h->n_compute_units), &p)) != hipSuccess)
-        return hip_fail(h, e, "allocate argmax workspace");
+    if ((e = grow_workspace(h->ws_argmax, need.argmax, &p)) != hipSuccess) return hip_fail(h, e, "allocate argmax workspace");
     h->argmax_best = static_cast<unsigned long long *>(p);
     // the top-k candidates: batch x segments x 64 words; a batch so large that this passes 1 GiB goes
     // without (pre3_apply_mask_topk then reports PRE3_E_LIMIT)
-    const size_t need_topk = masked_topk_workspace_bytes(stacks.batch, h->V.n_tokens);
-    h->topk_ready = need_topk <= ((size_t)1 << 30);
+    h->topk_ready = need.topk > 0;
     if (h->topk_ready) {
-        if ((e = grow_workspace(h->ws_topk, need_topk, &p)) != hipSuccess) return hip_fail(h, e, "allocate top-k workspace");
+        if ((e = grow_workspace(h->ws_topk, need.topk, &p)) != hipSuccess) return hip_fail(h, e, "allocate top-k workspace");
         h->topk_cand = static_cast<unsigned long long *>(p);
     }
     // private stacks of per-lane walks beside an advance (leftover tokens, jump-forward trials)
-    if ((e = grow_workspace(h->ws_af_spill, advance_fill_walk_spill_entries(stacks.batch, h->max_depth) * sizeof(int32_t), &p)) != hipSuccess)
-        return hip_fail(h, e, "allocate advance+fill spill area");
+    if ((e = grow_workspace(h->ws_af_spill, need.af_spill, &p)) != hipSuccess) return hip_fail(h, e, "allocate advance+fill spill area");
     h->af_walk_spill = static_cast<int32_t *>(p);
     h->b_states = states;
     h->b_stacks = stacks;
@@ -903,6 +921,14 @@ int pre3_symbol_edge_stats(const pre3_handle *h, int64_t out[4]) {
 
 // Every index a kernel follows in the compiled tables must stay inside its table: the kernels
 // themselves do not range-check table contents.  Returns the number of violations found.
+int pre3_debug_workspace_bytes(const pre3_handle *h, int32_t batch, int64_t *out) {
+    if (!h || !h->compiled || batch < 0 || !out) return PRE3_E_BADARG;
+    const BatchWorkspaces w = batch_workspaces(h, batch);
+    const size_t bytes[] = {w.adv, w.arrivals, w.argmax, w.topk, w.af_spill};
+    for (int i = 0; i < 5; ++i) out[i] = (int64_t)bytes[i];
+    return PRE3_OK;
+}
+
 int pre3_debug_validate_tables(const pre3_handle *h) {
     if (!h || !h->compiled) return PRE3_E_BADARG;
     int64_t bad = 0;

@@ -2,6 +2,7 @@
 // tokens.  Both read the [batch, vocab] bf16 logits once and write nothing back.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "argmax.hpp"
@@ -980,8 +981,10 @@ static int masked_argmax_segments(int batch, int vocab, int n_compute_units) {
     return n_seg < 1 ? 1 : n_seg;
 }
 
+// (for a batch of `batch` rows or fewer: fewer rows are split into more segments, at most units + rows in all)
 size_t masked_argmax_workspace_bytes(int batch, int vocab, int n_compute_units) {
-    return (size_t)batch * masked_argmax_segments(batch, vocab, n_compute_units) * sizeof(unsigned long long);
+    const size_t split = (size_t)batch * masked_argmax_segments(1, vocab, n_compute_units);
+    return std::min(split, (size_t)batch + n_compute_units) * sizeof(unsigned long long);
 }
 
 hipError_t launch_masked_argmax(const uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,

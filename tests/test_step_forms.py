@@ -65,3 +65,90 @@ def test_greedy_step_on_vocabularies_of_a_few_tokens(V, one_kernel):
         tokens = oracle_masked_argmax(host, mask, V)
         assert (tok_d.cpu().numpy() == tokens).all() and (err_d.cpu().numpy() == err).all(), s
         assert (s_d.cpu().numpy() == states).all() and (mask_d.cpu().numpy().view(np.uint32) == mask).all(), s
+
+
+def _nesting_vocab(n):
+    """n tokens of JSON text, the last one the end of sequence; some nest deep enough to spill a walk's private stack."""
+    from workloads.vocab import BASE_SEED, bpe_like_vocab
+    deep = [b"[" * 32, b"[" * 17 + b"1", b"{\"k\":" * 6, b"[" * 9 + b"]" * 9, b"[1," * 10, b"]" * 20]
+    return Vocab(bpe_like_vocab(n - len(deep), 16, BASE_SEED + n).tokens[:-1] + deep + [b""], n - 1)
+
+
+@pytest.mark.parametrize("V,compact", [(600, False), (8192, False), (20_003, False), (40_001, True), (128_256, False)])
+def test_a_smaller_batch_never_needs_a_larger_workspace(V, compact):
+    """Rebinding to fewer sequences must not replace (and free) a workspace that work recorded for the larger batch uses,
+    although the smaller batch may take a form with a spill column per block or more segments per row."""
+    from paper_2506_03887_amd import Pre3
+    v = _nesting_vocab(V)
+    lib = Pre3(G.JSON_RIGHT_RECURSIVE if compact else G.JSON, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, stack_cap=64,
+               compact_cycles=compact, host_only=True)
+    assert lib.walk_depth_bound > 16
+    sizes = [1, 2, 3, 7, 16, 31, 60, 64, 65, 85, 100, 128, 200, 255, 256, 257, 341, 342, 400, 512, 700, 1024, 1025, 1500, 2048, 5000]
+    held = [lib.workspace_bytes(b) for b in sizes]
+    for name in held[0]:
+        row = [h[name] for h in held]
+        assert row == sorted(row), (name, list(zip(sizes, row)))
+    seg, deep = -(-V // 8192), lib.walk_depth_bound - 16
+    for b, h in zip(sizes, held):                       # enough for the batch in whichever form it runs
+        blocks = b * seg if b * seg <= 1024 else 0
+        assert h["advance_spill"] >= 4 * deep * max(b, blocks) and h["walk_spill"] >= 4 * deep * 64 * b
+        assert h["step_counters"] >= 16 * (b if blocks else 0) and h["argmax"] >= 8 * b
+
+
+@pytest.mark.gpu
+def test_a_graph_of_a_larger_batch_outlives_rebinding_to_a_smaller_one():
+    """400 rows (20,003 tokens: the two launches) recorded, then 200 rows bound (spread over 600 blocks, more spill columns
+    than 400) and stepped: the replay on the 400 rows' buffers gives the oracle's states, stacks, masks and tokens."""
+    import torch
+    from paper_2506_03887_amd import Pre3
+    dev = torch.device("cuda:0")
+    v, o, cap = _nesting_vocab(20_003), Oracle(G.JSON), 64
+    lib = Pre3(G.JSON, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, stack_cap=cap)
+    rng = np.random.default_rng(11)
+
+    def batch(B):
+        h = dict(states=np.full(B, o.initial_state(0), np.int32), length=np.ones(B, np.int32), data=np.zeros((B, cap), np.int32))
+        h["data"][:, 0] = h["states"]
+        d = {k: torch.from_numpy(x.copy()).to(dev) for k, x in h.items()}
+        d.update(err=torch.zeros(B, dtype=torch.int32, device=dev), tok=torch.full((B,), -1, dtype=torch.int32, device=dev),
+                 mask=torch.zeros((B, v.words), dtype=torch.int32, device=dev),
+                 logits=torch.zeros((B, v.n_tokens), dtype=torch.bfloat16, device=dev))
+        lib.bind_state(d["states"], d["data"], d["length"], d["err"])
+        return h, d
+
+    def step(d):
+        lib.advance_fill_argmax(d["tok"], d["mask"], d["logits"], d["tok"])
+
+    def check(h, d, tokens, run):
+        """One step from `tokens` (deep ones among them: private stacks that spill) through run()."""
+        B = len(tokens)
+        host = bf16_logits(rng, B, v.n_tokens)
+        d["logits"].copy_(torch.from_numpy(host.view(np.int16)).to(dev).view(torch.bfloat16))
+        d["tok"].copy_(torch.from_numpy(tokens))
+        run()
+        torch.cuda.synchronize()
+        err = o.advance_batch(h["states"], h["data"], h["length"], tokens, v)
+        mask = o.fill_mask(h["states"], h["data"], h["length"], v)
+        assert (d["err"].cpu().numpy() == err).all() and (d["states"].cpu().numpy() == h["states"]).all()
+        live = np.arange(cap)[None, :] < h["length"][:, None]
+        assert (d["data"].cpu().numpy()[live] == h["data"][live]).all()
+        assert (d["mask"].cpu().numpy().view(np.uint32) == mask).all()
+        want = oracle_masked_argmax(host, mask, v.n_tokens)
+        assert (d["tok"].cpu().numpy() == want).all()
+        return want
+
+    def some_tokens(B):
+        return rng.choice([-1, *range(v.n_tokens - 7, v.n_tokens - 1), *rng.integers(0, v.n_tokens, 4)], size=B).astype(np.int32)
+
+    big_h, big_d = batch(400)
+    check(big_h, big_d, some_tokens(400), lambda: step(big_d))
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        step(big_d)
+    small_h, small_d = batch(200)
+    junk = [torch.full((1 << 18,), 0x7FFFFFFF, dtype=torch.int32, device=dev) for _ in range(16)]     # whoever takes freed memory
+    for s in range(4):
+        check(small_h, small_d, some_tokens(200), lambda: step(small_d))
+        check(big_h, big_d, some_tokens(400), graph.replay)
+    assert all(int((x != 0x7FFFFFFF).sum()) == 0 for x in junk)
