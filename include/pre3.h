@@ -151,7 +151,7 @@ int32_t pre3_initial_state(const pre3_handle *h, int32_t grammar_idx);
  * workspace (hipFree: waits for the device to go idle) and allocates the larger one, so a server
  * that resizes its batch does not accumulate device memory.  Work that was recorded into a HIP
  * graph before such a growing rebind points at the freed workspace and must be recorded again.
- * Errors: BADARG, HIP (allocation failed). */
+ * Errors: BADARG (the previous binding stays), HIP (allocation failed: nothing is bound). */
 int pre3_bind_state(pre3_handle *h, int32_t *states, pre3_stacks stacks, int32_t *err);
 
 /* Token mask of one decode step (Sec. 1: every token whose bytes leave the language of

@@ -130,7 +130,9 @@ hipError_t device_alloc(pre3_handle *h, size_t bytes, void **out, bool zero) {
 
 // Makes `w` hold at least `need` bytes: kept if large enough, else freed and allocated anew, so a
 // handle holds one workspace of each kind, sized for the largest batch bound so far.
-hipError_t grow_workspace(pre3_handle::Workspace &w, size_t need, void **out) {
+template <typename T>
+hipError_t grow_workspace(pre3_handle::Workspace &w, size_t need, T **out) {
+    *out = nullptr;
     if (need > w.bytes || !w.p) {
         if (w.p) { (void)hipFree(w.p); w.p = nullptr; w.bytes = 0; }
         const size_t bytes = need < 256 ? 256 : need;
@@ -138,7 +140,7 @@ hipError_t grow_workspace(pre3_handle::Workspace &w, size_t need, void **out) {
         if (e != hipSuccess) { w.p = nullptr; return e; }
         w.bytes = bytes;
     }
-    *out = w.p;
+    *out = static_cast<T *>(w.p);
     return hipSuccess;
 }
 
@@ -486,33 +488,32 @@ int pre3_bind_state(pre3_handle *h, int32_t *states, pre3_stacks stacks, int32_t
         return fail(h, PRE3_E_BADARG, "bind_state: null buffer, negative batch or cap outside 1..stack_cap");
     // per-batch workspaces: each is an allocation of its own that grows with the largest batch bound
     // so far; a superseded one is freed (hipFree waits until the device no longer uses it)
+    // A failure leaves nothing bound: the workspaces of the earlier binding may be gone.
+    h->b_states = h->b_err = nullptr;
+    h->b_stacks = {};
     const BatchWorkspaces need = batch_workspaces(h, stacks.batch);
+    auto failed = [&](hipError_t e, const char *what) {
+        (void)hipGetLastError();                        // (the next launch would report it)
+        return hip_fail(h, e, what);
+    };
     hipError_t e;
-    void *p = nullptr;
-    if ((e = grow_workspace(h->ws_adv, need.adv, &p)) != hipSuccess) return hip_fail(h, e, "allocate advance scratch");
-    h->adv_scratch = static_cast<int32_t *>(p);
+    if ((e = grow_workspace(h->ws_adv, need.adv, &h->adv_scratch)) != hipSuccess) return failed(e, "allocate advance scratch");
     if (need.arrivals > 0) {
         const size_t held = h->ws_arrivals.bytes;
-        if ((e = grow_workspace(h->ws_arrivals, need.arrivals, &p)) != hipSuccess) return hip_fail(h, e, "allocate step counters");
+        if ((e = grow_workspace(h->ws_arrivals, need.arrivals, &h->arrivals)) != hipSuccess) return failed(e, "allocate step counters");
         if (h->ws_arrivals.bytes != held) {             // new: the counters start at zero, on whatever stream the steps run
-            e = hipMemset(p, 0, h->ws_arrivals.bytes);
+            e = hipMemset(h->arrivals, 0, h->ws_arrivals.bytes);
             if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-            if (e != hipSuccess) { (void)hipFree(p); h->ws_arrivals = {}; h->arrivals = nullptr; return hip_fail(h, e, "clear step counters"); }
+            if (e != hipSuccess) { (void)hipFree(h->arrivals); h->ws_arrivals = {}; h->arrivals = nullptr; return failed(e, "clear step counters"); }
         }
-        h->arrivals = static_cast<StepArrivals *>(p);
     }
-    if ((e = grow_workspace(h->ws_argmax, need.argmax, &p)) != hipSuccess) return hip_fail(h, e, "allocate argmax workspace");
-    h->argmax_best = static_cast<unsigned long long *>(p);
+    if ((e = grow_workspace(h->ws_argmax, need.argmax, &h->argmax_best)) != hipSuccess) return failed(e, "allocate argmax workspace");
     // the top-k candidates: batch x segments x 64 words; a batch so large that this passes 1 GiB goes
     // without (pre3_apply_mask_topk then reports PRE3_E_LIMIT)
     h->topk_ready = need.topk > 0;
-    if (h->topk_ready) {
-        if ((e = grow_workspace(h->ws_topk, need.topk, &p)) != hipSuccess) return hip_fail(h, e, "allocate top-k workspace");
-        h->topk_cand = static_cast<unsigned long long *>(p);
-    }
+    if (h->topk_ready && (e = grow_workspace(h->ws_topk, need.topk, &h->topk_cand)) != hipSuccess) return failed(e, "allocate top-k workspace");
     // private stacks of per-lane walks beside an advance (leftover tokens, jump-forward trials)
-    if ((e = grow_workspace(h->ws_af_spill, need.af_spill, &p)) != hipSuccess) return hip_fail(h, e, "allocate advance+fill spill area");
-    h->af_walk_spill = static_cast<int32_t *>(p);
+    if ((e = grow_workspace(h->ws_af_spill, need.af_spill, &h->af_walk_spill)) != hipSuccess) return failed(e, "allocate advance+fill spill area");
     h->b_states = states;
     h->b_stacks = stacks;
     h->b_err = err;

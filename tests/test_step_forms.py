@@ -152,3 +152,42 @@ def test_a_graph_of_a_larger_batch_outlives_rebinding_to_a_smaller_one():
         check(small_h, small_d, some_tokens(200), lambda: step(small_d))
         check(big_h, big_d, some_tokens(400), graph.replay)
     assert all(int((x != 0x7FFFFFFF).sum()) == 0 for x in junk)
+
+
+@pytest.mark.gpu
+def test_a_bind_that_fails_leaves_nothing_bound():
+    """A batch whose workspaces exceed the device's memory is refused by the allocator; the calls on the handle then report
+    that nothing is bound instead of running on the workspaces that the attempt released, and the next bind works."""
+    import torch
+    from paper_2506_03887_amd import Pre3, binding
+    dev = torch.device("cuda:0")
+    v, o, B, cap = _nesting_vocab(3000), Oracle(G.JSON), 6, 64
+    lib = Pre3(G.JSON, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, stack_cap=cap)
+    s0 = lib.initial_state(0)
+    s_d, err_d = torch.full((B,), s0, dtype=torch.int32, device=dev), torch.zeros(B, dtype=torch.int32, device=dev)
+    d_d, l_d = torch.full((B, cap), s0, dtype=torch.int32, device=dev), torch.ones(B, dtype=torch.int32, device=dev)
+    tok = torch.full((B,), v.tokens.index(b"[" * 17 + b"1"), dtype=torch.int32, device=dev)
+    out, mask = torch.full_like(tok, -7), torch.zeros((B, v.words), dtype=torch.int32, device=dev)
+    logits = torch.zeros((B, v.n_tokens), dtype=torch.bfloat16, device=dev)
+    ids, jumped = torch.full((B, 4), -7, dtype=torch.int32, device=dev), torch.zeros((B, 8), dtype=torch.uint8, device=dev)
+    lib.bind_state(s_d, d_d, l_d, err_d)
+    too_many = 2 ** 31 - 1
+    assert lib.workspace_bytes(too_many)["advance_spill"] > torch.cuda.get_device_properties(0).total_memory
+    stacks = binding._Stacks(d_d.data_ptr(), l_d.data_ptr(), cap, too_many)       # the buffers are not read: no memory for the workspaces
+    assert binding.load().pre3_bind_state(lib._h, s_d.data_ptr(), stacks, err_d.data_ptr()) == binding.E_HIP
+    for call in (lambda: lib.advance(tok), lambda: lib.advance_fill_mask(tok, mask), lambda: lib.advance_fill_apply_mask(tok, mask, logits),
+                 lambda: lib.advance_fill_argmax(tok, mask, logits, out), lambda: lib.apply_mask_argmax(logits, mask, out),
+                 lambda: lib.apply_mask_topk(logits, mask, ids), lambda: lib.jump_forward(jumped, out), lambda: lib.step_is_one_kernel(logits)):
+        with pytest.raises(binding.Pre3Error) as e:
+            call()
+        assert e.value.status == binding.E_BADARG
+    torch.cuda.synchronize()
+    assert int((out != -7).sum()) == 0 and int((s_d != s0).sum()) == 0 and int((l_d != 1).sum()) == 0
+    lib.fill_apply_mask(s_d, d_d, l_d, mask, logits)                              # needs no binding
+    want = o.fill_mask(np.full(B, s0, np.int32), np.full((B, cap), s0, np.int32), np.ones(B, np.int32), v)
+    assert (mask.cpu().numpy().view(np.uint32) == want).all()
+    lib.bind_state(s_d, d_d, l_d, err_d)
+    lib.advance(tok)
+    rc, stack = o.advance([s0], b"[" * 17 + b"1")
+    assert rc == 0 and (l_d.cpu().numpy() == len(stack)).all() and int(err_d.abs().sum()) == 0
+    assert (d_d[:, : len(stack)].cpu().numpy() == np.array(stack)[None, :]).all()
