@@ -417,10 +417,7 @@ def main(argv=None):
     # =========================== headline: the step, then the dominant kernel ===========================
     step_kind = {"two-call": "fill+apply", "fused": "fused", "advance-fill": "advance-fill", "one-call": "one-call"}[args.step]
     step_launches = lib.step_kernel_launches(logits[0]) if step_kind == "one-call" else 0
-    # a batch whose rows, in blocks of 8,192 tokens, fill the chip at most four to a compute unit is spread over blocks
-    spread = (step_kind == "one-call" and
-              B * -(-V // 8192) <= 4 * torch.cuda.get_device_properties(0).multi_processor_count)
-    step_launches = 1 if spread else step_launches
+    spread = step_kind == "one-call" and lib.step_form(logits[0]) == "spread"
     if step_kind == "one-call" and step_launches == 0:
         # outside the batch sizes (or vocabulary) of the one kernel the call is pre3_advance_fill_mask + pre3_apply_mask:
         # time and label those
@@ -487,7 +484,8 @@ def main(argv=None):
         fused_us, _ = eager_pass("fused")
         # the call takes one of three forms by the batch size (the figures below are those of the whole call)
         units = torch.cuda.get_device_properties(0).multi_processor_count
-        dom_name = ("advance_fill_apply_kernel (without the advance)" if lib.step_kernel_launches(logits[0]) == 1 else
+        dom_name = ("advance_fill_apply_kernel (without the advance)"
+                    if 4 * B >= units and lib.step_kernel_launches(logits[0], one_kernel=True) == 1 else
                     "fill_mask_edges_kernel<false> + apply_mask_vec8_kernel" if B > units else "fill_mask_edges_kernel<true>")
         dom_bytes = BYTES_PER_PAIR * pairs
         dom_us = float(fused_us["fill_apply_mask"].mean())
@@ -815,7 +813,8 @@ def main(argv=None):
         return {"step": "pre3_apply_mask_argmax + pre3_advance_fill_mask, K steps in one HIP graph, tokens chosen on the device",
                 "one_call_step": "pre3_advance_fill_argmax (one launch per step where the batch size allows), K steps in one HIP graph",
                 "one_call_us_per_step": one_call_us, "one_call_tokens_per_s": pairs / (one_call_us * 1e-6),
-                "one_call_kernel_launches": lib.step_kernel_launches(logits[0]),
+                "one_call_form": lib.step_form(logits[0], greedy=True),
+                "one_call_kernel_launches": lib.step_kernel_launches(logits[0], greedy=True),
                 "us_per_step": step_us_g, "tokens_per_s": pairs / (step_us_g * 1e-6),
                 "argmax_launch_us": argmax_us, "argmax_algorithmic_bytes": nbytes,
                 "argmax_achieved_GBs": nbytes / (argmax_us * 1e-6) / 1e9,

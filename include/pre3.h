@@ -276,11 +276,12 @@ int pre3_advance_fill_apply_mask(pre3_handle *h, const int32_t *tokens, uint32_t
 int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bitmask, const uint16_t *logits_bf16,
                              int64_t row_stride, int32_t *out_tokens, int32_t flags, pre3_stream stream);
 
-/* Which form pre3_advance_fill_apply_mask takes for the bound batch and these logits: 0 = the two
- * calls, n >= 1 = the one kernel, launched n times on equal shares of the batch (n = 1 up to one
- * sequence per compute unit); a small batch that is spread over blocks (one launch) answers as if it
- * were not; BADARG if nothing is bound.  pre3_advance_fill_argmax takes the same
- * form for vocabularies of at most 153,600 tokens.  Host call, launches nothing. */
+/* Which form pre3_advance_fill_apply_mask -- with PRE3_STEP_GREEDY among the flags pre3_advance_fill_argmax -- takes
+ * for the bound batch and these logits: 0 = the two calls; n >= 1 = the one kernel, launched n times
+ * on equal shares of the batch (n = 1 up to one sequence per compute unit); PRE3_STEP_IS_SPREAD | 1 =
+ * every row spread over blocks, one launch; BADARG if nothing is bound.  Host call, launches nothing. */
+#define PRE3_STEP_GREEDY 4               /* of this query only */
+#define PRE3_STEP_IS_SPREAD 0x40000000
 int32_t pre3_step_is_one_kernel(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride, int32_t flags);
 
 /* Greedy sampling fused behind the mask (Sec. 1: invalid tokens are excluded, then a token is

@@ -23,6 +23,8 @@ FLAG_COMPACT_CYCLES = 8
 FLAG_NO_TOKEN_EFFECTS = 16
 ADVANCE_RESTART_ON_EOS = 1
 STEP_ONE_KERNEL = 2
+STEP_GREEDY = 4
+STEP_IS_SPREAD = 0x40000000
 STATE_DONE = -1
 
 EXPORTS = [
@@ -367,13 +369,23 @@ class Pre3:
                                                        (ADVANCE_RESTART_ON_EOS if restart_on_eos else 0) |
                                                        (STEP_ONE_KERNEL if one_kernel else 0), _stream_ptr(stream)))
 
-    def step_kernel_launches(self, logits, one_kernel=False):
-        """0 if advance_fill_apply_mask is two calls for the bound batch and these logits, else the number of launches
-        of its one kernel (1 up to one sequence per compute unit, equal shares of the batch beyond)."""
-        rc = self._lib.pre3_step_is_one_kernel(self._h, _dev(logits, "u16"), logits.stride(0), STEP_ONE_KERNEL if one_kernel else 0)
+    def _step_form(self, logits, one_kernel, greedy):
+        rc = self._lib.pre3_step_is_one_kernel(self._h, _dev(logits, "u16"), logits.stride(0),
+                                               (STEP_ONE_KERNEL if one_kernel else 0) | (STEP_GREEDY if greedy else 0))
         if rc < 0:
             raise Pre3Error(rc, "step_is_one_kernel")
         return rc
+
+    def step_form(self, logits, one_kernel=False, greedy=False):
+        """The form advance_fill_apply_mask (greedy: advance_fill_argmax) takes for the bound batch and these logits:
+        "two calls", "one kernel" (a sequence per compute unit) or "spread" (every row over several blocks)."""
+        rc = self._step_form(logits, one_kernel, greedy)
+        return "two calls" if rc == 0 else "spread" if rc & STEP_IS_SPREAD else "one kernel"
+
+    def step_kernel_launches(self, logits, one_kernel=False, greedy=False):
+        """0 if the step call is two calls for the bound batch and these logits, else the number of launches of its kernel
+        (1 up to one sequence per compute unit and in the spread form, equal shares of the batch beyond)."""
+        return self._step_form(logits, one_kernel, greedy) & ~STEP_IS_SPREAD
 
     def step_is_one_kernel(self, logits, one_kernel=False):
         """Whether advance_fill_apply_mask runs as one kernel for the bound batch and these logits."""

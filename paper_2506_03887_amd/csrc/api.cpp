@@ -643,19 +643,48 @@ int pre3_advance_fill_mask(pre3_handle *h, const int32_t *tokens, uint32_t *bitm
 }
 
 namespace {
-// Whether the step call takes its one-kernel form: asked for or a suitable batch size, and the kernel's conditions.
-bool step_takes_one_kernel(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride, int32_t flags, bool greedy) {
-    const int batch = h->b_stacks.batch;
+// Whether the one-kernel form can serve the bound batch: its conditions on the logits, the vocabulary and the tables.
+bool one_kernel_serves(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride, bool greedy) {
     const bool cycles = h->compact && h->T.n_cycles > 0;
-    const bool wanted = (flags & PRE3_STEP_ONE_KERNEL) || step_kernel_batch(h, batch);
-    return wanted && h->use_edges && reinterpret_cast<uintptr_t>(logits_bf16) % 16 == 0 && row_stride % 8 == 0 &&
+    return h->use_edges && reinterpret_cast<uintptr_t>(logits_bf16) % 16 == 0 && row_stride % 8 == 0 &&
            row_stride >= h->V.n_tokens && advance_fill_apply_fits(h->V.n_tokens, h->V.n_words, h->b_stacks.cap, cycles, greedy);
+}
+
+// The form a step call takes for the bound batch: both calls and the query that reports it go by this.
+enum class StepForm { kTwoCalls, kOneKernel, kSpread };
+StepForm step_form(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride, int32_t flags, bool greedy) {
+    const int batch = h->b_stacks.batch;
+    const bool asked = flags & PRE3_STEP_ONE_KERNEL;
+    const bool one_kernel = (asked || step_kernel_batch(h, batch)) && one_kernel_serves(h, logits_bf16, row_stride, greedy);
+    // The blocks of a spread row meet through atomics to choose the token, which costs more the more of them there are: from
+    // half a row per compute unit on the one kernel is the better form where it serves the logits (250 x 32,000: 12.8
+    // against 14.3 us; 64 x 32,000: 13.1 against 11.6 us).
+    if (!asked && spread_step_blocks(h, batch) > 0 && !(greedy && one_kernel && 2 * batch >= h->n_compute_units)) return StepForm::kSpread;
+    return one_kernel ? StepForm::kOneKernel : StepForm::kTwoCalls;
+}
+
+// The step as one launch (or launches of equal shares) in the form that step_form chose; out_tokens: the greedy step.
+hipError_t launch_step(pre3_handle *h, StepForm form, const int32_t *tokens, uint32_t *bitmask, uint16_t *logits_bf16, int64_t row_stride,
+                       int32_t *out_tokens, int32_t flags, hipStream_t s) {
+    const bool cycles = h->compact && h->T.n_cycles > 0;
+    const int restart = (flags & PRE3_ADVANCE_RESTART_ON_EOS) ? 1 : 0;
+    const int32_t *head = cycles ? h->cycle_head : nullptr, *pool = cycles ? h->cycle_pool : nullptr;
+    const pre3_stacks &st = h->b_stacks;
+    if (form == StepForm::kSpread)
+        return launch_step_spread(h->dev, h->dev_edges, tokens, h->b_states, st.data, st.len, st.cap, st.batch, h->b_err, bitmask, restart,
+                                  h->adv_scratch, h->af_walk_spill, head, pool, logits_bf16, row_stride, out_tokens, h->arrivals, s);
+    return launch_advance_fill_apply(h->dev, h->dev_edges, tokens, h->b_states, st.data, st.len, st.cap, st.batch, h->b_err, bitmask,
+                                     restart, h->adv_scratch, h->af_walk_spill, head, pool, logits_bf16, row_stride, out_tokens,
+                                     h->n_compute_units, s);
 }
 }  // namespace
 
 int32_t pre3_step_is_one_kernel(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride, int32_t flags) {
     if (!usable(h) || (!h->b_states && !h->bound_empty)) return PRE3_E_BADARG;
-    if (h->bound_empty || !step_takes_one_kernel(h, logits_bf16, row_stride, flags, false)) return 0;
+    if (h->bound_empty || row_stride < h->V.n_tokens || reinterpret_cast<uintptr_t>(logits_bf16) % 2 != 0) return 0;   // (the call refuses such logits)
+    const StepForm form = step_form(h, logits_bf16, row_stride, flags, flags & PRE3_STEP_GREEDY);
+    if (form == StepForm::kTwoCalls) return 0;
+    if (form == StepForm::kSpread) return PRE3_STEP_IS_SPREAD | 1;
     // launches of equal shares, counted as the launcher deals them out
     const int batch = h->b_stacks.batch, most = (batch + h->n_compute_units - 1) / h->n_compute_units;
     const int share = (batch + most - 1) / most;
@@ -671,21 +700,9 @@ int pre3_advance_fill_apply_mask(pre3_handle *h, const int32_t *tokens, uint32_t
     if (flags & ~(PRE3_ADVANCE_RESTART_ON_EOS | PRE3_STEP_ONE_KERNEL)) return fail(h, PRE3_E_BADARG, "advance_fill_apply_mask: unknown flag");
     if (row_stride < h->V.n_tokens) return fail(h, PRE3_E_BADARG, "advance_fill_apply_mask: row stride below vocabulary size");
     if (reinterpret_cast<uintptr_t>(logits_bf16) % 2 != 0) return fail(h, PRE3_E_BADARG, "advance_fill_apply_mask: misaligned logits");
-    const bool cycles = h->compact && h->T.n_cycles > 0;
-    if (!(flags & PRE3_STEP_ONE_KERNEL) && spread_step_blocks(h, h->b_stacks.batch) > 0) {
-        hipError_t e = launch_step_spread(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,
-                                          h->b_stacks.batch, h->b_err, bitmask, flags & PRE3_ADVANCE_RESTART_ON_EOS, h->adv_scratch,
-                                          h->af_walk_spill, cycles ? h->cycle_head : nullptr, cycles ? h->cycle_pool : nullptr,
-                                          logits_bf16, row_stride, nullptr, h->arrivals, static_cast<hipStream_t>(stream));
-        return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_fill_apply_mask");
-    }
-    if (step_takes_one_kernel(h, logits_bf16, row_stride, flags, false)) {
-        const int restart = (flags & PRE3_ADVANCE_RESTART_ON_EOS) ? 1 : 0;
-        hipError_t e = launch_advance_fill_apply(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len,
-                                                 h->b_stacks.cap, h->b_stacks.batch, h->b_err, bitmask, restart, h->adv_scratch,
-                                                 h->af_walk_spill, cycles ? h->cycle_head : nullptr,
-                                                 cycles ? h->cycle_pool : nullptr, logits_bf16, row_stride, nullptr,
-                                                 h->n_compute_units, static_cast<hipStream_t>(stream));
+    const StepForm form = step_form(h, logits_bf16, row_stride, flags, false);
+    if (form != StepForm::kTwoCalls) {
+        hipError_t e = launch_step(h, form, tokens, bitmask, logits_bf16, row_stride, nullptr, flags, static_cast<hipStream_t>(stream));
         return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_fill_apply_mask");
     }
     const int rc = pre3_advance_fill_mask(h, tokens, bitmask, flags & PRE3_ADVANCE_RESTART_ON_EOS, stream);
@@ -704,29 +721,11 @@ int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bi
     if (flags & ~(PRE3_ADVANCE_RESTART_ON_EOS | PRE3_STEP_ONE_KERNEL)) return fail(h, PRE3_E_BADARG, "advance_fill_argmax: unknown flag");
     if (row_stride < h->V.n_tokens) return fail(h, PRE3_E_BADARG, "advance_fill_argmax: row stride below vocabulary size");
     if (reinterpret_cast<uintptr_t>(logits_bf16) % 2 != 0) return fail(h, PRE3_E_BADARG, "advance_fill_argmax: misaligned logits");
-    // The blocks of a spread row meet through atomics to choose the token, which costs more the more of them there are: from
-    // half a row per compute unit on the one kernel is the better form where it serves the logits (250 x 32,000: 12.8
-    // against 14.3 us; 64 x 32,000: 13.1 against 11.6 us).
-    const bool one_kernel = step_takes_one_kernel(h, logits_bf16, row_stride, flags, true);
-    if (!(flags & PRE3_STEP_ONE_KERNEL) && spread_step_blocks(h, h->b_stacks.batch) > 0 &&
-        !(one_kernel && 2 * h->b_stacks.batch >= h->n_compute_units)) {
-        const bool cycles = h->compact && h->T.n_cycles > 0;
-        hipError_t e = launch_step_spread(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,
-                                          h->b_stacks.batch, h->b_err, bitmask, flags & PRE3_ADVANCE_RESTART_ON_EOS, h->adv_scratch,
-                                          h->af_walk_spill, cycles ? h->cycle_head : nullptr, cycles ? h->cycle_pool : nullptr,
-                                          const_cast<uint16_t *>(logits_bf16), row_stride, out_tokens, h->arrivals,
-                                          static_cast<hipStream_t>(stream));
-        return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_fill_argmax");
-    }
-    if (one_kernel) {
-        const bool cycles = h->compact && h->T.n_cycles > 0;
-        const int restart = (flags & PRE3_ADVANCE_RESTART_ON_EOS) ? 1 : 0;
-        // the kernel only reads the logits in this form
-        hipError_t e = launch_advance_fill_apply(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len,
-                                                 h->b_stacks.cap, h->b_stacks.batch, h->b_err, bitmask, restart, h->adv_scratch,
-                                                 h->af_walk_spill, cycles ? h->cycle_head : nullptr,
-                                                 cycles ? h->cycle_pool : nullptr, const_cast<uint16_t *>(logits_bf16), row_stride,
-                                                 out_tokens, h->n_compute_units, static_cast<hipStream_t>(stream));
+    const StepForm form = step_form(h, logits_bf16, row_stride, flags, true);
+    if (form != StepForm::kTwoCalls) {
+        // (the logits are only read in the greedy forms)
+        hipError_t e = launch_step(h, form, tokens, bitmask, const_cast<uint16_t *>(logits_bf16), row_stride, out_tokens, flags,
+                                   static_cast<hipStream_t>(stream));
         return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_fill_argmax");
     }
     const int rc = pre3_advance_fill_mask(h, tokens, bitmask, flags & PRE3_ADVANCE_RESTART_ON_EOS, stream);

@@ -191,3 +191,50 @@ def test_a_bind_that_fails_leaves_nothing_bound():
     rc, stack = o.advance([s0], b"[" * 17 + b"1")
     assert rc == 0 and (l_d.cpu().numpy() == len(stack)).all() and int(err_d.abs().sum()) == 0
     assert (d_d[:, : len(stack)].cpu().numpy() == np.array(stack)[None, :]).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V,options,expect", [
+    # rows of 1, 3 and 5 blocks of 8,192 tokens; four blocks per compute unit are the limit of the spread form
+    (8192, {}, {4: "spread", 256: "spread", 257: "spread", 1024: "spread", 1025: "two calls"}),
+    (20_003, {}, {1: "spread", 341: "spread", 342: "two calls"}),
+    (40_001, {}, {4: "spread", 63: "spread", 204: "spread", 205: "one kernel", 256: "one kernel", 257: "two calls"}),
+    (40_001, dict(row_threshold=64), {4: "two calls", 63: "two calls", 64: "one kernel", 256: "one kernel"}),       # id lists
+    (40_001, dict(token_edges=False), {4: "two calls", 64: "two calls"})])
+def test_the_query_names_the_kernel_that_runs(V, options, expect):
+    """step_form against the names of the kernels that the two step calls launch, at both sides of every line of the rule;
+    rows at 16-byte boundaries and rows one logit off them (which the one kernel does not serve)."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    from paper_2506_03887_amd import Pre3
+    dev = torch.device("cuda:0")
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    v = _nesting_vocab(V)
+    lib = Pre3(G.JSON, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, stack_cap=16, **options)
+    stride = -(-V // 8) * 8
+    for B, form in expect.items():
+        s0 = lib.initial_state(0)
+        keep = (torch.full((B,), s0, dtype=torch.int32, device=dev), torch.full((B, 16), s0, dtype=torch.int32, device=dev),
+                torch.ones(B, dtype=torch.int32, device=dev), torch.zeros(B, dtype=torch.int32, device=dev))
+        lib.bind_state(*keep)
+        mask = torch.zeros((B, v.words), dtype=torch.int32, device=dev)
+        flat = torch.zeros(B * stride + 8, dtype=torch.int16, device=dev)
+        tok = torch.full((B,), -1, dtype=torch.int32, device=dev)
+        for off in (0, 1):
+            logits = flat[off: off + B * stride].view(B, stride)
+            for greedy in (False, True):
+                want = form if form != "one kernel" or off == 0 else "two calls"
+                # the greedy step takes the one kernel from half a row per compute unit on, where that serves the logits
+                if greedy and form == "spread" and off == 0 and 128 <= B <= 256:
+                    want = "one kernel"
+                assert lib.step_form(logits, greedy=greedy) == want, (B, off, greedy)
+                run = (lambda: lib.advance_fill_argmax(tok, mask, logits, torch.empty_like(tok))) if greedy else \
+                    (lambda: lib.advance_fill_apply_mask(tok, mask, logits))
+                run()
+                torch.cuda.synchronize()
+                with profile(activities=[ProfilerActivity.CUDA]) as prof:
+                    run()
+                    torch.cuda.synchronize()
+                names = " ".join(e.key for e in prof.key_averages())
+                ran = "spread" if "step_spread_kernel" in names else "one kernel" if "advance_fill_apply_kernel" in names else "two calls"
+                assert ran == want, (B, off, greedy, names)
