@@ -238,3 +238,92 @@ def test_the_query_names_the_kernel_that_runs(V, options, expect):
                 names = " ".join(e.key for e in prof.key_averages())
                 ran = "spread" if "step_spread_kernel" in names else "one kernel" if "advance_fill_apply_kernel" in names else "two calls"
                 assert ran == want, (B, off, greedy, names)
+
+
+def _bound(lib, B, cap):
+    """Buffers of B sequences at their start, bound to lib: (states, length, data) and the mask and token buffers."""
+    import torch
+    dev = torch.device("cuda:0")
+    states = torch.full((B,), lib.initial_state(0), dtype=torch.int32, device=dev)
+    data = torch.zeros((B, cap), dtype=torch.int32, device=dev)
+    data[:, 0] = states
+    length, err = torch.ones(B, dtype=torch.int32, device=dev), torch.zeros(B, dtype=torch.int32, device=dev)
+    lib.bind_state(states, data, length, err)
+    return (states, length, data, err), torch.zeros((B, lib.words), dtype=torch.int32, device=dev), \
+        torch.full((B,), -1, dtype=torch.int32, device=dev)
+
+
+def _graph_us(call, n=8, rounds=5):
+    """us per call, the fastest of a few replays of n calls in a graph."""
+    import torch
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(n):
+            call()
+    best = float("inf")
+    for _ in range(rounds + 2):
+        a, b = torch.cuda.Event(True), torch.cuda.Event(True)
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / n)
+    return best
+
+
+@pytest.mark.gpu
+def test_values_the_keys_cannot_decide_meet_across_the_blocks_of_a_row():
+    """Zeros of either sign and NaN patterns on top of one block of a row (three blocks of 8,192 tokens), with equal, larger
+    or no values in the others."""
+    import torch
+    from paper_2506_03887_amd import Pre3
+    dev = torch.device("cuda:0")
+    v, o, B = _nesting_vocab(20_003), Oracle(G.JSON), 16
+    V = v.n_tokens
+    lib = Pre3(G.JSON, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, stack_cap=16)
+    (states, length, data, _), mask_d, tok = _bound(lib, B, 16)
+    mask = o.fill_mask(states.cpu().numpy(), data.cpu().numpy(), length.cpu().numpy(), v)
+    ids = np.flatnonzero((mask[0][np.arange(V) >> 5] >> (np.arange(V) & 31).astype(np.uint32)) & 1)
+    part = [ids[ids // 8192 == i] for i in range(3)]
+    assert all(len(p) > 4 for p in part)
+    host = np.full((B, V), 0xBF80, np.uint16)                                # -1
+    host[0, part[1][2]], host[0, part[2][1]] = 0x8000, 0x0000                # -0 before +0
+    host[1, part[1][2]], host[1, part[2][1]] = 0x0000, 0x8000                # +0 before -0
+    host[2, part[0][3]], host[2, part[0][1]], host[2, part[1][0]] = 0x0000, 0x8000, 0x0000
+    host[3, part[0]], host[3, part[1][3]] = 0x7FC1, 0x3F80                   # NaN around one value in another block
+    host[4] = 0x7FC1                                                         # ... around -inf in the last
+    host[4, part[2][2]] = 0xFF80
+    host[5, part[0][0]], host[5, part[2][0]] = 0x0000, 0x3F80                # a zero beaten by another block
+    host[6] = 0x7FC1                                                         # nothing but NaN
+    host[7], host[7, part[2]] = 0xFF80, 0x8000                               # -inf, then zeros in the last block only
+    host[8, part[1][1]], host[8, part[1][0]] = 0x7FC1, 0x0000
+    host[9, part[2]] = np.where(np.arange(len(part[2])) % 2, 0x0000, 0x8000)
+    host[10:] = bf16_logits(np.random.default_rng(3), B - 10, V)
+    logits = torch.from_numpy(host.view(np.int16)).to(dev).view(torch.bfloat16)
+    assert lib.step_form(logits, greedy=True) == "spread"
+    for _ in range(2):                                                       # the counters are back at zero
+        tok.fill_(-1)
+        lib.advance_fill_argmax(tok, mask_d, logits, tok)
+        assert (tok.cpu().numpy() == oracle_masked_argmax(host, mask, V)).all()
+
+
+@pytest.mark.gpu
+def test_a_zero_or_a_nan_on_top_costs_the_spread_greedy_step_little():
+    """The block that holds such a value settles it on its own groups: 1.6 times the time of ordinary rows at 1 x 128,256
+    (7 to 15 times when one block did that for the whole row).  The bound leaves room for a slow run."""
+    import torch
+    from paper_2506_03887_amd import Pre3
+    v = _nesting_vocab(128_256)
+    lib = Pre3(G.JSON, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, stack_cap=16)
+    us = {}
+    for B in (1, 16):
+        keep, mask, tok = _bound(lib, B, 16)
+        logits = -torch.rand((B, v.n_tokens), dtype=torch.float32, device=tok.device).add_(0.5).to(torch.bfloat16)
+        out = torch.empty_like(tok)
+        assert lib.step_form(logits, greedy=True) == "spread"
+        for kind, value in (("plain", 1.0), ("zero", 0.0), ("nan", float("nan"))):
+            logits[:, ::7] = value
+            us[kind] = _graph_us(lambda: lib.advance_fill_argmax(tok, mask, logits, out))
+        assert max(us["zero"], us["nan"]) < 4 * us["plain"], (B, us)
