@@ -961,14 +961,29 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
     }
 }
 
+// The stack an advance leaves, as the wave that made it sees it before it is stored (kCompact: staged in LDS as a whole).
+template <bool kCompact>
+struct NewStack {
+    const int32_t *row, *staged;
+    const PrivateStack &priv;
+    int base;
+    __device__ int32_t at(int idx) const {
+        if (kCompact) return lds_read(staged + idx);
+        return idx < base ? global_read(row + idx) : priv.get(idx - base);
+    }
+};
+
 // The whole decode step of a small batch in one launch: every row of logits is spread over n_seg blocks, so that a few
 // sequences fill the chip.  Each block of a row advances the sequence for itself (wave 0, as in advance_fill_kernel, on
 // private stacks of its own) while its other four waves load the block's kSpreadGroups groups of 8 logits; the plan
 // of the new row is the same in all of them, so each masks its groups and stores its part of the mask row by itself.
 // Only one may store the advance, and none before all have read what it overwrites: the blocks of a row count
 // themselves in when their plan is done, and the last to arrive stores (and sets the count back to zero for the next
-// launch).  No block waits for another.  Rows that the condition tree leaves open (tokens to be walked on the
-// stored stack) are left to that last block as a whole.
+// launch).  No block waits for another.  Where the condition tree leaves tokens of a row open, the advancing wave of each
+// block walks those of the block's own groups, on the new stack as it has it (the stored one may not be there yet; what
+// of it lies in memory, the entries below the advance's, is not what the last block stores): 16 x 128,256 of which some
+// rows are walked whole 0.83 ms per step, 11.7 as two launches with a wave per row, 11.9 when the last block did such a
+// row by itself; 4 x 32,000 with short lists 34 us (37, 39).
 // kArgmax: the greedy step; the blocks' best words meet in best[row] through an atomic maximum, and the last block to
 // count itself in on a second counter takes the result.  A block whose best the keys cannot decide (zeros of both signs, a
 // NaN pattern) compares its own groups as numbers first: 1 x 128,256 with zeros on top 15.6 us per step, 71 when
@@ -985,14 +1000,14 @@ template <bool kCompact, bool kArgmax>
 __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
     DevTables T, DevTokenEdges E, const int32_t *tokens, int32_t *states, int32_t *data, int32_t *len, int cap,
     int32_t *__restrict__ err, uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_spill, int32_t *walk_spill,
-    size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
+    const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
     uint16_t *__restrict__ logits, int64_t row_stride, int32_t *out_tokens, int n_seg, StepArrivals *arrivals) {
-    extern __shared__ uint4 bits4[];                   // an open row's mask; kCompact: then cap stack entries [+ cycle tables]
+    extern __shared__ int32_t after_row[];             // kCompact: cap stack entries [+ cycle tables]
     __shared__ int32_t s_win[kWindow], s_new[kWindow], s_info[64];
     __shared__ int32_t s_adv_stack[kLdsDepth], s_walk_stack[kLdsDepth * 64];
+    __shared__ uint32_t s_bits[kSpreadGroups / 4];     // an open row: this block's mask words
     __shared__ RowPlan plan;
     __shared__ unsigned long long s_part[kArgmax ? kSpreadBlock / 64 + 1 : 1];
-    __shared__ int s_last;
     const int tid = threadIdx.x, lane = tid & 63, j = tid - 64;
     const int b = blockIdx.x / n_seg, seg = blockIdx.x - b * n_seg;
     const int n_vec = (T.n_words + 3) >> 2, g0 = seg * kSpreadGroups;
@@ -1001,7 +1016,6 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
     uint32_t *dst_row = bitmask + (size_t)b * T.n_words;
     uint16_t *lrow = logits + (size_t)b * row_stride;
     StepArrivals *mine = arrivals + b;
-    int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
     PrivateStack priv = wave_stack(s_adv_stack, adv_spill + blockIdx.x, (size_t)gridDim.x);
     Advanced r{};
     uint4 held[kSpreadHeld];
@@ -1023,7 +1037,8 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
     }
     lds_barrier();                                     // the plan is there
     const int mode = plan.mode;
-    const bool open = mode == kRowWalkAll || (mode == kRowFast && (plan.walk_count > 0 || plan.nseg > 0));
+    // (the form is only chosen for tables without id lists: a row is a materialised row and tokens left to the walk)
+    const bool open = mode == kRowWalkAll || (mode == kRowFast && plan.walk_count > 0);        // the same in every block of the row
     if (tid < 64) {
         uint32_t before = 0;
         loads_returned();                              // of the stack: the block that counts last overwrites it
@@ -1033,43 +1048,37 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
             commit_advance<kCompact>(r, priv, after_row, states, row, len, err, cap, b, lane);
             if (lane == 0) atomicExch(&mine->planned, 0u);
         }
-        if (lane == 0) s_last = last;
-    }
-    if (open) {                                        // the same in every block of the row
-        __syncthreads();                               // s_last; the walks read the stored stack
-        if (!s_last) return;
-        PrivateStack wp;
-        wp.lds = s_walk_stack + lane;
-        wp.lds_stride = 64;
-        wp.spill = walk_spill + (size_t)b * 64 + lane;
-        wp.spill_stride = walk_spill_stride;
-        const bool vector_ok = (T.n_words & 3) == 0 && (reinterpret_cast<uintptr_t>(bitmask) & 15) == 0;
-        build_and_store_row<kSpreadBlock, true>(T, E, plan, bits4, 0, n_vec, row, wp, dst_row, vector_ok, tid);
-        const uint8_t *mask_bytes = reinterpret_cast<const uint8_t *>(bits4);
-        if (kArgmax) {
-            const unsigned long long w = argmax_block_max<kSpreadBlock>(
-                argmax_by_compare<kSpreadBlock>(lrow, [&](int g) { return (uint32_t)mask_bytes[g]; }, 0, groups, T.n_tokens, tid), s_part, tid);
-            if (tid == 0) out_tokens[b] = w != 0ull ? (int32_t)(0xFFFFFFFFu - (uint32_t)w) : -1;
-        } else {
-            for (int g = tid; g < groups; g += kSpreadBlock) {
-                const uint32_t mu = mask_bytes[g];
-                if (mu == 0xFFu) continue;
-                if (g < whole) {
-                    stream_store(mask_group(stream_load(lrow + (size_t)g * 8), mu), lrow + (size_t)g * 8);
-                } else {
-                    for (int k = 0; k < tail; ++k)
-                        if (!((mu >> k) & 1u)) lrow[whole * 8 + k] = 0xFF80;
-                }
-            }
-        }
-        return;
     }
     // the mask byte of a group: from the materialised row, else nothing (a finished sequence: the EOS bit) is allowed
     const uint32_t *dense = mode == kRowFast && plan.dense >= 0 ? E.dense_rows + (size_t)plan.dense * n_vec * 4 : nullptr;
     const int eos_group = mode == kRowDone ? T.eos_id >> 3 : -1;
+    const int w0 = seg * (kSpreadGroups / 4);          // the block's first mask word
+    if (open) {
+        static_assert(kSpreadGroups / 4 == kSpreadLanes, "a mask word per lane");
+        if (tid >= 64) s_bits[j] = dense && w0 + j < T.n_words ? dense[w0 + j] : 0u;
+        lds_barrier();
+        if (tid < 64) {
+            const NewStack<kCompact> stack{row, after_row, priv, r.base};
+            PrivateStack wp;
+            wp.lds = s_walk_stack + lane;
+            wp.lds_stride = 64;
+            wp.spill = walk_spill + (size_t)blockIdx.x * 64 + lane;
+            wp.spill_stride = (size_t)gridDim.x * 64;
+            const int n = plan.len, top0 = plan.top;
+            const int t_lo = mode == kRowWalkAll ? w0 * 32 : 0;
+            const int count = mode == kRowWalkAll ? min(T.n_tokens - t_lo, kSpreadGroups * 8) : plan.walk_count;
+            for (int k = lane; k < count; k += 64) {
+                const int t = mode == kRowWalkAll ? t_lo + k : E.walk_ids[plan.walk_begin + k], w = (t >> 5) - w0;
+                if ((unsigned)w < (unsigned)(kSpreadGroups / 4) && walk_token_id_on(T, wp, t, stack, n, top0))
+                    atomicOr(&s_bits[w], 1u << (t & 31));
+            }
+        }
+        lds_barrier();
+    }
     auto mask_byte = [&](int g) {
         uint32_t mu = g == eos_group ? 1u << (T.eos_id & 7) : 0u;
         if (dense) mu = reinterpret_cast<const uint8_t *>(dense)[g];
+        if (open) mu = reinterpret_cast<const uint8_t *>(s_bits)[g - g0];
         return mu;
     };
     unsigned long long word = 0ull;                    // kArgmax: this lane's candidate
@@ -1080,9 +1089,8 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
             const int g = g0 + i * kSpreadLanes + j;
             m[i] = g < groups ? mask_byte(g) : 0u;
         }
-        const int w = seg * (kSpreadGroups / 4) + j;   // this block's part of the mask row: a word per lane
-        static_assert(kSpreadGroups / 4 == kSpreadLanes, "a mask word per lane");
-        if (w < T.n_words) dst_row[w] = dense ? dense[w] : (w == (eos_group >> 2) && eos_group >= 0) ? 1u << (T.eos_id & 31) : 0u;
+        const int w = w0 + j;                          // this block's part of the mask row: a word per lane
+        if (w < T.n_words) dst_row[w] = open ? s_bits[j] : dense ? dense[w] : (w == (eos_group >> 2) && eos_group >= 0) ? 1u << (T.eos_id & 31) : 0u;
         uint32_t tail_x[4] = {0u, 0u, 0u, 0u};         // the last, partial group: in the lane whose group it is
         if (kArgmax) {
             int best = kOrderNegInf - 1, best_g = -1;
@@ -1517,10 +1525,11 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E,
         return hipErrorInvalidValue;
     const int held = ((T.n_tokens >> 3) + kStepData - 1) / kStepData;
     const int held_variant = held <= 9 ? 9 : held <= 17 ? 17 : kStepHeldMaxGreedy;
-    size_t lds = (size_t)edge_row_stride_words(T.n_words) * sizeof(uint32_t);
+    size_t lds = 0;
     int stage = 0;
     if (cycle_head) {
-        lds += (size_t)cap * sizeof(int32_t);
+        lds = (size_t)cap * sizeof(int32_t);
+        if (cap > kCompactMaxLen || lds > kAfDynamicLdsMax) return hipErrorInvalidValue;
         const size_t tables = (size_t)(T.n_states + T.cycle_pool_n) * sizeof(int32_t);
         stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) && lds + tables <= kAfDynamicLdsMax;
         if (stage) lds += tables;
@@ -1570,19 +1579,19 @@ hipError_t launch_step_spread(const DevTables &T, const DevTokenEdges &E, const 
                               int32_t *adv_spill, int32_t *walk_spill, const int32_t *cycle_head, const int32_t *cycle_pool,
                               uint16_t *logits, int64_t row_stride, int32_t *out_tokens, StepArrivals *arrivals, hipStream_t stream) {
     if (batch == 0) return hipSuccess;
-    size_t lds = (size_t)edge_row_stride_words(T.n_words) * sizeof(uint32_t);
+    size_t lds = 0;
     int stage = 0;
     if (cycle_head) {
-        lds += (size_t)cap * sizeof(int32_t);
+        lds = (size_t)cap * sizeof(int32_t);
+        if (cap > kCompactMaxLen || lds > kAfDynamicLdsMax) return hipErrorInvalidValue;
         const size_t tables = (size_t)(T.n_states + T.cycle_pool_n) * sizeof(int32_t);
         stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) && lds + tables <= kAfDynamicLdsMax;
         if (stage) lds += tables;
     }
-    if (lds > kAfDynamicLdsMax) return hipErrorInvalidValue;
     const int n_seg = step_spread_segments(T.n_tokens);
 #define PRE3_SPREAD(C, A)                                                                                                   \
     hipLaunchKernelGGL((step_spread_kernel<C, A>), dim3(batch * n_seg), dim3(kSpreadBlock), lds, stream, T, E, tokens, states, data, \
-                       len, cap, err, bitmask, restart_on_eos, adv_spill, walk_spill, (size_t)batch * 64, cycle_head, cycle_pool,   \
+                       len, cap, err, bitmask, restart_on_eos, adv_spill, walk_spill, cycle_head, cycle_pool,   \
                        stage, logits, row_stride, out_tokens, n_seg, arrivals)
     if (cycle_head) {
         if (out_tokens) PRE3_SPREAD(true, true);
@@ -1594,8 +1603,6 @@ hipError_t launch_step_spread(const DevTables &T, const DevTokenEdges &E, const 
 #undef PRE3_SPREAD
     return hipGetLastError();
 }
-
-bool advance_fill_fits(int n_words) { return (size_t)edge_row_stride_words(n_words) * sizeof(uint32_t) <= kAfDynamicLdsMax; }
 
 bool advance_fill_fits_compact(int n_words, int cap) {
     return cap <= kCompactMaxLen &&

@@ -355,15 +355,13 @@ bool locate(const pre3_handle *h, int state, int *g, int *local) {
 // blocks (four per compute unit) are on the chip at once: 64 sequences x 128,256 tokens take 12.5 us against 14.5 us in the
 // one-kernel form, 256 x 32,000 12.7 against 13.3 us, 60 x 128,256 12.3 against 15.6 us as two launches; with twice as
 // many blocks the second half starts when the first ends and it loses (128 x 128,256: 24.5 against 15.2 us).  It needs
-// tables without id lists, rows that fit the kernel's LDS, and spill columns (one per block) of at most 64 MiB.
+// tables without id lists and spill columns (for the walks of 64 lanes per block) of at most 256 MiB.
 int spread_step_rows(const pre3_handle *h) {
-    const bool cycles = h->compact && h->T.n_cycles > 0;
     if (!(h->use_edges || (h->host_only && h->E.enabled)) || !h->E.delta_ids.empty()) return 0;
-    if (cycles ? !advance_fill_fits_compact(h->V.n_words, h->stack_cap) : !advance_fill_fits(h->V.n_words)) return 0;
     const int segments = step_spread_segments(h->V.n_tokens);
-    const size_t per_row = advance_scratch_entries(segments, h->max_depth) * sizeof(int32_t);
+    const size_t per_row = advance_fill_walk_spill_entries(segments, h->max_depth) * sizeof(int32_t);
     int rows = 4 * h->n_compute_units / segments;
-    if (per_row > 0) rows = (int)std::min((size_t)rows, ((size_t)64 << 20) / per_row);
+    if (per_row > 0) rows = (int)std::min((size_t)rows, ((size_t)256 << 20) / per_row);
     return rows;
 }
 // Blocks of the spread step for a batch, 0 where that form does not serve it.
@@ -372,18 +370,18 @@ int spread_step_blocks(const pre3_handle *h, int batch) {
 }
 
 // Bytes of the per-batch workspaces that serve `batch` AND every smaller batch (a smaller one may take a form that needs
-// more: one spill column per block of the spread step, partial results of more segments per row): rebinding to fewer
+// more: spill columns per block of the spread step, partial results of more segments per row): rebinding to fewer
 // sequences never replaces a workspace.  topk 0: beyond 1 GiB, the call then reports PRE3_E_LIMIT.
 struct BatchWorkspaces { size_t adv, arrivals, argmax, topk, af_spill; };
 BatchWorkspaces batch_workspaces(const pre3_handle *h, int batch) {
-    const int spread_rows = std::min(batch, spread_step_rows(h));
+    const int spread_rows = std::min(batch, spread_step_rows(h)), columns = std::max(batch, spread_step_blocks(h, spread_rows));
     BatchWorkspaces w;
-    w.adv = advance_scratch_entries(std::max(batch, spread_step_blocks(h, spread_rows)), h->max_depth) * sizeof(int32_t);
+    w.adv = advance_scratch_entries(columns, h->max_depth) * sizeof(int32_t);
     w.arrivals = (size_t)spread_rows * sizeof(StepArrivals);
     w.argmax = masked_argmax_workspace_bytes(batch, h->V.n_tokens, h->n_compute_units);
     w.topk = masked_topk_workspace_bytes(batch, h->V.n_tokens);
     if (w.topk > (size_t)1 << 30) w.topk = 0;
-    w.af_spill = advance_fill_walk_spill_entries(batch, h->max_depth) * sizeof(int32_t);
+    w.af_spill = advance_fill_walk_spill_entries(columns, h->max_depth) * sizeof(int32_t);
     return w;
 }
 

@@ -59,7 +59,6 @@ hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const
                                int32_t *data, int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask,
                                int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
                                const int32_t *cycle_head, const int32_t *cycle_pool, int n_compute_units, hipStream_t stream);
-bool advance_fill_fits(int n_words);                    // the row bitmap within 64 KB of LDS
 bool advance_fill_fits_compact(int n_words, int cap);   // row bitmap + staged stack within 64 KB of LDS
 // The same followed by the masking of the logits with the new rows, as one kernel that fetches a
 // sequence's logits while its token is still being walked.  Needs advance_fill_apply_fits, logits
@@ -80,9 +79,10 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E,
                                      const int32_t *cycle_head, const int32_t *cycle_pool, uint16_t *logits,
                                      int64_t row_stride, int32_t *out_tokens, int rows_per_launch, hipStream_t stream);
 // The same step (mask + masking, or the greedy step) for a small batch: every row is spread over
-// step_spread_segments(n_tokens) blocks.  Any layout of the logits.  Needs the row (and, with cycle-aware stacks, the
-// staged stack) within the kernel's LDS, no id lists in the condition trees (each block masks from the materialised row),
-// adv_spill of advance_scratch_entries(batch * segments, ...) entries, and one StepArrivals per row, all zero.
+// step_spread_segments(n_tokens) blocks.  Any layout of the logits.  Needs tables without id lists in the condition trees
+// (each block masks from the materialised row), with cycle-aware stacks the staged stack within the kernel's LDS,
+// adv_spill of advance_scratch_entries and walk_spill of advance_fill_walk_spill_entries(batch * segments, ...)
+// entries, and one StepArrivals per row, all zero.
 struct StepArrivals {
     unsigned long long best;       // greedy: largest candidate word so far
     uint32_t planned, sampled;     // blocks of the row that have planned, that have sampled; zero again when the launch ends

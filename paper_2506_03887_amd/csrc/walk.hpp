@@ -145,6 +145,7 @@ struct StackView {
     }
 };
 
+// `row` (feed, and the walks below): a StackView, or whatever else shows the entries of the stack through at(index).
 // Consumes one input symbol (`info` = byte class column | target offset << 8) from the configuration
 //   row[0 .. base) ++ priv[0 .. d),  top = last entry.
 // First the merged reduction edge is looked up: starting at the top state's condition node, the
@@ -154,9 +155,9 @@ struct StackView {
 // the exposed state (its stack-matching condition) and pushes the goto target, until an
 // acceptance edge shifts the symbol.
 // With kCheckCap the walk reports kOverflow exactly when a push would exceed `cap` entries.
-template <bool kCheckCap, bool kUniform = false, bool kScalarOnly = false>
+template <bool kCheckCap, bool kUniform = false, bool kScalarOnly = false, class View>
 __device__ __forceinline__ int feed(const DevTables &T, PrivateStack &priv, int info, int &base, int &d,
-                                    int &top, int &tree, const StackView &row, int cap, int *run_node = nullptr) {
+                                    int &top, int &tree, const View &row, int cap, int *run_node = nullptr) {
     const int col = info & 0xFF, delta = info >> 8;    // byte class and per-byte target offset
     // `tree` names the condition tree of the top state (states that behave alike share one, and all
     // bytes of a class shift to states of one kind, so the kind after an edge is stored with it)
@@ -380,22 +381,30 @@ __device__ __forceinline__ bool walk_token(const DevTables &T, PrivateStack &pri
     return true;
 }
 
+template <class View>
+__device__ __forceinline__ bool walk_end_on(const DevTables &T, PrivateStack &priv, const View &view, int len, int top0) {
+    int base = len, d = 0, top = top0, kind = T.state_kind ? T.state_kind[top0] : 0;
+    return feed<false>(T, priv, T.end_col, base, d, top, kind, view, 0) == kAccepted;
+}
 __device__ __forceinline__ bool walk_end(const DevTables &T, PrivateStack &priv, const int32_t *__restrict__ row,
                                          int len, int top0) {
-    int base = len, d = 0, top = top0, kind = T.state_kind ? T.state_kind[top0] : 0;
-    return feed<false>(T, priv, T.end_col, base, d, top, kind, StackView{row, nullptr, len}, 0) == kAccepted;
+    return walk_end_on(T, priv, StackView{row, nullptr, len}, len, top0);
 }
 
-// Walks token id `t` (bytes in id order) from the stack row[0..len).
-__device__ __forceinline__ bool walk_token_id(const DevTables &T, PrivateStack &priv, int t,
-                                              const int32_t *__restrict__ row, int len, int top0) {
-    if (t == T.eos_id) return walk_end(T, priv, row, len, top0);
+// Walks token id `t` (bytes in id order) from the stack of `len` entries that `view` shows.
+template <class View>
+__device__ __forceinline__ bool walk_token_id_on(const DevTables &T, PrivateStack &priv, int t, const View &view, int len, int top0) {
+    if (t == T.eos_id) return walk_end_on(T, priv, view, len, top0);
     int base = len, d = 0, top = top0, kind = T.state_kind ? T.state_kind[top0] : 0;
     const int lo = T.voffsets[t], hi = T.voffsets[t + 1];
     if (hi <= lo) return false;
     for (int i = lo; i < hi; ++i)
-        if (feed<false>(T, priv, T.byte_info[T.vbytes[i]], base, d, top, kind, StackView{row, nullptr, len}, 0) != kFed) return false;
+        if (feed<false>(T, priv, T.byte_info[T.vbytes[i]], base, d, top, kind, view, 0) != kFed) return false;
     return true;
+}
+__device__ __forceinline__ bool walk_token_id(const DevTables &T, PrivateStack &priv, int t,
+                                              const int32_t *__restrict__ row, int len, int top0) {
+    return walk_token_id_on(T, priv, t, StackView{row, nullptr, len}, len, top0);
 }
 
 }  // namespace

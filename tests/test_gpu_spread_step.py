@@ -28,7 +28,8 @@ def _vocab(n):
     (600, 5, 0, 0, {}), (8191, 3, 0, 1, {}), (8192, 4, 0, 0, {}), (8193, 4, 0, 0, {}), (20_003, 30, 0, 0, {}), (20_003, 8, 5, 3, {}),
     (16_392, 9, 0, 0, dict(max_condition_depth=3)), (3003, 70, 0, 0, dict(max_condition_depth=2)),
     (12_000, 12, 8, 0, dict(token_effects=False)), (9001, 6, 0, 0, dict(row_threshold=64)),
-    (16_777, 10, 0, 0, dict(compact_cycles=True)), (1001, 300, 0, 0, {}), (65_003, 100, 0, 0, {})])
+    (16_777, 10, 0, 0, dict(compact_cycles=True)), (1001, 300, 0, 0, {}), (65_003, 100, 0, 0, {}),
+    (24_577, 6, 3, 1, dict(max_condition_depth=2)), (16_392, 9, 0, 0, dict(compact_cycles=True, max_condition_depth=3))])
 def test_spread_step_in_lockstep_with_the_oracle(V, B, pad, offset, options, greedy):
     """Allowed, refused, skipped, out-of-range and EOS tokens, overflow of a small stack, finished rows and restarts;
     masked logits with what lies around the rows, or the greedy choice on special rows fed back as the next token
