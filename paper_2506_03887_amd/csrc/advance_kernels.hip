@@ -1525,11 +1525,10 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E,
         return hipErrorInvalidValue;
     const int held = ((T.n_tokens >> 3) + kStepData - 1) / kStepData;
     const int held_variant = held <= 9 ? 9 : held <= 17 ? 17 : kStepHeldMaxGreedy;
-    size_t lds = 0;
+    size_t lds = (size_t)edge_row_stride_words(T.n_words) * sizeof(uint32_t);
     int stage = 0;
     if (cycle_head) {
-        lds = (size_t)cap * sizeof(int32_t);
-        if (cap > kCompactMaxLen || lds > kAfDynamicLdsMax) return hipErrorInvalidValue;
+        lds += (size_t)cap * sizeof(int32_t);
         const size_t tables = (size_t)(T.n_states + T.cycle_pool_n) * sizeof(int32_t);
         stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) && lds + tables <= kAfDynamicLdsMax;
         if (stage) lds += tables;
