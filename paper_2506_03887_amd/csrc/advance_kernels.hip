@@ -1476,7 +1476,7 @@ hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const
 
 // (27 groups per lane, 207,360 tokens, is what fits the 128 vector registers of a 1,024-thread block beside the
 // masking code; the greedy fold needs more registers and stops at 20 groups, 153,600 tokens)
-constexpr int kStepHeldMax = 27, kStepHeldMaxGreedy = 20;
+constexpr int kStepHeldShort = 9, kStepHeldMax = 27, kStepHeldMaxGreedy = 20;
 // Largest vocabulary the fused step kernel can hold in registers, and the choice of its variant.
 bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bool greedy) {
     const size_t row_bytes = (size_t)edge_row_stride_words(n_words) * sizeof(uint32_t);
@@ -1486,6 +1486,8 @@ bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bo
     if (cycles) return cap <= kCompactMaxLen && row_bytes + (size_t)cap * sizeof(int32_t) <= kAfDynamicLdsMax;
     return row_bytes <= kAfDynamicLdsMax;
 }
+
+bool advance_fill_apply_short_row(int n_tokens) { return (n_tokens >> 3) <= kStepHeldShort * kStepData; }
 
 template <bool kCompact, bool kArgmax>
 static void launch_step_variant(int held, dim3 grid, size_t lds, hipStream_t stream, const DevTables &T, const DevTokenEdges &E,
@@ -1497,7 +1499,7 @@ static void launch_step_variant(int held, dim3 grid, size_t lds, hipStream_t str
     hipLaunchKernelGGL((advance_fill_apply_kernel<kCompact, H, kArgmax>), grid, dim3(kStepBlock), lds, stream, T, E, tokens,  \
                        states, data, len, cap, batch, err, bitmask, restart_on_eos, adv_scratch, walk_spill,                 \
                        (size_t)batch * 64, cycle_head, cycle_pool, stage, logits, row_stride, out_tokens, first_row)
-    if (held <= 9) PRE3_STEP(9);
+    if (held <= kStepHeldShort) PRE3_STEP(kStepHeldShort);
     else if (held <= 17) PRE3_STEP(17);
     else if (held <= kStepHeldMaxGreedy || kArgmax) PRE3_STEP(20);
     else if constexpr (!kArgmax) PRE3_STEP(27);

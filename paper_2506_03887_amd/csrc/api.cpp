@@ -654,10 +654,20 @@ StepForm step_form(const pre3_handle *h, const uint16_t *logits_bf16, int64_t ro
     const int batch = h->b_stacks.batch;
     const bool asked = flags & PRE3_STEP_ONE_KERNEL;
     const bool one_kernel = (asked || step_kernel_batch(h, batch)) && one_kernel_serves(h, logits_bf16, row_stride, greedy);
-    // The blocks of a spread row meet through atomics to choose the token, which costs more the more of them there are: from
-    // half a row per compute unit on the one kernel is the better form where it serves the logits (250 x 32,000: 12.8
-    // against 14.3 us; 64 x 32,000: 13.1 against 11.6 us).
-    if (!asked && spread_step_blocks(h, batch) > 0 && !(greedy && one_kernel && 2 * batch >= h->n_compute_units)) return StepForm::kSpread;
+    const int blocks = asked ? 0 : spread_step_blocks(h, batch);
+    if (blocks > 0 && !one_kernel) return StepForm::kSpread;
+    // Where the one kernel serves the batch too, the spread form is only taken while it has few blocks, since each of them
+    // advances the sequence for itself.  Rows that the one kernel holds in few registers: up to three blocks per unit
+    // (us per step, spread and one kernel, eight schemas: 128 x 64,000 11.9 and 10.9, 170 x 48,000 12.1 and 10.6,
+    // 256 x 32,000 11.8 and 11.2, but 96 x 64,000 10.9 and 10.5, 100 x 48,000 10.4 and 10.5; JSON 12.6 and 12.7, 12.5 and 12.4,
+    // 12.6 and 13.2, 11.1 and 12.2, 10.7 and 11.5); longer rows as above (102 x 80,000 11.7 and 11.9, 64 x 128,256 11.5
+    // and 12.5).  The greedy step, whose blocks then meet through atomics to choose the token: up to one block per unit and
+    // half a row per unit (eight schemas: 64 x 128,256 14.0 and 11.9, 96 x 64,000 13.1 and 10.5, 96 x 24,000 11.2 and
+    // 10.5, but 64 x 32,000 11.0 and 10.7, 127 x 16,000 10.9 and 10.9; JSON 14.8 and 13.3, 13.8 and 12.1, 11.6 and 11.4, 11.9
+    // and 12.5, 11.6 and 12.0).
+    const bool spread = blocks > 0 && (greedy ? blocks <= h->n_compute_units && 2 * batch < h->n_compute_units
+                                              : blocks <= 3 * h->n_compute_units || !advance_fill_apply_short_row(h->V.n_tokens));
+    if (spread) return StepForm::kSpread;
     return one_kernel ? StepForm::kOneKernel : StepForm::kTwoCalls;
 }
 

@@ -68,6 +68,7 @@ bool advance_fill_fits_compact(int n_words, int cap);   // row bitmap + staged s
 // rows_per_launch: a batch of more rows goes as several launches of equal shares of at most that many
 // (the number of compute units: a block fills one); 0: one launch.
 bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bool greedy);   // greedy: the arg-max form
+bool advance_fill_apply_short_row(int n_tokens);        // rows of its smallest variant (69,120 tokens)
 // The same kernel without the advance: mask rows of the stacks as they are, applied to the logits
 // (walk_spill: advance_fill_walk_spill_entries(batch, ...) entries; same conditions on the logits).
 hipError_t launch_fill_apply_rows(const DevTables &T, const DevTokenEdges &E, const int32_t *states, const int32_t *data,

@@ -197,8 +197,10 @@ def test_a_bind_that_fails_leaves_nothing_bound():
 @pytest.mark.parametrize("V,options,expect", [
     # rows of 1, 3 and 5 blocks of 8,192 tokens; four blocks per compute unit are the limit of the spread form
     (8192, {}, {4: "spread", 256: "spread", 257: "spread", 1024: "spread", 1025: "two calls"}),
-    (20_003, {}, {1: "spread", 341: "spread", 342: "two calls"}),
-    (40_001, {}, {4: "spread", 63: "spread", 204: "spread", 205: "one kernel", 256: "one kernel", 257: "two calls"}),
+    (20_003, {}, {1: "spread", 63: "spread", 85: "spread", 86: "spread", 341: "spread", 342: "two calls"}),
+    # ... three where the one kernel serves rows of at most 69,120 tokens
+    (40_001, {}, {4: "spread", 63: "spread", 153: "spread", 154: "one kernel", 205: "one kernel", 256: "one kernel", 257: "two calls"}),
+    (69_127, {}, {85: "spread", 86: "one kernel"}), (69_128, {}, {113: "spread", 114: "one kernel"}),
     (40_001, dict(row_threshold=64), {4: "two calls", 63: "two calls", 64: "one kernel", 256: "one kernel"}),       # id lists
     (40_001, dict(token_edges=False), {4: "two calls", 64: "two calls"})])
 def test_the_query_names_the_kernel_that_runs(V, options, expect):
@@ -223,9 +225,11 @@ def test_the_query_names_the_kernel_that_runs(V, options, expect):
         for off in (0, 1):
             logits = flat[off: off + B * stride].view(B, stride)
             for greedy in (False, True):
-                want = form if form != "one kernel" or off == 0 else "two calls"
-                # the greedy step takes the one kernel from half a row per compute unit on, where that serves the logits
-                if greedy and form == "spread" and off == 0 and 128 <= B <= 256:
+                want = form
+                if form == "one kernel" and off == 1:
+                    want = "spread" if B * -(-V // 8192) <= 1024 and not options else "two calls"
+                # the greedy step takes the one kernel from half a row or more than one block per compute unit on, where that serves
+                if greedy and form == "spread" and off == 0 and not options and 64 <= B <= 256 and (B >= 128 or B * -(-V // 8192) > 256):
                     want = "one kernel"
                 assert lib.step_form(logits, greedy=greedy) == want, (B, off, greedy)
                 run = (lambda: lib.advance_fill_argmax(tok, mask, logits, torch.empty_like(tok))) if greedy else \
