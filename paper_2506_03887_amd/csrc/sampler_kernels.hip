@@ -621,15 +621,6 @@ __device__ __forceinline__ void masked_topk_chunked(
         if (r * 64 + lane < n_mine && rank[r] < k) emit(rank[r], w[r]);
 }
 
-template <int kBlock>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void masked_topk_kernel(
-    const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
-    int n_words, int k, int chunks_per_seg, unsigned long long *__restrict__ out,
-    int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_vals) {
-    masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, chunks_per_seg, out, out_ids, out_vals,
-                                blockIdx.x, blockIdx.y, gridDim.y);
-}
-
 // The stored bf16 pattern behind a key of bf16_key, or -1 for the key of zero, which -0 and +0 share.
 __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
     const uint32_t folded = key + 0x7Fu;
@@ -751,6 +742,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ unsigned long long s_cand[kTopkRowList];
     __shared__ int s_count, s_groups;
     const int b = blockIdx.x, seg = blockIdx.y, n_seg = gridDim.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (kBlock == kTopkBlock && vocab < 8) {                  // not one group of eight logits that the loads below could take
+        topk_in_chunks<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, 1, workspace, out_ids, out_vals, b, 0, 1);
+        return;
+    }
     const unsigned long long lanes_below = (1ull << lane) - 1ull;
     const uint16_t *whole_row = logits + (size_t)b * row_stride;
     const int first_token = seg * kSegTokens, n_tokens = min(vocab - first_token, kSegTokens);
@@ -1018,16 +1013,12 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     if (batch == 0) return hipSuccess;
     if (!masked_topk_fits(vocab, k)) return hipErrorInvalidValue;
     const int n_words = (vocab + 31) / 32;
-    if (vocab < 8) {                                   // not one group of eight logits
-        hipLaunchKernelGGL(masked_topk_kernel<kTopkBlock>, dim3(batch, 1), dim3(kTopkBlock), 0, stream, logits, bitmask, vocab,
-                           row_stride, n_words, k, masked_topk_chunks(vocab), workspace, out_ids, out_vals);
-        return hipGetLastError();
-    }
     // A row that fits the registers of a block is one block's, whatever the batch (128,256 tokens, k = 50: 8.0 us for one
     // row, 10.7 for 64, 15.4 for 256, against 9.9 and 14.1 us for 1 and 64 rows in segments of 16,384 tokens and a second
     // launch); the block and its groups per thread are the smallest that hold it.  A longer row is cut into such
-    // blocks of 98,304 or 131,072 tokens (152,064 tokens: 14.4 us for 100 rows, 49 for 512) unless the batch
-    // is too small to fill the chip with them (16 rows: 11.8 against 13.4 us in segments of 16,384).
+    // blocks of 98,304 or 131,072 tokens (152,064 tokens: 13.2 us for 100 rows, 49 for 512) unless the batch
+    // is too small to fill the chip with them (16 rows: 11.8 us in segments of 16,384 against 13.4; at the line, 31 rows
+    // take 13.4 to 13.9 us in such segments and 32 rows 12.2 in blocks, at 200,000 tokens 13.8 to 14.4 and 13.7).
 #define PRE3_TOPK_ROW(BLOCK, GROUPS)                                                                                         \
     n_seg = masked_topk_chunks(vocab, BLOCK * GROUPS * 8);                                                                   \
     hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, vocab, \
