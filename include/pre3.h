@@ -252,7 +252,9 @@ int pre3_advance_fill_mask(pre3_handle *h, const int32_t *tokens, uint32_t *bitm
  * and pre3_apply_mask does not read what is masked as a whole.
  * A batch whose rows, in blocks of 8,192 tokens, fill the GPU at most four blocks to a compute unit (64
  * sequences of 128,256 tokens on 256 units) is neither: it runs as one launch in which every row is
- * spread over its blocks, whatever the layout of the logits, unless PRE3_STEP_ONE_KERNEL is given.
+ * spread over its blocks, whatever the layout of the logits, unless PRE3_STEP_ONE_KERNEL is given (at
+ * most three blocks to a unit where the one kernel would be chosen for rows of up to 69,120 tokens).
+ * pre3_step_is_one_kernel tells which form a call takes.
  * flags: PRE3_ADVANCE_RESTART_ON_EOS as for pre3_advance_fill_mask, PRE3_STEP_ONE_KERNEL.
  * Errors: BADARG (nothing bound, null pointer, unknown flag, row_stride < n_tokens, logits not
  * 2-byte aligned), HIP. */
@@ -268,9 +270,9 @@ int pre3_advance_fill_apply_mask(pre3_handle *h, const int32_t *tokens, uint32_t
  * The call takes its one-kernel form -- the logits are fetched while the token is walked and the
  * arg max is taken from the registers that hold them -- under the conditions and for the batch
  * sizes of pre3_advance_fill_apply_mask, except that the vocabulary may have at most 153,600 tokens
- * (the fold needs registers of its own), spreads the rows of the smaller batches over blocks as there
- * (up to half a row per compute unit where the one kernel could serve the logits), and is the two
- * calls otherwise; flags as there.
+ * (the fold needs registers of its own) and has to have 8, spreads the rows of the smaller batches over
+ * blocks as there (up to one block and half a row per compute unit where the one kernel would be
+ * chosen), and is the two calls otherwise; flags as there.
  * Errors: BADARG (nothing bound, null pointer, unknown flag, row_stride < n_tokens, logits not
  * 2-byte aligned), HIP. */
 int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bitmask, const uint16_t *logits_bf16,
@@ -307,8 +309,7 @@ int pre3_apply_mask_argmax(pre3_handle *h, const uint16_t *logits_bf16, int64_t 
  * equal values (+0 and -0 are equal) in ascending order of id; NaN logits are never listed;
  * out_logits[b*k + j] (if not null) = that token's bf16 pattern as stored.  Rows with fewer than k
  * such tokens are padded with -1 and 0xFF80.  out_tokens[b*k] equals the choice of
- * pre3_apply_mask_argmax.  The logits are read once and not modified (groups of 8 masked tokens
- * are not read).  1 <= k <= PRE3_TOPK_MAX; layouts and the workspace rule as for
+ * pre3_apply_mask_argmax.  The logits are read once, masked ones among them, and not modified.  1 <= k <= PRE3_TOPK_MAX; layouts and the workspace rule as for
  * pre3_apply_mask_argmax.  Errors: BADARG (nothing bound, null pointer, row_stride < n_tokens, k out
  * of range), LIMIT (ceil(n_tokens / 16384) * k above 1024: k = 64 serves up to 262,144 tokens; or a
  * bound batch whose candidate workspace, batch * ceil(n_tokens / 16384) * 512 bytes, would pass 1 GiB). */

@@ -577,8 +577,8 @@ __device__ __forceinline__ PrivateStack wave_stack(int32_t *s_adv_stack, int32_t
 }
 
 // Advance and next mask in one launch: one block per sequence.  Wave 0 walks the sampled token
-// exactly like advance_kernel (scalar table loads), commits the new stack, stages the NEW top
-// of the stack in LDS and descends the condition tree of the token-level edges with it; then the
+// exactly like advance_kernel (scalar table loads), stages the NEW top of the stack in LDS, descends
+// the condition tree of the token-level edges with it and commits the new stack; then the
 // whole block builds the sequence's next mask row (dense row copy, delta lists, leftover walks)
 // and stores it.  The sequence's inputs are loaded once, no kernel boundary separates the two
 // halves, and the long walks of a few sequences overlap the mask building of all others.
@@ -588,7 +588,7 @@ __device__ __forceinline__ PrivateStack wave_stack(int32_t *s_adv_stack, int32_t
 // Threads per block: 512 while two blocks of that size per compute unit hold the batch, half of that for larger ones (more
 // of their blocks are on the chip at once: 1,024 x 128,256 tokens 10.4 against 14.2 us, 2,048 16.2 against 20.0; 256 x 128,256
 // 8.8 against 8.6 us), and two waves for large batches of short rows (2,048 x 8,000: 10.3 us; 13.7 with 256 threads, 18.9
-// with 512).
+// with 512; 2,048 x 32,000 10.1 us with two waves, 2,048 x 33,000 13.6 with 256 threads, 18.5 and 18.7 with 512).
 constexpr int kAfBlock = 512, kAfBlockMany = 256, kAfBlockShort = 128;
 constexpr int kAfShortWords = 1024;                    // mask words of a short row (32,768 tokens)
 // LDS the kernel declares statically (stack windows, token bytes, private stacks, the row plan),
