@@ -22,19 +22,20 @@ def _vocab(n):
     return Vocab(base + deep + [b""], n - 1)
 
 
-# the number of blocks per row changes at 8,192 tokens; 3 condition entries leave tokens and whole rows to the walk
+# the number of blocks per row changes at 8,192 tokens
 @pytest.mark.parametrize("greedy", [False, True])
 @pytest.mark.parametrize("V,B,pad,offset,options", [
     (600, 5, 0, 0, {}), (8191, 3, 0, 1, {}), (8192, 4, 0, 0, {}), (8193, 4, 0, 0, {}), (20_003, 30, 0, 0, {}), (20_003, 8, 5, 3, {}),
     (16_392, 9, 0, 0, dict(max_condition_depth=3)), (3003, 70, 0, 0, dict(max_condition_depth=2)),
     (12_000, 12, 8, 0, dict(token_effects=False)), (9001, 6, 0, 0, dict(row_threshold=64)),
-    (16_777, 10, 0, 0, dict(compact_cycles=True)), (1001, 300, 0, 0, {}), (65_003, 100, 0, 0, {}),
+    (16_777, 10, 0, 0, dict(compact_cycles=True)), (1001, 300, 0, 0, {}), (65_003, 100, 0, 0, {}), (65_003, 130, 0, 0, {}),
     (24_577, 6, 3, 1, dict(max_condition_depth=2)), (16_392, 9, 0, 0, dict(compact_cycles=True, max_condition_depth=3))])
 def test_spread_step_in_lockstep_with_the_oracle(V, B, pad, offset, options, greedy):
     """Allowed, refused, skipped, out-of-range and EOS tokens, overflow of a small stack, finished rows and restarts;
     masked logits with what lies around the rows, or the greedy choice on special rows fed back as the next token
-    (the token buffer updated in place).  70 x 3,003 and 300 x 1,001 have a block per row, 65,003 x 100 exceeds four
-    blocks per compute unit (the two calls), row_threshold keeps id lists (the two calls)."""
+    (the token buffer updated in place).  70 x 3,003 and 300 x 1,001 have a block per row, 130 x 65,003 exceeds four
+    blocks per compute unit (the two calls), row_threshold keeps id lists (the two calls); a depth of 2 or 3 entries leaves
+    tokens and whole rows open."""
     from paper_2506_03887_amd import Pre3
     torch, dev = _torch()
     v = _vocab(V)
@@ -55,6 +56,8 @@ def test_spread_step_in_lockstep_with_the_oracle(V, B, pad, offset, options, gre
     flat = torch.full((B * stride + offset + 16,), 0x2345, dtype=torch.int16, device=dev)
     view = flat[offset: offset + B * stride].view(B, stride)
     tok_d = torch.zeros(B, dtype=torch.int32, device=dev)
+    spread = "row_threshold" not in options and B * -(-V // 8192) <= 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    assert lib.step_form(view, greedy=greedy) == ("spread" if spread else "two calls")
     tokens = None
     for s in range(14):
         mask = o.fill_mask(states, data, length, v)
