@@ -38,6 +38,21 @@ def test_masked_rows_at_every_offset(V, pad, offset):
     assert (flat[:offset] == 0x2345).all() and (flat[offset + B * stride:] == 0x2345).all()
 
 
+@pytest.mark.parametrize("B", [65_528, 65_529, 131_100])
+@pytest.mark.parametrize("V,stride", [(9, 9), (64, 64)])
+def test_masked_rows_of_very_large_batches(B, V, stride):
+    """More rows than one grid's second dimension holds go as several launches (rows at any offset, rows on 128-byte lines)."""
+    torch, dev = _torch()
+    from paper_2506_03887_amd import apply_mask
+    rng = np.random.default_rng(B + V)
+    host = bf16_logits(rng, B, stride)
+    mask = rng.integers(0, 2 ** 32, size=(B, (V + 31) // 32), dtype=np.uint64).astype(np.uint32)
+    rows = torch.from_numpy(host.view(np.int16)).to(dev)
+    apply_mask(rows, torch.from_numpy(mask.view(np.int32)).to(dev), V)
+    oracle_apply_mask(host, mask, V)
+    assert (rows.cpu().numpy().view(np.uint16) == host).all()
+
+
 @pytest.mark.parametrize("V,B", [(65, 3), (1003, 70), (40_005, 9), (20_011, 256), (131_071, 257)])
 @pytest.mark.parametrize("pad,offset", [(0, 1), (3, 0), (16, 5)])
 def test_sampled_rows_at_every_offset(V, B, pad, offset):
