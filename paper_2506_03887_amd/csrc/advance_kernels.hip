@@ -990,8 +990,8 @@ struct NewStack {
 // the last block did that for the whole row.
 // A launch is bound by the chain of dependent loads of the advance (about 5 us) where the two-launch form pays for a
 // second launch and for reading the mask row back.  us per step inside a graph, against the form used before: 1 x 128,256
-// 7.4 (9.0), 16 x 128,256 9.1, 60 x 128,256 12.3 (15.6), 4 x 513 8.3 (9.9), 64 x 32,000 9.6 (11.6); greedy
-// 1 x 128,256 9.3 (13.7), 16 x 128,256 11.3 (15.0).  Four groups per lane and 256 lanes: with eight groups 8.2 and 10.0 us
+// 7.6 (9.0), 16 x 128,256 9.1 (11.4), 60 x 128,256 12.2 (15.7), 4 x 513 8.3 (9.9), 64 x 32,000 9.4 (11.6); greedy
+// 1 x 128,256 9.7 (13.1), 16 x 128,256 11.5 (15.2).  Four groups per lane and 256 lanes: with eight groups 8.2 and 10.0 us
 // at 1 and 16 x 128,256, with 512 lanes 7.8 and 9.6; with the advance through scalar loads (as in the kernel above,
 // where vector loads wait behind a whole row's) 8.8 and 10.5.
 constexpr int kSpreadLanes = 256, kSpreadBlock = kSpreadLanes + 64, kSpreadHeld = 4;

@@ -352,9 +352,9 @@ bool locate(const pre3_handle *h, int state, int *g, int *local) {
 }
 
 // Most sequences of a batch that runs as the spread step, 0 if the tables do not allow that form.  It is chosen while all its
-// blocks (four per compute unit) are on the chip at once: 64 sequences x 128,256 tokens take 12.5 us against 14.5 us in the
-// one-kernel form, 256 x 32,000 12.7 against 13.3 us, 60 x 128,256 12.3 against 15.6 us as two launches; with twice as
-// many blocks the second half starts when the first ends and it loses (128 x 128,256: 24.5 against 15.2 us).  It needs
+// blocks (four per compute unit) are on the chip at once: 64 sequences x 128,256 tokens take 12.4 us against 14.5 us in the
+// one-kernel form, 60 x 128,256 12.2 against 15.7 us as two launches; with twice as many blocks the second half
+// starts when the first ends and it loses (128 x 128,256: 24.5 against 15.2 us); step_form draws closer lines.  It needs
 // tables without id lists and spill columns (for the walks of 64 lanes per block) of at most 256 MiB.
 int spread_step_rows(const pre3_handle *h) {
     if (!(h->use_edges || (h->host_only && h->E.enabled)) || !h->E.delta_ids.empty()) return 0;

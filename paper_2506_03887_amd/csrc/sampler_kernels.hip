@@ -648,7 +648,7 @@ __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
 // Lists that would run full (hundreds of ties with the bound, or a dense row where the threads' maxima do not
 // say enough) are given up: the block then takes the row chunk by chunk with masked_topk_chunked, which has no
 // such limit.
-// (15.3 us per launch at 256 x 128,256, k = 50, 4.6 TB/s: 9.4 us until the row has arrived and is worked on, 0.8 for
+// (14.6 us per launch at 256 x 128,256, k = 50, 4.8 TB/s; 15.4 us per call in a graph: 9.4 us until the row has arrived and is worked on, 0.8 for
 // the bound, 1.4 for the list, 0.7 for the ranks.  24.9 us before, with keys computed for every token, all sixteen
 // loads issued first -- behind branches, so that nothing was worked on before the last had arrived: a wave that wants
 // to issue its sixteenth load waits for it until 8 us --, a bound from quotas per wave (147 words listed) and one
