@@ -480,13 +480,13 @@ int pre3_bind_state(pre3_handle *h, int32_t *states, pre3_stacks stacks, int32_t
         h->b_states = nullptr; h->b_err = nullptr; h->b_stacks = stacks; h->bound_empty = true;
         return PRE3_OK;
     }
-    h->bound_empty = false;
     if (!states || !err || !stacks.data || !stacks.len || stacks.batch < 0 || stacks.cap < 1 ||
         stacks.cap > h->stack_cap)
         return fail(h, PRE3_E_BADARG, "bind_state: null buffer, negative batch or cap outside 1..stack_cap");
     // per-batch workspaces: each is an allocation of its own that grows with the largest batch bound
     // so far; a superseded one is freed (hipFree waits until the device no longer uses it)
-    // A failure leaves nothing bound: the workspaces of the earlier binding may be gone.
+    // A failure from here on leaves nothing bound: the workspaces of the earlier binding may be gone.
+    h->bound_empty = false;
     h->b_states = h->b_err = nullptr;
     h->b_stacks = {};
     const BatchWorkspaces need = batch_workspaces(h, stacks.batch);

@@ -366,3 +366,23 @@ def test_rows_left_open_are_walked_by_all_their_blocks():
     want = o.fill_mask(states, data, length, v)
     assert (mask.cpu().numpy().view(np.uint32) == want).all()
     assert spread < 0.5 * _graph_us(two_calls, n=2, rounds=2)
+
+
+@pytest.mark.gpu
+def test_a_refused_bind_keeps_the_earlier_binding():
+    """Bad arguments leave what is bound as it is, an empty batch included."""
+    import torch
+    from paper_2506_03887_amd import Pre3, binding
+    v, cap = _tiny_vocab(9), 16
+    lib = Pre3(G.ARITHMETIC, v.bytes, v.offsets, v.eos_id, stack_cap=cap)
+    (states, length, data, err), mask, tok = _bound(lib, 4, cap)
+    bad = binding._Stacks(data.data_ptr(), length.data_ptr(), cap + 1, 4)                 # cap beyond stack_cap
+    refuse = lambda: binding.load().pre3_bind_state(lib._h, states.data_ptr(), bad, err.data_ptr())
+    tok.fill_(0)                                                                          # "a"
+    assert refuse() == binding.E_BADARG
+    lib.advance(tok)
+    assert (length.cpu().numpy() == len(Oracle(G.ARITHMETIC).advance([lib.initial_state(0)], b"a")[1])).all()
+    empty = torch.zeros((0, cap), dtype=torch.int32, device=tok.device)
+    lib.bind_state(states[:0], empty, length[:0], err[:0])
+    assert refuse() == binding.E_BADARG
+    lib.advance(tok[:0])                                                                  # nothing to do, and no error
