@@ -262,8 +262,8 @@ __device__ __forceinline__ void copy_cycle_tables(int32_t *lds, int n_states, in
 constexpr int kAdvSeqPerBlock = 4;
 template <bool kCompact>
 __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
-    DevTables T, DevTokenEdges E, const int32_t *__restrict__ tokens, int32_t *__restrict__ states,
-    int32_t *__restrict__ data, int32_t *__restrict__ len, int cap, int batch, int32_t *__restrict__ err, int32_t *scratch,
+    const int32_t *__restrict__ tokens, int32_t *__restrict__ len, int32_t *__restrict__ states,
+    int32_t *__restrict__ data, int cap, int batch, DevTables T, DevTokenEdges E, int32_t *__restrict__ err, int32_t *scratch,
     int restart_on_eos, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles) {
     extern __shared__ int32_t adv_stage[];             // kCompact: kAdvSeqPerBlock x (cap stack entries [+ cycle tables])
     __shared__ int32_t lds_stack[kLdsDepth * kAdvSeqPerBlock];
@@ -598,8 +598,8 @@ constexpr size_t kAfStaticLdsBytes =
 constexpr size_t kAfDynamicLdsMax = 65536 - kAfStaticLdsBytes;
 template <bool kCompact, int kThreads>
 __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
-    DevTables T, DevTokenEdges E, const int32_t *__restrict__ tokens, int32_t *__restrict__ states,
-    int32_t *__restrict__ data, int32_t *__restrict__ len, int cap, int batch, int32_t *__restrict__ err,
+    const int32_t *__restrict__ tokens, int32_t *__restrict__ len, int32_t *__restrict__ states,
+    int32_t *__restrict__ data, int cap, int batch, DevTables T, DevTokenEdges E, int32_t *__restrict__ err,
     uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
     size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles) {
     extern __shared__ uint4 bits4[];                   // whole row: n_words rounded up to a multiple of 4;
@@ -724,11 +724,10 @@ constexpr int kStepAhead = 8;                          // greedy: groups of logi
 static_assert(kStepBlock == kArgBlock && kStepBlock == 16 * 64, "the step kernel combines its lanes with argmax_block_max and step_block_best");
 template <bool kCompact, int kHeld, bool kArgmax>
 __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
-    DevTables T, DevTokenEdges E, const int32_t *tokens, int32_t *__restrict__ states,
-    int32_t *__restrict__ data, int32_t *__restrict__ len, int cap, int batch, int32_t *__restrict__ err,
+    const int32_t *tokens, int32_t *__restrict__ len, int32_t *__restrict__ states, int32_t *__restrict__ data, int cap, int first_row,
+    uint16_t *__restrict__ logits, int64_t row_stride, DevTables T, DevTokenEdges E, int batch, int32_t *__restrict__ err,
     uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
-    size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
-    uint16_t *__restrict__ logits, int64_t row_stride, int32_t *out_tokens, int first_row) {
+    size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles, int32_t *out_tokens) {
     extern __shared__ uint4 bits4[];                   // the mask row; kCompact: then cap stack entries [+ cycle tables]
     __shared__ int32_t s_win[kWindow], s_new[kWindow], s_info[64];
     __shared__ int32_t s_adv_stack[kLdsDepth], s_walk_stack[kLdsDepth * 64];
@@ -998,10 +997,10 @@ constexpr int kSpreadLanes = 256, kSpreadBlock = kSpreadLanes + 64, kSpreadHeld 
 constexpr int kSpreadGroups = kSpreadLanes * kSpreadHeld;
 template <bool kCompact, bool kArgmax>
 __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
-    DevTables T, DevTokenEdges E, const int32_t *tokens, int32_t *states, int32_t *data, int32_t *len, int cap,
-    int32_t *__restrict__ err, uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_spill, int32_t *walk_spill,
-    const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
-    uint16_t *__restrict__ logits, int64_t row_stride, int32_t *out_tokens, int n_seg, StepArrivals *arrivals) {
+    const int32_t *tokens, int32_t *len, int32_t *states, int32_t *data, int cap, int n_seg, uint16_t *__restrict__ logits,
+    int64_t row_stride, DevTables T, DevTokenEdges E, int32_t *__restrict__ err, uint32_t *__restrict__ bitmask, int restart_on_eos,
+    int32_t *adv_spill, int32_t *walk_spill, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
+    int32_t *out_tokens, StepArrivals *arrivals) {
     extern __shared__ int32_t after_row[];             // kCompact: cap stack entries [+ cycle tables]
     __shared__ int32_t s_win[kWindow], s_new[kWindow], s_info[64];
     __shared__ int32_t s_adv_stack[kLdsDepth], s_walk_stack[kLdsDepth * 64];
@@ -1245,8 +1244,8 @@ __device__ __forceinline__ int try_symbols(const DevTables &T, PrivateStack &tri
 constexpr int kJfSeqPerBlock = 4;
 template <bool kCompact>
 __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
-    DevTables T, int32_t *__restrict__ states, int32_t *__restrict__ data, int32_t *__restrict__ len, int cap,
-    int batch, uint8_t *__restrict__ out_bytes, int32_t *__restrict__ out_len, int max_bytes, int32_t *adv_scratch,
+    int32_t *__restrict__ len, int32_t *__restrict__ states, int32_t *__restrict__ data, int cap, int batch, DevTables T,
+    uint8_t *__restrict__ out_bytes, int32_t *__restrict__ out_len, int max_bytes, int32_t *adv_scratch,
     int32_t *lane_spill, size_t lane_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool,
     int stage_cycles) {
     extern __shared__ int32_t jf_stage[];              // kCompact: kJfSeqPerBlock x (cap stack entries [+ cycle tables])
@@ -1460,8 +1459,8 @@ hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const
         return hipErrorInvalidValue;
     }
 #define PRE3_AF(C, THREADS)                                                                                                 \
-    hipLaunchKernelGGL((advance_fill_kernel<C, THREADS>), dim3(batch), dim3(THREADS), lds, stream, T, E, tokens, states, data,   \
-                       len, cap, batch, err, bitmask, restart_on_eos, adv_scratch, walk_spill, (size_t)batch * 64, cycle_head,  \
+    hipLaunchKernelGGL((advance_fill_kernel<C, THREADS>), dim3(batch), dim3(THREADS), lds, stream, tokens, len, states, data,   \
+                       cap, batch, T, E, err, bitmask, restart_on_eos, adv_scratch, walk_spill, (size_t)batch * 64, cycle_head,  \
                        cycle_pool, stage)
 #define PRE3_AF_SIZES(C)                                                                    \
     if (batch <= 2 * n_compute_units) PRE3_AF(C, kAfBlock);                                  \
@@ -1496,9 +1495,9 @@ static void launch_step_variant(int held, dim3 grid, size_t lds, hipStream_t str
                                 const int32_t *cycle_head, const int32_t *cycle_pool, int stage, uint16_t *logits,
                                 int64_t row_stride, int32_t *out_tokens, int first_row) {
 #define PRE3_STEP(H)                                                                                                        \
-    hipLaunchKernelGGL((advance_fill_apply_kernel<kCompact, H, kArgmax>), grid, dim3(kStepBlock), lds, stream, T, E, tokens,  \
-                       states, data, len, cap, batch, err, bitmask, restart_on_eos, adv_scratch, walk_spill,                 \
-                       (size_t)batch * 64, cycle_head, cycle_pool, stage, logits, row_stride, out_tokens, first_row)
+    hipLaunchKernelGGL((advance_fill_apply_kernel<kCompact, H, kArgmax>), grid, dim3(kStepBlock), lds, stream, tokens, len,   \
+                       states, data, cap, first_row, logits, row_stride, T, E, batch, err, bitmask, restart_on_eos,          \
+                       adv_scratch, walk_spill, (size_t)batch * 64, cycle_head, cycle_pool, stage, out_tokens)
     if (held <= kStepHeldShort) PRE3_STEP(kStepHeldShort);
     else if (held <= 17) PRE3_STEP(17);
     else if (held <= kStepHeldMaxGreedy || kArgmax) PRE3_STEP(20);
@@ -1591,9 +1590,9 @@ hipError_t launch_step_spread(const DevTables &T, const DevTokenEdges &E, const 
     }
     const int n_seg = step_spread_segments(T.n_tokens);
 #define PRE3_SPREAD(C, A)                                                                                                   \
-    hipLaunchKernelGGL((step_spread_kernel<C, A>), dim3(batch * n_seg), dim3(kSpreadBlock), lds, stream, T, E, tokens, states, data, \
-                       len, cap, err, bitmask, restart_on_eos, adv_spill, walk_spill, cycle_head, cycle_pool,   \
-                       stage, logits, row_stride, out_tokens, n_seg, arrivals)
+    hipLaunchKernelGGL((step_spread_kernel<C, A>), dim3(batch * n_seg), dim3(kSpreadBlock), lds, stream, tokens, len, states, data, cap, \
+                       n_seg, logits, row_stride, T, E, err, bitmask, restart_on_eos, adv_spill, walk_spill, cycle_head,        \
+                       cycle_pool, stage, out_tokens, arrivals)
     if (cycle_head) {
         if (out_tokens) PRE3_SPREAD(true, true);
         else PRE3_SPREAD(true, false);
@@ -1625,10 +1624,10 @@ hipError_t launch_advance(const DevTables &T, const DevTokenEdges &E, const int3
         const int stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) &&
                           (size_t)kAdvSeqPerBlock * cap * sizeof(int32_t) + tables + 4096 <= 65536;
         const size_t lds = (size_t)kAdvSeqPerBlock * cap * sizeof(int32_t) + (stage ? tables : 0);
-        hipLaunchKernelGGL(advance_kernel<true>, grid, block, lds, stream, T, E, tokens, states, data, len, cap, batch, err,
+        hipLaunchKernelGGL(advance_kernel<true>, grid, block, lds, stream, tokens, len, states, data, cap, batch, T, E, err,
                            scratch, restart_on_eos, cycle_head, cycle_pool, stage);
     } else {
-        hipLaunchKernelGGL(advance_kernel<false>, grid, block, 0, stream, T, E, tokens, states, data, len, cap, batch, err,
+        hipLaunchKernelGGL(advance_kernel<false>, grid, block, 0, stream, tokens, len, states, data, cap, batch, T, E, err,
                            scratch, restart_on_eos, nullptr, nullptr, 0);
     }
     return hipGetLastError();
@@ -1650,10 +1649,10 @@ hipError_t launch_jump_forward(const DevTables &T, int32_t *states, int32_t *dat
         const int stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) &&
                           (size_t)kJfSeqPerBlock * cap * sizeof(int32_t) + tables + 20480 <= 65536;
         const size_t lds = (size_t)kJfSeqPerBlock * cap * sizeof(int32_t) + (stage ? tables : 0);
-        hipLaunchKernelGGL(jump_forward_kernel<true>, grid, block, lds, stream, T, states, data, len, cap, batch, out_bytes,
+        hipLaunchKernelGGL(jump_forward_kernel<true>, grid, block, lds, stream, len, states, data, cap, batch, T, out_bytes,
                            out_len, max_bytes, adv_scratch, lane_spill, (size_t)batch * 64, cycle_head, cycle_pool, stage);
     } else {
-        hipLaunchKernelGGL(jump_forward_kernel<false>, grid, block, 0, stream, T, states, data, len, cap, batch, out_bytes,
+        hipLaunchKernelGGL(jump_forward_kernel<false>, grid, block, 0, stream, len, states, data, cap, batch, T, out_bytes,
                            out_len, max_bytes, adv_scratch, lane_spill, (size_t)batch * 64, nullptr, nullptr, 0);
     }
     return hipGetLastError();
