@@ -20,24 +20,25 @@ namespace {
 
 // -------------------------------------------------------------------------- advance
 
-// The bytes of a sampled token as the walk needs them: hi - lo bytes; the class/offset word of
-// byte i < 64 is staged in LDS, later ones are read through the id-ordered vocabulary at lo + i.
+// The bytes of a sampled token as the walk needs them: lane i holds the class/offset word of byte i (of the first 64;
+// later ones are read through the id-ordered vocabulary at lo + i).
 struct StagedToken {
-    int lo, hi;
+    int32_t infos;
+    int lo, n_bytes;
 };
 
-// All 64 lanes of the wave call this with the same token id: lane i fetches byte i.
-__device__ __forceinline__ StagedToken stage_token(const DevTables &T, int t, int lane, int32_t *s_info) {
-    StagedToken tok{0, 0};
-    const int32_t *rec = T.tok_info + (size_t)t * 32;           // the token's line: length and byte infos
-    const int n_bytes = rec[0];
-    if (n_bytes >= 0) {
-        tok.hi = n_bytes;
-        if (lane < n_bytes) s_info[lane] = rec[1 + lane];
-    } else {
+// The token's line (length, then 31 byte words) as one load that waits for nothing: lane i gets byte i's word, lane 31
+// the length.  finish_token makes a staged token of it (tokens longer than the line are fetched there).
+__device__ __forceinline__ int32_t fetch_token_line(const DevTables &T, int t, int lane) {
+    static_assert(kTokInfoBytes == 31, "a line is the length and 31 bytes");
+    return T.tok_info[(size_t)t * 32 + ((lane + 1) & 31)];
+}
+__device__ __forceinline__ StagedToken finish_token(const DevTables &T, int t, int32_t line, int lane) {
+    StagedToken tok{line, 0, __builtin_amdgcn_readlane(line, 31)};
+    if (tok.n_bytes < 0) {
         tok.lo = T.voffsets[t];
-        tok.hi = T.voffsets[t + 1];
-        if (tok.lo + lane < tok.hi) s_info[lane] = T.byte_info[T.vbytes[tok.lo + lane]];
+        tok.n_bytes = T.voffsets[t + 1] - tok.lo;
+        tok.infos = lane < tok.n_bytes ? T.byte_info[T.vbytes[tok.lo + lane]] : 0;
     }
     return tok;
 }
@@ -54,30 +55,23 @@ __device__ __forceinline__ int32_t deal_to_lanes(int32_t w, const NativeInt16 &v
     }
 }
 
-// stage_token through the scalar cache: the token's 128-byte line comes as two 16-word loads, whose words
-// are dealt out to the lanes (lane i gets byte i's word) and stored with one LDS write.  Tokens longer
-// than the line holds take the vector path.
-__device__ __forceinline__ StagedToken stage_token_scalar(const DevTables &T, int t, int lane, int32_t *s_info) {
+// fetch_token_line through the scalar cache: the line comes as two 16-word loads, whose words are dealt out to the lanes.
+__device__ __forceinline__ int32_t fetch_token_line_scalar(const DevTables &T, int t) {
     const int32_t *rec = T.tok_info + (size_t)t * 32;
     const NativeInt16 a = scalar_load16(rec), b = scalar_load16(rec + 16);
-    const int n_bytes = a[0];
-    if (n_bytes < 0) return stage_token(T, t, lane, s_info);
-    static_assert(kTokInfoBytes == 31, "two 16-word loads hold the length and 31 bytes");
     int32_t w = 0;
     w = deal_to_lanes<0, 1, 15>(w, a);
     w = deal_to_lanes<15, 0, 16>(w, b);
-    if (lane < n_bytes) s_info[lane] = w;
-    return StagedToken{0, n_bytes};
+    return deal_to_lanes<31, 0, 1>(w, a);
 }
 
-// The top 64 entries of a stack (win[k] = entry k below the top, -1 beyond the bottom) through the scalar
+// The top 64 entries of a stack (lane k: entry k below the top, -1 beyond the bottom) through the scalar
 // cache: four 16-entry loads that end at the top -- each moved to where it lies wholly inside the row's
-// cap entries, cap >= 16 --, dealt out to the lanes and stored with one LDS write.
-__device__ __forceinline__ void stage_window_scalar(const int32_t *row, int n, int cap, bool shape_ok, int lane, int32_t *win) {
-    win[lane] = -1;
-    if (!shape_ok) return;
+// cap entries, cap >= 16 --, dealt out to the lanes and put in order with one lane permute.
+__device__ __forceinline__ int32_t fetch_window_scalar(const int32_t *row, int n, int cap, bool shape_ok, int lane) {
+    if (!shape_ok) return -1;
     int32_t w = 0;
-    int my_lo = 0;
+    int my_lo = 0;                                      // first entry of the chunk that holds this lane's entry
     auto chunk_begin = [&](int c) {
         int lo = n - 16 * (c + 1);
         lo = lo < 0 ? 0 : lo;
@@ -88,60 +82,54 @@ __device__ __forceinline__ void stage_window_scalar(const int32_t *row, int n, i
     const int lo0 = chunk_begin(0);
     w = deal_to_lanes<0, 0, 16>(w, scalar_load16(row + lo0));
     my_lo = lo0;
-    int dealt = 16;                                     // lanes that hold an entry
     if (n > 16) {
         const int lo1 = chunk_begin(1);
         w = deal_to_lanes<16, 0, 16>(w, scalar_load16(row + lo1));
         if (lane >= 16) my_lo = lo1;
-        dealt = 32;
         if (n > 32) {
             const int lo2 = chunk_begin(2);
             w = deal_to_lanes<32, 0, 16>(w, scalar_load16(row + lo2));
             if (lane >= 32) my_lo = lo2;
-            dealt = 48;
             if (n > 48) {
                 const int lo3 = chunk_begin(3);
                 w = deal_to_lanes<48, 0, 16>(w, scalar_load16(row + lo3));
                 if (lane >= 48) my_lo = lo3;
-                dealt = 64;
             }
         }
     }
-    const int idx = my_lo + (lane & 15), k = n - 1 - idx;
-    if (lane < dealt && idx < n && k >= 0 && k < kWindow) win[k] = w;
+    // entry k below the top is entry n - 1 - k, in the chunk k / 16 (whose begin the lanes of that chunk hold)
+    const int idx = n - 1 - lane;
+    const int32_t x = __shfl(w, (lane & 48) + ((idx - my_lo) & 15));
+    return idx >= 0 ? x : -1;
 }
 
 constexpr int kScalarRunMin = 8;       // bytes left in a token before a scalar-only walk looks for a run
 
-// Walks a staged token from the configuration  view ++ priv[0..d)  with capacity checks.  Runs on
-// all 64 lanes with identical values (scalar table loads, LDS broadcast reads); a run of
+// Walks a staged token from the configuration  row[0..base) ++ pushed[0..d)  with capacity checks.  Runs on
+// all 64 lanes with identical values (scalar table loads, single lanes of the wave's registers); a run of
 // self-similar edges is applied in one step.  Returns kFed, kRejected or kOverflow.
 template <bool kScalar = false>
-__device__ __forceinline__ int walk_staged_token(const DevTables &T, PrivateStack &priv, const int32_t *s_info,
-                                                 StagedToken tok, const StackView &view, int cap, int &base, int &d,
-                                                 int &top, int &kind) {
-    const int n_bytes = tok.hi - tok.lo;
-    int rc = n_bytes > 0 ? kFed : kRejected;
-    for (int i = 0; i < n_bytes && rc == kFed; ++i) {
-        int info = lds_read(s_info + (i < 64 ? i : 63));
-        if (i >= 64) info = T.byte_info[T.vbytes[tok.lo + i]];
-        info = __builtin_amdgcn_readfirstlane(info);
+__device__ __forceinline__ int walk_staged_token(const DevTables &T, WaveStack &ws, const StagedToken &tok, int cap, int &base,
+                                                 int &d, int &top, int &kind) {
+    int rc = tok.n_bytes > 0 ? kFed : kRejected;
+    for (int i = 0; i < tok.n_bytes && rc == kFed; ++i) {
+        int info = __builtin_amdgcn_readlane(tok.infos, i < 64 ? i : 63);
+        if (i >= 64) info = __builtin_amdgcn_readfirstlane(T.byte_info[T.vbytes[tok.lo + i]]);
         int run_node = -1;
-        rc = feed<true, true, kScalar>(T, priv, info, base, d, top, kind, view, cap, &run_node);
+        rc = feed<true, true, kScalar>(T, ws, info, base, d, top, kind, ws, cap, &run_node);
         // (a run is examined with one vector load per lane: a wave that keeps to scalar loads takes short tails byte by byte)
-        if (rc == kFed && run_node >= 0 && i + 1 < n_bytes && (!kScalar || n_bytes - (i + 1) >= kScalarRunMin))
-            i += apply_run<true>(T, priv, s_info, i + 1, n_bytes, run_node, kind, base, d, top, cap);
+        if (rc == kFed && run_node >= 0 && i + 1 < tok.n_bytes && (!kScalar || tok.n_bytes - (i + 1) >= kScalarRunMin))
+            i += apply_run<true>(T, ws, tok.infos, i + 1, tok.n_bytes, run_node, kind, base, d, top, cap);
     }
     return rc;
 }
 
-// Writes the d private entries of a finished walk above row[0..base): the first kLdsDepth by one
-// lane each, entries that spilled to global memory by lane 0.
-__device__ __forceinline__ void commit_overlay(int32_t *row, const PrivateStack &priv, int base, int d, int lane) {
-    const int in_lds = d < kLdsDepth ? d : kLdsDepth;
-    if (lane < in_lds) row[base + lane] = priv.get(lane);
+// Writes the d pushed states of a finished walk above row[0..base): the first 64 by one lane each, states that
+// spilled to global memory by lane 0.
+__device__ __forceinline__ void commit_pushed(int32_t *row, const WaveStack &ws, int base, int d, int lane) {
+    if (lane < d) row[base + lane] = ws.pushed;
     if (lane == 0)
-        for (int i = kLdsDepth; i < d; ++i) row[base + i] = priv.get(i);
+        for (int i = kWindow; i < d; ++i) row[base + i] = global_read(ws.spill + (size_t)(i - kWindow) * ws.spill_stride);
 }
 
 // Cycle-aware stack compaction (Sec. 3.2.3; Alg. 1 step 1) of a stack staged in LDS, s[0 .. n): a
@@ -251,12 +239,170 @@ __device__ __forceinline__ void copy_cycle_tables(int32_t *lds, int n_states, in
     for (int i = first; i < pool_n; i += step) lds[n_states + i] = pool[i];
 }
 
+// What an advance leaves to be stored: the new stack is  row[0 .. base) ++ pushed[0 .. d)  (or, compacted, the first
+// nl entries staged in LDS, of which those from `from` on changed; just its bottom entry after a restart).
+struct Advanced {
+    int base, d, nl, from, n, token, out_err, out_state;
+    bool shape_ok, restarted;
+};
+
+// Walks one sequence's sampled token on its stack (or applies the token's stack-effect record): the work of one
+// wave, all 64 lanes with identical values, the stack in the wave's registers (ws).  Only a walk that succeeds changes the
+// stack; nothing is stored: commit_advance does that.  `meet` is called once, when the inputs' loads are under way.
+// The launches that wait for it are bound by this chain of dependent look-ups, and what a link costs is as much its
+// instructions as its load.  The window, the token's bytes and the pushed states are in registers instead of LDS (one lane
+// read looks at an entry), a child's record comes out of its lane with lane reads instead of permutes, and the token's
+// line and the state's kind are in the round of loads that fetches the window: bursts of 8 steps of 64 x 32,000 in a graph
+// 76.8 -> 68.6 us, 1 x 128,256 57.9 -> 54.2, fill + mask + advance of 96 x 100,003 168 -> 158, advance + fill before a top-k
+// of 256 x 128,256 187 -> 181, greedy steps of 320 x 128,256 with cycle-aware stacks 265 -> 255.
+template <bool kScalar, class Meet>
+__device__ __forceinline__ Advanced advance_stack(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens,
+                                                  const int32_t *states, const int32_t *len, int cap, int restart_on_eos,
+                                                  WaveStack &ws, int b, int lane, Meet meet) {
+    const int32_t *row = ws.row;
+    const int t = table<true>(tokens, b), n = table<true>(len, b), st = table<true>(states, b);
+    const bool shape_ok = n >= 1 && n <= cap;
+    const bool live = t >= 0 && t < T.n_tokens && st >= 0 && shape_ok;
+    // one round: the stack window, the token's line, and -- states[b] names the stack's top -- that state's kind and the root
+    // of its condition tree, from which the look-up of the token's stack operations starts
+    int fx_root = -1, kind = 0;
+    DevConditionNode fx_nd{};
+    int32_t line = 0;
+    if (live && (unsigned)st < (unsigned)T.n_states) {
+        if (T.state_kind) kind = table<true>(T.state_kind, st);
+        if (E.fx_slots && t != T.eos_id) {
+            fx_root = table<true>(E.root_id, st);
+            fx_nd = scalar_node(E.root_nodes + st);
+        }
+    }
+    if (kScalar && cap >= 16) ws.win = fetch_window_scalar(row, n, cap, shape_ok, lane);
+    else ws.win = (shape_ok && n - 1 - lane >= 0) ? row[n - 1 - lane] : -1;
+    if (live && t != T.eos_id) line = kScalar ? fetch_token_line_scalar(T, t) : fetch_token_line(T, t, lane);
+    ws.pushed = 0;
+    ws.n = n;
+    meet();
+    int out_err = 0, out_state = st, out_len = n, base = n, d = 0;
+    bool restarted = false;
+    if (t >= 0) {
+        int top = live ? __builtin_amdgcn_readlane(ws.win, 0) : -1;
+        if (!live || (unsigned)top >= (unsigned)T.n_states) {
+            out_err = 1;
+        } else {
+            if (top != st && T.state_kind) kind = table<true>(T.state_kind, top);
+            if (t == T.eos_id) {
+                if (feed<false, true, kScalar>(T, ws, T.end_col, base, d, top, kind, ws, 0) == kAccepted) {
+                    out_state = -1;
+                    if (restart_on_eos) {               // slot reuse: back to the initial state, the stack's bottom entry
+                        out_state = ws.at(0);
+                        out_len = 1;
+                        restarted = true;
+                    }
+                } else {
+                    out_err = 1;
+                }
+                base = n;
+                d = 0;                               // the '$' walk never changes the stack
+            } else {
+                // a longer token whose merged edge carries its stack operations is applied in one
+                // step (look-up, truncate, push); every other token is walked byte by byte
+                const StagedToken tok = finish_token(T, t, line, lane);
+                EffectHit fx{0, 0, 0, 0, 0, 0, 0};
+                if (fx_root >= 0 && top == st && tok.n_bytes >= E.fx_min_len) {
+                    auto deeper = [&](int k2) { return global_read(row + (n - 1 - k2)); };
+                    fx = kScalar ? find_effect_scalar(E, fx_root, fx_nd, ws.win, n, deeper, t)
+                                 : find_effect(E, fx_root, fx_nd, ws.win, n, deeper, t, lane);
+                }
+                int rc;
+                if (fx.found && fx.k <= n && fx.np <= T.max_depth) {
+                    if (n + fx.peak >= cap) {
+                        rc = kOverflow;
+                    } else {
+                        base = n - fx.k + 1;
+                        d = fx.np;
+                        if (fx.inline_count > 0) {
+                            top = fx.inline_count == 2 ? fx.x1 : fx.x0;
+                            ws.pushed = lane == 0 ? fx.x0 : fx.x1;
+                        } else {
+                            for (int i0 = 0; i0 < d; i0 += 64) {         // (64 states at a time, one load)
+                                const int32_t v = i0 + lane < d ? E.fx_pool[fx.x0 + i0 + lane] : 0;
+                                if (i0 == 0) ws.pushed = v;
+                                else if (i0 + lane < d) ws.spill[(size_t)(i0 - kWindow + lane) * ws.spill_stride] = v;
+                                if (d - i0 <= 64) top = __builtin_amdgcn_readlane(v, d - 1 - i0);
+                            }
+                            if (d > kWindow) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // other lanes read them back
+                        }
+                        rc = kFed;
+                    }
+                } else {
+                    rc = walk_staged_token<kScalar>(T, ws, tok, cap, base, d, top, kind);
+                }
+                if (rc != kFed) {
+                    out_err = rc == kOverflow ? 2 : 1;
+                    base = n;
+                    d = 0;
+                } else {
+                    out_len = base + d;
+                    out_state = top;
+                }
+            }
+        }
+    }
+    return Advanced{base, d, out_len, 0, n, t, out_err, out_state, shape_ok, restarted};
+}
+
+// The entries 0 .. 63 below the top of  row[0 .. base) ++ pushed[0 .. d), one per lane (-1 beyond the bottom).
+__device__ __forceinline__ int32_t new_window(const WaveStack &ws, int base, int d, int lane) {
+    const int i = d - 1 - lane, idx = base + i, k = ws.n - 1 - idx;      // pushed[i] if i >= 0, else row[idx], k below the old top
+    int32_t pushed = __shfl(ws.pushed, i & 63), old = __shfl(ws.win, k & 63);
+    if (i >= kWindow) pushed = global_read(ws.spill + (size_t)(i - kWindow) * ws.spill_stride);
+    if (i < 0 && idx >= 0 && k >= kWindow && ws.n >= 1) old = global_read(ws.row + idx);
+    return i >= 0 ? pushed : idx >= 0 ? old : -1;
+}
+
+// Cycle-aware stacks: puts the new stack together at `stack` (LDS, cap entries), takes complete traversals of
+// reduction cycles out of it and notes in `r` what is left and what of it changed.
+__device__ __forceinline__ void fold_new_stack(Advanced &r, const WaveStack &ws, int32_t *stack, const int32_t *cycle_head,
+                                               const int32_t *cycle_pool, int n_states, int lane) {
+    for (int i0 = 0; i0 < r.nl; i0 += 64) {
+        const int i = i0 + lane, k = ws.n - 1 - i, p = i - r.base;
+        int32_t old = __shfl(ws.win, k & 63), pushed = __shfl(ws.pushed, p & 63);
+        if (i < r.nl) {
+            if (p < 0 && k >= kWindow) old = global_read(ws.row + i);
+            if (p >= kWindow) pushed = global_read(ws.spill + (size_t)(p - kWindow) * ws.spill_stride);
+            stack[i] = p < 0 ? old : pushed;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    int nl = r.nl, first_moved = nl;                    // (1 after a restart: only the bottom entry stays)
+    if (nl >= 2) nl = fold_cycles(stack, nl, cycle_head, cycle_pool, n_states, lane, &first_moved);
+    r.from = r.restarted ? nl : (first_moved < r.base ? first_moved : r.base);
+    r.nl = nl;
+}
+
+// Stores what an advance found: the entries of the new stack that changed, states, len and err.
+template <bool kCompact>
+__device__ __forceinline__ void commit_advance(const Advanced &r, const WaveStack &ws, const int32_t *after_row, int32_t *states,
+                                               int32_t *row, int32_t *len, int32_t *err, int cap, int b, int lane) {
+    if (kCompact && r.shape_ok) {
+        for (int i = r.from + lane; i < r.nl; i += 64) row[i] = after_row[i];
+        if (lane == 0) {
+            err[b] = r.out_err;
+            if ((r.out_err == 0 && r.token >= 0) || r.nl != r.n) { states[b] = r.out_state; len[b] = r.nl; }
+        }
+    } else {
+        commit_pushed(row, ws, r.base, r.d, lane);
+        if (lane == 0) {
+            err[b] = r.out_err;
+            if (r.out_err == 0 && r.token >= 0) { states[b] = r.out_state; len[b] = r.nl; }
+        }
+    }
+}
+
 // One wave per sequence: the walk of a single token is a chain of dependent table look-ups, so
 // giving every sequence its own wave keeps control flow uniform (lanes of a shared wave would
 // serialise each other's reduction chains) and lets the chip overlap the chains of all
-// sequences.  The walk runs on a private overlay exactly like in the mask kernels; only a walk
-// that succeeds is committed to the sequence's stack.
-// kCompact (cycle-aware stacks): instead of committing the private entries, the wave puts the new
+// sequences.
+// kCompact (cycle-aware stacks): instead of storing the pushed states, the wave puts the new
 // stack together in LDS (cap entries per sequence), takes complete traversals of reduction cycles
 // out of it (fold_cycles) and writes back what changed.
 constexpr int kAdvSeqPerBlock = 4;
@@ -266,10 +412,7 @@ __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
     int32_t *__restrict__ data, int cap, int batch, DevTables T, DevTokenEdges E, int32_t *__restrict__ err, int32_t *scratch,
     int restart_on_eos, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles) {
     extern __shared__ int32_t adv_stage[];             // kCompact: kAdvSeqPerBlock x (cap stack entries [+ cycle tables])
-    __shared__ int32_t lds_stack[kLdsDepth * kAdvSeqPerBlock];
-    __shared__ int32_t s_win[kAdvSeqPerBlock][kWindow], s_info[kAdvSeqPerBlock][64];
-    __shared__ int32_t s_base[kAdvSeqPerBlock], s_depth[kAdvSeqPerBlock];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int b = blockIdx.x * kAdvSeqPerBlock + wave;
     // kCompact with small cycle tables: the block copies them into LDS behind the staged stacks; every
     // wave passes exactly one block barrier (a wave without a sequence right here, the others once
@@ -284,301 +427,63 @@ __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
         if (kCompact && stage_cycles) __syncthreads();
         return;
     }
-    int32_t *row = data + (size_t)b * cap;
-    PrivateStack priv;
-    priv.lds = lds_stack + wave;
-    priv.lds_stride = kAdvSeqPerBlock;
-    priv.spill = scratch + b;
-    priv.spill_stride = (size_t)batch;
-    // every lane: the sequence's inputs, then (in parallel across lanes) the top of the stack and
-    // the byte classes of the token, so that the walk finds them in LDS
-    const int t = tokens[b];
-    const int n = len[b];
-    const int st = states[b];
-    const bool live = t >= 0 && t < T.n_tokens && st >= 0 && n >= 1 && n <= cap;
-    StagedToken tok{0, 0};
-    // the root of the condition tree of the stack's top (states[b] names it) is fetched together with
-    // the stack window and the token's bytes: the look-up of the token's stack operations starts from it
-    int fx_root = -1;
-    DevConditionNode fx_nd{};
-    if (E.fx_slots && live && t != T.eos_id && (unsigned)st < (unsigned)T.n_states) {
-        fx_root = E.root_id[st];
-        fx_nd = E.root_nodes[st];
-    }
-    if (live) {
-        s_win[wave][lane] = n - 1 - lane >= 0 ? row[n - 1 - lane] : -1;
-        if (t != T.eos_id) tok = stage_token(T, t, lane, s_info[wave]);
-    }
-    if (kCompact && stage_cycles) __syncthreads();
-    __builtin_amdgcn_wave_barrier();
-    // all lanes hold identical values from here on; lane 0 alone writes the results
-    int commit = -1, out_err = 0, out_state = st, out_len = n;
-    int new_base = n, new_d = 0;                        // the new stack is  row[0 .. new_base) ++ priv[0 .. new_d)
-    if (t >= 0) {
-        int top = live ? __builtin_amdgcn_readfirstlane(s_win[wave][0]) : -1;
-        if (!live || (unsigned)top >= (unsigned)T.n_states) {
-            out_err = 1;
-        } else {
-            const StackView view{row, s_win[wave], n};
-            int base = n, d = 0;
-            int kind = T.state_kind ? table<true>(T.state_kind, top) : 0;
-            if (t == T.eos_id) {
-                if (feed<false, true>(T, priv, T.end_col, base, d, top, kind, view, 0) == kAccepted) {
-                    out_state = -1;
-                    if (restart_on_eos) { out_state = row[0]; out_len = 1; }   // slot reuse: back to the initial state
-                } else {
-                    out_err = 1;
-                }
-            } else {
-                // a longer token whose merged edge carries its stack operations is applied in one step
-                // (look-up, truncate, push), as in advance_fill_kernel; every other token is walked
-                EffectHit fx{0, 0, 0, 0, 0, 0, 0};
-                if (fx_root >= 0 && top == st && tok.hi - tok.lo >= E.fx_min_len)
-                    fx = find_effect(E, __builtin_amdgcn_readfirstlane(fx_root), fx_nd, s_win[wave], n,
-                                     [&](int k2) { return global_read(row + (n - 1 - k2)); }, t, lane);
-                int rc;
-                if (fx.found && fx.k <= n && fx.np <= T.max_depth) {
-                    if (n + fx.peak >= cap) {
-                        rc = kOverflow;
-                    } else {
-                        base = n - fx.k + 1;
-                        if (fx.inline_count > 0) {
-                            priv.set(0, fx.x0);
-                            top = fx.x0;
-                            if (fx.inline_count == 2) { priv.set(1, fx.x1); top = fx.x1; }
-                        } else {
-                            for (int i = 0; i < fx.np; ++i) {
-                                top = table<true>(E.fx_pool, fx.x0 + i);
-                                priv.set(i, top);
-                            }
-                        }
-                        d = fx.np;
-                        rc = kFed;
-                    }
-                } else {
-                    rc = walk_staged_token(T, priv, s_info[wave], tok, view, cap, base, d, top, kind);
-                }
-                if (rc != kFed) {
-                    out_err = rc == kOverflow ? 2 : 1;
-                } else {
-                    commit = d;
-                    out_len = base + d;
-                    out_state = top;
-                    s_base[wave] = base;
-                    new_base = base;
-                    new_d = d;
-                }
-            }
-        }
-        if (lane == 0) {
-            err[b] = out_err;
-            if (out_err == 0) { states[b] = out_state; len[b] = out_len; }
-        }
-    } else if (lane == 0) {
-        err[b] = 0;
-    }
-    if (kCompact && n >= 1 && n <= cap) {
-        int32_t *stack = adv_stage + wave * cap;
-        int nl = out_len;                               // 1 after a restart: only the bottom entry stays
-        for (int i = lane; i < nl; i += 64) stack[i] = i < new_base ? row[i] : priv.get(i - new_base);
-        __builtin_amdgcn_wave_barrier();
-        int first_moved = nl;
-        if (nl >= 2) nl = fold_cycles(stack, nl, cycle_head, cycle_pool, T.n_states, lane, &first_moved);
-        const int from = first_moved < new_base ? first_moved : new_base;
-        for (int i = from + lane; i < nl; i += 64) row[i] = stack[i];
-        if (lane == 0 && nl != out_len) len[b] = nl;    // the top, hence states[b], is the same
-        return;
-    }
-    s_depth[wave] = commit;
-    __builtin_amdgcn_wave_barrier();
-    const int d = s_depth[wave];
-    if (d > 0) commit_overlay(row, priv, s_base[wave], d, lane);
+    int32_t *row = data + (size_t)b * cap, *stack = adv_stage + wave * cap;
+    WaveStack ws{row, scratch + b, (size_t)batch, 0, 0, 0};
+    Advanced r = advance_stack<false>(T, E, tokens, states, len, cap, restart_on_eos, ws, b, lane,
+                                      [&] { if (kCompact && stage_cycles) __syncthreads(); });
+    if (kCompact && r.shape_ok) fold_new_stack(r, ws, stack, cycle_head, cycle_pool, T.n_states, lane);
+    commit_advance<kCompact>(r, ws, stack, states, row, len, err, cap, b, lane);
 }
 
-// What an advance leaves to be stored: the new stack is  row[0 .. base) ++ priv[0 .. d)  (or, compacted, the first
-// nl entries staged in LDS, of which those from `from` on changed).
-struct Advanced {
-    int base, d, nl, from, n, token, out_err, out_state;
-};
-
-// The work of the wave that advances one sequence (all 64 lanes with identical values): walks the
-// sampled token (or applies its stack-effect record), stages the new top of
-// the stack in s_new and descends the condition tree of the token-level edges with it; the result is
-// `plan`.  Nothing is stored: commit_advance does that.  kCompact: the new stack is put together at after_row (LDS, cap
+// The work of the wave that advances one sequence and looks up its next mask row: walks the sampled token
+// (advance_stack), then descends the condition tree of the token-level edges with the new stack; the result is
+// `plan`.  kCompact: the new stack is put together at after_row (LDS, cap
 // entries), folded and only then looked up; stage_cycles: the block's other waves copy the cycle tables to
 // after_row + cap meanwhile and meet this wave at one block barrier.
+// The tree is descended BEFORE anything is stored: a wave that has stores in flight waits for them wherever it next waits
+// for a load, and in the one-launch step kernel they complete only behind the row loads of the block's other waves.
 template <bool kCompact, bool kScalar = false>
-__device__ __forceinline__ Advanced advance_and_plan(const DevTables &T, const DevTokenEdges &E, const int32_t *__restrict__ tokens,
-                                                 const int32_t *states, const int32_t *row, const int32_t *len,
-                                                 int cap, int restart_on_eos,
-                                                 PrivateStack &priv, const int32_t *cycle_head, const int32_t *cycle_pool,
-                                                 int stage_cycles, int32_t *after_row, int32_t *s_win, int32_t *s_new,
-                                                 int32_t *s_info, RowPlan &plan, int b, int lane) {
-    const int t = kScalar ? table<true>(tokens, b) : tokens[b];
-    const int n = kScalar ? table<true>(len, b) : len[b];
-    const int st = kScalar ? table<true>(states, b) : states[b];
-    const bool shape_ok = n >= 1 && n <= cap;
-    const bool live = t >= 0 && t < T.n_tokens && st >= 0 && shape_ok;
-    StagedToken tok{0, 0};
-    // the root of the condition tree of the stack's top (states[b] names it) is fetched together
-    // with the stack window and the token's bytes: the effect look-up starts from it
-    int fx_root = -1;
-    DevConditionNode fx_nd{};
-    if (E.fx_slots && live && t != T.eos_id && (unsigned)st < (unsigned)T.n_states) {
-        fx_root = kScalar ? table<true>(E.root_id, st) : E.root_id[st];
-        fx_nd = kScalar ? scalar_node(E.root_nodes + __builtin_amdgcn_readfirstlane(st)) : E.root_nodes[st];
-    }
-    if (kScalar && cap >= 16) {
-        stage_window_scalar(row, n, cap, shape_ok, lane, s_win);
-        if (live && t != T.eos_id) tok = stage_token_scalar(T, __builtin_amdgcn_readfirstlane(t), lane, s_info);
-    } else {
-        s_win[lane] = (shape_ok && n - 1 - lane >= 0) ? row[n - 1 - lane] : -1;
-        if (live && t != T.eos_id) tok = stage_token(T, t, lane, s_info);
-    }
-    if (kCompact && stage_cycles) {                 // the other waves have copied the cycle tables meanwhile
-        __syncthreads();
-        int32_t *cycle_lds = after_row + cap;
-        cycle_head = cycle_lds;
-        cycle_pool = cycle_lds + T.n_states;
-    }
-    __builtin_amdgcn_wave_barrier();
-    // ---- advance (all lanes hold identical values)
-    int out_err = 0, out_state = st, out_len = n, base = n, d = 0;
-    bool restarted = false;
-    if (t >= 0) {
-        int top = live ? __builtin_amdgcn_readfirstlane(s_win[0]) : -1;
-        if (!live || (unsigned)top >= (unsigned)T.n_states) {
-            out_err = 1;
-        } else {
-            const StackView view{row, s_win, n};
-            int kind = T.state_kind ? table<true>(T.state_kind, top) : 0;
-            if (t == T.eos_id) {
-                if (feed<false, true, kScalar>(T, priv, T.end_col, base, d, top, kind, view, 0) == kAccepted) {
-                    out_state = -1;
-                    if (restart_on_eos) { out_state = row[0]; out_len = 1; restarted = true; }   // slot reuse
-                } else {
-                    out_err = 1;
-                }
-                base = n;
-                d = 0;                               // the '$' walk never changes the stack
-            } else {
-                // a longer token whose merged edge carries its stack operations is applied in one
-                // step (look-up, truncate, push); every other token is walked byte by byte
-                EffectHit fx{0, 0, 0, 0, 0, 0, 0};
-                if (fx_root >= 0 && top == st && tok.hi - tok.lo >= E.fx_min_len) {
-                    if (kScalar)
-                        fx = find_effect_scalar(E, __builtin_amdgcn_readfirstlane(fx_root), fx_nd, s_win, n,
-                                                [&](int k2) { return global_read(row + (n - 1 - k2)); }, __builtin_amdgcn_readfirstlane(t));
-                    else
-                        fx = find_effect(E, __builtin_amdgcn_readfirstlane(fx_root), fx_nd, s_win, n,
-                                         [&](int k2) { return global_read(row + (n - 1 - k2)); }, t, lane);
-                }
-                int rc;
-                if (fx.found && fx.k <= n && fx.np <= T.max_depth) {
-                    if (n + fx.peak >= cap) {
-                        rc = kOverflow;
-                    } else {
-                        base = n - fx.k + 1;
-                        if (fx.inline_count > 0) {
-                            priv.set(0, fx.x0);
-                            top = fx.x0;
-                            if (fx.inline_count == 2) { priv.set(1, fx.x1); top = fx.x1; }
-                        } else {
-                            for (int i = 0; i < fx.np; ++i) {
-                                top = table<true>(E.fx_pool, fx.x0 + i);
-                                priv.set(i, top);
-                            }
-                        }
-                        d = fx.np;
-                        rc = kFed;
-                    }
-                } else {
-                    rc = walk_staged_token<kScalar>(T, priv, s_info, tok, view, cap, base, d, top, kind);
-                }
-                if (rc != kFed) {
-                    out_err = rc == kOverflow ? 2 : 1;
-                    base = n;
-                    d = 0;
-                } else {
-                    out_len = base + d;
-                    out_state = top;
-                }
-            }
+__device__ __forceinline__ Advanced advance_and_plan(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens,
+                                                 const int32_t *states, const int32_t *len, int cap, int restart_on_eos,
+                                                 WaveStack &ws, const int32_t *cycle_head, const int32_t *cycle_pool,
+                                                 int stage_cycles, int32_t *after_row, RowPlan &plan, int b, int lane) {
+    Advanced r = advance_stack<kScalar>(T, E, tokens, states, len, cap, restart_on_eos, ws, b, lane, [&] {
+        if (kCompact && stage_cycles) {                 // the other waves have copied the cycle tables meanwhile
+            __syncthreads();
+            int32_t *cycle_lds = after_row + cap;
+            cycle_head = cycle_lds;
+            cycle_pool = cycle_lds + T.n_states;
         }
+    });
+    int32_t win;                                        // the top of the new stack
+    if (kCompact && r.shape_ok) {
+        fold_new_stack(r, ws, after_row, cycle_head, cycle_pool, T.n_states, lane);
+        win = lane < r.nl ? after_row[r.nl - 1 - lane] : -1;
+    } else {
+        win = r.restarted ? (lane == 0 ? r.out_state : -1) : new_window(ws, r.base, r.d, lane);
     }
-    // ---- the new stack is  row[0 .. base) ++ priv[0 .. d)  (or just its bottom after a restart).
-    // Its top is staged and the condition tree descended BEFORE anything is stored: a wave that has
-    // stores in flight waits for them wherever it next waits for a load, and in the one-launch step
-    // kernel they complete only behind the row loads of the block's other waves.
-    Advanced r;
-    r.base = base; r.d = d; r.nl = out_len; r.from = 0; r.n = n; r.token = t; r.out_err = out_err; r.out_state = out_state;
-    int nl = out_len;
-    int32_t *stack = after_row;                         // kCompact
-    if (kCompact && shape_ok) {
-        // put it together in LDS and compact it
-        for (int i = lane; i < nl; i += 64)
-            stack[i] = i < base ? StackView{row, s_win, n}.at(i) : priv.get(i - base);
-        __builtin_amdgcn_wave_barrier();
-        int first_moved = nl;
-        if (nl >= 2) nl = fold_cycles(stack, nl, cycle_head, cycle_pool, T.n_states, lane, &first_moved);
-        r.from = restarted ? nl : (first_moved < base ? first_moved : base);
-        r.nl = nl;
-        s_new[lane] = lane < nl ? stack[nl - 1 - lane] : -1;
-    }
-    auto new_at = [&](int k) -> int32_t {               // entry k below the new top
-        if (kCompact && shape_ok) return k < nl ? stack[nl - 1 - k] : -1;
-        if (restarted) return k == 0 ? (kScalar ? table<true>(row, 0) : row[0]) : -1;
-        if (k < d) return priv.get(d - 1 - k);
-        const int idx = base - 1 - (k - d);
-        return idx >= 0 ? StackView{row, s_win, n}.at(idx) : -1;
+    auto deeper = [&](int k) -> int32_t {               // entry k >= 64 below the new top
+        if (kCompact && r.shape_ok) return after_row[r.nl - 1 - k];
+        return k < r.d ? ws.get(r.d - 1 - k) : ws.at(r.base - 1 - (k - r.d));
     };
-    if (!(kCompact && shape_ok)) s_new[lane] = (shape_ok && lane < nl) ? new_at(lane) : -1;
-    __builtin_amdgcn_wave_barrier();
     // ---- descent of the condition tree with the new stack
-    const int top = s_new[0];
-    if (out_state < 0) {
+    const int top = __builtin_amdgcn_readlane(win, 0);
+    if (r.out_state < 0) {
         if (lane == 0) plan.mode = kRowDone;
-    } else if (!shape_ok || (unsigned)top >= (unsigned)T.n_states) {
+    } else if (!r.shape_ok || (unsigned)top >= (unsigned)T.n_states) {
         if (lane == 0) plan.mode = kRowEmpty;
     } else {
-        if (kScalar) plan_row_scalar(E, scalar_node(E.root_nodes + __builtin_amdgcn_readfirstlane(top)), s_new, nl, new_at, &plan, lane);
-        else plan_row(E, E.root_nodes[top], s_new, nl, new_at, &plan, lane);
+        const DevConditionNode root = scalar_node(E.root_nodes + top);
+        if (kScalar) plan_row_scalar(E, root, win, r.nl, deeper, &plan, lane);
+        else plan_row(E, root, win, r.nl, deeper, &plan, lane);
     }
-    if (lane == 0) { plan.top = top; plan.len = nl; }
+    if (lane == 0) { plan.top = top; plan.len = r.nl; }
     return r;
 }
 
-// Stores what advance_and_plan found: the entries of the new stack that changed, states, len and err.
-template <bool kCompact>
-__device__ __forceinline__ void commit_advance(const Advanced &r, const PrivateStack &priv, const int32_t *after_row, int32_t *states,
-                                               int32_t *row, int32_t *len, int32_t *err, int cap, int b, int lane) {
-    if (kCompact && r.n >= 1 && r.n <= cap) {
-        for (int i = r.from + lane; i < r.nl; i += 64) row[i] = after_row[i];
-        if (lane == 0) {
-            err[b] = r.out_err;
-            if ((r.out_err == 0 && r.token >= 0) || r.nl != r.n) { states[b] = r.out_state; len[b] = r.nl; }
-        }
-    } else {
-        commit_overlay(row, priv, r.base, r.d, lane);
-        if (lane == 0) {
-            err[b] = r.out_err;
-            if (r.out_err == 0 && r.token >= 0) { states[b] = r.out_state; len[b] = r.nl; }
-        }
-    }
-}
-
-__device__ __forceinline__ PrivateStack wave_stack(int32_t *s_adv_stack, int32_t *spill, size_t spill_stride) {
-    PrivateStack priv;
-    priv.lds = s_adv_stack;
-    priv.lds_stride = 1;
-    priv.spill = spill;
-    priv.spill_stride = spill_stride;
-    return priv;
-}
-
 // Advance and next mask in one launch: one block per sequence.  Wave 0 walks the sampled token
-// exactly like advance_kernel (scalar table loads), stages the NEW top of the stack in LDS, descends
-// the condition tree of the token-level edges with it and commits the new stack; then the
+// exactly like advance_kernel, descends
+// the condition tree of the token-level edges with the NEW top of the stack and commits the new stack; then the
 // whole block builds the sequence's next mask row (dense row copy, delta lists, leftover walks)
 // and stores it.  The sequence's inputs are loaded once, no kernel boundary separates the two
 // halves, and the long walks of a few sequences overlap the mask building of all others.
@@ -591,10 +496,10 @@ __device__ __forceinline__ PrivateStack wave_stack(int32_t *s_adv_stack, int32_t
 // with 512; 2,048 x 32,000 10.1 us with two waves, 2,048 x 33,000 13.6 with 256 threads, 18.5 and 18.7 with 512).
 constexpr int kAfBlock = 512, kAfBlockMany = 256, kAfBlockShort = 128;
 constexpr int kAfShortWords = 1024;                    // mask words of a short row (32,768 tokens)
-// LDS the kernel declares statically (stack windows, token bytes, private stacks, the row plan),
-// rounded up: what is left of the 64 KB for the dynamic part (mask row, staged stack)
-constexpr size_t kAfStaticLdsBytes =
-    ((sizeof(int32_t) * (2 * kWindow + 64 + kLdsDepth + kLdsDepth * 64) + sizeof(RowPlan)) + 1023) & ~(size_t)1023;
+// LDS kept for what the kernel declares statically (private stacks, the row plan): what is left of the 64 KB is for the
+// dynamic part (mask row, staged stack)
+constexpr size_t kAfStaticLdsBytes = 6144;
+static_assert(sizeof(int32_t) * kLdsDepth * 64 + sizeof(RowPlan) <= kAfStaticLdsBytes, "the static part fits");
 constexpr size_t kAfDynamicLdsMax = 65536 - kAfStaticLdsBytes;
 template <bool kCompact, int kThreads>
 __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
@@ -604,8 +509,7 @@ __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
     size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles) {
     extern __shared__ uint4 bits4[];                   // whole row: n_words rounded up to a multiple of 4;
                                                        // kCompact: followed by cap stack entries [+ cycle tables]
-    __shared__ int32_t s_win[kWindow], s_new[kWindow], s_info[64];
-    __shared__ int32_t s_adv_stack[kLdsDepth], s_walk_stack[kLdsDepth * 64];
+    __shared__ int32_t s_walk_stack[kLdsDepth * 64];
     __shared__ RowPlan plan;
     const int tid = threadIdx.x, lane = tid & 63;
     const int b = blockIdx.x;
@@ -628,11 +532,11 @@ __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
         }
     }
     if (tid < 64) {
-        PrivateStack priv = wave_stack(s_adv_stack, adv_scratch + b, (size_t)batch);
+        WaveStack ws{row, adv_scratch + b, (size_t)batch, 0, 0, 0};
         int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
-        const Advanced r = advance_and_plan<kCompact>(T, E, tokens, states, row, len, cap, restart_on_eos, priv, cycle_head, cycle_pool,
-                                                      stage_cycles, after_row, s_win, s_new, s_info, plan, b, lane);
-        commit_advance<kCompact>(r, priv, after_row, states, row, len, err, cap, b, lane);
+        const Advanced r = advance_and_plan<kCompact>(T, E, tokens, states, len, cap, restart_on_eos, ws, cycle_head, cycle_pool,
+                                                      stage_cycles, after_row, plan, b, lane);
+        commit_advance<kCompact>(r, ws, after_row, states, row, len, err, cap, b, lane);
     }
     __syncthreads();
     // ---- the next mask row, by the whole block
@@ -646,24 +550,23 @@ __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
 }
 
 // The part of advance_and_plan that is left when there is no token: the top of the stack as it stands is
-// staged in s_new and the condition tree descended with it, through scalar loads (the step kernel's
+// fetched and the condition tree descended with it, through scalar loads (the step kernel's
 // wave 0 when the kernel is asked for mask + masking only).
 __device__ __forceinline__ void plan_only_scalar(const DevTables &T, const DevTokenEdges &E, const int32_t *states,
-                                                 const int32_t *row, const int32_t *len, int cap, int32_t *s_new,
-                                                 RowPlan &plan, int b, int lane) {
+                                                 const int32_t *row, const int32_t *len, int cap, RowPlan &plan, int b, int lane) {
     const int n = table<true>(len, b);
     const int st = table<true>(states, b);
     const bool shape_ok = n >= 1 && n <= cap;
-    if (cap >= 16) stage_window_scalar(row, n, cap, shape_ok, lane, s_new);
-    else s_new[lane] = (shape_ok && n - 1 - lane >= 0) ? row[n - 1 - lane] : -1;
-    __builtin_amdgcn_wave_barrier();
-    const int top = s_new[0];
+    int32_t win;
+    if (cap >= 16) win = fetch_window_scalar(row, n, cap, shape_ok, lane);
+    else win = (shape_ok && n - 1 - lane >= 0) ? row[n - 1 - lane] : -1;
+    const int top = __builtin_amdgcn_readlane(win, 0);
     if (st < 0) {
         if (lane == 0) plan.mode = kRowDone;
     } else if (!shape_ok || (unsigned)top >= (unsigned)T.n_states) {
         if (lane == 0) plan.mode = kRowEmpty;
     } else {
-        plan_row_scalar(E, scalar_node(E.root_nodes + __builtin_amdgcn_readfirstlane(top)), s_new, n,
+        plan_row_scalar(E, scalar_node(E.root_nodes + top), win, n,
                         [&](int k) { return global_read(row + (n - 1 - k)); }, &plan, lane);
     }
     if (lane == 0) { plan.top = top; plan.len = n; }
@@ -729,8 +632,7 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
     uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
     size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles, int32_t *out_tokens) {
     extern __shared__ uint4 bits4[];                   // the mask row; kCompact: then cap stack entries [+ cycle tables]
-    __shared__ int32_t s_win[kWindow], s_new[kWindow], s_info[64];
-    __shared__ int32_t s_adv_stack[kLdsDepth], s_walk_stack[kLdsDepth * 64];
+    __shared__ int32_t s_walk_stack[kLdsDepth * 64];
     __shared__ RowPlan plan;
     const int tid = threadIdx.x, lane = tid & 63;
     const int b = first_row + blockIdx.x;          // (a large batch comes as several launches of one row per compute unit)
@@ -751,13 +653,13 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
 
     if (tid < 64) {
         if (tokens) {
-            PrivateStack priv = wave_stack(s_adv_stack, adv_scratch + b, (size_t)batch);
+            WaveStack ws{row, adv_scratch + b, (size_t)batch, 0, 0, 0};
             int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
-            const Advanced r = advance_and_plan<kCompact, true>(T, E, tokens, states, row, len, cap, restart_on_eos, priv, cycle_head,
-                                                                cycle_pool, stage_cycles, after_row, s_win, s_new, s_info, plan, b, lane);
-            commit_advance<kCompact>(r, priv, after_row, states, row, len, err, cap, b, lane);
+            const Advanced r = advance_and_plan<kCompact, true>(T, E, tokens, states, len, cap, restart_on_eos, ws, cycle_head,
+                                                                cycle_pool, stage_cycles, after_row, plan, b, lane);
+            commit_advance<kCompact>(r, ws, after_row, states, row, len, err, cap, b, lane);
         } else
-            plan_only_scalar(T, E, states, row, len, cap, s_new, plan, b, lane);
+            plan_only_scalar(T, E, states, row, len, cap, plan, b, lane);
         // (barriers that order LDS only: this wave's stores of the new stack are still on their way, and
         // nothing in this block reads them before the launch ends -- except the walks below, which wait)
         lds_barrier();                                 // the plan is there
@@ -960,15 +862,20 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
     }
 }
 
-// The stack an advance leaves, as the wave that made it sees it before it is stored (kCompact: staged in LDS as a whole).
+// The stack an advance leaves, as the wave that made it sees it before it is stored, for walks that look at other entries
+// in every lane: `staged` (LDS) holds it as a whole (kCompact) or the first 64 of the states pushed above row[0 .. base).
 template <bool kCompact>
 struct NewStack {
-    const int32_t *row, *staged;
-    const PrivateStack &priv;
+    const int32_t *row, *staged, *spill;
+    size_t spill_stride;
     int base;
     __device__ int32_t at(int idx) const {
         if (kCompact) return lds_read(staged + idx);
-        return idx < base ? global_read(row + idx) : priv.get(idx - base);
+        if (idx < base) return global_read(row + idx);
+        const int i = idx - base;
+        int32_t v = lds_read(staged + (i < kWindow ? i : kWindow - 1));
+        if (i >= kWindow) v = global_read(spill + (size_t)(i - kWindow) * spill_stride);
+        return v;
     }
 };
 
@@ -1002,8 +909,7 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
     int32_t *adv_spill, int32_t *walk_spill, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
     int32_t *out_tokens, StepArrivals *arrivals) {
     extern __shared__ int32_t after_row[];             // kCompact: cap stack entries [+ cycle tables]
-    __shared__ int32_t s_win[kWindow], s_new[kWindow], s_info[64];
-    __shared__ int32_t s_adv_stack[kLdsDepth], s_walk_stack[kLdsDepth * 64];
+    __shared__ int32_t s_pushed[kWindow], s_walk_stack[kLdsDepth * 64];   // of an open row
     __shared__ uint32_t s_bits[kSpreadGroups / 4];     // an open row: this block's mask words
     __shared__ RowPlan plan;
     __shared__ unsigned long long s_part[kArgmax ? kSpreadBlock / 64 + 1 : 1];
@@ -1015,12 +921,12 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
     uint32_t *dst_row = bitmask + (size_t)b * T.n_words;
     uint16_t *lrow = logits + (size_t)b * row_stride;
     StepArrivals *mine = arrivals + b;
-    PrivateStack priv = wave_stack(s_adv_stack, adv_spill + blockIdx.x, (size_t)gridDim.x);
+    WaveStack ws{row, adv_spill + blockIdx.x, (size_t)gridDim.x, 0, 0, 0};
     Advanced r{};
     uint4 held[kSpreadHeld];
     if (tid < 64) {
-        r = advance_and_plan<kCompact>(T, E, tokens, states, row, len, cap, restart_on_eos, priv, cycle_head, cycle_pool,
-                                       stage_cycles, after_row, s_win, s_new, s_info, plan, b, lane);
+        r = advance_and_plan<kCompact>(T, E, tokens, states, len, cap, restart_on_eos, ws, cycle_head, cycle_pool, stage_cycles,
+                                       after_row, plan, b, lane);
     } else {
 #pragma unroll
         for (int i = 0; i < kSpreadHeld; ++i) {
@@ -1044,7 +950,7 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
         if (lane == 0) before = atomicAdd(&mine->planned, 1u);
         const bool last = (uint32_t)__builtin_amdgcn_readfirstlane((int)before) == (uint32_t)(n_seg - 1);
         if (last) {
-            commit_advance<kCompact>(r, priv, after_row, states, row, len, err, cap, b, lane);
+            commit_advance<kCompact>(r, ws, after_row, states, row, len, err, cap, b, lane);
             if (lane == 0) atomicExch(&mine->planned, 0u);
         }
     }
@@ -1055,9 +961,10 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
     if (open) {
         static_assert(kSpreadGroups / 4 == kSpreadLanes, "a mask word per lane");
         if (tid >= 64) s_bits[j] = dense && w0 + j < T.n_words ? dense[w0 + j] : 0u;
+        else if (!kCompact) s_pushed[lane] = ws.pushed;
         lds_barrier();
         if (tid < 64) {
-            const NewStack<kCompact> stack{row, after_row, priv, r.base};
+            const NewStack<kCompact> stack{row, kCompact ? after_row : s_pushed, ws.spill, ws.spill_stride, r.base};
             PrivateStack wp;
             wp.lds = s_walk_stack + lane;
             wp.lds_stride = 64;
@@ -1168,7 +1075,8 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
 // cell.  (Left to feed(), each lane scans the children by itself, one dependent load after the other: 12.7 us per
 // jump_forward launch on 128 sequences of eight schemas, 5.6 us this way.)  Symbols whose merged edge was not
 // precomputed are walked by feed().
-__device__ __forceinline__ int try_symbols(const DevTables &T, PrivateStack &trial, int c, int n, int top, int kind, const StackView &view) {
+__device__ __forceinline__ int try_symbols(const DevTables &T, PrivateStack &trial, int c, int n, int top, int kind, const WaveStack &ws,
+                                           const StackView &view) {
     const int lane = threadIdx.x & 63;
     bool open = c < T.ncol, walk = false;
     int res = kRejected;
@@ -1203,7 +1111,7 @@ __device__ __forceinline__ int try_symbols(const DevTables &T, PrivateStack &tri
             const int idx = n - 1 - nd.x;
             int next = -1;
             if (idx >= 0) {
-                const int x = __builtin_amdgcn_readfirstlane(view.at(idx));
+                const int x = ws.at(idx);
                 int4 cnd = make_int4(0, 0, 0, 0);
                 for (int c0 = 0; c0 < nd.z && next < 0; c0 += 64) {
                     const int j = c0 + lane;
@@ -1250,9 +1158,8 @@ __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
     int stage_cycles) {
     extern __shared__ int32_t jf_stage[];              // kCompact: kJfSeqPerBlock x (cap stack entries [+ cycle tables])
     __shared__ int32_t s_trial[kJfSeqPerBlock][kLdsDepth * 64];
-    __shared__ int32_t s_adv[kJfSeqPerBlock][kLdsDepth];
-    __shared__ int32_t s_win[kJfSeqPerBlock][kWindow], s_new[kJfSeqPerBlock][kWindow];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ int32_t s_win[kJfSeqPerBlock][kWindow];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int b = blockIdx.x * kJfSeqPerBlock + wave;
     if (kCompact && stage_cycles) {                     // small cycle tables: copied into LDS by the whole block
         int32_t *cycle_lds = jf_stage + kJfSeqPerBlock * cap;
@@ -1263,13 +1170,15 @@ __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
     }
     if (b >= batch) return;
     int32_t *row = data + (size_t)b * cap;
-    int n = len[b];
-    const int st = states[b];
+    int n = table<true>(len, b);
+    const int st = table<true>(states, b);
     int count = 0;
     if (st >= 0 && n >= 1 && n <= cap && max_bytes > 0) {
-        s_win[wave][lane] = n - 1 - lane >= 0 ? row[n - 1 - lane] : -1;
-        __builtin_amdgcn_wave_barrier();
-        int top = __builtin_amdgcn_readfirstlane(s_win[wave][0]);
+        // the stack's top and what a forced byte's walk pushes, in the wave's registers; the lanes' own walks of byte classes
+        // whose merged edge was not precomputed read the window in LDS
+        WaveStack ws{row, adv_scratch + b, (size_t)batch, n, n - 1 - lane >= 0 ? row[n - 1 - lane] : -1, 0};
+        s_win[wave][lane] = ws.win;
+        int top = __builtin_amdgcn_readlane(ws.win, 0);
         if ((unsigned)top < (unsigned)T.n_states) {
             int kind = T.state_kind ? table<true>(T.state_kind, top) : 0;
             PrivateStack trial;                        // one column per lane
@@ -1277,11 +1186,6 @@ __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
             trial.lds_stride = 64;
             trial.spill = lane_spill + (size_t)b * 64 + lane;
             trial.spill_stride = lane_spill_stride;
-            PrivateStack adv;                          // the wave's own walk of a forced byte
-            adv.lds = s_adv[wave];
-            adv.lds_stride = 1;
-            adv.spill = adv_scratch + b;
-            adv.spill_stride = (size_t)batch;
             int new_top = top;
             while (count < max_bytes) {
                 // a state whose only edge shifts one byte starts a run of forced bytes known since the
@@ -1300,12 +1204,12 @@ __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
                     }
                     // the new top of the stack: the run's states, then what was the top before
                     const int from_run = __shfl(word, take - 1 - lane < 0 ? 0 : take - 1 - lane) >> 8;
-                    const int below = lane >= take ? s_win[wave][lane - take] : -1;
-                    __builtin_amdgcn_wave_barrier();
-                    s_win[wave][lane] = lane < take ? from_run : below;
-                    __builtin_amdgcn_wave_barrier();
+                    const int below = __shfl(ws.win, lane >= take ? lane - take : 0);
+                    ws.win = lane < take ? from_run : below;
+                    s_win[wave][lane] = ws.win;
                     n += take;
-                    top = __builtin_amdgcn_readfirstlane(s_win[wave][0]);
+                    ws.n = n;
+                    top = __builtin_amdgcn_readlane(ws.win, 0);
                     kind = T.state_kind ? table<true>(T.state_kind, top) : 0;
                     count += take;
                     continue;
@@ -1315,7 +1219,7 @@ __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
                 bool at_end = false;
                 for (int c0 = 0; c0 < T.ncol; c0 += 64) {
                     const int c = c0 + lane;
-                    const int res = try_symbols(T, trial, c, n, top, kind, view);
+                    const int res = try_symbols(T, trial, c, n, top, kind, ws, view);
                     if (__ballot(c == T.end_col && res == kAccepted)) at_end = true;
                     int bytes_here = (c < T.end_col && res == kFed) ? (T.class_info[c] & 0xFFFF) : 0;
                     const unsigned long long m = __ballot(bytes_here > 0);
@@ -1330,24 +1234,15 @@ __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
                 int base = n, d = 0;
                 new_top = top;
                 int new_kind = kind;
-                if (feed<true, true>(T, adv, info, base, d, new_top, new_kind, view, cap) != kFed) break;   // would exceed cap
+                if (feed<true, true>(T, ws, info, base, d, new_top, new_kind, ws, cap) != kFed) break;   // would exceed cap
                 // commit: stage the new top of the stack, then write the pushed entries
-                int entry = -1;
-                if (lane < base + d) {
-                    if (lane < d) {
-                        entry = adv.get(d - 1 - lane);
-                    } else {
-                        const int idx = base - 1 - (lane - d);
-                        entry = idx >= 0 ? view.at(idx) : -1;
-                    }
-                }
-                s_new[wave][lane] = entry;
-                commit_overlay(row, adv, base, d, lane);
+                const int32_t win = new_window(ws, base, d, lane);
+                commit_pushed(row, ws, base, d, lane);
                 if (lane == 0) out_bytes[(size_t)b * max_bytes + count] = (uint8_t)byte;
-                __builtin_amdgcn_wave_barrier();
-                s_win[wave][lane] = s_new[wave][lane];
-                __builtin_amdgcn_wave_barrier();
+                ws.win = win;
+                s_win[wave][lane] = win;
                 n = base + d;
+                ws.n = n;
                 top = new_top;
                 kind = new_kind;
                 ++count;

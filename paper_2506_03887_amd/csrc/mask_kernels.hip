@@ -86,7 +86,6 @@ __global__ __launch_bounds__(kEdgeBlock) void fill_mask_edges_kernel(
     extern __shared__ uint4 bits4[];                   // seg_vec
     uint32_t *bits = reinterpret_cast<uint32_t *>(bits4);
     __shared__ RowPlan plan;
-    __shared__ int32_t s_win[kWindow];
     __shared__ int32_t lds_stack[kLdsDepth * kWalkLanes];
     const int tid = threadIdx.x;
     PrivateStack priv;
@@ -117,13 +116,12 @@ __global__ __launch_bounds__(kEdgeBlock) void fill_mask_edges_kernel(
                 const bool guess = (unsigned)st < (unsigned)T.n_states;
                 if (guess) nd = E.root_nodes[st];      // overlaps the stack load below
                 const int xj = n - 1 - tid >= 0 ? row[n - 1 - tid] : -1;
-                s_win[tid] = xj;
-                top = __shfl(xj, 0);
+                top = __builtin_amdgcn_readlane(xj, 0);
                 if ((unsigned)top >= (unsigned)T.n_states) {
                     if (tid == 0) plan.mode = kRowEmpty;
                 } else {
                     if (!guess || top != st) nd = E.root_nodes[top];
-                    plan_row(E, nd, s_win, n, [&](int k) { return row[n - 1 - k]; }, &plan, tid);
+                    plan_row(E, nd, xj, n, [&](int k) { return row[n - 1 - k]; }, &plan, tid);
                 }
             }
             if (tid == 0) { plan.top = top; plan.len = n; }

@@ -22,6 +22,13 @@ struct RowPlan {
     int32_t top, len;         // the stack the row belongs to
 };
 
+// The stack entry k below the top: from the lanes, or from wherever the entries below the window are.
+template <typename Deeper>
+__device__ __forceinline__ int entry_below_top(int32_t win, int k, Deeper deeper) {
+    if (k < kWindow) return __builtin_amdgcn_readlane(win, k);
+    return __builtin_amdgcn_readfirstlane(deeper(k));
+}
+
 // Descent of the condition tree of the token-level edges, run by all 64 lanes of one wave with
 // identical values.  `win[k]` (LDS) is the stack entry k below the top for k < kWindow, deeper(k)
 // any entry below that; `n` the stack length; `nd` the root record of the top state.  Each node
@@ -29,7 +36,7 @@ struct RowPlan {
 // (children are stored consecutively), so one round of loads both verifies all of the node's
 // stack-matching conditions at once (wave ballot) and enters the matching child.
 template <typename Deeper>
-__device__ __forceinline__ void plan_row(const DevTokenEdges &E, DevConditionNode nd, const int32_t *win, int n,
+__device__ __forceinline__ void plan_row(const DevTokenEdges &E, DevConditionNode nd, int32_t win, int n,
                                          Deeper deeper, RowPlan *plan, int lane) {
     int mode = kRowFast, nseg = 0, dense = -1, walk_begin = 0, walk_count = 0;
     for (;;) {
@@ -47,8 +54,7 @@ __device__ __forceinline__ void plan_row(const DevTokenEdges &E, DevConditionNod
             break;
         }
         if (nd.known >= n || nseg >= kMaxPath) { mode = kRowWalkAll; break; }
-        int x = lds_read(win + (nd.known < kWindow ? nd.known : kWindow - 1));
-        if (nd.known >= kWindow) x = deeper(nd.known);
+        const int x = entry_below_top(win, nd.known, deeper);
         bool found = false;
         for (int c0 = 0; c0 < nd.child_count && !found; c0 += 64) {
             const int j = c0 + lane;
@@ -61,13 +67,13 @@ __device__ __forceinline__ void plan_row(const DevTokenEdges &E, DevConditionNod
             const unsigned long long m = __ballot(cstate == x);
             if (m) {
                 const int src = __ffsll((long long)m) - 1;
-                nd.known = __shfl(c.known, src);
-                nd.child_count = __shfl(c.child_count, src);
-                nd.a = __shfl(c.a, src);
-                nd.b = __shfl(c.b, src);
-                nd.dense_row = __shfl(c.dense_row, src);
-                nd.delta_begin = __shfl(c.delta_begin, src);
-                nd.delta_count = __shfl(c.delta_count, src);
+                nd.known = __builtin_amdgcn_readlane(c.known, src);
+                nd.child_count = __builtin_amdgcn_readlane(c.child_count, src);
+                nd.a = __builtin_amdgcn_readlane(c.a, src);
+                nd.b = __builtin_amdgcn_readlane(c.b, src);
+                nd.dense_row = __builtin_amdgcn_readlane(c.dense_row, src);
+                nd.delta_begin = __builtin_amdgcn_readlane(c.delta_begin, src);
+                nd.delta_count = __builtin_amdgcn_readlane(c.delta_count, src);
                 found = true;
             }
         }
@@ -94,7 +100,7 @@ __device__ __forceinline__ DevConditionNode scalar_node(const DevConditionNode *
 // plan_row with scalar loads only (see scalar_load16): per level one round for the condition states,
 // one for the child's record.
 template <typename Deeper>
-__device__ __forceinline__ void plan_row_scalar(const DevTokenEdges &E, DevConditionNode nd, const int32_t *win, int n,
+__device__ __forceinline__ void plan_row_scalar(const DevTokenEdges &E, DevConditionNode nd, int32_t win, int n,
                                                 Deeper deeper, RowPlan *plan, int lane) {
     int mode = kRowFast, nseg = 0, dense = -1, walk_begin = 0, walk_count = 0;
     for (;;) {
@@ -112,9 +118,7 @@ __device__ __forceinline__ void plan_row_scalar(const DevTokenEdges &E, DevCondi
             break;
         }
         if (nd.known >= n || nseg >= kMaxPath) { mode = kRowWalkAll; break; }
-        int x = lds_read(win + (nd.known < kWindow ? nd.known : kWindow - 1));
-        if (nd.known >= kWindow) x = deeper(nd.known);
-        x = __builtin_amdgcn_readfirstlane(x);
+        const int x = entry_below_top(win, nd.known, deeper);
         const int j = scalar_find<1>(E.child_state + nd.a, nd.child_count, x);
         if (j < 0) { mode = kRowWalkAll; break; }
         nd = scalar_node(E.nodes + nd.b + j);
@@ -142,7 +146,7 @@ struct EffectHit {
 // a ballot finds the record, another the child.  Run by all 64 lanes of a wave with identical
 // values; a miss means "walk the token".
 template <typename Deeper>
-__device__ __forceinline__ EffectHit find_effect(const DevTokenEdges &E, int node, DevConditionNode nd, const int32_t *win,
+__device__ __forceinline__ EffectHit find_effect(const DevTokenEdges &E, int node, DevConditionNode nd, int32_t win,
                                                  int n, Deeper deeper, int tok, int lane) {
     EffectHit r{0, 0, 0, 0, 0, 0, 0};
     for (int level = 0; level < 256; ++level) {
@@ -154,8 +158,7 @@ __device__ __forceinline__ EffectHit find_effect(const DevTokenEdges &E, int nod
         const bool inner = nd.child_count > 0 && nd.known < n;
         int x = -3;
         if (inner) {
-            x = lds_read(win + (nd.known < kWindow ? nd.known : kWindow - 1));
-            if (nd.known >= kWindow) x = deeper(nd.known);
+            x = entry_below_top(win, nd.known, deeper);
         }
         int cstate = -2;
         DevConditionNode c{};
@@ -168,7 +171,7 @@ __device__ __forceinline__ EffectHit find_effect(const DevTokenEdges &E, int nod
                                                 effect_slot_matches((uint32_t)slot.x, (uint32_t)slot.y, (uint32_t)node, (uint32_t)tok));
         if (hit) {
             const int src = __ffsll((long long)hit) - 1;
-            const EffectFields f = effect_unpack((uint32_t)__shfl(slot.y, src), (uint32_t)__shfl(slot.z, src), (uint32_t)__shfl(slot.w, src));
+            const EffectFields f = effect_unpack((uint32_t)__builtin_amdgcn_readlane(slot.y, src), (uint32_t)__builtin_amdgcn_readlane(slot.z, src), (uint32_t)__builtin_amdgcn_readlane(slot.w, src));
             r.found = 1;
             r.k = f.k;
             r.peak = f.peak;
@@ -195,10 +198,10 @@ __device__ __forceinline__ EffectHit find_effect(const DevTokenEdges &E, int nod
         if (!m) return r;
         const int src = __ffsll((long long)m) - 1;
         node = nd.b + child;
-        nd.known = __shfl(c.known, src);
-        nd.child_count = __shfl(c.child_count, src);
-        nd.a = __shfl(c.a, src);
-        nd.b = __shfl(c.b, src);
+        nd.known = __builtin_amdgcn_readlane(c.known, src);
+        nd.child_count = __builtin_amdgcn_readlane(c.child_count, src);
+        nd.a = __builtin_amdgcn_readlane(c.a, src);
+        nd.b = __builtin_amdgcn_readlane(c.b, src);
     }
     return r;
 }
@@ -206,7 +209,7 @@ __device__ __forceinline__ EffectHit find_effect(const DevTokenEdges &E, int nod
 // find_effect with scalar loads only (see scalar_load16): per level one round for the two buckets and
 // the node's first sixteen condition states, one for the child's record.
 template <typename Deeper>
-__device__ __forceinline__ EffectHit find_effect_scalar(const DevTokenEdges &E, int node, DevConditionNode nd, const int32_t *win,
+__device__ __forceinline__ EffectHit find_effect_scalar(const DevTokenEdges &E, int node, DevConditionNode nd, int32_t win,
                                                         int n, Deeper deeper, int tok) {
     EffectHit r{0, 0, 0, 0, 0, 0, 0};
     for (int level = 0; level < 256; ++level) {
@@ -219,9 +222,7 @@ __device__ __forceinline__ EffectHit find_effect_scalar(const DevTokenEdges &E, 
         const NativeInt16 first = scalar_load16(kids);
         int x = -3;
         if (inner) {
-            x = lds_read(win + (nd.known < kWindow ? nd.known : kWindow - 1));
-            if (nd.known >= kWindow) x = deeper(nd.known);
-            x = __builtin_amdgcn_readfirstlane(x);
+            x = entry_below_top(win, nd.known, deeper);
         }
         bool hit = false;
         uint32_t w1 = 0, w2 = 0, w3 = 0;

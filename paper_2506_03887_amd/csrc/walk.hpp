@@ -61,6 +61,33 @@ struct PrivateStack {
     }
 };
 
+// The stack of the one sequence that a whole wave walks, in the wave's registers: lane k holds the entry k below the
+// top of row[0 .. n) as it was before the walk, lane i the i-th state pushed since; deeper entries of either are in
+// memory.  All lanes read and write it at wave-uniform indices with one lane read or write each, where a copy in LDS
+// costs its latency at every link of the chain.
+constexpr int kWindow = 64;
+struct WaveStack {
+    const int32_t *row;
+    int32_t *spill;                    // this wave's column, for states pushed beyond the 64th
+    size_t spill_stride;
+    int n;
+    int32_t win, pushed;
+    // both as a walk's `row` and as its private stack (feed)
+    __device__ int32_t at(int idx) const {
+        const int k = n - 1 - idx;
+        if (k < kWindow) return __builtin_amdgcn_readlane(win, k);
+        return __builtin_amdgcn_readfirstlane(global_read(row + idx));
+    }
+    __device__ int32_t get(int i) const {
+        if (i < kWindow) return __builtin_amdgcn_readlane(pushed, i);
+        return __builtin_amdgcn_readfirstlane(global_read(spill + (size_t)(i - kWindow) * spill_stride));
+    }
+    __device__ void set(int i, int32_t v) {
+        if (i < kWindow) pushed = (int)(threadIdx.x & 63) == i ? v : pushed;
+        else spill[(size_t)(i - kWindow) * spill_stride] = v;
+    }
+};
+
 enum FeedResult { kFed = 0, kRejected = 1, kOverflow = 2, kAccepted = 3 };
 
 // Table look-ups.  In a wave that runs ONE walk (advance), every index is the same in all lanes:
@@ -131,7 +158,6 @@ __device__ __forceinline__ int scalar_find(const int32_t *list, int count, int x
 
 // The sequence's stack as the walk sees it: row[0..n), optionally with its top `kWindow` entries
 // staged in LDS (win[k] = entry k below the top).
-constexpr int kWindow = 64;
 struct StackView {
     const int32_t *row;
     const int32_t *win;
@@ -155,8 +181,8 @@ struct StackView {
 // the exposed state (its stack-matching condition) and pushes the goto target, until an
 // acceptance edge shifts the symbol.
 // With kCheckCap the walk reports kOverflow exactly when a push would exceed `cap` entries.
-template <bool kCheckCap, bool kUniform = false, bool kScalarOnly = false, class View>
-__device__ __forceinline__ int feed(const DevTables &T, PrivateStack &priv, int info, int &base, int &d,
+template <bool kCheckCap, bool kUniform = false, bool kScalarOnly = false, class Priv, class View>
+__device__ __forceinline__ int feed(const DevTables &T, Priv &priv, int info, int &base, int &d,
                                     int &top, int &tree, const View &row, int cap, int *run_node = nullptr) {
     const int col = info & 0xFF, delta = info >> 8;    // byte class and per-byte target offset
     // `tree` names the condition tree of the top state (states that behave alike share one, and all
@@ -251,10 +277,10 @@ __device__ __forceinline__ int feed(const DevTables &T, PrivateStack &priv, int 
                     if (m) {
                         const int src = __ffsll((long long)m) - 1;
                         next = nd.w + c0 + src;
-                        nd = make_int4(uni<true>(__shfl(cnd.x, src)), uni<true>(__shfl(cnd.y, src)),
-                                       uni<true>(__shfl(cnd.z, src)), uni<true>(__shfl(cnd.w, src)));
-                        cell = make_int4(uni<true>(__shfl(ccell.x, src)), uni<true>(__shfl(ccell.y, src)),
-                                         uni<true>(__shfl(ccell.z, src)), uni<true>(__shfl(ccell.w, src)));
+                        nd = make_int4(__builtin_amdgcn_readlane(cnd.x, src), __builtin_amdgcn_readlane(cnd.y, src),
+                                       __builtin_amdgcn_readlane(cnd.z, src), __builtin_amdgcn_readlane(cnd.w, src));
+                        cell = make_int4(__builtin_amdgcn_readlane(ccell.x, src), __builtin_amdgcn_readlane(ccell.y, src),
+                                         __builtin_amdgcn_readlane(ccell.z, src), __builtin_amdgcn_readlane(ccell.w, src));
                     }
                 }
                 if (next < 0) break;
@@ -321,20 +347,20 @@ __device__ __forceinline__ int feed(const DevTables &T, PrivateStack &priv, int 
 // replaces the top of the stack; after a growing edge (`node` carries kRunGrows: the stack gained a
 // second copy of the entry under its top) every following growing edge at the same node inserts one
 // more copy and replaces the top.  Each of the 64 lanes examines one upcoming byte
-// (infos[first + lane], staged in LDS); the run ends at the first byte that is not such an edge.
+// (lane i of `infos` holds byte i); the run ends at the first byte that is not such an edge.
 // Returns the number of bytes consumed; the last one's target becomes the new top, and a growing
 // run adds one private entry per byte (d grows).
 template <bool kCheckCap>
-__device__ __forceinline__ int apply_run(const DevTables &T, PrivateStack &priv, const int32_t *infos, int first,
+__device__ __forceinline__ int apply_run(const DevTables &T, WaveStack &priv, int32_t infos, int first,
                                          int n_bytes, int node, int tree, int base, int &d, int &top, int cap) {
     const bool grows = (node & kRunGrows) != 0;
     node &= ~kRunGrows;
     const int lane = threadIdx.x & 63, i = first + lane;
     const int gain = grows ? lane : 0;                  // entries added by the run's earlier bytes
     bool ok = i < n_bytes && i < 64;
+    const int info = __shfl(infos, i & 63);
     int new_top = 0, copy = 0;
     if (ok) {
-        const int info = infos[i];
         const int4 cell = T.sym_cell[node * T.ncol + (info & 0xFF)];
         const int code = cell.x;
         ok = code >= 0;
@@ -356,7 +382,7 @@ __device__ __forceinline__ int apply_run(const DevTables &T, PrivateStack &priv,
     int run = bad ? __ffsll((long long)bad) - 1 : 64;
     if (grows && d + run > T.max_depth) run = T.max_depth > d ? T.max_depth - d : 0;    // cannot happen: see the depth bound
     if (run > 0) {
-        top = __builtin_amdgcn_readfirstlane(__shfl(new_top, run - 1));
+        top = __builtin_amdgcn_readlane(new_top, run - 1);
         if (grows) {
             const int x = __builtin_amdgcn_readfirstlane(copy);       // the same entry for every byte of the run
             for (int j = 0; j < run; ++j) priv.set(d - 1 + j, x);

@@ -1,0 +1,66 @@
+"""The stack a wave walks in its registers: 64 entries of the window and 64 pushed states, everything beyond in memory.
+Tokens that push and pop 63, 64, 65 and more states, from stacks of 1 to 200 entries, through every call that advances."""
+import numpy as np
+import pytest
+
+from oracle import Oracle, apply_mask as oracle_apply_mask
+from workloads import grammars as G
+from workloads.vocab import BASE_SEED, Vocab, bf16_logits, bpe_like_vocab
+
+pytestmark = pytest.mark.gpu
+
+DEEP = [b"[" * n for n in (15, 16, 17, 31, 32, 63, 64, 65, 66, 128, 130)] + [b"]" * n for n in (16, 62, 63, 64, 65, 66, 130)] + \
+       [b"[" * 70 + b"]" * 69, b"]" * 60 + b",[", b"1" + b"]" * 63, b"1" + b"]" * 64 + b",", b"[1," * 40, b"{\"k\":" * 23, b" " * 70 + b"[" * 60]
+CALLS = ("advance", "advance_fill", "step", "one_kernel")
+
+
+@pytest.mark.parametrize("options", [{}, dict(token_effects=False), dict(max_condition_depth=2), dict(compact_cycles=True)])
+@pytest.mark.parametrize("call", CALLS)
+def test_tokens_deeper_than_the_registers(call, options):
+    import torch
+    from paper_2506_03887_amd import Pre3
+    dev = torch.device("cuda:0")
+    base = bpe_like_vocab(1000, 8, BASE_SEED + 91).tokens[:-1]
+    toks = base + DEEP + [b""]
+    v = Vocab(toks, len(toks) - 1)
+    cycles = "compact_cycles" in options
+    text = G.JSON_RIGHT_RECURSIVE if cycles else G.JSON
+    o = Oracle(text, compact_cycles=cycles)
+    cap = 512
+    lib = Pre3(text, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, **options)
+    rows = [(depth, t) for depth in (0, 1, 15, 62, 63, 64, 65, 130, 190) for t in range(len(base), len(base) + len(DEEP) + 1)]
+    if call == "one_kernel":
+        rows = rows[:: len(rows) // 100]            # (the form is asked for; one row per compute unit is enough)
+    B = len(rows)
+    data, length = np.zeros((B, cap), np.int32), np.ones(B, np.int32)
+    for b, (depth, _) in enumerate(rows):
+        st = o.initial_stack(0) if depth == 0 else o.advance(o.initial_stack(0), b"[" * depth)[1]
+        data[b, : len(st)], length[b] = st, len(st)
+    states = data[np.arange(B), length - 1].copy()
+    tokens = np.array([t for _, t in rows], np.int32)
+    s_d, d_d, l_d, t_d = (torch.from_numpy(x.copy()).to(dev) for x in (states, data, length, tokens))
+    e_d = torch.full((B,), -5, dtype=torch.int32, device=dev)
+    lib.bind_state(s_d, d_d, l_d, e_d)
+    mask = torch.full((B, v.words), 0x77777777, dtype=torch.int32, device=dev)
+    x = bf16_logits(np.random.default_rng(5), B, -(-v.n_tokens // 8) * 8)
+    x_d = torch.from_numpy(x.view(np.int16).copy()).to(dev)
+    if call == "advance":
+        lib.advance(t_d)
+    elif call == "advance_fill":
+        lib.advance_fill_mask(t_d, mask)
+    else:
+        lib.advance_fill_apply_mask(t_d, mask, x_d, one_kernel=call == "one_kernel")
+    s_h, d_h, l_h = states.copy(), data.copy(), length.copy()
+    err = o.advance_batch(s_h, d_h, l_h, tokens, v)
+    assert set(err.tolist()) >= {0, 1} and (l_h - length).max() >= (63 if not cycles else 20) and (cycles or (length - l_h).max() >= 63)
+    assert (e_d.cpu().numpy() == err).all()
+    assert (s_d.cpu().numpy() == s_h).all() and (l_d.cpu().numpy() == l_h).all()
+    live = np.arange(cap)[None, :] < l_h[:, None]
+    assert (d_d.cpu().numpy()[live] == d_h[live]).all()
+    if call != "advance":
+        want = o.fill_mask(s_h, d_h, l_h, v)
+        assert (mask.cpu().numpy().view(np.uint32) == want).all()
+        if call != "advance_fill":
+            oracle_apply_mask(x, want, v.n_tokens)
+            assert (x_d.cpu().numpy().view(np.uint16) == x).all()
+    assert lib.fault_count() == 0
