@@ -409,8 +409,11 @@ constexpr int kAdvSeqPerBlock = 4;
 template <bool kCompact>
 __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
     const int32_t *__restrict__ tokens, int32_t *__restrict__ len, int32_t *__restrict__ states,
-    int32_t *__restrict__ data, int cap, int batch, DevTables T, DevTokenEdges E, int32_t *__restrict__ err, int32_t *scratch,
+    int32_t *__restrict__ data, int cap, int batch, const DevPack *pack, int32_t *__restrict__ err, int32_t *scratch,
     int restart_on_eos, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles) {
+    DevTables T;
+    DevTokenEdges E;
+    load_tables(pack, T, E);
     extern __shared__ int32_t adv_stage[];             // kCompact: kAdvSeqPerBlock x (cap stack entries [+ cycle tables])
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int b = blockIdx.x * kAdvSeqPerBlock + wave;
@@ -504,9 +507,12 @@ constexpr size_t kAfDynamicLdsMax = 65536 - kAfStaticLdsBytes;
 template <bool kCompact, int kThreads>
 __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
     const int32_t *__restrict__ tokens, int32_t *__restrict__ len, int32_t *__restrict__ states,
-    int32_t *__restrict__ data, int cap, int batch, DevTables T, DevTokenEdges E, int32_t *__restrict__ err,
+    int32_t *__restrict__ data, int cap, int batch, const DevPack *pack, int32_t *__restrict__ err,
     uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
     size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles) {
+    DevTables T;
+    DevTokenEdges E;
+    load_tables(pack, T, E);
     extern __shared__ uint4 bits4[];                   // whole row: n_words rounded up to a multiple of 4;
                                                        // kCompact: followed by cap stack entries [+ cycle tables]
     __shared__ int32_t s_walk_stack[kLdsDepth * 64];
@@ -627,10 +633,13 @@ constexpr int kStepAhead = 8;                          // greedy: groups of logi
 static_assert(kStepBlock == kArgBlock && kStepBlock == 16 * 64, "the step kernel combines its lanes with argmax_block_max and step_block_best");
 template <bool kCompact, int kHeld, bool kArgmax>
 __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
-    const int32_t *tokens, int32_t *__restrict__ len, int32_t *__restrict__ states, int32_t *__restrict__ data, int cap, int first_row,
-    uint16_t *__restrict__ logits, int64_t row_stride, DevTables T, DevTokenEdges E, int batch, int32_t *__restrict__ err,
+    const int32_t *tokens, int32_t *__restrict__ len, int32_t *__restrict__ states, int32_t *__restrict__ data, const DevPack *pack,
+    int cap, int first_row, uint16_t *__restrict__ logits, int64_t row_stride, int batch, int32_t *__restrict__ err,
     uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
     size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles, int32_t *out_tokens) {
+    DevTables T;
+    DevTokenEdges E;
+    load_tables(pack, T, E);
     extern __shared__ uint4 bits4[];                   // the mask row; kCompact: then cap stack entries [+ cycle tables]
     __shared__ int32_t s_walk_stack[kLdsDepth * 64];
     __shared__ RowPlan plan;
@@ -1152,10 +1161,13 @@ __device__ __forceinline__ int try_symbols(const DevTables &T, PrivateStack &tri
 constexpr int kJfSeqPerBlock = 4;
 template <bool kCompact>
 __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
-    int32_t *__restrict__ len, int32_t *__restrict__ states, int32_t *__restrict__ data, int cap, int batch, DevTables T,
+    int32_t *__restrict__ len, int32_t *__restrict__ states, int32_t *__restrict__ data, int cap, int batch, const DevPack *pack,
     uint8_t *__restrict__ out_bytes, int32_t *__restrict__ out_len, int max_bytes, int32_t *adv_scratch,
     int32_t *lane_spill, size_t lane_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool,
     int stage_cycles) {
+    DevTables T;
+    DevTokenEdges E;
+    load_tables(pack, T, E);
     extern __shared__ int32_t jf_stage[];              // kCompact: kJfSeqPerBlock x (cap stack entries [+ cycle tables])
     __shared__ int32_t s_trial[kJfSeqPerBlock][kLdsDepth * 64];
     __shared__ int32_t s_win[kJfSeqPerBlock][kWindow];
@@ -1355,7 +1367,7 @@ hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const
     }
 #define PRE3_AF(C, THREADS)                                                                                                 \
     hipLaunchKernelGGL((advance_fill_kernel<C, THREADS>), dim3(batch), dim3(THREADS), lds, stream, tokens, len, states, data,   \
-                       cap, batch, T, E, err, bitmask, restart_on_eos, adv_scratch, walk_spill, (size_t)batch * 64, cycle_head,  \
+                       cap, batch, T.pack, err, bitmask, restart_on_eos, adv_scratch, walk_spill, (size_t)batch * 64, cycle_head,  \
                        cycle_pool, stage)
 #define PRE3_AF_SIZES(C)                                                                    \
     if (batch <= 2 * n_compute_units) PRE3_AF(C, kAfBlock);                                  \
@@ -1391,7 +1403,7 @@ static void launch_step_variant(int held, dim3 grid, size_t lds, hipStream_t str
                                 int64_t row_stride, int32_t *out_tokens, int first_row) {
 #define PRE3_STEP(H)                                                                                                        \
     hipLaunchKernelGGL((advance_fill_apply_kernel<kCompact, H, kArgmax>), grid, dim3(kStepBlock), lds, stream, tokens, len,   \
-                       states, data, cap, first_row, logits, row_stride, T, E, batch, err, bitmask, restart_on_eos,          \
+                       states, data, T.pack, cap, first_row, logits, row_stride, batch, err, bitmask, restart_on_eos,          \
                        adv_scratch, walk_spill, (size_t)batch * 64, cycle_head, cycle_pool, stage, out_tokens)
     if (held <= kStepHeldShort) PRE3_STEP(kStepHeldShort);
     else if (held <= 17) PRE3_STEP(17);
@@ -1519,10 +1531,10 @@ hipError_t launch_advance(const DevTables &T, const DevTokenEdges &E, const int3
         const int stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) &&
                           (size_t)kAdvSeqPerBlock * cap * sizeof(int32_t) + tables + 4096 <= 65536;
         const size_t lds = (size_t)kAdvSeqPerBlock * cap * sizeof(int32_t) + (stage ? tables : 0);
-        hipLaunchKernelGGL(advance_kernel<true>, grid, block, lds, stream, tokens, len, states, data, cap, batch, T, E, err,
+        hipLaunchKernelGGL(advance_kernel<true>, grid, block, lds, stream, tokens, len, states, data, cap, batch, T.pack, err,
                            scratch, restart_on_eos, cycle_head, cycle_pool, stage);
     } else {
-        hipLaunchKernelGGL(advance_kernel<false>, grid, block, 0, stream, tokens, len, states, data, cap, batch, T, E, err,
+        hipLaunchKernelGGL(advance_kernel<false>, grid, block, 0, stream, tokens, len, states, data, cap, batch, T.pack, err,
                            scratch, restart_on_eos, nullptr, nullptr, 0);
     }
     return hipGetLastError();
@@ -1544,10 +1556,10 @@ hipError_t launch_jump_forward(const DevTables &T, int32_t *states, int32_t *dat
         const int stage = cycles_fit_lds(T.n_states, T.cycle_pool_n) &&
                           (size_t)kJfSeqPerBlock * cap * sizeof(int32_t) + tables + 20480 <= 65536;
         const size_t lds = (size_t)kJfSeqPerBlock * cap * sizeof(int32_t) + (stage ? tables : 0);
-        hipLaunchKernelGGL(jump_forward_kernel<true>, grid, block, lds, stream, len, states, data, cap, batch, T, out_bytes,
+        hipLaunchKernelGGL(jump_forward_kernel<true>, grid, block, lds, stream, len, states, data, cap, batch, T.pack, out_bytes,
                            out_len, max_bytes, adv_scratch, lane_spill, (size_t)batch * 64, cycle_head, cycle_pool, stage);
     } else {
-        hipLaunchKernelGGL(jump_forward_kernel<false>, grid, block, 0, stream, len, states, data, cap, batch, T, out_bytes,
+        hipLaunchKernelGGL(jump_forward_kernel<false>, grid, block, 0, stream, len, states, data, cap, batch, T.pack, out_bytes,
                            out_len, max_bytes, adv_scratch, lane_spill, (size_t)batch * 64, nullptr, nullptr, 0);
     }
     return hipGetLastError();

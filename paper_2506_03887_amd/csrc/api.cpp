@@ -315,6 +315,9 @@ int upload_tables(pre3_handle *h) {
         if ((e = upload(h, h->T.cycle_head, &h->cycle_head)) != hipSuccess) return hip_fail(h, e, "upload cycle_head");
         if ((e = upload(h, device_cycle_pool(h->T), &h->cycle_pool)) != hipSuccess) return hip_fail(h, e, "upload cycle_pool");
     }
+    const DevPack *pack = nullptr;       // last: every pointer is known
+    if ((e = upload(h, std::vector<DevPack>{DevPack{D, h->dev_edges}}, &pack)) != hipSuccess) return hip_fail(h, e, "upload tables");
+    D.pack = pack;
     return PRE3_OK;
 }
 

@@ -51,6 +51,7 @@ struct DevTables {
     // the small tables every advance touches lie next to each other: idle waves pull them into L2
     const char *hot_begin;
     int32_t hot_bytes;             // 0 = no such region
+    const struct DevPack *pack;    // the copy of these tables (and of the token edges) in device memory
 };
 
 // Condition tree of the token-level prefix-conditioned edges (see token_edges.hpp), device form.
@@ -73,6 +74,12 @@ struct DevTokenEdges {
     const int32_t *fx_pool;                // pushes of records with more than one
     uint32_t fx_mask;
     int32_t fx_min_len;                    // tokens shorter than this have no record
+};
+
+// What the kernels read the table pointers from: one copy in device memory, uploaded once per handle.
+struct DevPack {
+    DevTables T;
+    DevTokenEdges E;
 };
 
 }  // namespace pre3

@@ -81,8 +81,11 @@ constexpr uint32_t kNegInfPair = 0xFF80FF80u;
 template <bool kApply>
 __global__ __launch_bounds__(kEdgeBlock) void fill_mask_edges_kernel(
     const int32_t *__restrict__ states, const int32_t *__restrict__ len, const int32_t *__restrict__ data, int cap, int batch,
-    int n_seg, int seg_vec, DevTables T, DevTokenEdges E, uint32_t *__restrict__ bitmask, uint16_t *__restrict__ logits,
+    int n_seg, int seg_vec, const DevPack *pack, uint32_t *__restrict__ bitmask, uint16_t *__restrict__ logits,
     int64_t row_stride, int32_t *spill, size_t spill_stride) {
+    DevTables T;
+    DevTokenEdges E;
+    load_tables(pack, T, E);
     extern __shared__ uint4 bits4[];                   // seg_vec
     uint32_t *bits = reinterpret_cast<uint32_t *>(bits4);
     __shared__ RowPlan plan;
@@ -217,10 +220,10 @@ hipError_t launch_fill_mask_edges(const DevTables &T, const DevTokenEdges &E, co
     const size_t stride = (size_t)grid_blocks * kWalkLanes;
     if (logits)
         hipLaunchKernelGGL(fill_mask_edges_kernel<true>, dim3(grid), dim3(kEdgeBlock), lds, stream, states, len, data,
-                           cap, batch, n_seg, seg_vec, T, E, bitmask, logits, row_stride, spill, stride);
+                           cap, batch, n_seg, seg_vec, T.pack, bitmask, logits, row_stride, spill, stride);
     else
         hipLaunchKernelGGL(fill_mask_edges_kernel<false>, dim3(grid), dim3(kEdgeBlock), lds, stream, states, len, data,
-                           cap, batch, n_seg, seg_vec, T, E, bitmask, logits, row_stride, spill, stride);
+                           cap, batch, n_seg, seg_vec, T.pack, bitmask, logits, row_stride, spill, stride);
     return hipGetLastError();
 }
 

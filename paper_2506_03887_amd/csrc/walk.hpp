@@ -127,6 +127,30 @@ __device__ __forceinline__ int uni(int v) {
     return kUniform ? __builtin_amdgcn_readfirstlane(v) : v;
 }
 
+// The tables as a kernel sees them, read from the handle's copy in device memory: it stays in the L2s from launch to
+// launch, where 350 bytes of pointers among a launch's arguments come from HBM every time (8 x fill, mask, advance of
+// 96 x 100,003 159.6 -> 155.0 us, 8 x jump-forward, mask + masking, advance of 128 x 128,256 195.4 -> 190.4).  The spread step,
+// whose arguments do not all arrive preloaded, waits for the others anyway and takes the tables by value (1 x 128,256: 57.5
+// against 58.5 us).  (A pointer that is itself loaded is generic to the compiler, and its accesses flat; the casts say
+// that all of them are global.)
+__device__ __forceinline__ void load_tables(const DevPack *pack, DevTables &T, DevTokenEdges &E) {
+    const ConstPtr<DevPack> from = (ConstPtr<DevPack>)pack;
+#define PRE3_PTR(f) f = (decltype(f))(const __attribute__((address_space(1))) void *)from->f
+#define PRE3_VAL(f) f = from->f
+    PRE3_PTR(T.byte_info); PRE3_PTR(T.edge); PRE3_PTR(T.goto_row); PRE3_PTR(T.goto_flat); PRE3_VAL(T.n_states); PRE3_VAL(T.ncol);
+    PRE3_VAL(T.end_col); PRE3_PTR(T.sym_nodes); PRE3_PTR(T.sym_pairs); PRE3_PTR(T.sym_cell); PRE3_PTR(T.sym_pool);
+    PRE3_PTR(T.state_kind); PRE3_PTR(T.class_info); PRE3_PTR(T.tok_len); PRE3_PTR(T.tok_bit); PRE3_PTR(T.tok_words);
+    PRE3_VAL(T.n_padded); PRE3_VAL(T.n_chunks); PRE3_VAL(T.n_words); PRE3_VAL(T.n_tokens); PRE3_VAL(T.eos_id); PRE3_PTR(T.vbytes);
+    PRE3_PTR(T.voffsets); PRE3_PTR(T.tok_info); PRE3_PTR(T.run_off); PRE3_PTR(T.run_pool); PRE3_VAL(T.max_depth);
+    PRE3_VAL(T.cycle_pool_n); PRE3_PTR(T.fault); PRE3_PTR(T.hot_begin); PRE3_VAL(T.hot_bytes);
+    PRE3_PTR(E.root_nodes); PRE3_PTR(E.nodes); PRE3_PTR(E.child_state); PRE3_PTR(E.dense_rows); PRE3_PTR(E.delta_ids);
+    PRE3_PTR(E.walk_ids); PRE3_PTR(E.root_id); PRE3_PTR(E.fx_slots); PRE3_PTR(E.fx_pool); PRE3_VAL(E.fx_mask);
+    PRE3_VAL(E.fx_min_len);
+#undef PRE3_VAL
+#undef PRE3_PTR
+    T.pack = pack;
+}
+
 // Wider scalar loads for a wave that must stay off the vector-memory path (its block's other waves
 // have a long queue of loads in flight there, and vector loads return in order): 8 or 16 consecutive
 // 32-bit words at a wave-uniform, 4-byte aligned address of a read-only table.  A 16-word load may
