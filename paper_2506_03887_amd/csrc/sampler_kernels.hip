@@ -648,6 +648,7 @@ __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
 // Lists that would run full (hundreds of ties with the bound, or a dense row where the threads' maxima do not
 // say enough) are given up: the block then takes the row chunk by chunk with masked_topk_chunked, which has no
 // such limit.
+// Twenty groups per thread (163,840 tokens) is what the 128 vector registers hold without spills.
 // (14.6 us per launch at 256 x 128,256, k = 50, 4.8 TB/s; 15.4 us per call in a graph: 9.4 us until the row has arrived and is worked on, 0.8 for
 // the bound, 1.4 for the list, 0.7 for the ranks.  24.9 us before, with keys computed for every token, all sixteen
 // loads issued first -- behind branches, so that nothing was worked on before the last had arrived: a wave that wants
@@ -667,7 +668,7 @@ __device__ __noinline__ void topk_in_chunks(const uint16_t *logits, const uint32
                                             uint16_t *out_vals, int b, int seg, int n_seg) {
     masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, chunks_per_seg, workspace, out_ids, out_vals, b, seg, n_seg);
 }
-constexpr int kTopkRowTokens = 16 * 8 * kTopkBlockWide;        // longest row that one block keeps in registers
+constexpr int kTopkRowTokens = 20 * 8 * kTopkBlockWide;        // longest row that one block keeps in registers
 constexpr int kTopkRowList = 512, kTopkRowGroupList = 256;
 constexpr int kTopkMaxima = 128;                   // thread maxima that give the bound
 static_assert(kTopkMax <= kTopkMaxima, "the k-th of them has to exist");
@@ -1015,19 +1016,21 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     const int n_words = (vocab + 31) / 32;
     // A row that fits the registers of a block is one block's, whatever the batch (128,256 tokens, k = 50: 8.0 us for one
     // row, 10.7 for 64, 15.4 for 256, against 9.9 and 14.1 us for 1 and 64 rows in segments of 16,384 tokens and a second
-    // launch); the block and its groups per thread are the smallest that hold it.  A longer row is cut into such
-    // blocks of 98,304 or 131,072 tokens (152,064 tokens: 13.2 us for 100 rows, 49 for 512) unless the batch
-    // is too small to fill the chip with them (16 rows: 11.8 us in segments of 16,384 against 13.4; at the line, 31 rows
-    // take 13.4 to 13.9 us in such segments and 32 rows 12.2 in blocks, at 200,000 tokens 13.8 to 14.4 and 13.7).
+    // launch; 152,064 tokens: 14.5 us for 200 rows, 31.8 for 512 on a schema, against 21.7 and 42.0 in two blocks a row and a
+    // second launch; 11.1 for 16 rows against 11.9 in segments of 16,384, 10.6 for one against 10.0); the block and its
+    // groups per thread are the smallest that hold it.  A longer row is cut into such blocks of 98,304, 131,072 or 163,840
+    // tokens unless the batch is too small to fill the chip with them (at the line, 31 rows of 200,000 tokens take 13.8 to
+    // 14.4 us in segments of 16,384 and 13.7 in blocks).
 #define PRE3_TOPK_ROW(BLOCK, GROUPS)                                                                                         \
     n_seg = masked_topk_chunks(vocab, BLOCK * GROUPS * 8);                                                                   \
     hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, vocab, \
                        row_stride, n_words, k, workspace, out_ids, out_vals)
     int n_seg = 1;
     if (vocab <= kTopkChunk || (vocab > kTopkRowTokens && batch * 8 < n_compute_units)) { PRE3_TOPK_ROW(kTopkBlock, 4); }
-    else if (vocab <= kTopkRowTokens / 2) { PRE3_TOPK_ROW(kTopkBlockWide, 8); }
-    else if (vocab <= kTopkRowTokens / 4 * 3 || (vocab > kTopkRowTokens && vocab <= kTopkRowTokens / 2 * 3)) { PRE3_TOPK_ROW(kTopkBlockWide, 12); }
-    else { PRE3_TOPK_ROW(kTopkBlockWide, 16); }
+    else if (vocab <= kTopkRowTokens / 20 * 8) { PRE3_TOPK_ROW(kTopkBlockWide, 8); }
+    else if (vocab <= kTopkRowTokens / 20 * 12 || (vocab > kTopkRowTokens && vocab <= kTopkRowTokens / 20 * 24)) { PRE3_TOPK_ROW(kTopkBlockWide, 12); }
+    else if (vocab <= kTopkRowTokens / 20 * 16 || (vocab > kTopkRowTokens && vocab <= kTopkRowTokens / 20 * 32)) { PRE3_TOPK_ROW(kTopkBlockWide, 16); }
+    else { PRE3_TOPK_ROW(kTopkBlockWide, 20); }
 #undef PRE3_TOPK_ROW
     if (n_seg > 1)
         hipLaunchKernelGGL(masked_topk_finish_kernel, dim3(batch), dim3(kTopkFinishBlock), 0, stream, workspace, n_seg * k, k, logits,

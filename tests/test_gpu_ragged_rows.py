@@ -129,3 +129,9 @@ def test_topk_of_rows_kept_in_registers(V, B):
         want_ids, want_vals = masked_topk(host, mask, V, k)
         bad = np.argwhere((ids.cpu().numpy() != want_ids) | (vals.cpu().numpy().view(np.uint16) != want_vals))
         assert len(bad) == 0, (k, bad[:4].tolist())
+
+
+@pytest.mark.parametrize("V,B", [(131_080, 300), (147_457, 4), (163_839, 40), (163_840, 4), (163_841, 17), (163_848, 48), (262_147, 33)])
+def test_topk_of_rows_at_the_longest_variant(V, B):
+    """One block per row up to 163,840 tokens at any batch, several blocks beyond."""
+    test_topk_of_rows_kept_in_registers(V, B)
