@@ -272,7 +272,10 @@ int pre3_advance_fill_apply_mask(pre3_handle *h, const int32_t *tokens, uint32_t
  * sizes of pre3_advance_fill_apply_mask, except that the vocabulary may have at most 153,600 tokens
  * (the fold needs registers of its own) and has to have 8, spreads the rows of the smaller batches over
  * blocks as there (up to one block and half a row per compute unit where the one kernel would be
- * chosen), and is the two calls otherwise; flags as there.
+ * chosen), and is the two calls otherwise; flags as there.  Batches of more rows than compute units, on
+ * rows of at least 61,440 tokens, are one launch of that kernel with two rows to a unit: up to two rows
+ * per unit, beyond on rows of at least 122,880 tokens (any length the mask row's LDS allows; 320 x
+ * 128,256: 24.0 against 29.2 us per step).
  * Errors: BADARG (nothing bound, null pointer, unknown flag, row_stride < n_tokens, logits not
  * 2-byte aligned), HIP. */
 int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bitmask, const uint16_t *logits_bf16,
@@ -280,7 +283,8 @@ int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bi
 
 /* Which form pre3_advance_fill_apply_mask -- with PRE3_STEP_GREEDY among the flags pre3_advance_fill_argmax -- takes
  * for the bound batch and these logits: 0 = the two calls; n >= 1 = the one kernel, launched n times
- * on equal shares of the batch (n = 1 up to one sequence per compute unit); PRE3_STEP_IS_SPREAD | 1 =
+ * on equal shares of the batch (n = 1 up to one sequence per compute unit, and where the greedy step
+ * runs with two rows to a unit); PRE3_STEP_IS_SPREAD | 1 =
  * every row spread over blocks, one launch; BADARG if nothing is bound.  Host call, launches nothing. */
 #define PRE3_STEP_GREEDY 4               /* of this query only */
 #define PRE3_STEP_IS_SPREAD 0x40000000

@@ -626,13 +626,21 @@ __device__ __forceinline__ bool order_undecided(int key) { return key > kOrderPo
 // largest value, first of equal values, +0 = -0, NaN never), the block combines the lanes, and out_tokens[b]
 // is the sequence's next token (-1 if nothing is allowed).  out_tokens may be the tokens buffer: block b
 // reads tokens[b] before anything else and writes out_tokens[b] last.
+// kRows = 2 (greedy, batches of more rows than compute units): two blocks share a unit, so a lane has half the registers; a block
+// holds the first kHeld groups per lane, fetched under the advance, and streams what follows once it knows the mask,
+// reading nothing that is masked as a whole.  Neither the advance as a launch of its own nor the second round of a grid of
+// whole-row blocks stands in front of the stream.  us per step in a graph, against the two launches: 257 x 128,256 JSON 21.6
+// (26.8), 320 24.0 (29.2), cycle-aware stacks 25.8 (32.3), 512 27.6 (34.2); schema 300 x 152,064 23.0 (27.9), 512 27.9 (32.6);
+// 400 x 80,000 cycle-aware 21.5 (26.5); 1,024 x 128,256 50.1 (57.8), 2,048 95.1 (102.7).  Blocks of 512 threads with 16 groups
+// per lane: the same.  (The masking step in this form loses: a block's loads and stores wait for one another, 512 x 128,256
+// 52.2 against 51.2 us, a schema at 300 x 152,064 43.2 against 35.4.)
 // tokens == nullptr: no advance -- the mask of the stacks as they are, and the masking (states, data and
 // len are then only read).
 constexpr int kStepBlock = 1024, kStepData = kStepBlock - 64;
-constexpr int kStepAhead = 8;                          // greedy: groups of logits a lane has in flight
+constexpr int kStepAhead = 8, kRestAhead = 4;          // greedy: groups of logits a lane has in flight (the rest of a longer row)
 static_assert(kStepBlock == kArgBlock && kStepBlock == 16 * 64, "the step kernel combines its lanes with argmax_block_max and step_block_best");
-template <bool kCompact, int kHeld, bool kArgmax>
-__global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
+template <bool kCompact, int kHeld, bool kArgmax, int kRows>
+__global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * kRows))) void advance_fill_apply_kernel(
     const int32_t *tokens, int32_t *__restrict__ len, int32_t *__restrict__ states, int32_t *__restrict__ data, const DevPack *pack,
     int cap, int first_row, uint16_t *__restrict__ logits, int64_t row_stride, int batch, int32_t *__restrict__ err,
     uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
@@ -640,6 +648,7 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
     DevTables T;
     DevTokenEdges E;
     load_tables(pack, T, E);
+    static_assert(kRows == 1 || (kRows == 2 && kArgmax), "the masking form fills a unit's registers with one row");
     extern __shared__ uint4 bits4[];                   // the mask row; kCompact: then cap stack entries [+ cycle tables]
     __shared__ int32_t s_walk_stack[kLdsDepth * 64];
     __shared__ RowPlan plan;
@@ -772,7 +781,6 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
             // get the lowest key and three packed maxima fold the group; what is left of it (one register) stays, and
             // one more packed maximum is the lane's best.  The block's best key is found first (step_block_best);
             // only the lanes that hold it then look for the group, and in the group for the token.
-            uint32_t fold[kHeld];
             auto group_fold = [&](uint4 v, uint32_t mu) {        // v: the group's order keys
                 const uint2 lo = s_expand[mu & 15u], hi = s_expand[mu >> 4];
                 const uint32_t k01 = packed_max_s16(mask_order_keys(v.x, lo.x), mask_order_keys(v.y, lo.y));
@@ -780,19 +788,9 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
                 return packed_max_s16(k01, k23);
             };
             auto half_max = [](uint32_t x) { return max((int)(int16_t)(x & 0xFFFFu), (int)x >> 16); };
-            uint32_t best2 = 0x80008000u;
-#pragma unroll
-            for (int i = 0; i < kHeld; ++i) {
-                // no branches: a group outside the row or without an allowed token gets the lowest key in every
-                // half, and the LDS reads of the groups can overlap (the row's LDS area is at least
-                // kHeld * kStepData bytes, so the byte is read at a fixed offset)
-                const int g = i * kStepData + j;
-                const uint32_t mu = mask_bytes[g];
-                fold[i] = group_fold(held[i], g < whole ? mu : 0u);
-                best2 = packed_max_s16(best2, fold[i]);
-            }
             uint4 tail_keys = make_uint4(0, 0, 0, 0);
-            uint32_t tail_m = 0u, tail_fold = 0x80008000u;
+            uint32_t tail_m = 0u;
+            int tail_fold = -32768;
             const int tail = T.n_tokens & 7;
             if (tail > 0 && j == 0) {                   // the last, partial group: its logits one at a time
                 uint32_t x[4] = {0u, 0u, 0u, 0u};
@@ -801,22 +799,76 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
                     if (k < tail) x[k >> 1] |= (uint32_t)lrow[whole * 8 + k] << (16 * (k & 1));
                 tail_m = mask_bytes[whole] & ((1u << tail) - 1u);
                 tail_keys = make_uint4(bf16_order_keys(x[0]), bf16_order_keys(x[1]), bf16_order_keys(x[2]), bf16_order_keys(x[3]));
-                tail_fold = group_fold(tail_keys, tail_m);
-                best2 = packed_max_s16(best2, tail_fold);
+                tail_fold = half_max(group_fold(tail_keys, tail_m));
             }
-            const int best = half_max(best2);
-            top = step_block_best(best, s_key, tid);
-            if (best == top && top >= kOrderNegInf && !order_undecided(top)) {
-                // the first of a lane's groups that holds the value (its groups ascend, the partial one is the last)
-                uint4 keys = tail_keys;
-                uint32_t m = tail_m;
-                int at = whole;
+            int best, at = -1, first = 0;               // the lane's best key, and (once it is the block's) where it is
+            uint4 keys = make_uint4(0, 0, 0, 0);
+            uint32_t m = 0u;
+            if constexpr (kRows == 1) {
+                uint32_t fold[kHeld], best2 = 0x80008000u;
 #pragma unroll
-                for (int i = kHeld - 1; i >= 0; --i)
-                    if (half_max(fold[i]) == top) { keys = held[i]; at = i * kStepData + j; }
-                if (at != whole) m = mask_bytes[at];
+                for (int i = 0; i < kHeld; ++i) {
+                    // no branches: a group outside the row or without an allowed token gets the lowest key in every
+                    // half, and the LDS reads of the groups can overlap (the row's LDS area is at least
+                    // kHeld * kStepData bytes, so the byte is read at a fixed offset)
+                    const int g = i * kStepData + j;
+                    const uint32_t mu = mask_bytes[g];
+                    fold[i] = group_fold(held[i], g < whole ? mu : 0u);
+                    best2 = packed_max_s16(best2, fold[i]);
+                }
+                best = max(half_max(best2), tail_fold);
+                top = step_block_best(best, s_key, tid);
+                if (best == top) {
+                    // the first of a lane's groups that holds the value (its groups ascend, the partial one is the last)
+                    at = whole;
+#pragma unroll
+                    for (int i = kHeld - 1; i >= 0; --i)
+                        if (half_max(fold[i]) == top) { keys = held[i]; at = i * kStepData + j; }
+                }
+            } else {
+                // What the block does not hold is streamed now that the mask is known: nothing of a group without an
+                // allowed token is read, and the loads are issued without a branch, kStepAhead ahead, the first of them
+                // before the groups that are held are worked on.
+                const RowBuffer buffer = row_buffer(lrow, (uint32_t)whole * 16u);
+                auto mask_of = [&](int g) { const uint32_t mu = mask_bytes[min(g, whole - 1)]; return g < whole ? mu : 0u; };
+                auto load_rest = [&](int g) { return buffer_load(buffer, mask_of(g) != 0u ? (uint32_t)g * 16u : kNowhere); };
+                best = kOrderNegInf - 1;                // (only a valid value or a positive NaN pattern beats the start)
+                auto work_on = [&](uint4 v, int g) {    // no branch: the LDS reads of several groups overlap
+                    const uint32_t mu = mask_of(g);
+                    const int group_best = half_max(group_fold(v, mu));
+                    const bool better = group_best > best;                       // strictly: the first of equals stays
+                    best = better ? group_best : best;
+                    at = better ? g : at;
+                    keys.x = better ? v.x : keys.x; keys.y = better ? v.y : keys.y; keys.z = better ? v.z : keys.z; keys.w = better ? v.w : keys.w;
+                };
+                constexpr int kBatch = kRestAhead / 2;  // groups a lane works on together, while as many are in flight
+                uint4 v[kRestAhead];
+                int g = kHeld * kStepData + j;
+#pragma unroll
+                for (int u = 0; u < kRestAhead; ++u) v[u] = load_rest(g + u * kStepData);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < kHeld; ++i) work_on(held[i], i * kStepData + j);
+                for (int r = kHeld * kStepData; r < whole; r += kRestAhead * kStepData) {
+#pragma unroll
+                    for (int u0 = 0; u0 < kRestAhead; u0 += kBatch) {
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int u = u0; u < u0 + kBatch; ++u)
+                            work_on(make_uint4(bf16_order_keys(v[u].x), bf16_order_keys(v[u].y), bf16_order_keys(v[u].z), bf16_order_keys(v[u].w)),
+                                    g + u * kStepData);
+#pragma unroll
+                        for (int u = u0; u < u0 + kBatch; ++u) v[u] = load_rest(g + (u + kRestAhead) * kStepData);
+                    }
+                    g += kRestAhead * kStepData;
+                }
+                if (tail_fold > best) { best = tail_fold; at = whole; }
+                top = step_block_best(best, s_key, tid);
+            }
+            if (best == top && top >= kOrderNegInf && !order_undecided(top)) {
+                if (at == whole) { keys = tail_keys; m = tail_m; }
+                else m = mask_bytes[at];
                 const uint32_t x[4] = {keys.x, keys.y, keys.z, keys.w};
-                int first = 0;
 #pragma unroll
                 for (int k = 7; k >= 0; --k) {          // descending: the smallest k is assigned last
                     const int key = (k & 1) ? ((int)x[k >> 1] >> 16) : (int)(int16_t)(x[k >> 1] & 0xFFFFu);
@@ -864,8 +916,9 @@ __global__ __launch_bounds__(kStepBlock) void advance_fill_apply_kernel(
         } else if (!order_undecided(top)) {
             if (tid == 0) out_tokens[b] = s_token;
         } else {
-            const unsigned long long mine = argmax_block_max(argmax_segment_by_compare_inline(lrow, reinterpret_cast<const uint8_t *>(bits4), 0,
-                                                                                              (T.n_tokens + 7) >> 3, T.n_tokens, tid), s_part, tid);
+            const unsigned long long mine = argmax_block_max(
+                argmax_by_compare<kArgBlock>(lrow, [&](int g) { return (uint32_t)reinterpret_cast<const uint8_t *>(bits4)[g]; }, 0,
+                                          (T.n_tokens + 7) >> 3, T.n_tokens, tid), s_part, tid);
             if (tid == 0) out_tokens[b] = mine != 0ull ? (int32_t)(0xFFFFFFFFu - (uint32_t)mine) : -1;
         }
     }
@@ -1383,6 +1436,7 @@ hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const
 // (27 groups per lane, 207,360 tokens, is what fits the 128 vector registers of a 1,024-thread block beside the
 // masking code; the greedy fold needs more registers and stops at 20 groups, 153,600 tokens)
 constexpr int kStepHeldShort = 9, kStepHeldMax = 27, kStepHeldMaxGreedy = 20;
+constexpr int kStepHeldTwoRows = 8, kTwoRowsPerUnit = -1;   // the greedy form with two rows to a unit
 // Largest vocabulary the fused step kernel can hold in registers, and the choice of its variant.
 bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bool greedy) {
     const size_t row_bytes = (size_t)edge_row_stride_words(n_words) * sizeof(uint32_t);
@@ -1393,6 +1447,14 @@ bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bo
     return row_bytes <= kAfDynamicLdsMax;
 }
 
+bool greedy_two_rows_fit(int n_tokens, int n_words, int cap, bool cycles) {
+    const size_t row_bytes = (size_t)edge_row_stride_words(n_words) * sizeof(uint32_t);
+    if ((n_tokens >> 3) < kStepHeldTwoRows * kStepData) return false;        // (whole registers of groups; shorter rows take other forms)
+    return cycles ? cap <= kCompactMaxLen && row_bytes + (size_t)cap * sizeof(int32_t) <= kAfDynamicLdsMax : row_bytes <= kAfDynamicLdsMax;
+}
+
+bool greedy_two_rows_long_row(int n_tokens) { return (n_tokens >> 3) >= 2 * kStepHeldTwoRows * kStepData; }
+
 bool advance_fill_apply_short_row(int n_tokens) { return (n_tokens >> 3) <= kStepHeldShort * kStepData; }
 
 template <bool kCompact, bool kArgmax>
@@ -1401,14 +1463,16 @@ static void launch_step_variant(int held, dim3 grid, size_t lds, hipStream_t str
                                 int32_t *err, uint32_t *bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
                                 const int32_t *cycle_head, const int32_t *cycle_pool, int stage, uint16_t *logits,
                                 int64_t row_stride, int32_t *out_tokens, int first_row) {
-#define PRE3_STEP(H)                                                                                                        \
-    hipLaunchKernelGGL((advance_fill_apply_kernel<kCompact, H, kArgmax>), grid, dim3(kStepBlock), lds, stream, tokens, len,   \
+#define PRE3_STEP(H, ROWS)                                                                                                  \
+    hipLaunchKernelGGL((advance_fill_apply_kernel<kCompact, H, kArgmax, ROWS>), grid, dim3(kStepBlock), lds, stream, tokens, len,   \
                        states, data, T.pack, cap, first_row, logits, row_stride, batch, err, bitmask, restart_on_eos,          \
                        adv_scratch, walk_spill, (size_t)batch * 64, cycle_head, cycle_pool, stage, out_tokens)
-    if (held <= kStepHeldShort) PRE3_STEP(kStepHeldShort);
-    else if (held <= 17) PRE3_STEP(17);
-    else if (held <= kStepHeldMaxGreedy || kArgmax) PRE3_STEP(20);
-    else if constexpr (!kArgmax) PRE3_STEP(27);
+    if (held == kTwoRowsPerUnit) {
+        if constexpr (kArgmax) PRE3_STEP(kStepHeldTwoRows, 2);
+    } else if (held <= kStepHeldShort) PRE3_STEP(kStepHeldShort, 1);
+    else if (held <= 17) PRE3_STEP(17, 1);
+    else if (held <= kStepHeldMaxGreedy || kArgmax) PRE3_STEP(20, 1);
+    else if constexpr (!kArgmax) PRE3_STEP(27, 1);
 #undef PRE3_STEP
 }
 
@@ -1428,10 +1492,13 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E,
                                      const int32_t *cycle_head, const int32_t *cycle_pool, uint16_t *logits,
                                      int64_t row_stride, int32_t *out_tokens, int rows_per_launch, hipStream_t stream) {
     if (batch == 0) return hipSuccess;
-    if (!advance_fill_apply_fits(T.n_tokens, T.n_words, cap, cycle_head != nullptr, out_tokens != nullptr)) return hipErrorInvalidValue;
+    const bool two_rows = rows_per_launch == kRowsTwoPerUnit;
+    if (two_rows ? !out_tokens || !greedy_two_rows_fit(T.n_tokens, T.n_words, cap, cycle_head != nullptr)
+                 : !advance_fill_apply_fits(T.n_tokens, T.n_words, cap, cycle_head != nullptr, out_tokens != nullptr))
+        return hipErrorInvalidValue;
     if ((reinterpret_cast<uintptr_t>(logits) & 15) != 0 || (row_stride & 7) != 0 || row_stride < T.n_tokens)
         return hipErrorInvalidValue;
-    const int held = ((T.n_tokens >> 3) + kStepData - 1) / kStepData;
+    const int held = two_rows ? kTwoRowsPerUnit : ((T.n_tokens >> 3) + kStepData - 1) / kStepData;
     const int held_variant = held <= 9 ? 9 : held <= 17 ? 17 : kStepHeldMaxGreedy;
     size_t lds = (size_t)edge_row_stride_words(T.n_words) * sizeof(uint32_t);
     int stage = 0;
@@ -1442,10 +1509,10 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E,
         if (stage) lds += tables;
     }
     // the greedy fold reads a mask byte for every group slot of a lane, also those past the row's end
-    if (out_tokens && lds < (size_t)held_variant * kStepData + 16) lds = (size_t)held_variant * kStepData + 16;
+    if (out_tokens && !two_rows && lds < (size_t)held_variant * kStepData + 16) lds = (size_t)held_variant * kStepData + 16;
 #define PRE3_STEP_ARGS held, dim3(rows), lds, stream, T, E, tokens, states, data, len, cap, batch, err, bitmask, restart_on_eos, \
                        adv_scratch, walk_spill, cycle_head, cycle_pool, stage, logits, row_stride, out_tokens, first
-    const int share = step_rows_per_launch(batch, rows_per_launch);
+    const int share = two_rows ? batch : step_rows_per_launch(batch, rows_per_launch);
     for (int first = 0; first < batch; first += share) {
         const int rows = batch - first < share ? batch - first : share;
         if (cycle_head) {

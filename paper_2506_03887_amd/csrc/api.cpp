@@ -651,11 +651,25 @@ bool one_kernel_serves(const pre3_handle *h, const uint16_t *logits_bf16, int64_
            row_stride >= h->V.n_tokens && advance_fill_apply_fits(h->V.n_tokens, h->V.n_words, h->b_stacks.cap, cycles, greedy);
 }
 
+// Whether the greedy step runs with two rows to a compute unit: batches of more rows than units, of rows that a block cannot
+// hold (61,440 tokens).  Up to two rows per unit it wins on every workload (see the kernel); beyond, where blocks of a
+// second round start as others end, on rows of at least 122,880 tokens (us per step, two launches and this form: JSON
+// 600 x 152,064 46.0 and 42.2, 1,500 x 128,256 77.7 and 71.1, schema 600 x 122,880 32.6 and 31.3, 520 x 128,256 31.2 and 31.9;
+// but schema 1,024 x 110,000 42.4 and 44.0, 600 x 100,000 29.6 and 32.0, JSON 2,048 x 70,000 66.0 and 67.9).
+bool greedy_two_rows(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride) {
+    const bool cycles = h->compact && h->T.n_cycles > 0;
+    const int batch = h->b_stacks.batch, units = h->n_compute_units;
+    return batch > units && (batch <= 2 * units || greedy_two_rows_long_row(h->V.n_tokens)) && h->use_edges &&
+           reinterpret_cast<uintptr_t>(logits_bf16) % 16 == 0 && row_stride % 8 == 0 && row_stride >= h->V.n_tokens &&
+           greedy_two_rows_fit(h->V.n_tokens, h->V.n_words, h->b_stacks.cap, cycles);
+}
+
 // The form a step call takes for the bound batch: both calls and the query that reports it go by this.
-enum class StepForm { kTwoCalls, kOneKernel, kSpread };
+enum class StepForm { kTwoCalls, kOneKernel, kTwoRowsPerUnit, kSpread };
 StepForm step_form(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride, int32_t flags, bool greedy) {
     const int batch = h->b_stacks.batch;
     const bool asked = flags & PRE3_STEP_ONE_KERNEL;
+    if (!asked && greedy && greedy_two_rows(h, logits_bf16, row_stride)) return StepForm::kTwoRowsPerUnit;
     const bool one_kernel = (asked || step_kernel_batch(h, batch)) && one_kernel_serves(h, logits_bf16, row_stride, greedy);
     const int blocks = asked ? 0 : spread_step_blocks(h, batch);
     if (blocks > 0 && !one_kernel) return StepForm::kSpread;
@@ -686,7 +700,7 @@ hipError_t launch_step(pre3_handle *h, StepForm form, const int32_t *tokens, uin
                                   h->adv_scratch, h->af_walk_spill, head, pool, logits_bf16, row_stride, out_tokens, h->arrivals, s);
     return launch_advance_fill_apply(h->dev, h->dev_edges, tokens, h->b_states, st.data, st.len, st.cap, st.batch, h->b_err, bitmask,
                                      restart, h->adv_scratch, h->af_walk_spill, head, pool, logits_bf16, row_stride, out_tokens,
-                                     h->n_compute_units, s);
+                                     form == StepForm::kTwoRowsPerUnit ? kRowsTwoPerUnit : h->n_compute_units, s);
 }
 }  // namespace
 
@@ -696,6 +710,7 @@ int32_t pre3_step_is_one_kernel(const pre3_handle *h, const uint16_t *logits_bf1
     const StepForm form = step_form(h, logits_bf16, row_stride, flags, flags & PRE3_STEP_GREEDY);
     if (form == StepForm::kTwoCalls) return 0;
     if (form == StepForm::kSpread) return PRE3_STEP_IS_SPREAD | 1;
+    if (form == StepForm::kTwoRowsPerUnit) return 1;
     // launches of equal shares, counted as the launcher deals them out
     const int batch = h->b_stacks.batch, most = (batch + h->n_compute_units - 1) / h->n_compute_units;
     const int share = (batch + most - 1) / most;

@@ -68,6 +68,11 @@ bool advance_fill_fits_compact(int n_words, int cap);   // row bitmap + staged s
 // rows_per_launch: a batch of more rows goes as several launches of equal shares of at most that many
 // (the number of compute units: a block fills one); 0: one launch.
 bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bool greedy);   // greedy: the arg-max form
+// rows_per_launch = kRowsTwoPerUnit: the greedy form whose blocks run two to a compute unit, one launch at any batch;
+// greedy_two_rows_fit: rows of at least what its blocks hold in registers (61,440 tokens), mask row and staged stack in LDS.
+constexpr int kRowsTwoPerUnit = -1;
+bool greedy_two_rows_fit(int n_tokens, int n_words, int cap, bool cycles);
+bool greedy_two_rows_long_row(int n_tokens);            // at least twice that
 bool advance_fill_apply_short_row(int n_tokens);        // rows of its smallest variant (69,120 tokens)
 // The same kernel without the advance: mask rows of the stacks as they are, applied to the logits
 // (walk_spill: advance_fill_walk_spill_entries(batch, ...) entries; same conditions on the logits).

@@ -34,6 +34,21 @@ __device__ __forceinline__ void stream_store(uint4 v, uint4 *p) {
     __builtin_nontemporal_store(x, reinterpret_cast<NativeUint4 *>(p));
 }
 
+// A row of logits (16-byte aligned) as a buffer of so many bytes: a load at an offset beyond it (kNowhere) reads nothing and
+// returns zeros.  A load that only some lanes need is then one instruction without a branch, and the wave knows how many
+// loads are in flight behind the one it waits for.
+typedef __amdgpu_buffer_rsrc_t RowBuffer;
+constexpr uint32_t kNowhere = 0xFFFFFFF0u;
+__device__ __forceinline__ RowBuffer row_buffer(const uint16_t *row, uint32_t bytes) {
+    constexpr int kRaw32Bit = 0x00020000, kNoStride = 0;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(row), kNoStride, (int)bytes, kRaw32Bit);
+}
+__device__ __forceinline__ uint4 buffer_load(RowBuffer row, uint32_t byte_offset) {
+    constexpr int kNonTemporal = 2;
+    const NativeUint4 x = __builtin_amdgcn_raw_buffer_load_b128(row, (int)byte_offset, 0, kNonTemporal);
+    return make_uint4(x.x, x.y, x.z, x.w);
+}
+
 constexpr uint32_t kNegInfPair = 0xFF80FF80u;   // two bf16 -inf
 
 }  // namespace pre3
