@@ -1453,6 +1453,8 @@ bool greedy_two_rows_fit(int n_tokens, int n_words, int cap, bool cycles) {
     return cycles ? cap <= kCompactMaxLen && row_bytes + (size_t)cap * sizeof(int32_t) <= kAfDynamicLdsMax : row_bytes <= kAfDynamicLdsMax;
 }
 
+bool greedy_any_offset_row(int n_tokens) { return (n_tokens >> 3) > 10 * kStepData; }
+
 bool greedy_two_rows_long_row(int n_tokens) { return (n_tokens >> 3) >= 2 * kStepHeldTwoRows * kStepData; }
 
 bool advance_fill_apply_short_row(int n_tokens) { return (n_tokens >> 3) <= kStepHeldShort * kStepData; }
@@ -1496,8 +1498,8 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E,
     if (two_rows ? !out_tokens || !greedy_two_rows_fit(T.n_tokens, T.n_words, cap, cycle_head != nullptr)
                  : !advance_fill_apply_fits(T.n_tokens, T.n_words, cap, cycle_head != nullptr, out_tokens != nullptr))
         return hipErrorInvalidValue;
-    if ((reinterpret_cast<uintptr_t>(logits) & 15) != 0 || (row_stride & 7) != 0 || row_stride < T.n_tokens)
-        return hipErrorInvalidValue;
+    const bool aligned = (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && (row_stride & 7) == 0;
+    if ((!aligned && (!out_tokens || two_rows)) || row_stride < T.n_tokens) return hipErrorInvalidValue;
     const int held = two_rows ? kTwoRowsPerUnit : ((T.n_tokens >> 3) + kStepData - 1) / kStepData;
     const int held_variant = held <= 9 ? 9 : held <= 17 ? 17 : kStepHeldMaxGreedy;
     size_t lds = (size_t)edge_row_stride_words(T.n_words) * sizeof(uint32_t);

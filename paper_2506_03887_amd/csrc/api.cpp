@@ -644,11 +644,14 @@ int pre3_advance_fill_mask(pre3_handle *h, const int32_t *tokens, uint32_t *bitm
 }
 
 namespace {
+bool aligned_rows(const uint16_t *logits_bf16, int64_t row_stride) {
+    return reinterpret_cast<uintptr_t>(logits_bf16) % 16 == 0 && row_stride % 8 == 0;
+}
+
 // Whether the one-kernel form can serve the bound batch: its conditions on the logits, the vocabulary and the tables.
 bool one_kernel_serves(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride, bool greedy) {
     const bool cycles = h->compact && h->T.n_cycles > 0;
-    return h->use_edges && reinterpret_cast<uintptr_t>(logits_bf16) % 16 == 0 && row_stride % 8 == 0 &&
-           row_stride >= h->V.n_tokens && advance_fill_apply_fits(h->V.n_tokens, h->V.n_words, h->b_stacks.cap, cycles, greedy);
+    return h->use_edges && (greedy || aligned_rows(logits_bf16, row_stride)) && row_stride >= h->V.n_tokens && advance_fill_apply_fits(h->V.n_tokens, h->V.n_words, h->b_stacks.cap, cycles, greedy);
 }
 
 // Whether the greedy step runs with two rows to a compute unit: batches of more rows than units, of rows that a block cannot
@@ -660,7 +663,7 @@ bool greedy_two_rows(const pre3_handle *h, const uint16_t *logits_bf16, int64_t 
     const bool cycles = h->compact && h->T.n_cycles > 0;
     const int batch = h->b_stacks.batch, units = h->n_compute_units;
     return batch > units && (batch <= 2 * units || greedy_two_rows_long_row(h->V.n_tokens)) && h->use_edges &&
-           reinterpret_cast<uintptr_t>(logits_bf16) % 16 == 0 && row_stride % 8 == 0 && row_stride >= h->V.n_tokens &&
+           aligned_rows(logits_bf16, row_stride) && row_stride >= h->V.n_tokens &&
            greedy_two_rows_fit(h->V.n_tokens, h->V.n_words, h->b_stacks.cap, cycles);
 }
 
@@ -670,8 +673,15 @@ StepForm step_form(const pre3_handle *h, const uint16_t *logits_bf16, int64_t ro
     const int batch = h->b_stacks.batch;
     const bool asked = flags & PRE3_STEP_ONE_KERNEL;
     if (!asked && greedy && greedy_two_rows(h, logits_bf16, row_stride)) return StepForm::kTwoRowsPerUnit;
-    const bool one_kernel = (asked || step_kernel_batch(h, batch)) && one_kernel_serves(h, logits_bf16, row_stride, greedy);
     const int blocks = asked ? 0 : spread_step_blocks(h, batch);
+    // The greedy form only reads the logits and takes rows at any offset, but slower: there it stands in for the two calls
+    // where the spread form does not serve, on rows of more than 76,800 tokens (us per step, two calls and one kernel:
+    // JSON 100 x 100,003 20.4 and 17.1, 200 x 128,257 27.4 and 19.2, 200 x 150,001 29.3 and 21.4, eight schemas
+    // 256 x 128,257 26.0 and 20.5, one schema 100 x 100,003 18.9 and 17.1; JSON 128 x 70,001 16.9 and 16.5; where the spread form
+    // serves, JSON 70 x 100,003, it takes 13.3 and the one kernel 16.7).  Asked for, it is kept to aligned rows.
+    const bool any_offset = greedy && !aligned_rows(logits_bf16, row_stride);
+    const bool one_kernel = (asked || step_kernel_batch(h, batch)) && one_kernel_serves(h, logits_bf16, row_stride, greedy) &&
+                            !(any_offset && (asked || blocks > 0 || !greedy_any_offset_row(h->V.n_tokens)));
     if (blocks > 0 && !one_kernel) return StepForm::kSpread;
     // Where the one kernel serves the batch too, the spread form is only taken while it has few blocks, since each of them
     // advances the sequence for itself.  Rows that the one kernel holds in few registers: up to three blocks per unit

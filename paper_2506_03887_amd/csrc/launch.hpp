@@ -61,8 +61,9 @@ hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const
                                const int32_t *cycle_head, const int32_t *cycle_pool, int n_compute_units, hipStream_t stream);
 bool advance_fill_fits_compact(int n_words, int cap);   // row bitmap + staged stack within 64 KB of LDS
 // The same followed by the masking of the logits with the new rows, as one kernel that fetches a
-// sequence's logits while its token is still being walked.  Needs advance_fill_apply_fits, logits
-// aligned to 16 bytes and a row stride that is a multiple of 8 and at least the vocabulary size.
+// sequence's logits while its token is still being walked.  Needs advance_fill_apply_fits, a row stride of at least the
+// vocabulary size and, unless it is the greedy form with one row to a unit, which only reads the logits, logits
+// aligned to 16 bytes and a row stride that is a multiple of 8.
 // out_tokens null: the logits are masked in place; else they are only read and out_tokens[b] becomes
 // the arg max of the allowed logits of row b (the greedy step).
 // rows_per_launch: a batch of more rows goes as several launches of equal shares of at most that many
@@ -72,6 +73,7 @@ bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bo
 // greedy_two_rows_fit: rows of at least what its blocks hold in registers (61,440 tokens), mask row and staged stack in LDS.
 constexpr int kRowsTwoPerUnit = -1;
 bool greedy_two_rows_fit(int n_tokens, int n_words, int cap, bool cycles);
+bool greedy_any_offset_row(int n_tokens);               // rows the greedy form takes at any offset: more than 76,800 tokens
 bool greedy_two_rows_long_row(int n_tokens);            // at least twice that
 bool advance_fill_apply_short_row(int n_tokens);        // rows of its smallest variant (69,120 tokens)
 // The same kernel without the advance: mask rows of the stacks as they are, applied to the logits

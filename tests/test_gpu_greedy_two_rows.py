@@ -1,5 +1,6 @@
 """The greedy step of more rows than compute units on long rows: two blocks share a unit, each holds the first 61,440 tokens of
-its row and streams the rest.  Lockstep with the oracle, the best token on either side of every edge of that split."""
+its row and streams the rest.  Lockstep with the oracle, the best token on either side of every edge of that split.  And the
+one-kernel form on long rows that start at any logit."""
 import numpy as np
 import pytest
 
@@ -23,6 +24,20 @@ def _vocab(n):
     (70_001, 300, dict(row_threshold=64), "one kernel"), (65_007, 257, dict(max_condition_depth=3), "one kernel"),
     (HELD + 16, 513, {}, "two calls"), (2 * HELD + 3, 520, {}, "one kernel")])
 def test_greedy_step_of_more_rows_than_units(V, B, options, form):
+    _lockstep(V, B, options, form, -V % 8, 0)
+
+
+# (beyond four blocks of 8,192 tokens to a unit, where the spread form does not serve, on rows of more than 76,800 tokens)
+@pytest.mark.parametrize("V,B,pad,offset,options,form", [
+    (76_807, 200, 0, 0, {}, "two calls"), (76_809, 200, 0, 0, {}, "one kernel"), (80_001, 256, 0, 1, {}, "one kernel"),
+    (100_003, 79, 4, 3, {}, "one kernel"), (100_003, 78, 4, 3, {}, "spread"), (100_003, 100, 5, 5, dict(compact_cycles=True), "one kernel"),
+    (78_000, 150, 1, 0, dict(max_condition_depth=3), "one kernel"), (153_607, 64, 0, 2, {}, "one kernel"), (153_608, 64, 4, 0, {}, "two calls"),
+    (100_000, 257, 1, 0, {}, "two calls")])
+def test_greedy_step_on_rows_at_any_offset(V, B, pad, offset, options, form):
+    _lockstep(V, B, options, form, pad, offset)
+
+
+def _lockstep(V, B, options, form, pad, offset):
     import torch
     from paper_2506_03887_amd import Pre3
     dev = torch.device("cuda:0")
@@ -39,10 +54,12 @@ def test_greedy_step_of_more_rows_than_units(V, B, options, form):
     err_d, tok_d = torch.zeros(B, dtype=torch.int32, device=dev), torch.full((B,), -1, dtype=torch.int32, device=dev)
     lib.bind_state(s_d, d_d, l_d, err_d)
     mask_d = torch.zeros((B, v.words), dtype=torch.int32, device=dev)
-    stride = -(-V // 8) * 8
-    view = torch.zeros((B, stride), dtype=torch.int16, device=dev).view(torch.bfloat16)
-    assert lib.step_form(view, greedy=True) == form and lib.step_form(view) == "two calls"
-    assert lib.step_kernel_launches(view, greedy=True) == (form == "one kernel")
+    stride = V + pad
+    view = torch.zeros(B * stride + offset, dtype=torch.int16, device=dev)[offset:].view(B, stride).view(torch.bfloat16)
+    assert lib.step_form(view, greedy=True) == form and lib.step_form(view) == ("spread" if form == "spread" else "two calls")
+    assert lib.step_kernel_launches(view, greedy=True) == (form != "two calls")
+    if pad or offset:
+        assert not lib.step_kernel_launches(view, one_kernel=True, greedy=True) or (stride % 8 == 0 and offset % 8 == 0)
     edges = [t for t in (0, 7, 8, HELD - 8, HELD - 1, HELD, HELD + 7, HELD + 8 * 960 - 1, HELD + 8 * 960, V - V % 8 - 8, V - V % 8 - 1, V - 2)
              if 0 <= t < V]
     tokens = np.full(B, -1, np.int32)
@@ -63,8 +80,8 @@ def test_greedy_step_of_more_rows_than_units(V, B, options, form):
         for b in range(7, B, 9):                                                # the largest at the edges, alone and twice
             host[b, rng.choice(edges, size=1 + b % 2, replace=False)] = 0x4300
             host[b, rng.choice(V, size=40)] = 0x4280
-        x = torch.from_numpy(host.view(np.int16)).to(dev).view(torch.bfloat16)
-        lib.advance_fill_argmax(tok_d, mask_d, x, tok_d, restart_on_eos=bool(s % 2))
+        view.copy_(torch.from_numpy(host.view(np.int16)).to(dev).view(torch.bfloat16))
+        lib.advance_fill_argmax(tok_d, mask_d, view, tok_d, restart_on_eos=bool(s % 2))
         want = oracle_masked_argmax(host, mask, V)
         got = tok_d.cpu().numpy()
         assert (got == want).all(), (s, np.flatnonzero(got != want)[:5], got[got != want][:5], want[got != want][:5])
@@ -72,7 +89,7 @@ def test_greedy_step_of_more_rows_than_units(V, B, options, form):
         live = np.arange(cap)[None, :] < length[:, None]
         assert (d_d.cpu().numpy()[live] == data[live]).all(), s
         assert (mask_d.cpu().numpy().view(np.uint32) == mask).all(), s
-        assert (x.view(torch.int16).cpu().numpy().view(np.uint16) == host).all(), s
+        assert (view.view(torch.int16).cpu().numpy().view(np.uint16) == host).all(), s
         # the next tokens: mostly the oracle's choice, some refused, skipped and the end of sequence
         tokens = want.copy()
         odd = rng.random(B) < 0.2
