@@ -209,7 +209,10 @@ hipError_t launch_fill_mask_edges(const DevTables &T, const DevTokenEdges &E, co
     // of at least 64 uint4 (8 KiB of mask = 16 Ki logits) so that the redundant descents stay cheap.
     const int n_vec = (T.n_words + 3) / 4;
     const int rows_padded = (batch + 7) & ~7;
-    int want = grid_blocks / rows_padded;
+    // Where only the mask is made, half of the grid's blocks do: the launch is over sooner with fewer blocks to start than
+    // with fewer words per block (96 x 100,003: 4.8 us with 480 blocks, 5.1 with 960, 5.2 with 192; 48 x 152,064 3.9 and 4.2,
+    // 128 x 128,256 4.7 and 5.1, 200 x 32,000 4.7 and 4.9).
+    int want = (logits ? grid_blocks : grid_blocks / 2) / rows_padded;
     int max_seg = (n_vec + 63) / 64;
     int n_seg = want < 1 ? 1 : (want > max_seg ? max_seg : want);
     int seg_vec = (n_vec + n_seg - 1) / n_seg;

@@ -135,3 +135,34 @@ def test_topk_of_rows_kept_in_registers(V, B):
 def test_topk_of_rows_at_the_longest_variant(V, B):
     """One block per row up to 163,840 tokens at any batch, several blocks beyond."""
     test_topk_of_rows_kept_in_registers(V, B)
+
+
+@pytest.mark.parametrize("V,B,options", [(16_385, 9, {}), (33_033, 70, {}), (33_033, 600, {}), (65_569, 40, dict(max_condition_depth=2)),
+                                         (100_003, 24, {}), (20_003, 30, dict(row_threshold=64))])
+def test_mask_rows_off_a_16_byte_boundary(V, B, options):
+    """pre3_fill_mask where rows of the bitmask start off a 16-byte boundary: rows in segments that are copied a word at a
+    time, whole rows, rows with tokens or everything left open, id lists, finished and empty stacks."""
+    from oracle import Oracle
+    from paper_2506_03887_amd import Pre3
+    from workloads import grammars as G
+    from workloads.vocab import BASE_SEED, bpe_like_vocab
+    torch, dev = _torch()
+    v, o = bpe_like_vocab(V, 16, BASE_SEED + V), Oracle(G.JSON)
+    assert v.words % 4 != 0
+    lib = Pre3(G.JSON, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, **options)
+    prefixes = [b"", b"[", b'{"a":[1,', b'"abc', b"[[[[[[[[[[[[", b'{"a":{"b":"', b"12", b'[{"k":true},']
+    data, length = np.zeros((B, 128), np.int32), np.ones(B, np.int32)
+    for b in range(B):
+        p = prefixes[b % len(prefixes)]
+        st = o.advance(o.initial_stack(0), p)[1] if p else o.initial_stack(0)
+        data[b, : len(st)], length[b] = st, len(st)
+    states = data[np.arange(B), length - 1].copy()
+    states[3::17] = -1                                                       # finished
+    length[5::19] = 0                                                        # no stack
+    m = torch.full((B + 1, v.words), 0x77777777, dtype=torch.int32, device=dev)
+    s_d, d_d, l_d = (torch.from_numpy(x).to(dev) for x in (states, data, length))
+    lib.fill_mask(s_d, d_d, l_d, m[:B])
+    live = length > 0
+    got, want = m.cpu().numpy().view(np.uint32), o.fill_mask(states[live], data[live], length[live], v)
+    assert (got[:B][live] == want).all() and (got[:B][~live & (states >= 0)] == 0).all() and (got[B] == 0x77777777).all()
+    assert lib.fault_count() == 0
