@@ -41,6 +41,7 @@ struct pre3_handle {
     bool use_edges = false;
     int edge_blocks = 0;
     int32_t *edge_spill = nullptr;
+    bool long_walks = false;             // a leaf of the condition trees leaves more tokens to the walk than a wave takes at once
 
     // binding used by pre3_advance
     int32_t *b_states = nullptr, *b_err = nullptr;
@@ -354,6 +355,14 @@ bool locate(const pre3_handle *h, int state, int *g, int *local) {
     return false;
 }
 
+// Blocks that a launch which only makes masks should come to, of at most edge_blocks.  Half of them where the condition trees
+// leave no row open: the launch is over sooner with fewer blocks to start than with fewer words per block (us, half and
+// all: 96 x 100,003 4.8 and 5.1, 48 x 152,064 3.9 and 4.2, 264 x 128,256 5.8 and 6.2, 500 x 128,256 6.2 and 6.4, 200 x 32,000
+// 4.7 and 4.9).  Where a leaf leaves more tokens than a wave walks at once (its whole vocabulary in the longest case), all
+// of them: a segment is walked by one wave (JSON with conditions cut at 3 entries, half and all: 66 x 128,256 2.3 and 1.2 ms,
+// 320 x 128,256 16.2 and 5.6 ms).
+int fill_mask_blocks(const pre3_handle *h, int edge_blocks) { return h->long_walks ? edge_blocks : edge_blocks / 2; }
+
 // Most sequences of a batch that runs as the spread step, 0 if the tables do not allow that form.  It is chosen while all its
 // blocks (four per compute unit) are on the chip at once: 64 sequences x 128,256 tokens take 12.4 us against 14.5 us in the
 // one-kernel form, 60 x 128,256 12.2 against 15.7 us as two launches; with twice as many blocks the second half
@@ -389,6 +398,13 @@ BatchWorkspaces batch_workspaces(const pre3_handle *h, int batch) {
 }
 
 }  // namespace
+
+namespace pre3 {
+// Blocks that make one row of a batch in pre3_fill_mask.
+int fill_mask_row_segments(const pre3_handle *h, int batch) {
+    return edge_row_segments(h->V.n_words, batch, fill_mask_blocks(h, edge_grid_blocks(h->n_compute_units)));
+}
+}  // namespace pre3
 
 extern "C" {
 
@@ -443,6 +459,8 @@ int pre3_compile(const char *const *grammars, int32_t n_grammars, const pre3_voc
             if (opt && (opt->flags & PRE3_FLAG_NO_TOKEN_EFFECTS)) lim.effect_min_len = 0;
             h->E = build_token_edges(h->T, h->V, lim);
             h->X = build_effect_table(h->E);
+            for (const ConditionNode &n : h->E.nodes)
+                h->long_walks |= n.child_count == 0 && (n.walk_count < 0 || n.walk_count > 64);
         }
     } catch (const CompileError &e) {
         return fail(h, e.status, e.text);
@@ -530,7 +548,7 @@ int pre3_fill_mask(pre3_handle *h, const int32_t *states, pre3_stacks stacks, ui
     hipError_t e =
         h->use_edges
             ? launch_fill_mask_edges(h->dev, h->dev_edges, states, stacks.data, stacks.len, stacks.cap, stacks.batch,
-                                     bitmask, nullptr, 0, h->edge_spill, h->edge_blocks,
+                                     bitmask, nullptr, 0, h->edge_spill, h->edge_blocks, fill_mask_blocks(h, h->edge_blocks),
                                      static_cast<hipStream_t>(stream))
             : launch_fill_mask_walk(h->dev, states, stacks.data, stacks.len, stacks.cap, stacks.batch, bitmask,
                                     h->spill, h->grid_blocks, static_cast<hipStream_t>(stream));
@@ -560,7 +578,7 @@ int pre3_fill_apply_mask(pre3_handle *h, const int32_t *states, pre3_stacks stac
     // grid of the masking kernel (66.3 against 49.4 us at 512 x 128,256, 78.6 against 51.9 us at 512 x 152,064).
     if (fused && stacks.batch <= h->n_compute_units) {
         hipError_t e = launch_fill_mask_edges(h->dev, h->dev_edges, states, stacks.data, stacks.len, stacks.cap,
-                                              stacks.batch, bitmask, logits, row_stride, h->edge_spill, h->edge_blocks, s);
+                                              stacks.batch, bitmask, logits, row_stride, h->edge_spill, h->edge_blocks, h->edge_blocks, s);
         return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch fill_apply_mask");
     }
     int rc = pre3_fill_mask(h, states, stacks, bitmask, stream);

@@ -21,10 +21,11 @@ int edge_grid_blocks(int n_compute_units);
 size_t edge_spill_entries(int grid_blocks, int max_depth);          // int32 entries
 int edge_row_stride_words(int n_words);                             // stride of dense rows on the device
 size_t edge_kernel_max_lds_words();                                 // largest bitmap row the kernel can hold
+int edge_row_segments(int n_words, int batch, int want_blocks);     // blocks per row of a launch of about want_blocks
 hipError_t launch_fill_mask_edges(const DevTables &T, const DevTokenEdges &E, const int32_t *states,
                                   const int32_t *data, const int32_t *len, int cap, int batch, uint32_t *bitmask,
                                   uint16_t *logits /* null: mask only */, int64_t row_stride, int32_t *spill,
-                                  int grid_blocks, hipStream_t stream);
+                                  int grid_blocks, int want_blocks, hipStream_t stream);
 // One thread writes the device's wall clock (100 MHz) to *out.
 hipError_t launch_timestamp(int64_t *out, hipStream_t stream);
 

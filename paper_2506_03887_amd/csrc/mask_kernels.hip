@@ -198,25 +198,27 @@ size_t edge_spill_entries(int grid_blocks, int max_depth) {
 size_t edge_kernel_max_lds_words() { return (size_t)(64 * 1024 - 8 * 1024) / 4; }
 int edge_row_stride_words(int n_words) { return (n_words + 3) & ~3; }
 
+// Segments per row: as many as give no block of the grid a second item (a second one doubles the
+// launch: 96 rows in 11 segments on 1,024 blocks took 8.1 us, in 10 segments 6.4 us; 520 rows of 128,256 tokens
+// 8.5 us in two segments, 6.6 whole, 1,000 rows 9.6 and 7.8, 1,000 rows of 32,000 tokens 9.3 and 6.6), but segments
+// of at least 64 uint4 (1 KiB of mask, 8,192 tokens) so that the redundant descents stay cheap.
+int edge_row_segments(int n_words, int batch, int want_blocks) {
+    const int n_vec = (n_words + 3) / 4, rows_padded = (batch + 7) & ~7;
+    const int want = want_blocks / rows_padded, max_seg = (n_vec + 63) / 64;
+    const int n_seg = want < 1 ? 1 : (want > max_seg ? max_seg : want);
+    const int seg_vec = (n_vec + n_seg - 1) / n_seg;
+    return (n_vec + seg_vec - 1) / seg_vec;
+}
+
 hipError_t launch_fill_mask_edges(const DevTables &T, const DevTokenEdges &E, const int32_t *states,
                                   const int32_t *data, const int32_t *len, int cap, int batch, uint32_t *bitmask,
-                                  uint16_t *logits, int64_t row_stride, int32_t *spill, int grid_blocks,
+                                  uint16_t *logits, int64_t row_stride, int32_t *spill, int grid_blocks, int want_blocks,
                                   hipStream_t stream) {
     if (batch == 0) return hipSuccess;
-    // Segments per row: as many as give no block of the grid a second item (a second one doubles the
-    // launch: 96 rows in 11 segments on 1,024 blocks took 8.1 us, in 10 segments 6.4 us; 520 rows of 128,256 tokens
-    // 8.5 us in two segments, 6.6 whole, 1,000 rows 9.6 and 7.8, 1,000 rows of 32,000 tokens 9.3 and 6.6), but segments
-    // of at least 64 uint4 (8 KiB of mask = 16 Ki logits) so that the redundant descents stay cheap.
     const int n_vec = (T.n_words + 3) / 4;
     const int rows_padded = (batch + 7) & ~7;
-    // Where only the mask is made, half of the grid's blocks do: the launch is over sooner with fewer blocks to start than
-    // with fewer words per block (96 x 100,003: 4.8 us with 480 blocks, 5.1 with 960, 5.2 with 192; 48 x 152,064 3.9 and 4.2,
-    // 128 x 128,256 4.7 and 5.1, 200 x 32,000 4.7 and 4.9).
-    int want = (logits ? grid_blocks : grid_blocks / 2) / rows_padded;
-    int max_seg = (n_vec + 63) / 64;
-    int n_seg = want < 1 ? 1 : (want > max_seg ? max_seg : want);
-    int seg_vec = (n_vec + n_seg - 1) / n_seg;
-    n_seg = (n_vec + seg_vec - 1) / seg_vec;
+    const int n_seg = edge_row_segments(T.n_words, batch, want_blocks);
+    const int seg_vec = (n_vec + n_seg - 1) / n_seg;
     const long long n_items = (long long)rows_padded * n_seg;
     const int grid = (int)(n_items < grid_blocks ? n_items : grid_blocks);
     const size_t lds = (size_t)seg_vec * sizeof(uint4);
