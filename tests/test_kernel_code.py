@@ -46,3 +46,16 @@ def test_a_block_of_the_spread_step_counts_itself_in_when_its_loads_have_returne
         assert waits and waits[-1] > loads[-1], name
         between = [x for x in code[waits[-1]: count] if re.match(r"s_cbranch|s_branch", x)]
         assert all(x.startswith("s_cbranch_execz") for x in between), (name, between)     # straight code, lanes switched off at most
+
+
+def test_inputs_that_a_launch_overwrites_are_kept_where_they_are_read():
+    """Loads through the constant address space may be moved behind a store or repeated after it, and no fence or wait orders
+    them: every place that reads tokens, states or len that way in a kernel that writes them keeps the value at once."""
+    src = open(os.path.join(os.path.dirname(__file__), "..", "paper_2506_03887_amd", "csrc", "advance_kernels.hip")).read()
+    plan_only = src[src.index("void plan_only_scalar"):]
+    src = src.replace(plan_only[: plan_only.index("\n}\n")], "")          # mask + masking: writes none of them
+    reads = re.findall(r"table<true>\((?:tokens|len|states), b\)", src)
+    places = re.findall(r"int ((?:\w+ = table<true>\((?:tokens|len|states), b\)(?:, )?)+);((?:\n *keep_input\(\w+\);)*)", src)
+    for read, kept in places:
+        assert re.findall(r"(\w+) = table", read) == re.findall(r"keep_input\((\w+)\)", kept), read
+    assert sum(kept.count("keep_input") for _, kept in places) == len(reads) == 5
