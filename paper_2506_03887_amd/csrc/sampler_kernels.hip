@@ -1008,29 +1008,51 @@ size_t masked_topk_workspace_bytes(int batch, int vocab) {
     return (size_t)batch * masked_topk_chunks(vocab) * kTopkMax * sizeof(unsigned long long);
 }
 
+// Groups of eight logits per thread of the blocks that a row is cut into (4: the narrow block, 16,384 tokens; else the wide
+// one).  A row that fits the registers of a block is one block's, the smallest that holds it (128,256 tokens, k = 50: 8.0 us
+// for one row, 10.7 for 64, 15.4 for 256, against 9.9 and 14.1 us for 1 and 64 rows in segments of 16,384 tokens and a second
+// launch).  Beyond sixteen groups that depends (us, one block of twenty groups and the other form):
+//   * rows on 16-byte boundaries: from four rows on, and below seven eighths of the twenty groups, where it is even (64 x 152,064
+//     11.8 and 12.6, 200 14.5 and 21.7, 512 31.8 and 42.0, 16 on a schema 11.1 and 11.9; but 1 x 152,064 10.5 and 9.9, 2 x 156,000
+//     11.0 and 10.2, 3 x 163,840 10.8 and 10.4);
+//   * other rows, whose loads a block gets through more slowly: only where two blocks a row are more than one round of the chip
+//     (160,003 tokens: 200 rows 20.8 and 28.3, 300 38.0 and 39.9; but 128 19.8 and 17.8, 32 18.3 and 16.1, and, against segments,
+//     16 17.8 and 12.4, 2 16.9 and 10.9).
+// A longer row is cut into wide blocks unless the batch is too small to fill the chip with them (at the line, 31 rows
+// of 200,000 tokens take 13.8 to 14.4 us in segments of 16,384 and 13.7 in blocks), of twenty groups where those come to
+// fewer rounds (280,000 tokens: 128 rows 19.4 us, 27.3 in blocks of sixteen; 256 33.5 and 40.6; but 500,000 x 32 15.9 and 14.3,
+// 400,000 x 64 16.3 and 15.4).
+int masked_topk_groups(int vocab, int batch, bool aligned, int n_compute_units) {
+    constexpr int kPerGroup = 8 * kTopkBlockWide;
+    if (vocab <= kTopkChunk) return 4;
+    for (int g : {8, 12, 16})
+        if (vocab <= g * kPerGroup) return g;
+    if (vocab <= kTopkRowTokens && aligned && (batch > 3 || vocab < kTopkRowTokens / 8 * 7)) return 20;
+    if (batch * 8 < n_compute_units) return 4;
+    const int shorter = vocab <= 24 * kPerGroup ? 12 : 16;
+    auto rounds = [&](int g) { return (batch * masked_topk_chunks(vocab, g * kPerGroup) + n_compute_units - 1) / n_compute_units; };
+    return rounds(20) < rounds(shorter) ? 20 : shorter;
+}
+
 hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,
                               int k, int n_compute_units, unsigned long long *workspace, int32_t *out_ids,
                               uint16_t *out_vals, hipStream_t stream) {
     if (batch == 0) return hipSuccess;
     if (!masked_topk_fits(vocab, k)) return hipErrorInvalidValue;
     const int n_words = (vocab + 31) / 32;
-    // A row that fits the registers of a block is one block's, whatever the batch (128,256 tokens, k = 50: 8.0 us for one
-    // row, 10.7 for 64, 15.4 for 256, against 9.9 and 14.1 us for 1 and 64 rows in segments of 16,384 tokens and a second
-    // launch; 152,064 tokens: 14.5 us for 200 rows, 31.8 for 512 on a schema, against 21.7 and 42.0 in two blocks a row and a
-    // second launch; 11.1 for 16 rows against 11.9 in segments of 16,384, 10.6 for one against 10.0); the block and its
-    // groups per thread are the smallest that hold it.  A longer row is cut into such blocks of 98,304, 131,072 or 163,840
-    // tokens unless the batch is too small to fill the chip with them (at the line, 31 rows of 200,000 tokens take 13.8 to
-    // 14.4 us in segments of 16,384 and 13.7 in blocks).
+    const bool aligned = (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && (row_stride & 7) == 0;
 #define PRE3_TOPK_ROW(BLOCK, GROUPS)                                                                                         \
     n_seg = masked_topk_chunks(vocab, BLOCK * GROUPS * 8);                                                                   \
     hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, vocab, \
                        row_stride, n_words, k, workspace, out_ids, out_vals)
     int n_seg = 1;
-    if (vocab <= kTopkChunk || (vocab > kTopkRowTokens && batch * 8 < n_compute_units)) { PRE3_TOPK_ROW(kTopkBlock, 4); }
-    else if (vocab <= kTopkRowTokens / 20 * 8) { PRE3_TOPK_ROW(kTopkBlockWide, 8); }
-    else if (vocab <= kTopkRowTokens / 20 * 12 || (vocab > kTopkRowTokens && vocab <= kTopkRowTokens / 20 * 24)) { PRE3_TOPK_ROW(kTopkBlockWide, 12); }
-    else if (vocab <= kTopkRowTokens / 20 * 16 || (vocab > kTopkRowTokens && vocab <= kTopkRowTokens / 20 * 32)) { PRE3_TOPK_ROW(kTopkBlockWide, 16); }
-    else { PRE3_TOPK_ROW(kTopkBlockWide, 20); }
+    switch (masked_topk_groups(vocab, batch, aligned, n_compute_units)) {
+        case 4: PRE3_TOPK_ROW(kTopkBlock, 4); break;
+        case 8: PRE3_TOPK_ROW(kTopkBlockWide, 8); break;
+        case 12: PRE3_TOPK_ROW(kTopkBlockWide, 12); break;
+        case 16: PRE3_TOPK_ROW(kTopkBlockWide, 16); break;
+        default: PRE3_TOPK_ROW(kTopkBlockWide, 20);
+    }
 #undef PRE3_TOPK_ROW
     if (n_seg > 1)
         hipLaunchKernelGGL(masked_topk_finish_kernel, dim3(batch), dim3(kTopkFinishBlock), 0, stream, workspace, n_seg * k, k, logits,

@@ -91,7 +91,7 @@ def test_sampled_rows_at_every_offset(V, B, pad, offset):
                                  (16_384, 17), (16_385, 17), (65_535, 256), (65_536, 17), (65_537, 17), (98_305, 17),
                                  (131_072, 256), (131_073, 17), (131_079, 48), (147_460, 17), (196_608, 48), (196_611, 48)])
 def test_topk_of_rows_kept_in_registers(V, B):
-    """A block per row, or two (or segments of 16,384 tokens of 17 rows) beyond 131,072 tokens: rows with values of one sign only, few allowed tokens, hundreds of ties (the lists
+    """A block per row (from four rows on up to 163,840 tokens), or several: rows with values of one sign only, few allowed tokens, hundreds of ties (the lists
     of the kernel run full), zeros of both signs, infinities, allowed NaN of both signs, and nothing allowed."""
     from test_gpu_argmax import _bound_lib
     from oracle import masked_topk
@@ -133,7 +133,7 @@ def test_topk_of_rows_kept_in_registers(V, B):
 
 @pytest.mark.parametrize("V,B", [(131_080, 300), (147_457, 4), (163_839, 40), (163_840, 4), (163_841, 17), (163_848, 48), (262_147, 33)])
 def test_topk_of_rows_at_the_longest_variant(V, B):
-    """One block per row up to 163,840 tokens at any batch, several blocks beyond."""
+    """One block of twenty groups per row (an aligned row, four rows or more), or several blocks."""
     test_topk_of_rows_kept_in_registers(V, B)
 
 
