@@ -275,8 +275,9 @@ int pre3_advance_fill_apply_mask(pre3_handle *h, const int32_t *tokens, uint32_t
  * chosen), and is the two calls otherwise; flags as there.  Batches of more rows than compute units, on
  * rows of at least 61,440 tokens, are one launch of that kernel with two rows to a unit: up to two rows
  * per unit, beyond on rows of at least 122,880 tokens (any length the mask row's LDS allows; 320 x
- * 128,256: 24.0 against 29.2 us per step).  Unless asked for, the one kernel also takes rows of more than 76,800
- * tokens that start at any logit, where the rows are not spread over blocks.
+ * 128,256: 24.0 against 29.2 us per step).  Unless asked for, the one kernel also takes rows of 76,808
+ * tokens and more that start at any logit, where the rows are not spread over blocks (beyond 130,567 tokens
+ * from a third of the compute units on).
  * Errors: BADARG (nothing bound, null pointer, unknown flag, row_stride < n_tokens, logits not
  * 2-byte aligned), HIP. */
 int pre3_advance_fill_argmax(pre3_handle *h, const int32_t *tokens, uint32_t *bitmask, const uint16_t *logits_bf16,

@@ -1457,7 +1457,10 @@ bool greedy_two_rows_fit(int n_tokens, int n_words, int cap, bool cycles) {
     return cycles ? cap <= kCompactMaxLen && row_bytes + (size_t)cap * sizeof(int32_t) <= kAfDynamicLdsMax : row_bytes <= kAfDynamicLdsMax;
 }
 
-bool greedy_any_offset_row(int n_tokens) { return (n_tokens >> 3) > 10 * kStepData; }
+bool greedy_any_offset_rows(int n_tokens, int batch, int n_compute_units) {
+    const int groups = n_tokens >> 3;
+    return groups > 10 * kStepData && (groups <= 17 * kStepData || 3 * batch >= n_compute_units);
+}
 
 bool greedy_two_rows_long_row(int n_tokens) { return (n_tokens >> 3) >= 2 * kStepHeldTwoRows * kStepData; }
 

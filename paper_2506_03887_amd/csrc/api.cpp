@@ -693,13 +693,16 @@ StepForm step_form(const pre3_handle *h, const uint16_t *logits_bf16, int64_t ro
     if (!asked && greedy && greedy_two_rows(h, logits_bf16, row_stride)) return StepForm::kTwoRowsPerUnit;
     const int blocks = asked ? 0 : spread_step_blocks(h, batch);
     // The greedy form only reads the logits and takes rows at any offset, but slower: there it stands in for the two calls
-    // where the spread form does not serve, on rows of more than 76,800 tokens (us per step, two calls and one kernel:
+    // where the spread form does not serve, on rows of 76,808 tokens and more (us per step, two calls and one kernel:
     // JSON 100 x 100,003 20.4 and 17.1, 200 x 128,257 27.4 and 19.2, 200 x 150,001 29.3 and 21.4, eight schemas
-    // 256 x 128,257 26.0 and 20.5, one schema 100 x 100,003 18.9 and 17.1; JSON 128 x 70,001 16.9 and 16.5; where the spread form
-    // serves, JSON 70 x 100,003, it takes 13.3 and the one kernel 16.7).  Asked for, it is kept to aligned rows.
+    // 256 x 128,257 26.0 and 20.5, one schema 100 x 100,003 18.9 and 17.1, 65 x 128,257 18.2 and 17.5; JSON 128 x 70,001 16.9 and 16.5;
+    // where the spread form serves, JSON 70 x 100,003, it takes 13.3 and the one kernel 16.7).  Beyond 130,567 tokens its
+    // largest variant takes 20 us whatever the batch: from a third of the units on (one schema 64 x 150,001 16.6 and 20.0, 80 x
+    // 140,001 19.3 and 20.1, 85 x 150,001 18.9 and 20.1, 90 20.9 and 20.4; JSON 17.5 and 20.0, 21.3 and 20.2, 20.5 and 20.2, 23.7 and
+    // 20.4).  Asked for, it is kept to aligned rows.
     const bool any_offset = greedy && !aligned_rows(logits_bf16, row_stride);
     const bool one_kernel = (asked || step_kernel_batch(h, batch)) && one_kernel_serves(h, logits_bf16, row_stride, greedy) &&
-                            !(any_offset && (asked || blocks > 0 || !greedy_any_offset_row(h->V.n_tokens)));
+                            !(any_offset && (asked || blocks > 0 || !greedy_any_offset_rows(h->V.n_tokens, batch, h->n_compute_units)));
     if (blocks > 0 && !one_kernel) return StepForm::kSpread;
     // Where the one kernel serves the batch too, the spread form is only taken while it has few blocks, since each of them
     // advances the sequence for itself.  Rows that the one kernel holds in few registers: up to three blocks per unit

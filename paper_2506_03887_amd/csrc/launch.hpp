@@ -75,7 +75,8 @@ bool advance_fill_apply_fits(int n_tokens, int n_words, int cap, bool cycles, bo
 // greedy_two_rows_fit: rows of at least what its blocks hold in registers (61,440 tokens), mask row and staged stack in LDS.
 constexpr int kRowsTwoPerUnit = -1;
 bool greedy_two_rows_fit(int n_tokens, int n_words, int cap, bool cycles);
-bool greedy_any_offset_row(int n_tokens);               // rows the greedy form takes at any offset: more than 76,800 tokens
+// rows the greedy form takes at any offset: from 76,808 tokens on, beyond 130,567 (its largest variant) from a third of the units on
+bool greedy_any_offset_rows(int n_tokens, int batch, int n_compute_units);
 bool greedy_two_rows_long_row(int n_tokens);            // at least twice that
 bool advance_fill_apply_short_row(int n_tokens);        // rows of its smallest variant (69,120 tokens)
 // The same kernel without the advance: mask rows of the stacks as they are, applied to the logits
