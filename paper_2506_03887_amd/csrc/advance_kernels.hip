@@ -260,10 +260,7 @@ __device__ __forceinline__ Advanced advance_stack(const DevTables &T, const DevT
                                                   const int32_t *states, const int32_t *len, int cap, int restart_on_eos,
                                                   WaveStack &ws, int b, int lane, Meet meet) {
     const int32_t *row = ws.row;
-    int t = table<true>(tokens, b), n = table<true>(len, b), st = table<true>(states, b);
-    keep_input(t);
-    keep_input(n);
-    keep_input(st);
+    const int t = table<true>(tokens, b), n = table<true>(len, b), st = table<true>(states, b);
     const bool shape_ok = n >= 1 && n <= cap;
     const bool live = t >= 0 && t < T.n_tokens && st >= 0 && shape_ok;
     // one round: the stack window, the token's line, and -- states[b] names the stack's top -- that state's kind and the root
@@ -1238,9 +1235,8 @@ __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
     }
     if (b >= batch) return;
     int32_t *row = data + (size_t)b * cap;
-    int n = table<true>(len, b), st = table<true>(states, b);
-    keep_input(n);
-    keep_input(st);
+    int n = table<true>(len, b);
+    const int st = table<true>(states, b);
     int count = 0;
     if (st >= 0 && n >= 1 && n <= cap && max_bytes > 0) {
         // the stack's top and what a forced byte's walk pushes, in the wave's registers; the lanes' own walks of byte classes

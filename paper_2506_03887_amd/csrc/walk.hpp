@@ -38,8 +38,8 @@ __device__ __forceinline__ void lds_barrier() {
 
 // Every load that the source has before this point has returned, none of those behind it has begun: what the loads
 // read may be overwritten by whoever learns that this point was passed.  (A relaxed atomic alone orders nothing, and
-// lds_barrier leaves global loads free to move.  Loads through the constant address space pass this asm as well: inputs that
-// are read that way are kept by keep_input, which no use behind it can pass.)
+// lds_barrier leaves global loads free to move.  Scalar loads through the constant address space are ordered by their use
+// alone: tests/test_kernel_code.py follows those of tokens, len and states through the compiled spread step.)
 __device__ __forceinline__ void loads_returned() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Private stack of one walk: the states pushed above the part of the sequence's stack that
@@ -96,8 +96,10 @@ enum FeedResult { kFed = 0, kRejected = 1, kOverflow = 2, kAccepted = 3 };
 // constant address space, which lets the compiler use scalar loads served by the scalar cache
 // (a chain of dependent look-ups then costs a fraction of the vector-memory latency).  The
 // tables are never written by a kernel, so the scalar cache cannot hold stale data; to the compiler such a load may move
-// past any store, or be repeated.  tokens, states and len are read this way too, before the launch's first store to them:
-// where it overwrites them, keep_input holds what was read.
+// past any store or fence, or be repeated.  tokens, states and len, which a launch overwrites, are read this way too, once
+// and before any store of it: the stores depend on all three.  Where another block of the launch does the storing (the spread
+// step) that they have returned before this block counts itself in, and are not read again, is checked in the compiled code; to
+// force it with an asm that holds the values costs 1 to 2 % of a step there (1 x 128,256 6.83 to 7.00 us).
 template <typename V>
 using ConstPtr = const __attribute__((address_space(4))) V *;
 
@@ -125,11 +127,6 @@ __device__ __forceinline__ int4 table(const int4 *p, int i) {
     }
     return p[i];
 }
-// An input that was read through the constant address space and that this launch overwrites: from here on its value is in a
-// register, so the load has returned and is not repeated.  (Measured in the spread step, the last block of which overwrites what
-// the others read: 1 x 128,256 6.95 against 6.92 us, 64 x 32,000 8.58 and 8.50, greedy 16 x 128,256 10.69 and 10.66.)
-__device__ __forceinline__ void keep_input(int32_t &v) { asm volatile("" : "+s"(v)); }
-
 template <bool kUniform>
 __device__ __forceinline__ int uni(int v) {
     return kUniform ? __builtin_amdgcn_readfirstlane(v) : v;

@@ -12,8 +12,8 @@ OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """name -> instructions, in the order of the code."""
+def listing(tmp_path_factory):
+    """name -> (address, instruction, address it branches to or None), in the order of the code."""
     from paper_2506_03887_amd.binding import LIB_PATH
     at = tmp_path_factory.mktemp("code")
     shutil.copy(LIB_PATH, at / "lib.so")
@@ -23,14 +23,24 @@ def kernels(tmp_path_factory):
         text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", f], check=True, capture_output=True, text=True).stdout
         name = None
         for line in text.splitlines():
-            m = re.match(r"^[0-9a-f]+ <(\S+)>:", line)
+            m = re.match(r"^([0-9a-f]+) <(\S+)>:", line)
             if m:
-                name = m.group(1)
+                begin, name = int(m.group(1), 16), m.group(2)
                 out[name] = []
-            elif name and line.strip():
-                out[name].append(line.split("//")[0].strip())
+                continue
+            # instruction // address: code words <kernel+0xoffset of a branch's target>
+            m = re.match(r"^\s+(\S.*?)\s*// ([0-9A-F]+):[ 0-9A-F]*(?:<[^+>]+(?:\+0x([0-9a-f]+))?>)?$", line)
+            if name and m:
+                target = begin + int(m.group(3) or "0", 16) if "<" in line else None
+                out[name].append((int(m.group(2), 16), m.group(1), target))
     assert out
     return out
+
+
+@pytest.fixture(scope="module")
+def kernels(listing):
+    """name -> instructions, in the order of the code."""
+    return {name: [text for _, text, _ in code] for name, code in listing.items()}
 
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
@@ -48,14 +58,127 @@ def test_a_block_of_the_spread_step_counts_itself_in_when_its_loads_have_returne
         assert all(x.startswith("s_cbranch_execz") for x in between), (name, between)     # straight code, lanes switched off at most
 
 
-def test_inputs_that_a_launch_overwrites_are_kept_where_they_are_read():
-    """Loads through the constant address space may be moved behind a store or repeated after it, and no fence or wait orders
-    them: every place that reads tokens, states or len that way in a kernel that writes them keeps the value at once."""
-    src = open(os.path.join(os.path.dirname(__file__), "..", "paper_2506_03887_amd", "csrc", "advance_kernels.hip")).read()
-    plan_only = src[src.index("void plan_only_scalar"):]
-    src = src.replace(plan_only[: plan_only.index("\n}\n")], "")          # mask + masking: writes none of them
-    reads = re.findall(r"table<true>\((?:tokens|len|states), b\)", src)
-    places = re.findall(r"int ((?:\w+ = table<true>\((?:tokens|len|states), b\)(?:, )?)+);((?:\n *keep_input\(\w+\);)*)", src)
-    for read, kept in places:
-        assert re.findall(r"(\w+) = table", read) == re.findall(r"keep_input\((\w+)\)", kept), read
-    assert sum(kept.count("keep_input") for _, kept in places) == len(reads) == 5
+def _registers(operand):
+    """The registers an operand names: s3, v[4:7], vcc, ..."""
+    m = re.match(r"^[-|]*([sva])\[(\d+):(\d+)\]|^[-|]*([sva])(\d+)\b", operand)
+    if not m:
+        return ["vcc"] if operand.startswith("vcc") else []
+    if m.group(1):
+        return [m.group(1) + str(i) for i in range(int(m.group(2)), int(m.group(3)) + 1)]
+    return [m.group(4) + m.group(5)]
+
+
+class _Inputs:
+    """Which registers (and lanes that spilled scalars sit in) hold addresses of tokens, len or states -- the first 24 bytes of the
+    arguments, in s[2:7] when the kernel starts --, and which of their loads are still out, at every instruction of a kernel:
+    a forward data flow over its branches, joined by union.  Addresses are moved, spilled and added to; other arithmetic on
+    what may hold one makes none."""
+    ADDRESS = re.compile(r"s_mov_b(32|64)|s_addc?_u32|s_cselect_b(32|64)|v_mov_b(32|64)|v_lshl_add_u64|v_addc?_co_u32|v_cndmask|v_read|s_or_b32|v_or_b32")
+    NO_RESULT = re.compile(r"(s_cmp|s_bitcmp|s_cbranch|s_branch|s_waitcnt|s_barrier|s_nop|s_endpgm|s_setprio|s_sleep|global_store|flat_store|"
+                           r"buffer_store|ds_write|s_dcache|buffer_|v_cmpx)")
+
+    def __init__(self, code):
+        self.code, self.at = code, {address: i for i, (address, _, _) in enumerate(code)}
+        self.seen = [None] * len(code)
+        self.loads = set()
+        self.run(0, frozenset("s%d" % i for i in range(2, 8)))
+
+    def run(self, start, state):
+        todo = [(start, state)]
+        while todo:
+            i, state = todo.pop()
+            if self.seen[i] is not None:
+                if state <= self.seen[i]:
+                    continue
+                state |= self.seen[i]
+            self.seen[i] = state
+            out = self.step(i, state)
+            todo += [(n, out) for n in self.follow(i)]
+
+    def follow(self, i):
+        _, text, target = self.code[i]
+        if text.startswith("s_endpgm"):
+            return []
+        assert not re.match(r"s_(setpc|swappc|call)", text), text
+        next_ = [] if text.startswith("s_branch") else [i + 1]
+        return next_ + ([self.at[target]] if re.match(r"s_c?branch", text) else [])
+
+    def step(self, i, state):
+        text = self.code[i][1]
+        name, _, rest = text.partition(" ")
+        ops = [o.strip() for o in rest.split(",")]
+        if name == "s_waitcnt":
+            return frozenset(x for x in state if not ((x == "scalar out" and "lgkmcnt(0)" in text) or (x == "vector out" and "vmcnt(0)" in text)))
+        if self.NO_RESULT.match(name) or not rest:
+            return state
+        results = 2 if re.match(r"v_\w+_co_\w+|v_div_scale|v_mad_[iu]64", name) else 1                  # (a carry)
+        made, used = [r for o in ops[:results] for r in _registers(o)], [r for o in ops[results:] for r in _registers(o)]
+        if name == "v_writelane_b32":
+            slot = "%s.%s" % (ops[0], ops[2])
+            return state | {slot} if made and _registers(ops[1])[:1] and _registers(ops[1])[0] in state else state - {slot}
+        if name == "v_readlane_b32" and ops[2].isdigit():
+            tainted = "%s.%s" % (ops[1], ops[2]) in state
+            return state | set(made) if tainted else state - set(made)
+        if re.match(r"(s_|s_buffer_|global_|flat_|buffer_|scratch_|ds_)(load|read)", name):
+            state -= set(made)
+            if name.startswith("s_load") and _registers(ops[1]) == ["s0", "s1"] and i < self.entry():
+                first = int(ops[2].split()[0], 16)                          # the arguments themselves
+                return state | {r for k, r in enumerate(made) if first + 4 * k < 24}
+            if any(r in self.seen[i] for r in used):
+                self.loads.add(i)
+                return state | {"scalar out" if name.startswith("s_") else "vector out"}
+            return state
+        if re.match(r"(global|flat|buffer)_", name):                            # an atomic
+            return state - set(made) if "sc0" in text else state
+        address = self.ADDRESS.match(name) and any(r in state for r in used)
+        return state | set(made) if address else state - set(made)
+
+    def entry(self):
+        """Up to here s[0:1] is the address of the arguments: its first change."""
+        if not hasattr(self, "_entry"):
+            changes = [i for i, (_, t, _) in enumerate(self.code) if not self.NO_RESULT.match(t) and
+                       set(_registers(t.partition(" ")[2].split(",")[0].strip())) & {"s0", "s1"}]
+            self._entry = min(changes, default=len(self.code))
+        return self._entry
+
+    def reachable(self, i):
+        out, todo = set(), list(self.follow(i))
+        while todo:
+            n = todo.pop()
+            if n not in out:
+                out.add(n)
+                todo += self.follow(n)
+        return out
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+def test_a_block_of_the_spread_step_has_read_its_inputs_when_it_counts_itself_in(listing):
+    """tokens, len and states come through scalar loads, which no fence orders, and the last block overwrites them: each is
+    loaded once, has returned before the count (the first atomic that returns a value), and is not loaded behind it."""
+    found = {n: code for n, code in listing.items() if "step_spread_kernel" in n}
+    assert len(found) == 4
+    for name, code in found.items():
+        flow = _Inputs(code)
+        count = next(i for i, (_, x, _) in enumerate(code) if re.match(r"global_atomic_add\b.*\bsc0\b", x))
+        assert flow.seen[count] is not None and len(flow.loads) == 3, (name, [code[i] for i in flow.loads])
+        assert not flow.seen[count] & {"scalar out", "vector out"}, name
+        assert not flow.loads & flow.reachable(count), name
+
+
+def test_the_flow_of_input_addresses_sees_a_late_load():
+    """The analysis on a few lines: an address spilled to a lane and used behind the count, and a load not waited for."""
+    def flow(*lines):
+        code = [(4 * i, x, None) for i, x in enumerate(lines)]
+        branches = [(4 * i, x, 4 * int(x.split()[1])) if x.startswith("s_cbranch") else (4 * i, x, None) for i, x in enumerate(lines)]
+        return _Inputs(branches if any(b[2] for b in branches) else code)
+    early = ("s_add_u32 s8, s2, s12", "s_addc_u32 s9, s3, s13", "s_load_dword s20, s[8:9], 0x0", "s_waitcnt lgkmcnt(0)")
+    count = "global_atomic_add v1, v2, v3, s[10:11] sc0"
+    f = flow(*early, count, "s_endpgm")
+    assert f.loads == {2} and "scalar out" not in f.seen[4]
+    assert "scalar out" in flow(*early[:3], count, "s_endpgm").seen[3]
+    f = flow("v_writelane_b32 v9, s6, 1", "s_mov_b32 s6, 0", "v_writelane_b32 v9, s7, 2", count, "v_readlane_b32 s30, v9, 1",
+             "v_readlane_b32 s31, v9, 2", "s_load_dword s20, s[30:31], 0x0", "s_endpgm")
+    assert f.loads == {6} and 6 in f.reachable(3)
+    f = flow("s_cbranch_scc1 3", "s_mov_b64 s[4:5], 0", "s_nop 0", "s_load_dword s20, s[4:5], 0x0", "s_endpgm")     # tainted on one way
+    assert f.loads == {3}
+    assert flow("s_mov_b64 s[4:5], 0", "s_load_dword s20, s[4:5], 0x0", "s_endpgm").loads == set()
