@@ -1402,7 +1402,7 @@ size_t advance_fill_walk_spill_entries(int batch, int max_depth) {
     return (size_t)batch * 64 * (size_t)deep;
 }
 
-hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states,
+hipError_t launch_advance_fill(const DevTables &T, const int32_t *tokens, int32_t *states,
                                int32_t *data, int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask,
                                int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
                                const int32_t *cycle_head, const int32_t *cycle_pool, int n_compute_units, hipStream_t stream) {
@@ -1463,7 +1463,7 @@ bool greedy_two_rows_long_row(int n_tokens) { return (n_tokens >> 3) >= 2 * kSte
 bool advance_fill_apply_short_row(int n_tokens) { return (n_tokens >> 3) <= kStepHeldShort * kStepData; }
 
 template <bool kCompact, bool kArgmax>
-static void launch_step_variant(int held, dim3 grid, size_t lds, hipStream_t stream, const DevTables &T, const DevTokenEdges &E,
+static void launch_step_variant(int held, dim3 grid, size_t lds, hipStream_t stream, const DevTables &T,
                                 const int32_t *tokens, int32_t *states, int32_t *data, int32_t *len, int cap, int batch,
                                 int32_t *err, uint32_t *bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
                                 const int32_t *cycle_head, const int32_t *cycle_pool, int stage, uint16_t *logits,
@@ -1491,7 +1491,7 @@ static int step_rows_per_launch(int batch, int rows_per_launch) {
     return (batch + launches - 1) / launches;
 }
 
-hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states,
+hipError_t launch_advance_fill_apply(const DevTables &T, const int32_t *tokens, int32_t *states,
                                      int32_t *data, int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask,
                                      int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
                                      const int32_t *cycle_head, const int32_t *cycle_pool, uint16_t *logits,
@@ -1515,7 +1515,7 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E,
     }
     // the greedy fold reads a mask byte for every group slot of a lane, also those past the row's end
     if (out_tokens && !two_rows && lds < (size_t)held_variant * kStepData + 16) lds = (size_t)held_variant * kStepData + 16;
-#define PRE3_STEP_ARGS held, dim3(rows), lds, stream, T, E, tokens, states, data, len, cap, batch, err, bitmask, restart_on_eos, \
+#define PRE3_STEP_ARGS held, dim3(rows), lds, stream, T, tokens, states, data, len, cap, batch, err, bitmask, restart_on_eos, \
                        adv_scratch, walk_spill, cycle_head, cycle_pool, stage, logits, row_stride, out_tokens, first
     const int share = two_rows ? batch : step_rows_per_launch(batch, rows_per_launch);
     for (int first = 0; first < batch; first += share) {
@@ -1532,7 +1532,7 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E,
     return hipGetLastError();
 }
 
-hipError_t launch_fill_apply_rows(const DevTables &T, const DevTokenEdges &E, const int32_t *states, const int32_t *data,
+hipError_t launch_fill_apply_rows(const DevTables &T, const int32_t *states, const int32_t *data,
                                   const int32_t *len, int cap, int batch, uint32_t *bitmask, int32_t *walk_spill,
                                   uint16_t *logits, int64_t row_stride, int rows_per_launch, hipStream_t stream) {
     if (batch == 0) return hipSuccess;
@@ -1544,7 +1544,7 @@ hipError_t launch_fill_apply_rows(const DevTables &T, const DevTokenEdges &E, co
     const int share = step_rows_per_launch(batch, rows_per_launch);
     // no tokens: the kernel only reads the states and the stacks
     for (int first = 0; first < batch; first += share)
-        launch_step_variant<false, false>(held, dim3(batch - first < share ? batch - first : share), lds, stream, T, E, nullptr,
+        launch_step_variant<false, false>(held, dim3(batch - first < share ? batch - first : share), lds, stream, T, nullptr,
                                           const_cast<int32_t *>(states), const_cast<int32_t *>(data), const_cast<int32_t *>(len),
                                           cap, batch, nullptr, bitmask, 0, nullptr, walk_spill, nullptr, nullptr, 0, logits,
                                           row_stride, nullptr, first);
@@ -1592,7 +1592,7 @@ bool advance_fits_compact(int cap) {
     return cap <= kCompactMaxLen && (size_t)kAdvSeqPerBlock * cap * sizeof(int32_t) + 4096 <= 65536;
 }
 
-hipError_t launch_advance(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states, int32_t *data,
+hipError_t launch_advance(const DevTables &T, const int32_t *tokens, int32_t *states, int32_t *data,
                           int32_t *len, int cap, int batch, int32_t *err, int32_t *scratch, int restart_on_eos,
                           const int32_t *cycle_head, const int32_t *cycle_pool, hipStream_t stream) {
     if (batch == 0) return hipSuccess;

@@ -335,9 +335,6 @@ bool step_kernel_batch(const pre3_handle *h, int batch) {
     return batch * 4 >= h->n_compute_units && batch <= h->n_compute_units;
 }
 
-// The token-level edges for pre3_advance: only their stack-effect records are used there.
-DevTokenEdges effect_edges(const pre3_handle *h) { return h->use_edges ? h->dev_edges : DevTokenEdges{}; }
-
 // After a call that changed the bound stacks: take complete traversals of reduction cycles out
 // again (only with PRE3_FLAG_COMPACT_CYCLES and a grammar that has such cycles).
 hipError_t compact_stacks(pre3_handle *h, const pre3_stacks &st, hipStream_t s) {
@@ -547,7 +544,7 @@ int pre3_fill_mask(pre3_handle *h, const int32_t *states, pre3_stacks stacks, ui
         return fail(h, PRE3_E_BADARG, "fill_mask: null buffer, negative batch or cap outside 1..stack_cap");
     hipError_t e =
         h->use_edges
-            ? launch_fill_mask_edges(h->dev, h->dev_edges, states, stacks.data, stacks.len, stacks.cap, stacks.batch,
+            ? launch_fill_mask_edges(h->dev, states, stacks.data, stacks.len, stacks.cap, stacks.batch,
                                      bitmask, nullptr, 0, h->edge_spill, h->edge_blocks, fill_mask_blocks(h, h->edge_blocks),
                                      static_cast<hipStream_t>(stream))
             : launch_fill_mask_walk(h->dev, states, stacks.data, stacks.len, stacks.cap, stacks.batch, bitmask,
@@ -569,7 +566,7 @@ int pre3_fill_apply_mask(pre3_handle *h, const int32_t *states, pre3_stacks stac
     // looked up) runs through it, without the advance; its walks spill into the workspace of the bound batch.
     if (fused && h->af_walk_spill && stacks.batch <= h->b_stacks.batch && step_kernel_batch(h, stacks.batch) &&
         advance_fill_apply_fits(h->V.n_tokens, h->V.n_words, stacks.cap, false, false)) {
-        hipError_t e = launch_fill_apply_rows(h->dev, h->dev_edges, states, stacks.data, stacks.len, stacks.cap, stacks.batch,
+        hipError_t e = launch_fill_apply_rows(h->dev, states, stacks.data, stacks.len, stacks.cap, stacks.batch,
                                               bitmask, h->af_walk_spill, logits, row_stride, h->n_compute_units, s);
         return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch fill_apply_mask");
     }
@@ -577,7 +574,7 @@ int pre3_fill_apply_mask(pre3_handle *h, const int32_t *states, pre3_stacks stac
     // below one sequence per compute unit; beyond, its few hundred blocks stream the logits more slowly than the flat
     // grid of the masking kernel (66.3 against 49.4 us at 512 x 128,256, 78.6 against 51.9 us at 512 x 152,064).
     if (fused && stacks.batch <= h->n_compute_units) {
-        hipError_t e = launch_fill_mask_edges(h->dev, h->dev_edges, states, stacks.data, stacks.len, stacks.cap,
+        hipError_t e = launch_fill_mask_edges(h->dev, states, stacks.data, stacks.len, stacks.cap,
                                               stacks.batch, bitmask, logits, row_stride, h->edge_spill, h->edge_blocks, h->edge_blocks, s);
         return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch fill_apply_mask");
     }
@@ -603,7 +600,7 @@ int pre3_advance(pre3_handle *h, const int32_t *tokens, pre3_stream stream) {
     if (!tokens) return fail(h, PRE3_E_BADARG, "advance: null tokens");
     // cycle-aware stacks: compacted inside the kernel when four staged stacks fit its LDS, else by a kernel of its own
     const bool fused = h->compact && h->T.n_cycles > 0 && advance_fits_compact(h->b_stacks.cap);
-    hipError_t e = launch_advance(h->dev, effect_edges(h), tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,
+    hipError_t e = launch_advance(h->dev, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,
                                   h->b_stacks.batch, h->b_err, h->adv_scratch, 0, fused ? h->cycle_head : nullptr,
                                   fused ? h->cycle_pool : nullptr, static_cast<hipStream_t>(stream));
     if (e == hipSuccess && !fused) e = compact_bound_stacks(h, static_cast<hipStream_t>(stream));
@@ -627,7 +624,7 @@ int pre3_advance_static(pre3_handle *h, const int32_t *tokens, int32_t *states, 
     if (e != hipSuccess) return hip_fail(h, e, "advance_static: address of the static scratch");
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool fused = h->compact && h->T.n_cycles > 0 && advance_fits_compact(stacks.cap);
-    e = launch_advance(h->dev, effect_edges(h), tokens, states, stacks.data, stacks.len, stacks.cap, stacks.batch, err, scratch, 0,
+    e = launch_advance(h->dev, tokens, states, stacks.data, stacks.len, stacks.cap, stacks.batch, err, scratch, 0,
                        fused ? h->cycle_head : nullptr, fused ? h->cycle_pool : nullptr, s);
     if (e == hipSuccess && !fused) e = compact_stacks(h, stacks, s);
     return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_static");
@@ -648,13 +645,13 @@ int pre3_advance_fill_mask(pre3_handle *h, const int32_t *tokens, uint32_t *bitm
     // next to the mask row, the call takes the three launches below.
     const bool cycles = h->compact && h->T.n_cycles > 0;
     if (h->use_edges && (!cycles || advance_fill_fits_compact(h->V.n_words, h->b_stacks.cap))) {
-        e = launch_advance_fill(h->dev, h->dev_edges, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len,
+        e = launch_advance_fill(h->dev, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len,
                                 h->b_stacks.cap, h->b_stacks.batch, h->b_err, bitmask, restart, h->adv_scratch,
                                 h->af_walk_spill, cycles ? h->cycle_head : nullptr, cycles ? h->cycle_pool : nullptr,
                                 h->n_compute_units, s);
         return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch advance_fill_mask");
     }
-    e = launch_advance(h->dev, effect_edges(h), tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,
+    e = launch_advance(h->dev, tokens, h->b_states, h->b_stacks.data, h->b_stacks.len, h->b_stacks.cap,
                        h->b_stacks.batch, h->b_err, h->adv_scratch, restart, nullptr, nullptr, s);
     if (e == hipSuccess) e = compact_bound_stacks(h, s);
     if (e != hipSuccess) return hip_fail(h, e, "launch advance");
@@ -729,7 +726,7 @@ hipError_t launch_step(pre3_handle *h, StepForm form, const int32_t *tokens, uin
     if (form == StepForm::kSpread)
         return launch_step_spread(h->dev, h->dev_edges, tokens, h->b_states, st.data, st.len, st.cap, st.batch, h->b_err, bitmask, restart,
                                   h->adv_scratch, h->af_walk_spill, head, pool, logits_bf16, row_stride, out_tokens, h->arrivals, s);
-    return launch_advance_fill_apply(h->dev, h->dev_edges, tokens, h->b_states, st.data, st.len, st.cap, st.batch, h->b_err, bitmask,
+    return launch_advance_fill_apply(h->dev, tokens, h->b_states, st.data, st.len, st.cap, st.batch, h->b_err, bitmask,
                                      restart, h->adv_scratch, h->af_walk_spill, head, pool, logits_bf16, row_stride, out_tokens,
                                      form == StepForm::kTwoRowsPerUnit ? kRowsTwoPerUnit : h->n_compute_units, s);
 }

@@ -10,6 +10,9 @@
 
 namespace pre3 {
 
+// Kernels that read the tables from device memory take T.pack, which holds the token-level edges as well (all null where the
+// handle has none); the others get what they need by value.
+
 int walk_grid_blocks(int n_compute_units);
 size_t walk_spill_entries(int grid_blocks, int max_depth);          // int32 entries
 size_t advance_scratch_entries(int batch, int max_depth);           // int32 entries
@@ -22,7 +25,7 @@ size_t edge_spill_entries(int grid_blocks, int max_depth);          // int32 ent
 int edge_row_stride_words(int n_words);                             // stride of dense rows on the device
 size_t edge_kernel_max_lds_words();                                 // largest bitmap row the kernel can hold
 int edge_row_segments(int n_words, int batch, int want_blocks);     // blocks per row of a launch of about want_blocks
-hipError_t launch_fill_mask_edges(const DevTables &T, const DevTokenEdges &E, const int32_t *states,
+hipError_t launch_fill_mask_edges(const DevTables &T, const int32_t *states,
                                   const int32_t *data, const int32_t *len, int cap, int batch, uint32_t *bitmask,
                                   uint16_t *logits /* null: mask only */, int64_t row_stride, int32_t *spill,
                                   int grid_blocks, int want_blocks, hipStream_t stream);
@@ -31,9 +34,8 @@ hipError_t launch_timestamp(int64_t *out, hipStream_t stream);
 
 hipError_t launch_apply_mask(uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,
                              hipStream_t stream);
-// cycle_head / cycle_pool: the cycle tables for cycle-aware stacks (needs advance_fits_compact(cap)), or null;
-// E: the token-level edges, whose stack-effect records apply longer tokens in one step (E.fx_slots null: every token is walked)
-hipError_t launch_advance(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states, int32_t *data,
+// cycle_head / cycle_pool: the cycle tables for cycle-aware stacks (needs advance_fits_compact(cap)), or null
+hipError_t launch_advance(const DevTables &T, const int32_t *tokens, int32_t *states, int32_t *data,
                           int32_t *len, int cap, int batch, int32_t *err, int32_t *scratch, int restart_on_eos,
                           const int32_t *cycle_head, const int32_t *cycle_pool, hipStream_t stream);
 bool advance_fits_compact(int cap);                     // four staged stacks within the kernel's LDS
@@ -57,7 +59,7 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
 size_t advance_fill_walk_spill_entries(int batch, int max_depth);   // int32 entries
 // cycle_head / cycle_pool: the cycle tables for cycle-aware stacks (the call then needs
 // advance_fill_fits_compact), or null.
-hipError_t launch_advance_fill(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states,
+hipError_t launch_advance_fill(const DevTables &T, const int32_t *tokens, int32_t *states,
                                int32_t *data, int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask,
                                int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
                                const int32_t *cycle_head, const int32_t *cycle_pool, int n_compute_units, hipStream_t stream);
@@ -81,10 +83,10 @@ bool greedy_two_rows_long_row(int n_tokens);            // at least twice that
 bool advance_fill_apply_short_row(int n_tokens);        // rows of its smallest variant (69,120 tokens)
 // The same kernel without the advance: mask rows of the stacks as they are, applied to the logits
 // (walk_spill: advance_fill_walk_spill_entries(batch, ...) entries; same conditions on the logits).
-hipError_t launch_fill_apply_rows(const DevTables &T, const DevTokenEdges &E, const int32_t *states, const int32_t *data,
+hipError_t launch_fill_apply_rows(const DevTables &T, const int32_t *states, const int32_t *data,
                                   const int32_t *len, int cap, int batch, uint32_t *bitmask, int32_t *walk_spill,
                                   uint16_t *logits, int64_t row_stride, int rows_per_launch, hipStream_t stream);
-hipError_t launch_advance_fill_apply(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states,
+hipError_t launch_advance_fill_apply(const DevTables &T, const int32_t *tokens, int32_t *states,
                                      int32_t *data, int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask,
                                      int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
                                      const int32_t *cycle_head, const int32_t *cycle_pool, uint16_t *logits,

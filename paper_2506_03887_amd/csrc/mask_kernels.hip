@@ -210,7 +210,7 @@ int edge_row_segments(int n_words, int batch, int want_blocks) {
     return (n_vec + seg_vec - 1) / seg_vec;
 }
 
-hipError_t launch_fill_mask_edges(const DevTables &T, const DevTokenEdges &E, const int32_t *states,
+hipError_t launch_fill_mask_edges(const DevTables &T, const int32_t *states,
                                   const int32_t *data, const int32_t *len, int cap, int batch, uint32_t *bitmask,
                                   uint16_t *logits, int64_t row_stride, int32_t *spill, int grid_blocks, int want_blocks,
                                   hipStream_t stream) {

@@ -4,6 +4,9 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "device_tables.hpp"
 #include "symbol_edges.hpp"
 #include "tables.hpp"
@@ -138,6 +141,14 @@ __device__ __forceinline__ int uni(int v) {
 // whose arguments do not all arrive preloaded, waits for the others anyway and takes the tables by value (1 x 128,256: 57.5
 // against 58.5 us).  (A pointer that is itself loaded is generic to the compiler, and its accesses flat; the casts say
 // that all of them are global.)
+struct AnyField { template <class F> operator F() const; };
+template <class S, class Fields, class = void> struct TakesFields : std::false_type {};
+template <class S, size_t... I>
+struct TakesFields<S, std::index_sequence<I...>, std::void_t<decltype(S{((void)I, AnyField{})...})>> : std::true_type {};
+template <class S, size_t kN>
+constexpr bool kHasFields = TakesFields<S, std::make_index_sequence<kN>>::value && !TakesFields<S, std::make_index_sequence<kN + 1>>::value;
+static_assert(kHasFields<DevTables, 32> && kHasFields<DevTokenEdges, 11>, "a field that load_tables does not read would stay undefined in most kernels");
+
 __device__ __forceinline__ void load_tables(const DevPack *pack, DevTables &T, DevTokenEdges &E) {
     const ConstPtr<DevPack> from = (ConstPtr<DevPack>)pack;
 #define PRE3_PTR(f) f = (decltype(f))(const __attribute__((address_space(1))) void *)from->f
