@@ -38,9 +38,17 @@ def _newest_header() -> float:
 
 def build(verbose: bool = False, incremental: bool = False) -> str:
     """Compiles every source to an object (in parallel) and links the shared library.  With
-    `incremental` an object newer than its source and every header is kept."""
+    `incremental` an object newer than its source and every header, and built with the same flags, is kept."""
     os.makedirs(OBJ, exist_ok=True)
     newest_h = _newest_header()
+    built_with = os.path.join(OBJ, "flags")              # of the objects that lie there
+    flags = " ".join(FLAGS)
+    if os.path.exists(built_with):
+        with open(built_with) as f:
+            incremental = incremental and f.read() == flags
+        os.remove(built_with)                            # until all of them are built
+    else:
+        incremental = False
     jobs = []
     for s in SOURCES:
         src, obj = os.path.join(CSRC, s), os.path.join(OBJ, s + ".o")
@@ -49,6 +57,8 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
             jobs.append(["hipcc", *FLAGS, "-c", "-o", obj, src])
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
         notes = list(pool.map(_run, jobs))
+    with open(built_with, "w") as f:
+        f.write(flags)
     notes.append(_run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-pthread", "-o", LIB,
                        *[os.path.join(OBJ, s + ".o") for s in SOURCES]]))
     if verbose:
