@@ -12,9 +12,11 @@ LIB = os.path.join(HERE, "libpre3.so")
 SOURCES = ["grammar.cpp", "lr1.cpp", "tables.cpp", "token_edges.cpp", "symbol_edges.cpp", "api.cpp",
            "mask_kernels.hip", "apply_kernels.hip", "sampler_kernels.hip", "advance_kernels.hip"]
 # The first 14 words of a kernel's arguments arrive in scalar registers with the launch, where they are plain pointers and
-# sizes (tables passed as structs end the sequence, so kernels take them last): a kernel's first loads do not wait for
-# its arguments.  Bursts of 8 steps: fill, mask and advance of 96 x 100,003 as three calls 173.8 -> 168.0 us, jump-forward
-# with 128 x 128,256 208.9 -> 202.5, 2,048 x 128,256 1,464 -> 1,446.
+# sizes (a struct ends the sequence: kernels that take the tables by value take them behind these): what reads an input or
+# the tables' copy in device memory does not wait for the argument segment first.  (jump-forward asks for its inputs at
+# once; the advancing kernels and the mask kernel still ask for the table pointers before.)  Bursts of 8 steps: fill, mask
+# and advance of 96 x 100,003 as three calls 173.8 -> 168.0 us, jump-forward with 128 x 128,256 208.9 -> 202.5,
+# 2,048 x 128,256 1,464 -> 1,446.
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-pthread",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-mllvm", "-amdgpu-kernarg-preload-count=14"]

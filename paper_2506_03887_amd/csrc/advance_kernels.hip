@@ -252,9 +252,12 @@ struct Advanced {
 // The launches that wait for it are bound by this chain of dependent look-ups, and what a link costs is as much its
 // instructions as its load.  The window, the token's bytes and the pushed states are in registers instead of LDS (one lane
 // read looks at an entry), a child's record comes out of its lane with lane reads instead of permutes, and the token's
-// line and the state's kind are in the round of loads that fetches the window: bursts of 8 steps of 64 x 32,000 in a graph
+// line and the state's kind do not wait for the stack's top: bursts of 8 steps of 64 x 32,000 in a graph
 // 76.8 -> 68.6 us, 1 x 128,256 57.9 -> 54.2, fill + mask + advance of 96 x 100,003 168 -> 158, advance + fill before a top-k
 // of 256 x 128,256 187 -> 181, greedy steps of 320 x 128,256 with cycle-aware stacks 265 -> 255.
+// (These first loads depend on the inputs alone, but each stands behind a condition whose other side is a default, and the
+// compiler waits where the two meet: inputs; kind and root; window and line are three rounds in the kernels with vector
+// loads, five in the spread step.)
 template <bool kScalar, class Meet>
 __device__ __forceinline__ Advanced advance_stack(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens,
                                                   const int32_t *states, const int32_t *len, int cap, int restart_on_eos,
@@ -263,8 +266,8 @@ __device__ __forceinline__ Advanced advance_stack(const DevTables &T, const DevT
     const int t = table<true>(tokens, b), n = table<true>(len, b), st = table<true>(states, b);
     const bool shape_ok = n >= 1 && n <= cap;
     const bool live = t >= 0 && t < T.n_tokens && st >= 0 && shape_ok;
-    // one round: the stack window, the token's line, and -- states[b] names the stack's top -- that state's kind and the root
-    // of its condition tree, from which the look-up of the token's stack operations starts
+    // what depends on the inputs alone: the stack window, the token's line, and -- states[b] names the stack's top -- that state's
+    // kind and the root of its condition tree, from which the look-up of the token's stack operations starts
     int fx_root = -1, kind = 0;
     DevConditionNode fx_nd{};
     int32_t line = 0;
@@ -957,10 +960,10 @@ struct NewStack {
 // NaN pattern) compares its own groups as numbers first: 1 x 128,256 with zeros on top 15.6 us per step, 71 when
 // the last block did that for the whole row.
 // A launch is bound by the chain of dependent loads of the advance (about 5 us) where the two-launch form pays for a
-// second launch and for reading the mask row back.  us per step inside a graph, against the form used before: 1 x 128,256
-// 7.6 (9.0), 16 x 128,256 9.1 (11.4), 60 x 128,256 12.2 (15.7), 4 x 513 8.3 (9.9), 64 x 32,000 9.4 (11.6); greedy
-// 1 x 128,256 9.7 (13.1), 16 x 128,256 11.5 (15.2).  Four groups per lane and 256 lanes: with eight groups 8.2 and 10.0 us
-// at 1 and 16 x 128,256, with 512 lanes 7.8 and 9.6; with the advance through scalar loads (as in the kernel above,
+// second launch and for reading the mask row back.  us per step inside a graph, against the two calls: 1 x 128,256
+// 6.8 (8.9), 16 x 128,256 8.2 (10.5), 60 x 128,256 11.2 (14.6), 4 x 513 7.3 (10.3), 64 x 32,000 8.6 (10.6); greedy
+// 1 x 128,256 9.1 (13.6), 16 x 128,256 10.6 (14.3).  Four groups per lane and 256 lanes: when 1 and 16 x 128,256 took 7.6 and
+// 9.1 us, eight groups took 8.2 and 10.0, 512 lanes 7.8 and 9.6, and the advance through scalar loads (as in the kernel above,
 // where vector loads wait behind a whole row's) 8.8 and 10.5.
 constexpr int kSpreadLanes = 256, kSpreadBlock = kSpreadLanes + 64, kSpreadHeld = 4;
 constexpr int kSpreadGroups = kSpreadLanes * kSpreadHeld;
@@ -1392,6 +1395,8 @@ hipError_t static_advance_scratch(int32_t **out) {
     return hipSuccess;
 }
 
+// (The header states this size, and pre3_advance_static refuses batches by it.  Since the stack of an advance lies in the
+// wave's registers its pushed states spill from the 65th on, so the last 48 of the columns' entries stay untouched.)
 size_t advance_scratch_entries(int batch, int max_depth) {
     const int deep = max_depth > kLdsDepth ? max_depth - kLdsDepth : 0;
     return (size_t)batch * (size_t)deep;

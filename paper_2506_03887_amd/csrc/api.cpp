@@ -669,11 +669,15 @@ bool one_kernel_serves(const pre3_handle *h, const uint16_t *logits_bf16, int64_
     return h->use_edges && (greedy || aligned_rows(logits_bf16, row_stride)) && row_stride >= h->V.n_tokens && advance_fill_apply_fits(h->V.n_tokens, h->V.n_words, h->b_stacks.cap, cycles, greedy);
 }
 
-// Whether the greedy step runs with two rows to a compute unit: batches of more rows than units, of rows that a block cannot
-// hold (61,440 tokens).  Up to two rows per unit it wins on every workload (see the kernel); beyond, where blocks of a
-// second round start as others end, on rows of at least 122,880 tokens (us per step, two launches and this form: JSON
-// 600 x 152,064 46.0 and 42.2, 1,500 x 128,256 77.7 and 71.1, schema 600 x 122,880 32.6 and 31.3, 520 x 128,256 31.2 and 31.9;
-// but schema 1,024 x 110,000 42.4 and 44.0, 600 x 100,000 29.6 and 32.0, JSON 2,048 x 70,000 66.0 and 67.9).
+// Whether the greedy step runs with two rows to a compute unit: batches of more rows than units, of rows that fill what a block
+// holds (61,440 tokens and more).  Up to two rows per unit it wins on every workload (see the kernel; schema 512 x 64,000 20.1
+// and 19.2 us per step in two launches and in this form is the least); beyond, where blocks of a
+// second round start as others end, on rows of at least 122,880 tokens (JSON
+// 600 x 152,064 46.0 and 42.2, 1,500 x 128,256 77.7 and 71.1, schema 600 x 122,880 33.8 and 31.6;
+// but schema 1,024 x 110,000 42.4 and 44.0, 600 x 100,000 29.6 and 32.0, JSON 2,048 x 70,000 66.0 and 67.9).  The first batches
+// beyond two rows per unit are even at 128,256 tokens -- 520 rows: schema 32.0 and 33.2, eight schemas 34.6 and 32.9, JSON 38.8 and 37.9;
+// from 560 rows on a schema is no slower -- and win on either side of it (schema 520 x 122,880 30.9 and 30.1, 520 x 152,064 36.8 and
+// 34.7, JSON 38.3 and 34.4, 44.0 and 40.1).
 bool greedy_two_rows(const pre3_handle *h, const uint16_t *logits_bf16, int64_t row_stride) {
     const bool cycles = h->compact && h->T.n_cycles > 0;
     const int batch = h->b_stacks.batch, units = h->n_compute_units;
@@ -703,13 +707,12 @@ StepForm step_form(const pre3_handle *h, const uint16_t *logits_bf16, int64_t ro
     if (blocks > 0 && !one_kernel) return StepForm::kSpread;
     // Where the one kernel serves the batch too, the spread form is only taken while it has few blocks, since each of them
     // advances the sequence for itself.  Rows that the one kernel holds in few registers: up to three blocks per unit
-    // (us per step, spread and one kernel, eight schemas: 128 x 64,000 11.9 and 10.9, 170 x 48,000 12.1 and 10.6,
-    // 256 x 32,000 11.8 and 11.2, but 96 x 64,000 10.9 and 10.5, 100 x 48,000 10.4 and 10.5; JSON 12.6 and 12.7, 12.5 and 12.4,
-    // 12.6 and 13.2, 11.1 and 12.2, 10.7 and 11.5); longer rows as above (102 x 80,000 11.7 and 11.9, 64 x 128,256 11.5
+    // (us per step, spread and one kernel, eight schemas: 128 x 64,000 11.0 and 10.8, 170 x 48,000 11.4 and 10.5,
+    // 256 x 32,000 11.0 and 10.7, but 96 x 64,000 10.0 and 10.3, 100 x 48,000 9.6 and 10.1; JSON 11.6 and 12.2, 11.5 and 11.9,
+    // 11.5 and 12.5, 10.3 and 11.6, 9.8 and 11.1); longer rows as above (102 x 80,000 11.0 and 11.7, 64 x 128,256 10.7
     // and 12.5).  The greedy step, whose blocks then meet through atomics to choose the token: up to one block per unit and
-    // half a row per unit (eight schemas: 64 x 128,256 14.0 and 11.9, 96 x 64,000 13.1 and 10.5, 96 x 24,000 11.2 and
-    // 10.5, but 64 x 32,000 11.0 and 10.7, 127 x 16,000 10.9 and 10.9; JSON 14.8 and 13.3, 13.8 and 12.1, 11.6 and 11.4, 11.9
-    // and 12.5, 11.6 and 12.0).
+    // half a row per unit (eight schemas: 64 x 128,256 13.4 and 11.9, 96 x 64,000 12.1 and 10.4, but 64 x 32,000 10.3 and 10.5;
+    // JSON 13.8 and 13.0, 12.6 and 11.8, 10.8 and 12.1).
     const bool spread = blocks > 0 && (greedy ? blocks <= h->n_compute_units && 2 * batch < h->n_compute_units
                                               : blocks <= 3 * h->n_compute_units || !advance_fill_apply_short_row(h->V.n_tokens));
     if (spread) return StepForm::kSpread;

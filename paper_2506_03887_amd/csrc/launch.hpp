@@ -79,7 +79,7 @@ constexpr int kRowsTwoPerUnit = -1;
 bool greedy_two_rows_fit(int n_tokens, int n_words, int cap, bool cycles);
 // rows the greedy form takes at any offset: from 76,808 tokens on, beyond 130,567 (its largest variant) from a third of the units on
 bool greedy_any_offset_rows(int n_tokens, int batch, int n_compute_units);
-bool greedy_two_rows_long_row(int n_tokens);            // at least twice that
+bool greedy_two_rows_long_row(int n_tokens);            // rows of at least 122,880 tokens, twice what its blocks hold
 bool advance_fill_apply_short_row(int n_tokens);        // rows of its smallest variant (69,120 tokens)
 // The same kernel without the advance: mask rows of the stacks as they are, applied to the logits
 // (walk_spill: advance_fill_walk_spill_entries(batch, ...) entries; same conditions on the logits).

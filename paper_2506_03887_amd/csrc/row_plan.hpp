@@ -30,7 +30,7 @@ __device__ __forceinline__ int entry_below_top(int32_t win, int k, Deeper deeper
 }
 
 // Descent of the condition tree of the token-level edges, run by all 64 lanes of one wave with
-// identical values.  `win[k]` (LDS) is the stack entry k below the top for k < kWindow, deeper(k)
+// identical values.  Lane k's `win` is the stack entry k below the top for k < kWindow, deeper(k)
 // any entry below that; `n` the stack length; `nd` the root record of the top state.  Each node
 // names the entry it tests; lane j fetches condition state j TOGETHER with child j's record
 // (children are stored consecutively), so one round of loads both verifies all of the node's
