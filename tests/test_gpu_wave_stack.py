@@ -75,6 +75,49 @@ def test_tokens_deeper_than_the_registers(call, options):
     assert lib.fault_count() == 0
 
 
+@pytest.mark.parametrize("options", [{}, dict(compact_cycles=True)])
+@pytest.mark.parametrize("call", ["one_kernel", "greedy_one_kernel", "step"])
+def test_effect_records_of_every_length(call, options):
+    """Tokens whose stack-effect records push 6 to 143 states: the lists come 16 words at a time where the advance keeps to
+    scalar loads (the one-kernel forms), as one vector load elsewhere, and in parts of 64."""
+    import torch
+    from paper_2506_03887_amd import Pre3
+    dev = torch.device("cuda:0")
+    base = bpe_like_vocab(2000, 8, BASE_SEED + 95).tokens[:-1]
+    new = [b"[" * n + tail for n in range(2, 71) for tail in (b"", b"1,")]
+    v = Vocab(base + new + [b""], len(base) + len(new))
+    cycles = "compact_cycles" in options
+    text = G.JSON_RIGHT_RECURSIVE if cycles else G.JSON
+    o, cap, B = Oracle(text, compact_cycles=cycles), 256, len(new)
+    lib = Pre3(text, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, stack_cap=cap, **options)
+    start = o.initial_stack(0)
+    pushes = {lib.debug_token_effect(start, len(base) + i)[3] for i in range(B) if lib.debug_token_effect(start, len(base) + i)}
+    assert pushes >= {*range(6, 70)} and max(pushes) > 128
+    data, length = np.zeros((B, cap), np.int32), np.full(B, len(start), np.int32)
+    data[:, : len(start)] = start
+    states, tokens = data[:, len(start) - 1].copy(), np.arange(len(base), len(base) + B, dtype=np.int32)
+    s_d, d_d, l_d, t_d = (torch.from_numpy(x.copy()).to(dev) for x in (states, data, length, tokens))
+    e_d, next_d = torch.full((B,), -5, dtype=torch.int32, device=dev), torch.full((B,), -7, dtype=torch.int32, device=dev)
+    lib.bind_state(s_d, d_d, l_d, e_d)
+    mask = torch.zeros((B, v.words), dtype=torch.int32, device=dev)
+    x = bf16_logits(np.random.default_rng(6), B, -(-v.n_tokens // 8) * 8)
+    x_d = torch.from_numpy(x.view(np.int16).copy()).to(dev)
+    if call == "greedy_one_kernel":
+        lib.advance_fill_argmax(t_d, mask, x_d.view(torch.bfloat16), next_d, one_kernel=True)
+    else:
+        lib.advance_fill_apply_mask(t_d, mask, x_d, one_kernel=call == "one_kernel")
+    err = o.advance_batch(states, data, length, tokens, v)
+    want = o.fill_mask(states, data, length, v)
+    assert (err == 0).all() and (e_d.cpu().numpy() == 0).all()
+    assert (s_d.cpu().numpy() == states).all() and (l_d.cpu().numpy() == length).all()
+    live = np.arange(cap)[None, :] < length[:, None]
+    assert (d_d.cpu().numpy()[live] == data[live]).all()
+    assert (mask.cpu().numpy().view(np.uint32) == want).all()
+    if call == "greedy_one_kernel":
+        assert (next_d.cpu().numpy() == oracle_masked_argmax(x, want, v.n_tokens)).all()
+    assert lib.fault_count() == 0
+
+
 @pytest.mark.parametrize("empties", [62, 63, 64, 65, 70])
 def test_forced_bytes_deeper_than_the_registers(empties):
     """One forced byte pushes `empties` states of empty nonterminals, another pops them again, and as many closing brackets as
