@@ -55,43 +55,38 @@ __device__ __forceinline__ int32_t deal_to_lanes(int32_t w, const NativeInt16 &v
     }
 }
 
-// fetch_token_line through the scalar cache: the line comes as two 16-word loads, whose words are dealt out to the lanes.
-__device__ __forceinline__ int32_t fetch_token_line_scalar(const DevTables &T, int t) {
-    const int32_t *rec = T.tok_info + (size_t)t * 32;
-    const NativeInt16 a = scalar_load16(rec), b = scalar_load16(rec + 16);
+// The words of a token's line, in two scalar loads' registers, dealt out to the lanes as fetch_token_line has them.
+__device__ __forceinline__ int32_t deal_token_line(const NativeInt16 &a, const NativeInt16 &b) {
     int32_t w = 0;
     w = deal_to_lanes<0, 1, 15>(w, a);
     w = deal_to_lanes<15, 0, 16>(w, b);
     return deal_to_lanes<31, 0, 1>(w, a);
 }
 
-// The top 64 entries of a stack (lane k: entry k below the top, -1 beyond the bottom) through the scalar
-// cache: four 16-entry loads that end at the top -- each moved to where it lies wholly inside the row's
-// cap entries, cap >= 16 --, dealt out to the lanes and put in order with one lane permute.
-__device__ __forceinline__ int32_t fetch_window_scalar(const int32_t *row, int n, int cap, bool shape_ok, int lane) {
-    if (!shape_ok) return -1;
-    int32_t w = 0;
-    int my_lo = 0;                                      // first entry of the chunk that holds this lane's entry
-    auto chunk_begin = [&](int c) {
-        int lo = n - 16 * (c + 1);
-        lo = lo < 0 ? 0 : lo;
-        return lo > cap - 16 ? cap - 16 : lo;
-    };
+// The top 64 entries of a stack of 1 <= n <= cap entries (lane k: entry k below the top, -1 beyond the bottom) through
+// the scalar cache: four 16-entry loads that end at the top -- each moved to where it lies wholly inside the row's
+// cap entries, cap >= 16 --, dealt out to the lanes and put in order with one lane permute.  The first load is the
+// caller's (`first`, at window_chunk(n, cap, 0)): it stands with the other loads that depend on the inputs alone.
+__device__ __forceinline__ int window_chunk(int n, int cap, int c) {
+    int lo = n - 16 * (c + 1);
+    lo = lo < 0 ? 0 : lo;
+    return lo > cap - 16 ? cap - 16 : lo;
+}
+__device__ __forceinline__ int32_t deal_window(const int32_t *row, const NativeInt16 &first, int n, int cap, int lane) {
+    int32_t w = deal_to_lanes<0, 0, 16>(0, first);
+    int my_lo = window_chunk(n, cap, 0);                // first entry of the chunk that holds this lane's entry
     // one chunk at a time, and only the chunks the stack reaches (few scalar registers live; the later loads
     // find their cache lines where the first one brought them)
-    const int lo0 = chunk_begin(0);
-    w = deal_to_lanes<0, 0, 16>(w, scalar_load16(row + lo0));
-    my_lo = lo0;
     if (n > 16) {
-        const int lo1 = chunk_begin(1);
+        const int lo1 = window_chunk(n, cap, 1);
         w = deal_to_lanes<16, 0, 16>(w, scalar_load16(row + lo1));
         if (lane >= 16) my_lo = lo1;
         if (n > 32) {
-            const int lo2 = chunk_begin(2);
+            const int lo2 = window_chunk(n, cap, 2);
             w = deal_to_lanes<32, 0, 16>(w, scalar_load16(row + lo2));
             if (lane >= 32) my_lo = lo2;
             if (n > 48) {
-                const int lo3 = chunk_begin(3);
+                const int lo3 = window_chunk(n, cap, 3);
                 w = deal_to_lanes<48, 0, 16>(w, scalar_load16(row + lo3));
                 if (lane >= 48) my_lo = lo3;
             }
@@ -262,6 +257,15 @@ struct Advanced {
     bool shape_ok, restarted;
 };
 
+// What a launch advances from: the sampled token, the stack's length, its top state.  The first loads of a kernel, or of its
+// branch that advances (the waves that fetch logits do not wait for them: greedy 256 x 128,256 127.9 us, 131.6 when they did).
+struct StepInputs { int t, n, st; };
+__device__ __forceinline__ StepInputs read_inputs(const int32_t *tokens, const int32_t *len, const int32_t *states, int b) {
+    const StepInputs in{table<true>(tokens, b), table<true>(len, b), table<true>(states, b)};
+    __builtin_amdgcn_sched_barrier(0);
+    return in;
+}
+
 // Walks one sequence's sampled token on its stack (or applies the token's stack-effect record): the work of one
 // wave, all 64 lanes with identical values, the stack in the wave's registers (ws).  Only a walk that succeeds changes the
 // stack; nothing is stored: commit_advance does that.  `meet` is called once, when the inputs' loads are under way.
@@ -271,32 +275,60 @@ struct Advanced {
 // line and the state's kind do not wait for the stack's top: bursts of 8 steps of 64 x 32,000 in a graph
 // 76.8 -> 68.6 us, 1 x 128,256 57.9 -> 54.2, fill + mask + advance of 96 x 100,003 168 -> 158, advance + fill before a top-k
 // of 256 x 128,256 187 -> 181, greedy steps of 320 x 128,256 with cycle-aware stacks 265 -> 255.
-// (These first loads depend on the inputs alone, but each stands behind a condition whose other side is a default, and the
-// compiler waits where the two meet: inputs; kind and root; window and line are three rounds in the kernels with vector
-// loads, five in the spread step.)
+// With vector loads the chain begins with two rounds, the inputs with the tables' pointers, then all that depends on the inputs
+// alone.  Behind a condition each of these loads was a round of its own wherever the compiler waited at the condition's end (three
+// rounds, five in the spread step): 1 x 128,256 54.2 -> 52.8 us, 64 x 32,000 67.9 -> 67.1, fill + mask + advance of 96 x 100,003
+// 153.1 -> 151.4, advance + fill before a top-k of 256 x 128,256 179.4 -> 178.2.  The wave that keeps to scalar loads is not held
+// to that order: it has not the registers for all of them at once (greedy 320 x 128,256, cycle-aware, 202.4 us and 203.7 held to it).
 template <bool kScalar, class Meet>
-__device__ __forceinline__ Advanced advance_stack(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens,
-                                                  const int32_t *states, const int32_t *len, int cap, int restart_on_eos,
-                                                  WaveStack &ws, int b, int lane, Meet meet) {
+__device__ __forceinline__ Advanced advance_stack(const DevTables &T, const DevTokenEdges &E, const StepInputs &in, int cap,
+                                                  int restart_on_eos, WaveStack &ws, int lane, Meet meet) {
     const int32_t *row = ws.row;
-    const int t = table<true>(tokens, b), n = table<true>(len, b), st = table<true>(states, b);
+    const int t = in.t, n = in.n, st = in.st;
+    if (!kScalar) {
+        // (the asm statements here and below: the loads of what they name are issued before this point and waited for together)
+        asm volatile("" :: "s"(t), "s"(n), "s"(st), "s"(T.n_tokens), "s"(T.n_states), "s"(T.eos_id), "s"(T.ncol), "s"(T.state_kind),
+                     "s"(T.tok_info), "s"(T.sym_nodes), "s"(T.sym_cell), "s"(E.root_id), "s"(E.root_nodes), "s"(E.fx_slots),
+                     "s"(E.nodes), "s"(E.child_state), "s"(E.fx_mask), "s"(E.fx_min_len));
+        __builtin_amdgcn_sched_barrier(0);
+    }
     const bool shape_ok = n >= 1 && n <= cap;
     const bool live = t >= 0 && t < T.n_tokens && st >= 0 && shape_ok;
-    // what depends on the inputs alone: the stack window, the token's line, and -- states[b] names the stack's top -- that state's
-    // kind and the root of its condition tree, from which the look-up of the token's stack operations starts
-    int fx_root = -1, kind = 0;
-    DevConditionNode fx_nd{};
-    int32_t line = 0;
-    if (live && (unsigned)st < (unsigned)T.n_states) {
-        if (T.state_kind) kind = table<true>(T.state_kind, st);
-        if (E.fx_slots && t != T.eos_id) {
-            fx_root = table<true>(E.root_id, st);
-            fx_nd = scalar_node(E.root_nodes + st);
+    // What depends on the inputs alone, one round of loads without a branch: the stack window, the token's line, and --
+    // states[b] names the stack's top -- that state's kind and the root of its condition tree, from which the look-up of the
+    // token's stack operations starts.  An input out of range, a table that was not built: the load is of something that is there
+    // (token 0, state 0, the bottom entry, the tables' own copy), and what it brings is not looked at.
+    const bool st_ok = (unsigned)st < (unsigned)T.n_states, look_up = live && st_ok && E.fx_slots && t != T.eos_id;
+    const int tc = (unsigned)t < (unsigned)T.n_tokens ? t : 0, sc = st_ok ? st : 0, nc = shape_ok ? n : 1;
+    const int32_t *spare = reinterpret_cast<const int32_t *>(T.pack);
+    const int32_t *kind_at = T.state_kind ? T.state_kind + sc : spare, *root_at = E.fx_slots ? E.root_id + sc : spare;
+    const DevConditionNode *nd_at = E.fx_slots ? E.root_nodes + sc : reinterpret_cast<const DevConditionNode *>(spare);
+    int kind = table<true>(kind_at, 0), fx_root = table<true>(root_at, 0);
+    const DevConditionNode fx_nd = scalar_node(nd_at);
+    int32_t line;
+    if (kScalar) {
+        const int32_t *rec = T.tok_info + (size_t)tc * 32;
+        const NativeInt16 line0 = scalar_load16(rec), line1 = scalar_load16(rec + 16);
+        if (cap >= 16) {
+            const NativeInt16 first = scalar_load16(row + window_chunk(nc, cap, 0));
+            line = deal_token_line(line0, line1);
+            ws.win = deal_window(row, first, nc, cap, lane);
+        } else {
+            line = deal_token_line(line0, line1);
+            ws.win = nc - 1 - lane >= 0 ? row[nc - 1 - lane] : -1;
         }
+    } else {
+        const int at = nc - 1 - lane;
+        const int32_t entry = row[at >= 0 ? at : 0];
+        line = fetch_token_line(T, tc, lane);
+        asm volatile("" :: "v"(entry), "v"(line), "s"(kind), "s"(fx_root), "s"(fx_nd.known), "s"(fx_nd.child_count), "s"(fx_nd.a),
+                     "s"(fx_nd.b));
+        __builtin_amdgcn_sched_barrier(0);
+        ws.win = at >= 0 ? entry : -1;
     }
-    if (kScalar && cap >= 16) ws.win = fetch_window_scalar(row, n, cap, shape_ok, lane);
-    else ws.win = (shape_ok && n - 1 - lane >= 0) ? row[n - 1 - lane] : -1;
-    if (live && t != T.eos_id) line = kScalar ? fetch_token_line_scalar(T, t) : fetch_token_line(T, t, lane);
+    if (!shape_ok) ws.win = -1;
+    if (!T.state_kind) kind = 0;
+    if (!look_up) fx_root = -1;
     ws.pushed = 0;
     ws.n = n;
     meet();
@@ -434,12 +466,13 @@ __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
     const int32_t *__restrict__ tokens, int32_t *__restrict__ len, int32_t *__restrict__ states,
     int32_t *__restrict__ data, int cap, int batch, const DevPack *pack, int32_t *__restrict__ err, int32_t *scratch,
     int restart_on_eos, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int b = blockIdx.x * kAdvSeqPerBlock + wave;
+    const StepInputs in = read_inputs(tokens, len, states, b < batch ? b : 0);
     DevTables T;
     DevTokenEdges E;
     load_tables(pack, T, E);
     extern __shared__ int32_t adv_stage[];             // kCompact: kAdvSeqPerBlock x (cap stack entries [+ cycle tables])
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int b = blockIdx.x * kAdvSeqPerBlock + wave;
     // kCompact with small cycle tables: the block copies them into LDS behind the staged stacks; every
     // wave passes exactly one block barrier (a wave without a sequence right here, the others once
     // their own input loads are under way)
@@ -455,7 +488,7 @@ __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
     }
     int32_t *row = data + (size_t)b * cap, *stack = adv_stage + wave * cap;
     WaveStack ws{row, scratch + b, (size_t)batch, 0, 0, 0};
-    Advanced r = advance_stack<false>(T, E, tokens, states, len, cap, restart_on_eos, ws, b, lane,
+    Advanced r = advance_stack<false>(T, E, in, cap, restart_on_eos, ws, lane,
                                       [&] { if (kCompact && stage_cycles) __syncthreads(); });
     if (kCompact && r.shape_ok) fold_new_stack(r, ws, stack, cycle_head, cycle_pool, T.n_states, lane);
     commit_advance<kCompact>(r, ws, stack, states, row, len, err, cap, b, lane);
@@ -469,11 +502,11 @@ __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
 // The tree is descended BEFORE anything is stored: a wave that has stores in flight waits for them wherever it next waits
 // for a load, and in the one-launch step kernel they complete only behind the row loads of the block's other waves.
 template <bool kCompact, bool kScalar = false>
-__device__ __forceinline__ Advanced advance_and_plan(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens,
-                                                 const int32_t *states, const int32_t *len, int cap, int restart_on_eos,
-                                                 WaveStack &ws, const int32_t *cycle_head, const int32_t *cycle_pool,
-                                                 int stage_cycles, int32_t *after_row, RowPlan &plan, int b, int lane) {
-    Advanced r = advance_stack<kScalar>(T, E, tokens, states, len, cap, restart_on_eos, ws, b, lane, [&] {
+__device__ __forceinline__ Advanced advance_and_plan(const DevTables &T, const DevTokenEdges &E, const StepInputs &in, int cap,
+                                                 int restart_on_eos, WaveStack &ws, const int32_t *cycle_head,
+                                                 const int32_t *cycle_pool, int stage_cycles, int32_t *after_row, RowPlan &plan,
+                                                 int lane) {
+    Advanced r = advance_stack<kScalar>(T, E, in, cap, restart_on_eos, ws, lane, [&] {
         if (kCompact && stage_cycles) {                 // the other waves have copied the cycle tables meanwhile
             __syncthreads();
             int32_t *cycle_lds = after_row + cap;
@@ -481,6 +514,8 @@ __device__ __forceinline__ Advanced advance_and_plan(const DevTables &T, const D
             cycle_pool = cycle_lds + T.n_states;
         }
     });
+    // the root of the new top's condition tree is under way while the new window is put together (taking cycles out keeps the top)
+    const DevConditionNode root = scalar_node(E.root_nodes + ((unsigned)r.out_state < (unsigned)T.n_states ? r.out_state : 0));
     int32_t win;                                        // the top of the new stack
     if (kCompact && r.shape_ok) {
         fold_new_stack(r, ws, after_row, cycle_head, cycle_pool, T.n_states, lane);
@@ -499,9 +534,9 @@ __device__ __forceinline__ Advanced advance_and_plan(const DevTables &T, const D
     } else if (!r.shape_ok || (unsigned)top >= (unsigned)T.n_states) {
         if (lane == 0) plan.mode = kRowEmpty;
     } else {
-        const DevConditionNode root = scalar_node(E.root_nodes + top);
-        if (kScalar) plan_row_scalar(E, root, win, r.nl, deeper, &plan, lane);
-        else plan_row(E, root, win, r.nl, deeper, &plan, lane);
+        const DevConditionNode nd = top == r.out_state ? root : scalar_node(E.root_nodes + top);    // (states[b] and the stack's top may differ)
+        if (kScalar) plan_row_scalar(E, nd, win, r.nl, deeper, &plan, lane);
+        else plan_row(E, nd, win, r.nl, deeper, &plan, lane);
     }
     if (lane == 0) { plan.top = top; plan.len = r.nl; }
     return r;
@@ -533,6 +568,7 @@ __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
     int32_t *__restrict__ data, int cap, int batch, const DevPack *pack, int32_t *__restrict__ err,
     uint32_t *__restrict__ bitmask, int restart_on_eos, int32_t *adv_scratch, int32_t *walk_spill,
     size_t walk_spill_stride, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles) {
+    const StepInputs in = read_inputs(tokens, len, states, blockIdx.x);
     DevTables T;
     DevTokenEdges E;
     load_tables(pack, T, E);
@@ -563,8 +599,8 @@ __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
     if (tid < 64) {
         WaveStack ws{row, adv_scratch + b, (size_t)batch, 0, 0, 0};
         int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
-        const Advanced r = advance_and_plan<kCompact>(T, E, tokens, states, len, cap, restart_on_eos, ws, cycle_head, cycle_pool,
-                                                      stage_cycles, after_row, plan, b, lane);
+        const Advanced r = advance_and_plan<kCompact>(T, E, in, cap, restart_on_eos, ws, cycle_head, cycle_pool,
+                                                      stage_cycles, after_row, plan, lane);
         commit_advance<kCompact>(r, ws, after_row, states, row, len, err, cap, b, lane);
     }
     __syncthreads();
@@ -581,14 +617,15 @@ __global__ __launch_bounds__(kThreads) void advance_fill_kernel(
 // The part of advance_and_plan that is left when there is no token: the top of the stack as it stands is
 // fetched and the condition tree descended with it, through scalar loads (the step kernel's
 // wave 0 when the kernel is asked for mask + masking only).
-__device__ __forceinline__ void plan_only_scalar(const DevTables &T, const DevTokenEdges &E, const int32_t *states,
-                                                 const int32_t *row, const int32_t *len, int cap, RowPlan &plan, int b, int lane) {
-    const int n = table<true>(len, b);
-    const int st = table<true>(states, b);
+__device__ __forceinline__ void plan_only_scalar(const DevTables &T, const DevTokenEdges &E, const StepInputs &in,
+                                                 const int32_t *row, int cap, RowPlan &plan, int lane) {
+    const int n = in.n, st = in.st;
     const bool shape_ok = n >= 1 && n <= cap;
-    int32_t win;
-    if (cap >= 16) win = fetch_window_scalar(row, n, cap, shape_ok, lane);
-    else win = (shape_ok && n - 1 - lane >= 0) ? row[n - 1 - lane] : -1;
+    int32_t win = -1;
+    if (shape_ok) {
+        if (cap >= 16) win = deal_window(row, scalar_load16(row + window_chunk(n, cap, 0)), n, cap, lane);
+        else if (n - 1 - lane >= 0) win = row[n - 1 - lane];
+    }
     const int top = __builtin_amdgcn_readlane(win, 0);
     if (st < 0) {
         if (lane == 0) plan.mode = kRowDone;
@@ -692,15 +729,16 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
     __shared__ uint2 s_expand[kArgmax ? 16 : 1];
     __shared__ unsigned long long s_part[kArgmax ? kStepBlock / 64 + 1 : 1];
 
-    if (tid < 64) {
+    if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
+        const StepInputs in = read_inputs(tokens ? tokens : len, len, states, b);
         if (tokens) {
             WaveStack ws{row, adv_scratch + b, (size_t)batch, 0, 0, 0};
             int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
-            const Advanced r = advance_and_plan<kCompact, true>(T, E, tokens, states, len, cap, restart_on_eos, ws, cycle_head,
-                                                                cycle_pool, stage_cycles, after_row, plan, b, lane);
+            const Advanced r = advance_and_plan<kCompact, true>(T, E, in, cap, restart_on_eos, ws, cycle_head, cycle_pool,
+                                                                stage_cycles, after_row, plan, lane);
             commit_advance<kCompact>(r, ws, after_row, states, row, len, err, cap, b, lane);
         } else
-            plan_only_scalar(T, E, states, row, len, cap, plan, b, lane);
+            plan_only_scalar(T, E, in, row, cap, plan, lane);
         // (barriers that order LDS only: this wave's stores of the new stack are still on their way, and
         // nothing in this block reads them before the launch ends -- except the walks below, which wait)
         lds_barrier();                                 // the plan is there
@@ -990,28 +1028,28 @@ constexpr int kSpreadGroups = kSpreadLanes * kSpreadHeld;
 template <bool kCompact, bool kArgmax>
 __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
     const int32_t *tokens, int32_t *len, int32_t *states, int32_t *data, int cap, int n_seg, uint16_t *__restrict__ logits,
-    int64_t row_stride, DevTables T, DevTokenEdges E, int32_t *__restrict__ err, uint32_t *__restrict__ bitmask, int restart_on_eos,
-    int32_t *adv_spill, int32_t *walk_spill, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
+    int64_t row_stride, size_t columns, DevTables T, DevTokenEdges E, int32_t *__restrict__ err, uint32_t *__restrict__ bitmask,
+    int restart_on_eos, int32_t *adv_spill, int32_t *walk_spill, const int32_t *cycle_head, const int32_t *cycle_pool, int stage_cycles,
     int32_t *out_tokens, StepArrivals *arrivals) {
+    const int b = blockIdx.y, seg = blockIdx.x, column = b * n_seg + seg;      // (columns: one spill column per block)
     extern __shared__ int32_t after_row[];             // kCompact: cap stack entries [+ cycle tables]
     __shared__ int32_t s_pushed[kWindow], s_walk_stack[kLdsDepth * 64];   // of an open row
     __shared__ uint32_t s_bits[kSpreadGroups / 4];     // an open row: this block's mask words
     __shared__ RowPlan plan;
     __shared__ unsigned long long s_part[kArgmax ? kSpreadBlock / 64 + 1 : 1];
     const int tid = threadIdx.x, lane = tid & 63, j = tid - 64;
-    const int b = blockIdx.x / n_seg, seg = blockIdx.x - b * n_seg;
     const int n_vec = (T.n_words + 3) >> 2, g0 = seg * kSpreadGroups;
     const int whole = T.n_tokens >> 3, tail = T.n_tokens & 7, groups = (T.n_tokens + 7) >> 3;
     int32_t *row = data + (size_t)b * cap;
     uint32_t *dst_row = bitmask + (size_t)b * T.n_words;
     uint16_t *lrow = logits + (size_t)b * row_stride;
     StepArrivals *mine = arrivals + b;
-    WaveStack ws{row, adv_spill + blockIdx.x, (size_t)gridDim.x, 0, 0, 0};
+    WaveStack ws{row, adv_spill + column, columns, 0, 0, 0};
     Advanced r{};
     uint4 held[kSpreadHeld];
-    if (tid < 64) {
-        r = advance_and_plan<kCompact>(T, E, tokens, states, len, cap, restart_on_eos, ws, cycle_head, cycle_pool, stage_cycles,
-                                       after_row, plan, b, lane);
+    if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
+        const StepInputs in = read_inputs(tokens, len, states, b);
+        r = advance_and_plan<kCompact>(T, E, in, cap, restart_on_eos, ws, cycle_head, cycle_pool, stage_cycles, after_row, plan, lane);
     } else {
 #pragma unroll
         for (int i = 0; i < kSpreadHeld; ++i) {
@@ -1053,8 +1091,8 @@ __global__ __launch_bounds__(kSpreadBlock) void step_spread_kernel(
             PrivateStack wp;
             wp.lds = s_walk_stack + lane;
             wp.lds_stride = 64;
-            wp.spill = walk_spill + (size_t)blockIdx.x * 64 + lane;
-            wp.spill_stride = (size_t)gridDim.x * 64;
+            wp.spill = walk_spill + (size_t)column * 64 + lane;
+            wp.spill_stride = columns * 64;
             const int n = plan.len, top0 = plan.top;
             const int t_lo = mode == kRowWalkAll ? w0 * 32 : 0;
             const int count = mode == kRowWalkAll ? min(T.n_tokens - t_lo, kSpreadGroups * 8) : plan.walk_count;
@@ -1594,9 +1632,9 @@ hipError_t launch_step_spread(const DevTables &T, const DevTokenEdges &E, const 
     }
     const int n_seg = step_spread_segments(T.n_tokens);
 #define PRE3_SPREAD(C, A)                                                                                                   \
-    hipLaunchKernelGGL((step_spread_kernel<C, A>), dim3(batch * n_seg), dim3(kSpreadBlock), lds, stream, tokens, len, states, data, cap, \
-                       n_seg, logits, row_stride, T, E, err, bitmask, restart_on_eos, adv_spill, walk_spill, cycle_head,        \
-                       cycle_pool, stage, out_tokens, arrivals)
+    hipLaunchKernelGGL((step_spread_kernel<C, A>), dim3(n_seg, batch), dim3(kSpreadBlock), lds, stream, tokens, len, states, data, cap, \
+                       n_seg, logits, row_stride, (size_t)batch * n_seg, T, E, err, bitmask, restart_on_eos, adv_spill, walk_spill,  \
+                       cycle_head, cycle_pool, stage, out_tokens, arrivals)
     if (cycle_head) {
         if (out_tokens) PRE3_SPREAD(true, true);
         else PRE3_SPREAD(true, false);
