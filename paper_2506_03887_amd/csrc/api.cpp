@@ -386,7 +386,7 @@ BatchWorkspaces batch_workspaces(const pre3_handle *h, int batch) {
     const int spread_rows = std::min(batch, spread_step_rows(h)), columns = std::max(batch, spread_step_blocks(h, spread_rows));
     BatchWorkspaces w;
     w.adv = advance_scratch_entries(columns, h->max_depth) * sizeof(int32_t);
-    w.arrivals = (size_t)spread_rows * sizeof(StepArrivals);
+    w.arrivals = (size_t)std::max(spread_rows, batch) * sizeof(StepArrivals);
     w.argmax = masked_argmax_workspace_bytes(batch, h->V.n_tokens, h->n_compute_units);
     w.topk = masked_topk_workspace_bytes(batch, h->V.n_tokens);
     if (w.topk > (size_t)1 << 30) w.topk = 0;
@@ -815,7 +815,7 @@ int pre3_apply_mask_topk(pre3_handle *h, const uint16_t *logits_bf16, int64_t ro
     if (!masked_topk_fits(h->V.n_tokens, k))
         return fail(h, PRE3_E_LIMIT, "apply_mask_topk: ceil(n_tokens / 16384) * k must not exceed 1024");
     hipError_t e = launch_masked_topk(logits_bf16, bitmask, h->b_stacks.batch, h->V.n_tokens, row_stride, k, h->n_compute_units,
-                                      h->topk_cand, out_tokens, out_logits, static_cast<hipStream_t>(stream));
+                                      h->topk_cand, h->arrivals, out_tokens, out_logits, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? PRE3_OK : hip_fail(h, e, "launch apply_mask_topk");
 }
 

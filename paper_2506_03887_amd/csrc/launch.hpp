@@ -47,15 +47,22 @@ hipError_t static_advance_scratch(int32_t **out);
 hipError_t launch_masked_argmax(const uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,
                                 int n_compute_units, unsigned long long *workspace, int32_t *out, hipStream_t stream);
 size_t masked_argmax_workspace_bytes(int batch, int vocab, int n_compute_units);   // per-segment partial results
+// What the blocks of one row of a batch count themselves in with.
+struct StepArrivals {
+    unsigned long long best;       // greedy: largest candidate word so far
+    uint32_t planned, sampled;     // blocks of the row that have planned, that have sampled; zero again when the launch ends
+    uint32_t listed, spare;        // top-k: blocks of the row that have handed their candidates over; zero again when the launch ends
+};
 // The k largest allowed logits of every row (k <= kTopkMax), ids in out_ids[batch * k] (-1 padded),
 // their bf16 patterns in out_vals (may be null; 0xFF80 padded).
 constexpr int kTopkMax = 64;
 bool masked_topk_fits(int vocab, int k);      // (chunks of 16,384 tokens) x k <= 1,024 candidates per row
 size_t masked_topk_workspace_bytes(int batch, int vocab);
 int masked_topk_groups(int vocab, int batch, bool aligned, int n_compute_units);   // groups of 8 logits per thread of its blocks
+bool masked_topk_spread(int vocab, int batch, int n_compute_units);   // a row over blocks of 16,384 tokens instead
 hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,
-                              int k, int n_compute_units, unsigned long long *workspace, int32_t *out_ids,
-                              uint16_t *out_vals, hipStream_t stream);
+                              int k, int n_compute_units, unsigned long long *workspace, StepArrivals *arrivals /* batch, all zero */,
+                              int32_t *out_ids, uint16_t *out_vals, hipStream_t stream);
 size_t advance_fill_walk_spill_entries(int batch, int max_depth);   // int32 entries
 // cycle_head / cycle_pool: the cycle tables for cycle-aware stacks (the call then needs
 // advance_fill_fits_compact), or null.
@@ -96,10 +103,6 @@ hipError_t launch_advance_fill_apply(const DevTables &T, const int32_t *tokens, 
 // (each block masks from the materialised row), with cycle-aware stacks the staged stack within the kernel's LDS,
 // adv_spill of advance_scratch_entries and walk_spill of advance_fill_walk_spill_entries(batch * segments, ...)
 // entries, and one StepArrivals per row, all zero.
-struct StepArrivals {
-    unsigned long long best;       // greedy: largest candidate word so far
-    uint32_t planned, sampled;     // blocks of the row that have planned, that have sampled; zero again when the launch ends
-};
 int step_spread_segments(int n_tokens);
 hipError_t launch_step_spread(const DevTables &T, const DevTokenEdges &E, const int32_t *tokens, int32_t *states, int32_t *data,
                               int32_t *len, int cap, int batch, int32_t *err, uint32_t *bitmask, int restart_on_eos,

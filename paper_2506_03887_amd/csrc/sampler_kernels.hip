@@ -285,6 +285,12 @@ __device__ __noinline__ uint32_t topk_cut_list(unsigned long long *list, int n, 
     return (uint32_t)(thr >> kTopkIdBits);
 }
 
+// What the blocks of a row hand to the one that merges them: kTopkMax words a block (512 bytes, lines of its own), of which those
+// behind its last candidate are zero.  Stored and loaded past the L2s: the blocks run on different XCDs.
+__device__ __forceinline__ void topk_hand_over(unsigned long long *workspace, int b, int seg, int n_seg, int i, unsigned long long word) {
+    __hip_atomic_store(workspace + ((size_t)b * n_seg + seg) * kTopkMax + i, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <int kBlock>
 __device__ __forceinline__ void masked_topk_chunked(
     const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
@@ -303,11 +309,10 @@ __device__ __forceinline__ void masked_topk_chunked(
     const uint8_t *mrow = reinterpret_cast<const uint8_t *>(bitmask + (size_t)b * n_words);
     const uint16_t *lrow = logits + (size_t)b * row_stride;
     const int n_mask_bytes = n_words * 4;
-    unsigned long long *dst = out + ((size_t)b * n_seg + seg) * (size_t)k;
     // with one segment per row (out_ids given) the ranked words are the row's result and go out as ids and patterns
     auto emit = [&](int rank, unsigned long long word) {
         if (out_ids == nullptr) {
-            dst[rank] = word;
+            topk_hand_over(out, b, seg, n_seg, rank, word);
         } else if (word != 0ull) {
             const uint32_t id = kTopkIdMask - ((uint32_t)word & kTopkIdMask);
             out_ids[(size_t)b * k + rank] = (int32_t)id;
@@ -726,11 +731,27 @@ __device__ __forceinline__ void topk_rank(const unsigned long long *s_cand, int 
     }
 }
 
-template <int kBlock, int kG>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void masked_topk_row_kernel(
+// One of a row's results: the id and the pattern of `word`, or the padding.
+__device__ __forceinline__ void topk_put(int rank, unsigned long long word, int k, int b, const uint16_t *__restrict__ row,
+                                         int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_vals) {
+    int32_t id = -1;
+    uint16_t value = 0xFF80u;
+    if (word != 0ull) {
+        id = (int32_t)(kTopkIdMask - ((uint32_t)word & kTopkIdMask));
+        const int pattern = bf16_pattern_of_key((uint32_t)(word >> kTopkIdBits));
+        if (out_vals) value = pattern >= 0 ? (uint16_t)pattern : row[id];
+    }
+    out_ids[(size_t)b * k + rank] = id;
+    if (out_vals) out_vals[(size_t)b * k + rank] = value;
+}
+
+// A row's segment: its k best to out_ids and out_vals, or, where the row has several, its candidates to the workspace
+// (topk_hand_over: `width` words, the k best of the segment among them).
+template <int kBlock, int kG, bool kSeveral>
+__device__ __forceinline__ void topk_segment(
     const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
     int n_words, int k, unsigned long long *__restrict__ workspace, int32_t *__restrict__ out_ids,
-    uint16_t *__restrict__ out_vals) {
+    uint16_t *__restrict__ out_vals, int b, int seg, int n_seg, int width, int tid) {
     constexpr int kWaves = kBlock / 64, kSegTokens = kBlock * kG * 8;
     constexpr int kAhead = kG < 8 ? kG : 8;                   // groups a thread has in flight
     static_assert(kG % 4 == 0 && kSegTokens % (kTopkPerThread * kBlock) == 0, "mask words of four rounds at a time, whole chunks");
@@ -742,7 +763,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ int s_group_at[kTopkRowGroupList];
     __shared__ unsigned long long s_cand[kTopkRowList];
     __shared__ int s_count, s_groups;
-    const int b = blockIdx.x, seg = blockIdx.y, n_seg = gridDim.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     if (kBlock == kTopkBlock && vocab < 8) {                  // not one group of eight logits that the loads below could take
         topk_in_chunks<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, 1, workspace, out_ids, out_vals, b, 0, 1);
         return;
@@ -836,22 +857,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
     const uint32_t bound = kth != 0u ? kth : first != 0u ? 1u : 0u;      // fewer than k: every candidate
     auto emit = [&](int rank, unsigned long long word) {
-        if (n_seg > 1) {                                      // masked_topk_finish_kernel merges the segments
-            workspace[((size_t)b * n_seg + seg) * (size_t)k + rank] = word;
-        } else if (word != 0ull) {
-            const uint32_t id = kTopkIdMask - ((uint32_t)word & kTopkIdMask);
-            out_ids[(size_t)b * k + rank] = (int32_t)id;
-            if (out_vals) {
-                const int pattern = bf16_pattern_of_key((uint32_t)(word >> kTopkIdBits));
-                out_vals[(size_t)b * k + rank] = pattern >= 0 ? (uint16_t)pattern : whole_row[id];
-            }
-        } else {
-            out_ids[(size_t)b * k + rank] = -1;
-            if (out_vals) out_vals[(size_t)b * k + rank] = 0xFF80u;
-        }
+        if (kSeveral) topk_hand_over(workspace, b, seg, n_seg, rank, word);
+        else topk_put(rank, word, k, b, whole_row, out_ids, out_vals);
+    };
+    auto nothing_behind = [&](int n) {                        // no candidates beyond the n that are handed over
+        if (kSeveral && tid >= n && tid < width) topk_hand_over(workspace, b, seg, n_seg, tid, 0ull);
     };
     if (bound == 0u) {                                        // nothing is allowed (or only NaN)
-        if (tid < k) emit(tid, 0ull);
+        if (kSeveral) nothing_behind(0);
+        else if (tid < k) emit(tid, 0ull);
         return;
     }
     // (2) the groups that hold a value of at least `bound`, then the tokens
@@ -908,61 +922,85 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const int n = s_count;
     if (n > kTopkRowList || n_groups > kTopkRowGroupList) {   // same in every thread
         constexpr int kChunks = kSegTokens / (kTopkPerThread * kBlock);
-        topk_in_chunks<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, kChunks, workspace, n_seg > 1 ? nullptr : out_ids,
+        topk_in_chunks<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, kChunks, workspace, kSeveral ? nullptr : out_ids,
                                out_vals, b, seg, n_seg);
+        nothing_behind(k);
+        return;
+    }
+    if (kSeveral && n <= width) {                             // the block that merges ranks them
+        if (tid < n) topk_hand_over(workspace, b, seg, n_seg, tid, s_cand[tid]);
+        nothing_behind(n);
         return;
     }
     // (3) ranks
     if (tid >= n && tid < k) emit(tid, 0ull);
     topk_rank<kBlock>(s_cand, n, k, tid, emit);
+    nothing_behind(k);
 }
 
-// Merges the segments' candidates of one row: n_cand words (0 = empty), at most kTopkFinishPer per thread.  As above, the
-// k-th largest of 128 thread maxima bounds the k-th largest key from below, and the words that reach it are ranked.
-constexpr int kTopkFinishBlock = 512, kTopkFinishPer = 2;
-__global__ __launch_bounds__(kTopkFinishBlock) void masked_topk_finish_kernel(
-    const unsigned long long *__restrict__ cand, int n_cand, int k, const uint16_t *__restrict__ logits,
-    int64_t row_stride, int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_vals) {
+// The k best of a row out of what its blocks handed over (n_cand <= kTopkMergeMax words, 0 = empty), by the last of them.  As
+// above, the k-th largest of 128 thread maxima bounds the k-th largest key from below, and the words that reach it are ranked.
+constexpr int kTopkMergeMax = 1024;
+template <int kBlock>
+__device__ __forceinline__ void topk_merge(const unsigned long long *__restrict__ workspace, int n_seg, int width, int k,
+                                           const uint16_t *__restrict__ row, int32_t *__restrict__ out_ids,
+                                           uint16_t *__restrict__ out_vals, int b, int tid) {
+    constexpr int kPer = kTopkMergeMax / kBlock;
     __shared__ __align__(16) uint32_t s_pub[kTopkMaxima];
     __shared__ uint32_t s_bound[2];
-    __shared__ unsigned long long s_cand[kTopkFinishBlock * kTopkFinishPer];
+    __shared__ unsigned long long s_words[kTopkMergeMax];
     __shared__ int s_count;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    unsigned long long c[kTopkFinishPer], top = 0ull;
+    const int lane = tid & 63, n_cand = n_seg * width;
+    unsigned long long c[kPer], top = 0ull;
 #pragma unroll
-    for (int i = 0; i < kTopkFinishPer; ++i) {
-        const int at = i * kTopkFinishBlock + tid;
-        c[i] = at < n_cand ? cand[(size_t)b * n_cand + at] : 0ull;
+    for (int i = 0; i < kPer; ++i) {
+        const int at = i * kBlock + tid, from = at / width;
+        c[i] = 0ull;
+        if (at < n_cand)
+            c[i] = __hip_atomic_load(workspace + ((size_t)b * n_seg + from) * kTopkMax + (at - from * width), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         top = c[i] > top ? c[i] : top;
     }
     if (tid == 0) { s_count = 0; s_bound[0] = s_bound[1] = 0u; }
     uint32_t first, kth;
-    topk_bound<kTopkFinishBlock>((uint32_t)(top >> kTopkIdBits), k, s_pub, s_bound, tid, &first, &kth);
+    topk_bound<kBlock>((uint32_t)(top >> kTopkIdBits), k, s_pub, s_bound, tid, &first, &kth);
 #pragma unroll
-    for (int i = 0; i < kTopkFinishPer; ++i) {
+    for (int i = 0; i < kPer; ++i) {
         const bool keep = c[i] != 0ull && (uint32_t)(c[i] >> kTopkIdBits) >= kth;
         const unsigned long long m = __ballot(keep);
         if (m == 0ull) continue;
         int base = 0;
         if (lane == 0) base = atomicAdd(&s_count, __popcll(m));
         base = __builtin_amdgcn_readfirstlane(base);
-        if (keep) s_cand[base + __popcll(m & ((1ull << lane) - 1ull))] = c[i];
+        if (keep) s_words[base + __popcll(m & ((1ull << lane) - 1ull))] = c[i];
     }
     lds_barrier();
     const int n = s_count;
-    auto emit = [&](int rank, unsigned long long w) {
-        const uint32_t id = kTopkIdMask - ((uint32_t)w & kTopkIdMask);
-        out_ids[(size_t)b * k + rank] = (int32_t)id;
-        if (out_vals) {
-            const int pattern = bf16_pattern_of_key((uint32_t)(w >> kTopkIdBits));
-            out_vals[(size_t)b * k + rank] = pattern >= 0 ? (uint16_t)pattern : logits[(size_t)b * row_stride + id];
-        }
-    };
-    if (tid >= n && tid < k) {
-        out_ids[(size_t)b * k + tid] = -1;
-        if (out_vals) out_vals[(size_t)b * k + tid] = 0xFF80u;
+    auto put = [&](int rank, unsigned long long word) { topk_put(rank, word, k, b, row, out_ids, out_vals); };
+    if (tid >= n && tid < k) put(tid, 0ull);
+    topk_rank<kBlock>(s_words, n, k, tid, put);
+}
+
+// A row per blockIdx.x, a segment per blockIdx.y (kSeveral: of more than one).  The blocks of a row that has several count
+// themselves in when what they hand over has arrived; the last one merges, and sets the count back to zero for the next
+// launch.  No block waits for another.
+template <int kBlock, int kG, bool kSeveral>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void masked_topk_row_kernel(
+    const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
+    int n_words, int k, unsigned long long *__restrict__ workspace, int32_t *__restrict__ out_ids,
+    uint16_t *__restrict__ out_vals, StepArrivals *__restrict__ arrivals) {
+    const int b = blockIdx.x, seg = kSeveral ? blockIdx.y : 0, n_seg = kSeveral ? gridDim.y : 1, tid = threadIdx.x;
+    const int width = n_seg * kTopkMax <= kTopkMergeMax ? kTopkMax : k;
+    topk_segment<kBlock, kG, kSeveral>(logits, bitmask, vocab, row_stride, n_words, k, workspace, out_ids, out_vals, b, seg, n_seg, width, tid);
+    if constexpr (kSeveral) {
+        __shared__ int s_last;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this wave's candidates are where the other XCDs see them ...
+        __syncthreads();                                           // ... and those of the block's other waves
+        if (tid == 0) s_last = atomicAdd(&arrivals[b].listed, 1u) == (uint32_t)(n_seg - 1);
+        __syncthreads();
+        if (!s_last) return;
+        if (tid == 0) atomicExch(&arrivals[b].listed, 0u);
+        topk_merge<kBlock>(workspace, n_seg, width, k, logits + (size_t)b * row_stride, out_ids, out_vals, b, tid);
     }
-    topk_rank<kTopkFinishBlock>(s_cand, n, k, tid, emit);
 }
 
 }  // namespace
@@ -1001,7 +1039,7 @@ static int masked_topk_chunks(int vocab, int chunk = kTopkChunk) { return (vocab
 
 bool masked_topk_fits(int vocab, int k) {
     return k >= 1 && k <= kTopkMax && vocab >= 1 && vocab <= (1 << kTopkIdBits) &&
-           masked_topk_chunks(vocab) * k <= kTopkFinishBlock * kTopkFinishPer;
+           masked_topk_chunks(vocab) * k <= kTopkMergeMax;
 }
 
 size_t masked_topk_workspace_bytes(int batch, int vocab) {
@@ -1021,7 +1059,9 @@ size_t masked_topk_workspace_bytes(int batch, int vocab) {
 // A longer row is cut into wide blocks unless the batch is too small to fill the chip with them (at the line, 31 rows
 // of 200,000 tokens take 13.8 to 14.4 us in segments of 16,384 and 13.7 in blocks), of twenty groups where those come to
 // fewer rounds (280,000 tokens: 128 rows 19.4 us, 27.3 in blocks of sixteen; 256 33.5 and 40.6; but 500,000 x 32 15.9 and 14.3,
-// 400,000 x 64 16.3 and 15.4).
+// 400,000 x 64 16.3 and 15.4).  (The forms in several blocks were measured with a second launch that merged their lists; merged by
+// the last of the blocks they take 0.6 to 1.9 us less: 2 x 160,003 10.6 -> 9.4, 31 x 160,003 13.0 -> 11.9, 16 x 200,000 11.2 -> 10.3,
+// 40 x 200,000 13.6 -> 13.0, 16 x 131,075 11.2 -> 10.3, with few allowed tokens 12.6 -> 10.8.)
 int masked_topk_groups(int vocab, int batch, bool aligned, int n_compute_units) {
     constexpr int kPerGroup = 8 * kTopkBlockWide;
     if (vocab <= kTopkChunk) return 4;
@@ -1034,8 +1074,17 @@ int masked_topk_groups(int vocab, int batch, bool aligned, int n_compute_units) 
     return rounds(20) < rounds(shorter) ? 20 : shorter;
 }
 
+// Small batches of rows that one block streams longest: cut into blocks of 16,384 tokens, which hand over in one launch.  What that
+// costs is the exchange (a store, a count and a load past the L2s, about 2.5 us); what it saves is the stream of one compute unit.
+// us per call, spread and not: 1 x 152,064 7.9 and 9.3, 4 x 152,064 8.8 and 10.7, 16 x 152,064 9.9 and 11.1 (few allowed: 10.5 and 10.7),
+// 24 x 152,064 10.4 and 11.2 (11.2 and 11.2); 1 x 128,256 8.2 and 8.8, 4 x 128,256 8.9 and 9.6, but 8 x 128,256 9.0 and 9.3 (10.3 and 9.8),
+// 32 x 128,256 10.2 and 10.1, 16 x 65,000 10.0 and 7.8.
+bool masked_topk_spread(int vocab, int batch, int n_compute_units) {
+    return vocab > 7 * kTopkChunk && batch * masked_topk_chunks(vocab) <= (vocab > 8 * kTopkChunk ? n_compute_units * 5 / 8 : n_compute_units / 8);
+}
+
 hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,
-                              int k, int n_compute_units, unsigned long long *workspace, int32_t *out_ids,
+                              int k, int n_compute_units, unsigned long long *workspace, StepArrivals *arrivals, int32_t *out_ids,
                               uint16_t *out_vals, hipStream_t stream) {
     if (batch == 0) return hipSuccess;
     if (!masked_topk_fits(vocab, k)) return hipErrorInvalidValue;
@@ -1043,20 +1092,21 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     const bool aligned = (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && (row_stride & 7) == 0;
 #define PRE3_TOPK_ROW(BLOCK, GROUPS)                                                                                         \
     n_seg = masked_topk_chunks(vocab, BLOCK * GROUPS * 8);                                                                   \
-    hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, vocab, \
-                       row_stride, n_words, k, workspace, out_ids, out_vals)
+    if (n_seg > 1) PRE3_TOPK_BLOCKS(BLOCK, GROUPS, true);                                                                    \
+    else PRE3_TOPK_BLOCKS(BLOCK, GROUPS, false)
+#define PRE3_TOPK_BLOCKS(BLOCK, GROUPS, SEVERAL)                                                                             \
+    hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS, SEVERAL>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, \
+                       vocab, row_stride, n_words, k, workspace, out_ids, out_vals, arrivals)
     int n_seg = 1;
-    switch (masked_topk_groups(vocab, batch, aligned, n_compute_units)) {
+    switch (masked_topk_spread(vocab, batch, n_compute_units) ? 4 : masked_topk_groups(vocab, batch, aligned, n_compute_units)) {
         case 4: PRE3_TOPK_ROW(kTopkBlock, 4); break;
         case 8: PRE3_TOPK_ROW(kTopkBlockWide, 8); break;
         case 12: PRE3_TOPK_ROW(kTopkBlockWide, 12); break;
         case 16: PRE3_TOPK_ROW(kTopkBlockWide, 16); break;
         default: PRE3_TOPK_ROW(kTopkBlockWide, 20);
     }
+#undef PRE3_TOPK_BLOCKS
 #undef PRE3_TOPK_ROW
-    if (n_seg > 1)
-        hipLaunchKernelGGL(masked_topk_finish_kernel, dim3(batch), dim3(kTopkFinishBlock), 0, stream, workspace, n_seg * k, k, logits,
-                           row_stride, out_ids, out_vals);
     return hipGetLastError();
 }
 

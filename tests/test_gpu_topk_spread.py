@@ -1,0 +1,68 @@
+"""Rows whose k best are found by several blocks that hand over within one launch (small batches of long rows, and rows longer
+than a block's registers): against the oracle at the lines of the rule, launch after launch and replayed as a graph (the
+counters that the last block of a row sets back), and with lists of every length between none and full."""
+import numpy as np
+import pytest
+
+from oracle import masked_topk
+from workloads.vocab import Vocab, bf16_logits
+
+
+def test_lines_of_the_rule():
+    import ctypes
+    from paper_2506_03887_amd import load
+    rule = load()["_ZN4pre318masked_topk_spreadEiii"]
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_int] * 3
+    spread = lambda V, batch: bool(rule(V, batch, 256))
+    assert not spread(16_384, 1) and not spread(114_688, 1)
+    assert spread(114_689, 4) and not spread(114_689, 5) and spread(131_072, 4)
+    assert spread(131_073, 17) and not spread(131_073, 18) and spread(152_064, 16) and not spread(163_841, 15)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V,B,pad,offset", [(114_689, 4, 7, 0), (128_256, 1, 0, 0), (131_073, 17, 0, 1), (152_064, 16, 0, 0), (163_840, 16, 3, 3),
+                                            (180_225, 14, 0, 0), (262_149, 40, 0, 0)])
+def test_blocks_that_hand_over(V, B, pad, offset):
+    import torch
+    from test_gpu_argmax import _bound_lib
+    dev, rng, W, stride = torch.device("cuda:0"), np.random.default_rng(V + B), (V + 31) // 32, V + pad
+    lib = _bound_lib(Vocab([bytes([97 + i % 5]) for i in range(V - 1)] + [b""], V - 1), B)
+    graph, static = None, None
+    for turn in range(4):
+        host = bf16_logits(rng, B, stride)
+        mask = rng.integers(0, 2 ** 32, size=(B, W), dtype=np.uint64).astype(np.uint32)
+        for b in range(B):
+            kind = (b + turn) % 8
+            if kind == 1:                               # a few allowed tokens, some rows none in most blocks
+                mask[b] = 0
+                mask[b, rng.integers(0, W, size=int(rng.integers(1, 90)))] = 1 << int(rng.integers(0, 32))
+            elif kind == 2:
+                mask[b] = 0
+            elif kind == 3:                             # ties everywhere: no list holds them
+                host[b] = rng.choice([0x3F80, 0x0000, 0x8000, 0xBF80], size=stride)
+            elif kind == 4:
+                host[b] |= 0x8000                       # nothing above zero
+            elif kind == 5:
+                host[b, rng.integers(0, V, size=70)] = rng.choice([0x7FC0, 0xFFC0, 0x7F80, 0xFF80], size=70)
+            elif kind == 6:                             # all of the best in one block
+                at = int(rng.integers(0, V // 16_384)) * 16_384
+                host[b, at:at + 60] = 0x4300 + np.arange(60)
+        mask[:, -1] &= np.uint32(0xFFFFFFFF >> (W * 32 - V))
+        if static is None:
+            flat = torch.zeros(B * stride + offset, dtype=torch.int16, device=dev)
+            static = flat[offset:].view(B, stride), torch.zeros((B, W), dtype=torch.int32, device=dev)
+        static[0].copy_(torch.from_numpy(host.view(np.int16)).to(dev))
+        static[1].copy_(torch.from_numpy(mask.view(np.int32)).to(dev))
+        for k in (1, 50):
+            ids, vals = torch.empty((B, k), dtype=torch.int32, device=dev), torch.empty((B, k), dtype=torch.int16, device=dev)
+            lib.apply_mask_topk(static[0].view(torch.bfloat16), static[1], ids, vals)
+            want_ids, want_vals = masked_topk(host, mask, V, k)
+            assert (ids.cpu().numpy() == want_ids).all() and (vals.cpu().numpy().view(np.uint16) == want_vals).all(), (turn, k)
+        if graph is None:                               # k = 50, recorded once and replayed on the later turns' inputs
+            g_ids, g_vals = torch.empty_like(ids), torch.empty_like(vals)
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                lib.apply_mask_topk(static[0].view(torch.bfloat16), static[1], g_ids, g_vals)
+        graph.replay()
+        graph.replay()
+        assert (g_ids.cpu().numpy() == want_ids).all() and (g_vals.cpu().numpy().view(np.uint16) == want_vals).all(), turn
