@@ -650,6 +650,26 @@ __device__ __forceinline__ uint4 mask_group(uint4 v, uint32_t mu) {
                       (v.w & a.w) | (~a.w & kNegInfPair));
 }
 
+// The plan is a materialised row as it stands.
+__device__ __forceinline__ bool plan_is_a_row(const RowPlan &plan) {
+    return plan.mode == kRowFast && plan.dense >= 0 && plan.nseg == 0 && plan.walk_count == 0;
+}
+// A materialised row to the mask, by one wave: sixteen bytes per lane, whatever the row's alignment.
+__device__ __forceinline__ void copy_mask_row(const uint32_t *src, uint32_t *dst, int n_words, int lane) {
+    typedef NativeUint4 __attribute__((aligned(4))) NativeUint4AtWord;
+    constexpr int kInFlight = 8;
+    const int n_vec = n_words >> 2;
+    for (int v0 = lane; v0 < n_vec; v0 += 64 * kInFlight) {
+        NativeUint4 x[kInFlight];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) x[u] = reinterpret_cast<const NativeUint4 *>(src)[min(v0 + u * 64, n_vec - 1)];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u)
+            if (v0 + u * 64 < n_vec) __builtin_nontemporal_store(x[u], reinterpret_cast<NativeUint4AtWord *>(dst) + v0 + u * 64);
+    }
+    if (lane < (n_words & 3)) dst[n_vec * 4 + lane] = src[n_vec * 4 + lane];
+}
+
 // The largest of all threads' keys, in every thread of a block of 1,024 (s_key: a word per wave).
 __device__ __forceinline__ int step_block_best(int key, int *s_key, int tid) {
     auto row_max = [](int v) {                          // of sixteen lanes
@@ -721,6 +741,9 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
     const bool vector_ok = (T.n_words & 3) == 0 && (reinterpret_cast<uintptr_t>(bitmask) & 15) == 0;
     uint16_t *lrow = logits + (size_t)b * row_stride;
     int top = -32768;                                  // kArgmax: the block's best order key
+    // (not with twenty groups per lane, which leave no registers for the mask words)
+    constexpr bool kByLane = kArgmax && kRows == 1 && kHeld <= 17;
+    bool by_lane = false;                              // kByLane: every lane fetches the mask bytes of its groups, the row is not in LDS
     __shared__ int s_key[kArgmax ? kStepBlock / 64 : 1], s_token;
     if (kArgmax && tid == 0) s_token = 0x7FFFFFFF;     // (read behind three barriers)
     // kArgmax: half a mask byte -> AND masks of two registers.  Sixteen entries: lanes that read the same entry are
@@ -729,6 +752,29 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
     __shared__ uint2 s_expand[kArgmax ? 16 : 1];
     __shared__ unsigned long long s_part[kArgmax ? kStepBlock / 64 + 1 : 1];
 
+    // kByLane: a wave goes on when the plan is there, whether the others have their logits or not (their loads are served one wave
+    // after the other: the first has its row at a third of the fetch, the last at its end).  The wave that advances sets the flag,
+    // whatever it finds, so every wait ends.
+    __shared__ int s_ready;
+    auto plan_ready = [&] {
+        if (!kByLane) { lds_barrier(); return; }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        if (lane == 0) __hip_atomic_store(&s_ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto plan_is_there = [&] {
+        const bool there = __hip_atomic_load(&s_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        return __builtin_amdgcn_readfirstlane(there) != 0;
+    };
+    auto plan_awaited = [&] {
+        if (!kByLane) lds_barrier();
+        else while (!plan_is_there()) __builtin_amdgcn_s_sleep(1);
+    };
+    if (kArgmax) mask_nibble_table_init(s_expand, tid);
+    if (kByLane) {
+        if (tid == 0) s_ready = 0;
+        lds_barrier();
+    }
     if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
         const StepInputs in = read_inputs(tokens ? tokens : len, len, states, b);
         if (tokens) {
@@ -736,12 +782,21 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
             const Advanced r = advance_and_plan<kCompact, true>(T, E, in, cap, restart_on_eos, ws, cycle_head, cycle_pool,
                                                                 stage_cycles, after_row, plan, lane);
+            if (kArgmax) plan_ready();
             commit_advance<kCompact>(r, ws, after_row, states, row, len, err, cap, b, lane);
-        } else
+            if (!kArgmax) plan_ready();
+        } else {
             plan_only_scalar(T, E, in, row, cap, plan, lane);
+            plan_ready();
+        }
         // (barriers that order LDS only: this wave's stores of the new stack are still on their way, and
         // nothing in this block reads them before the launch ends -- except the walks below, which wait)
-        lds_barrier();                                 // the plan is there
+        by_lane = kByLane && plan_is_a_row(plan);
+        if (by_lane) {
+            // the mask row goes out as it lies there, while the other waves apply it
+            copy_mask_row(E.dense_rows + (size_t)plan.dense * n_vec * 4, dst_row, T.n_words, lane);
+            if (kArgmax) top = step_block_best(-32768, s_key, tid);
+        } else {
         lds_barrier();                                 // the materialised row (or zeros) is in LDS
         // tokens the tree leaves undetermined are walked on the committed stack, one lane per token
         PrivateStack wp;
@@ -766,6 +821,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
         }
         lds_barrier();                                 // the row is complete
         if (kArgmax) top = step_block_best(-32768, s_key, tid);
+        }
     } else {
         const int j = tid - 64;
         if (kCompact && stage_cycles) {
@@ -776,13 +832,65 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
         // the row of logits: every group of 8 that lies wholly inside the vocabulary
         const int whole = T.n_tokens >> 3;
         uint4 held[kHeld];
-        if (kArgmax) {
-            if (j < 16) {
-                uint32_t am[2];
-#pragma unroll
-                for (int q = 0; q < 2; ++q) am[q] = (((j >> (2 * q)) & 1) ? 0x0000FFFFu : 0u) | (((j >> (2 * q + 1)) & 1) ? 0xFFFF0000u : 0u);
-                s_expand[j] = make_uint2(am[0], am[1]);
+        auto group_keys = [](uint4 &v) {
+            v = make_uint4(bf16_order_keys(v.x), bf16_order_keys(v.y), bf16_order_keys(v.z), bf16_order_keys(v.w));
+            asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+        };
+        auto half_max = [](uint32_t x) { return max((int)(int16_t)(x & 0xFFFFu), (int)x >> 16); };
+        auto fold = [](const uint4 &v) { return packed_max_s16(packed_max_s16(v.x, v.y), packed_max_s16(v.z, v.w)); };
+        auto mask_keys = [&](uint4 &v, uint32_t mu) {   // v: the group's order keys
+            const uint4 allow = expand_mask_byte(s_expand, mu);
+            v = make_uint4(mask_order_keys(v.x, allow.x), mask_order_keys(v.y, allow.y), mask_order_keys(v.z, allow.z), mask_order_keys(v.w, allow.w));
+        };
+        // the mask row put together in LDS, and stored
+        auto row_in_lds = [&] {
+            const int mode = plan.mode;
+            if (mode == kRowFast && plan.dense >= 0) {
+                const uint4 *src = reinterpret_cast<const uint4 *>(E.dense_rows) + (size_t)plan.dense * n_vec;
+                for (int w = j; w < n_vec; w += kStepData) bits4[w] = src[w];
+            } else {
+                for (int w = j; w < n_vec; w += kStepData) bits4[w] = make_uint4(0, 0, 0, 0);
             }
+            lds_barrier();                                 // the materialised row (or zeros) is in LDS
+            if (mode == kRowFast) {
+                const int nseg = plan.nseg;
+                for (int i = 0; i < nseg; ++i) {
+                    const int32_t *ids = E.delta_ids + plan.seg_begin[i];
+                    const int cnt = plan.seg_count[i];
+                    for (int k = j; k < cnt; k += kStepData) {
+                        const int t = ids[k];
+                        atomicOr(&bits[t >> 5], 1u << (t & 31));
+                    }
+                }
+            }
+            lds_barrier();                                 // the row is complete
+            if (vector_ok) {
+                uint4 *dst4 = reinterpret_cast<uint4 *>(dst_row);
+                for (int w = j; w < n_vec; w += kStepData) stream_store(bits4[w], dst4 + w);
+            } else {
+                for (int w = j; w < T.n_words; w += kStepData) dst_row[w] = bits[w];
+            }
+        };
+        auto group_fold = [&](uint4 v, uint32_t mu) { mask_keys(v, mu); return fold(v); };
+        uint32_t best2 = 0x80008000u, folded[kArgmax && kRows == 1 ? kHeld : 1];   // kArgmax, one row: the lane's best keys, the best of each of its groups (two halves)
+        const uint8_t *mask_bytes = reinterpret_cast<const uint8_t *>(bits4);     // byte g = bits of group g
+        auto masked = [&](int i, uint32_t mu) {
+            folded[i] = group_fold(held[i], mu);
+            best2 = packed_max_s16(best2, folded[i]);
+        };
+        auto masked_from_lds = [&] {
+#pragma unroll
+            for (int i = 0; i < kHeld; ++i) {
+                // no branches: a group outside the row or without an allowed token gets the lowest key in every half, and the
+                // LDS reads of the groups can overlap (the row's LDS area is at least kHeld * kStepData bytes, so the byte
+                // is read at a fixed offset)
+                const int g = i * kStepData + j;
+                const uint32_t mu = mask_bytes[g];
+                masked(i, g < whole ? mu : 0u);
+            }
+        };
+        const int tail = T.n_tokens & 7;               // tokens of the last, partial group
+        if (kArgmax) {
             // The patterns become order keys as the groups arrive: kStepAhead groups in flight, the loads without a branch
             // (a slot beyond the row loads its last group and is not looked at), each group worked on when it is its turn
             // (the compiler would otherwise leave all of that to the fold behind the barriers).  With the fold below that keeps
@@ -792,13 +900,38 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             auto load_group = [&](int i) { held[i] = stream_load_at(lrow, min((uint32_t)j * 16u + (uint32_t)(i * kStepData * 16), last_group)); };
 #pragma unroll
             for (int i = 0; i < (kStepAhead < kHeld ? kStepAhead : kHeld); ++i) load_group(i);
-#pragma unroll
-            for (int i = 0; i < kHeld; ++i) {
+            auto arrived = [&](int i) {                 // group i's keys, with the load that follows
                 if (i + kStepAhead < kHeld) load_group(i + kStepAhead);
                 __builtin_amdgcn_sched_barrier(0);
-                held[i] = make_uint4(bf16_order_keys(held[i].x), bf16_order_keys(held[i].y), bf16_order_keys(held[i].z),
-                                     bf16_order_keys(held[i].w));
-                asm volatile("" : "+v"(held[i].x), "+v"(held[i].y), "+v"(held[i].z), "+v"(held[i].w));
+                group_keys(held[i]);
+            };
+            if constexpr (kByLane) {
+                // Where the row is a materialised one nobody puts it together: a lane fetches the mask bytes of its groups, which
+                // return behind the logits then in flight.
+                constexpr int kEarly = kHeld > kStepAhead ? kHeld - kStepAhead : 0;
+#pragma unroll
+                for (int i = 0; i < kEarly; ++i) arrived(i);
+                plan_awaited();
+                by_lane = plan_is_a_row(plan);
+                if (by_lane) {
+                    const uint8_t *bytes = reinterpret_cast<const uint8_t *>(E.dense_rows + (size_t)__builtin_amdgcn_readfirstlane(plan.dense) * n_vec * 4);
+                    uint32_t mu[kHeld];
+#pragma unroll
+                    for (int i = 0; i < kHeld; ++i) mu[i] = bytes[min(i * kStepData + j, whole - 1)];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = kEarly; i < kHeld; ++i) arrived(i);
+#pragma unroll
+                    for (int i = 0; i < kHeld; ++i) masked(i, i * kStepData + j < whole ? mu[i] : 0u);
+                } else {
+#pragma unroll
+                    for (int i = kEarly; i < kHeld; ++i) arrived(i);
+                    row_in_lds();
+                    masked_from_lds();
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kHeld; ++i) arrived(i);
             }
         } else {
 #pragma unroll
@@ -809,56 +942,25 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
                 if (g < whole) held[i] = stream_load(lrow + (size_t)i * (kStepData * 8) + (uint32_t)(j * 8));
             }
         }
-        lds_barrier();                                 // the plan is there
-        const int mode = plan.mode;
-        if (mode == kRowFast && plan.dense >= 0) {
-            const uint4 *src = reinterpret_cast<const uint4 *>(E.dense_rows) + (size_t)plan.dense * n_vec;
-            for (int w = j; w < n_vec; w += kStepData) bits4[w] = src[w];
-        } else {
-            for (int w = j; w < n_vec; w += kStepData) bits4[w] = make_uint4(0, 0, 0, 0);
-        }
-        lds_barrier();                                 // the materialised row (or zeros) is in LDS
-        if (mode == kRowFast) {
-            const int nseg = plan.nseg;
-            for (int i = 0; i < nseg; ++i) {
-                const int32_t *ids = E.delta_ids + plan.seg_begin[i];
-                const int cnt = plan.seg_count[i];
-                for (int k = j; k < cnt; k += kStepData) {
-                    const int t = ids[k];
-                    atomicOr(&bits[t >> 5], 1u << (t & 31));
-                }
-            }
-        }
-        lds_barrier();                                 // the row is complete
-        if (vector_ok) {
-            uint4 *dst4 = reinterpret_cast<uint4 *>(dst_row);
-            for (int w = j; w < n_vec; w += kStepData) stream_store(bits4[w], dst4 + w);
-        } else {
-            for (int w = j; w < T.n_words; w += kStepData) dst_row[w] = bits[w];
-        }
-        const uint8_t *mask_bytes = reinterpret_cast<const uint8_t *>(bits4);     // byte g = bits of group g
+        if (!kByLane) { plan_awaited(); row_in_lds(); }
         if (kArgmax) {
             // Per group: the AND masks of the two halves of the mask byte come from the LDS table, masked halves
             // get the lowest key and three packed maxima fold the group; what is left of it (one register) stays, and
             // one more packed maximum is the lane's best.  The block's best key is found first (step_block_best);
             // only the lanes that hold it then look for the group, and in the group for the token.
-            auto group_fold = [&](uint4 v, uint32_t mu) {        // v: the group's order keys
-                const uint2 lo = s_expand[mu & 15u], hi = s_expand[mu >> 4];
-                const uint32_t k01 = packed_max_s16(mask_order_keys(v.x, lo.x), mask_order_keys(v.y, lo.y));
-                const uint32_t k23 = packed_max_s16(mask_order_keys(v.z, hi.x), mask_order_keys(v.w, hi.y));
-                return packed_max_s16(k01, k23);
+            auto mask_byte_of = [&](int g) -> uint32_t {
+                if (by_lane) return (E.dense_rows[(size_t)plan.dense * n_vec * 4 + (g >> 2)] >> ((g & 3) * 8)) & 0xFFu;
+                return mask_bytes[g];
             };
-            auto half_max = [](uint32_t x) { return max((int)(int16_t)(x & 0xFFFFu), (int)x >> 16); };
             uint4 tail_keys = make_uint4(0, 0, 0, 0);
             uint32_t tail_m = 0u;
             int tail_fold = -32768;
-            const int tail = T.n_tokens & 7;
             if (tail > 0 && j == 0) {                   // the last, partial group: its logits one at a time
                 uint32_t x[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int k = 0; k < 7; ++k)
                     if (k < tail) x[k >> 1] |= (uint32_t)lrow[whole * 8 + k] << (16 * (k & 1));
-                tail_m = mask_bytes[whole] & ((1u << tail) - 1u);
+                tail_m = mask_byte_of(whole) & ((1u << tail) - 1u);
                 tail_keys = make_uint4(bf16_order_keys(x[0]), bf16_order_keys(x[1]), bf16_order_keys(x[2]), bf16_order_keys(x[3]));
                 tail_fold = half_max(group_fold(tail_keys, tail_m));
             }
@@ -866,25 +968,58 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             uint4 keys = make_uint4(0, 0, 0, 0);
             uint32_t m = 0u;
             if constexpr (kRows == 1) {
-                uint32_t fold[kHeld], best2 = 0x80008000u;
-#pragma unroll
-                for (int i = 0; i < kHeld; ++i) {
-                    // no branches: a group outside the row or without an allowed token gets the lowest key in every
-                    // half, and the LDS reads of the groups can overlap (the row's LDS area is at least
-                    // kHeld * kStepData bytes, so the byte is read at a fixed offset)
-                    const int g = i * kStepData + j;
-                    const uint32_t mu = mask_bytes[g];
-                    fold[i] = group_fold(held[i], g < whole ? mu : 0u);
-                    best2 = packed_max_s16(best2, fold[i]);
-                }
+                if (!kByLane) masked_from_lds();
                 best = max(half_max(best2), tail_fold);
                 top = step_block_best(best, s_key, tid);
-                if (best == top) {
-                    // the first of a lane's groups that holds the value (its groups ascend, the partial one is the last)
-                    at = whole;
+                unsigned long long holders = __ballot(best == top);
+                if constexpr (!kByLane) {
+                    if (best == top) {
+                        // the first of a lane's groups that holds the value (its groups ascend, the partial one is the last)
+                        at = whole;
 #pragma unroll
-                    for (int i = kHeld - 1; i >= 0; --i)
-                        if (half_max(fold[i]) == top) { keys = held[i]; at = i * kStepData + j; }
+                        for (int i = kHeld - 1; i >= 0; --i)
+                            if (half_max(folded[i]) == top) { keys = held[i]; at = i * kStepData + j; }
+                    }
+                } else if (holders != 0ull && top >= kOrderNegInf && !order_undecided(top)) {
+                    // Where: a lane that holds the value lays the best keys of its groups in LDS (the walks' private stacks, which
+                    // nobody uses any more), every lane looks at one of them; then the keys of that group, in the same way.
+                    const int wave = __builtin_amdgcn_readfirstlane(j >> 6);
+                    constexpr int kSpot = kLdsDepth * 64 / (kStepData / 64) & ~3;  // words per wave
+                    static_assert(kHeld * 4 <= kSpot, "a lane's groups in the wave's part of the stacks");
+                    uint32_t *spot = reinterpret_cast<uint32_t *>(s_walk_stack) + wave * kSpot;
+                    auto has = [&](uint32_t x) {
+                        return (int)(int16_t)(x & 0xFFFFu) == top || (int)x >> 16 == top;
+                    };
+                    int token = 0x7FFFFFFF;
+                    do {                                // (one lane but for ties)
+                        const int who = __ffsll((long long)holders) - 1;
+                        holders &= holders - 1ull;
+                        __builtin_amdgcn_wave_barrier();
+                        if (lane == who) {
+#pragma unroll
+                            for (int i = 0; i < kHeld; ++i) spot[i] = folded[i];
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                        const uint32_t f = spot[lane < kHeld ? lane : 0];
+                        const unsigned long long here = __ballot(lane < kHeld && has(f));
+                        const int i = here != 0ull ? __ffsll((long long)here) - 1 : -1;       // -1: in the partial group
+                        at = i >= 0 ? i * kStepData + wave * 64 + who : whole;
+                        __builtin_amdgcn_wave_barrier();
+                        if (lane == who) {
+                            if (i < 0) {
+                                *reinterpret_cast<uint4 *>(spot) = tail_keys;
+                            } else {
+#pragma unroll
+                                for (int u = 0; u < kHeld; ++u) reinterpret_cast<uint4 *>(spot)[u] = held[u];
+                            }
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                        const int key = reinterpret_cast<const int16_t *>(spot)[(i > 0 ? i * 8 : 0) + (lane & 7)];
+                        uint32_t hold = (uint32_t)__ballot(lane < 8 && key == top);            // tokens with that key, masked ones among them
+                        if ((hold & (hold - 1u)) != 0u) hold &= i < 0 ? (uint32_t)__builtin_amdgcn_readfirstlane(tail_m) : mask_byte_of(at);
+                        token = min(token, at * 8 + __builtin_ctz(hold | 0x80u));
+                    } while (holders != 0ull);
+                    if (lane == 0) atomicMin(&s_token, token);
                 }
             } else {
                 // What the block does not hold is streamed now that the mask is known: nothing of a group without an
@@ -926,7 +1061,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
                 if (tail_fold > best) { best = tail_fold; at = whole; }
                 top = step_block_best(best, s_key, tid);
             }
-            if (best == top && top >= kOrderNegInf && !order_undecided(top)) {
+            if (!kByLane && best == top && top >= kOrderNegInf && !order_undecided(top)) {
                 if (at == whole) { keys = tail_keys; m = tail_m; }
                 else m = mask_bytes[at];
                 const uint32_t x[4] = {keys.x, keys.y, keys.z, keys.w};
@@ -961,7 +1096,6 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             }
         }
         // the last, partial group of a vocabulary that is not a multiple of 8
-        const int tail = T.n_tokens & 7;
         if (j < tail) {
             const int t = whole * 8 + j;
             if (!((bits[t >> 5] >> (t & 31)) & 1u)) lrow[t] = 0xFF80;
@@ -978,8 +1112,10 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             if (tid == 0) out_tokens[b] = s_token;
         } else {
             const unsigned long long mine = argmax_block_max(
-                argmax_by_compare<kArgBlock>(lrow, [&](int g) { return (uint32_t)reinterpret_cast<const uint8_t *>(bits4)[g]; }, 0,
-                                          (T.n_tokens + 7) >> 3, T.n_tokens, tid), s_part, tid);
+                argmax_by_compare<kArgBlock>(lrow, [&](int g) {
+                    if (by_lane) return (E.dense_rows[(size_t)plan.dense * n_vec * 4 + (g >> 2)] >> ((g & 3) * 8)) & 0xFFu;
+                    return (uint32_t)reinterpret_cast<const uint8_t *>(bits4)[g];
+                }, 0, (T.n_tokens + 7) >> 3, T.n_tokens, tid), s_part, tid);
             if (tid == 0) out_tokens[b] = mine != 0ull ? (int32_t)(0xFFFFFFFFu - (uint32_t)mine) : -1;
         }
     }
