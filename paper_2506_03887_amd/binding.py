@@ -63,7 +63,7 @@ _lib = None
 
 def load():
     """Loads the built library; raises if it has not been built (no fallback exists)."""
-    global _lib, _torch
+    global _lib, _torch, _current_device, _current_stream
     if _lib is not None:
         return _lib
     # PyTorch ships its own HIP runtime: it must be in the process before libpre3.so is
@@ -115,27 +115,30 @@ def load():
             getattr(lib, name).restype = i32
     _KINDS.update(i32=(torch.int32,), u16=(torch.bfloat16, torch.uint16, torch.int16), u32=(torch.int32, torch.uint32),
                   u8=(torch.uint8,))
+    if hasattr(torch._C, "_cuda_getDevice"):
+        _current_device, _current_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
     _torch, _lib = torch, lib
     return lib
 
 
-_torch = None          # set by load(), with the dtypes each kind of buffer may have
+_torch = _current_device = _current_stream = None          # set by load(), with the dtypes each kind of buffer may have
 _KINDS = {}
 
 
 def _stream_ptr(stream):
     """Handle of `stream` (a torch stream or a plain handle), by default the current stream of the current device.
-    The handle is asked for directly: building a torch.cuda.Stream object for it took 3.0 of the 13 us of a call."""
+    The handle is asked for directly: building a torch.cuda.Stream object for it took 3.0 of the 13 us of a call.  (Where the
+    tensors are, the GPU has been initialised, which is what torch.cuda.current_device looks for first.)"""
     if stream is None:
-        return _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device())
+        return _current_stream(_current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _dev(t, dtype_name):
     """Device pointer of a contiguous torch tensor of the expected dtype."""
-    if not (t.is_cuda and t.dtype in _KINDS[dtype_name]):
-        raise TypeError(f"expected a CUDA tensor of kind {dtype_name}, got {t.dtype} on {t.device}")
-    return t.data_ptr()
+    if t.is_cuda and t.dtype in _KINDS[dtype_name]:
+        return t.data_ptr()
+    raise TypeError(f"expected a CUDA tensor of kind {dtype_name}, got {t.dtype} on {t.device}")
 
 
 class Pre3:
@@ -351,23 +354,31 @@ class Pre3:
     def advance_fill_apply_mask(self, tokens, bitmask, logits, restart_on_eos=False, one_kernel=False, stream=None):
         """The whole decode step: advance, next mask rows, and those rows applied to `logits` in place.
         one_kernel: ask for the one-kernel form at any batch size (the library chooses by itself otherwise)."""
-        assert tokens.is_contiguous() and bitmask.is_contiguous() and bitmask.shape[1] == self.words
-        assert logits.dim() == 2 and logits.stride(1) == 1 and logits.shape[0] == bitmask.shape[0]
-        self._check(self._lib.pre3_advance_fill_apply_mask(self._h, _dev(tokens, "i32"), _dev(bitmask, "u32"),
-                                                           _dev(logits, "u16"), logits.stride(0),
-                                                           (ADVANCE_RESTART_ON_EOS if restart_on_eos else 0) |
-                                                           (STEP_ONE_KERNEL if one_kernel else 0),
-                                                           _stream_ptr(stream)))
+        rows, words = bitmask.shape[:2]
+        assert tokens.is_contiguous() and bitmask.is_contiguous() and words == self.words
+        assert logits.dim() == 2 and logits.shape[0] == rows
+        stride, one = logits.stride()
+        assert one == 1
+        # (a small batch's step takes the GPU 6 us, about what a call takes here: nothing is asked of torch twice)
+        rc = self._lib.pre3_advance_fill_apply_mask(self._h, _dev(tokens, "i32"), _dev(bitmask, "u32"), _dev(logits, "u16"), stride,
+                                                    (ADVANCE_RESTART_ON_EOS if restart_on_eos else 0) |
+                                                    (STEP_ONE_KERNEL if one_kernel else 0), _stream_ptr(stream))
+        if rc != PRE3_OK:
+            self._check(rc)
 
     def advance_fill_argmax(self, tokens, bitmask, logits, out_tokens, restart_on_eos=False, one_kernel=False, stream=None):
         """The whole greedy step: advance, next mask rows, and out_tokens[b] = arg max of the allowed logits of
         row b (the logits are only read; out_tokens may be `tokens`)."""
-        assert tokens.is_contiguous() and bitmask.is_contiguous() and bitmask.shape[1] == self.words and out_tokens.is_contiguous()
-        assert logits.dim() == 2 and logits.stride(1) == 1 and logits.shape[0] == bitmask.shape[0] == out_tokens.numel()
-        self._check(self._lib.pre3_advance_fill_argmax(self._h, _dev(tokens, "i32"), _dev(bitmask, "u32"),
-                                                       _dev(logits, "u16"), logits.stride(0), _dev(out_tokens, "i32"),
-                                                       (ADVANCE_RESTART_ON_EOS if restart_on_eos else 0) |
-                                                       (STEP_ONE_KERNEL if one_kernel else 0), _stream_ptr(stream)))
+        rows, words = bitmask.shape[:2]
+        assert tokens.is_contiguous() and bitmask.is_contiguous() and words == self.words and out_tokens.is_contiguous()
+        assert logits.dim() == 2 and logits.shape[0] == rows == out_tokens.numel()
+        stride, one = logits.stride()
+        assert one == 1
+        rc = self._lib.pre3_advance_fill_argmax(self._h, _dev(tokens, "i32"), _dev(bitmask, "u32"), _dev(logits, "u16"), stride,
+                                                _dev(out_tokens, "i32"), (ADVANCE_RESTART_ON_EOS if restart_on_eos else 0) |
+                                                (STEP_ONE_KERNEL if one_kernel else 0), _stream_ptr(stream))
+        if rc != PRE3_OK:
+            self._check(rc)
 
     def _step_form(self, logits, one_kernel, greedy):
         rc = self._lib.pre3_step_is_one_kernel(self._h, _dev(logits, "u16"), logits.stride(0),
