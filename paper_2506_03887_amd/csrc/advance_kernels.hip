@@ -706,6 +706,12 @@ __device__ __forceinline__ bool order_undecided(int key) { return key > kOrderPo
 // largest value, first of equal values, +0 = -0, NaN never), the block combines the lanes, and out_tokens[b]
 // is the sequence's next token (-1 if nothing is allowed).  out_tokens may be the tokens buffer: block b
 // reads tokens[b] before anything else and writes out_tokens[b] last.
+// With one row to a unit and up to seventeen groups per lane (kByLane) the waves do not meet before the mask: a block's row loads
+// are served one wave after the other (the first wave has its groups at 5,800 cycles, the last at 20,100), and a wave that has
+// issued all of its loads waits for nothing but the plan, a flag in LDS.  Where the plan is a materialised row, every lane then
+// fetches the mask bytes of its own groups and folds, and the wave that advances copies the mask row out; other rows are put
+// together in LDS.  15.9 -> 14.4 us per launch at 256 x 128,256, 8 greedy steps 127.4 -> 122.7 us.  (The masking step loses by it:
+// stores that begin while other waves fetch, 191 against 215 us per 8 steps.)
 // kRows = 2 (greedy, batches of more rows than compute units): two blocks share a unit, so a lane has half the registers; a block
 // holds the first kHeld groups per lane, fetched under the advance, and streams what follows once it knows the mask,
 // reading nothing that is masked as a whole.  Neither the advance as a launch of its own nor the second round of a grid of
@@ -730,7 +736,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
     load_tables(pack, T, E);
     static_assert(kRows == 1 || (kRows == 2 && kArgmax), "the masking form fills a unit's registers with one row");
     extern __shared__ uint4 bits4[];                   // the mask row; kCompact: then cap stack entries [+ cycle tables]
-    __shared__ int32_t s_walk_stack[kLdsDepth * 64];
+    __shared__ __align__(16) int32_t s_walk_stack[kLdsDepth * 64];
     __shared__ RowPlan plan;
     const int tid = threadIdx.x, lane = tid & 63;
     const int b = first_row + blockIdx.x;          // (a large batch comes as several launches of one row per compute unit)
@@ -797,30 +803,30 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             copy_mask_row(E.dense_rows + (size_t)plan.dense * n_vec * 4, dst_row, T.n_words, lane);
             if (kArgmax) top = step_block_best(-32768, s_key, tid);
         } else {
-        lds_barrier();                                 // the materialised row (or zeros) is in LDS
-        // tokens the tree leaves undetermined are walked on the committed stack, one lane per token
-        PrivateStack wp;
-        wp.lds = s_walk_stack + lane;
-        wp.lds_stride = 64;
-        wp.spill = walk_spill + (size_t)b * 64 + lane;
-        wp.spill_stride = walk_spill_stride;
-        const int mode = plan.mode, n = plan.len, top0 = plan.top;
-        if (mode == kRowWalkAll || (mode == kRowFast && plan.walk_count > 0))
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // the walks read the committed stack
-        if (mode == kRowFast) {
-            const int wc = plan.walk_count;
-            for (int k = lane; k < wc; k += 64) {
-                const int t = E.walk_ids[plan.walk_begin + k];
-                if (walk_token_id(T, wp, t, row, n, top0)) atomicOr(&bits[t >> 5], 1u << (t & 31));
+            lds_barrier();                                 // the materialised row (or zeros) is in LDS
+            // tokens the tree leaves undetermined are walked on the committed stack, one lane per token
+            PrivateStack wp;
+            wp.lds = s_walk_stack + lane;
+            wp.lds_stride = 64;
+            wp.spill = walk_spill + (size_t)b * 64 + lane;
+            wp.spill_stride = walk_spill_stride;
+            const int mode = plan.mode, n = plan.len, top0 = plan.top;
+            if (mode == kRowWalkAll || (mode == kRowFast && plan.walk_count > 0))
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");      // the walks read the committed stack
+            if (mode == kRowFast) {
+                const int wc = plan.walk_count;
+                for (int k = lane; k < wc; k += 64) {
+                    const int t = E.walk_ids[plan.walk_begin + k];
+                    if (walk_token_id(T, wp, t, row, n, top0)) atomicOr(&bits[t >> 5], 1u << (t & 31));
+                }
+            } else if (mode == kRowWalkAll) {
+                for (int t = lane; t < T.n_tokens; t += 64)
+                    if (walk_token_id(T, wp, t, row, n, top0)) atomicOr(&bits[t >> 5], 1u << (t & 31));
+            } else if (mode == kRowDone && lane == 0) {
+                bits[T.eos_id >> 5] = 1u << (T.eos_id & 31);
             }
-        } else if (mode == kRowWalkAll) {
-            for (int t = lane; t < T.n_tokens; t += 64)
-                if (walk_token_id(T, wp, t, row, n, top0)) atomicOr(&bits[t >> 5], 1u << (t & 31));
-        } else if (mode == kRowDone && lane == 0) {
-            bits[T.eos_id >> 5] = 1u << (T.eos_id & 31);
-        }
-        lds_barrier();                                 // the row is complete
-        if (kArgmax) top = step_block_best(-32768, s_key, tid);
+            lds_barrier();                                 // the row is complete
+            if (kArgmax) top = step_block_best(-32768, s_key, tid);
         }
     } else {
         const int j = tid - 64;
@@ -851,7 +857,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             } else {
                 for (int w = j; w < n_vec; w += kStepData) bits4[w] = make_uint4(0, 0, 0, 0);
             }
-            lds_barrier();                                 // the materialised row (or zeros) is in LDS
+            lds_barrier();                             // the materialised row (or zeros) is in LDS
             if (mode == kRowFast) {
                 const int nseg = plan.nseg;
                 for (int i = 0; i < nseg; ++i) {
@@ -863,7 +869,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
                     }
                 }
             }
-            lds_barrier();                                 // the row is complete
+            lds_barrier();                             // the row is complete
             if (vector_ok) {
                 uint4 *dst4 = reinterpret_cast<uint4 *>(dst_row);
                 for (int w = j; w < n_vec; w += kStepData) stream_store(bits4[w], dst4 + w);
@@ -872,7 +878,8 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             }
         };
         auto group_fold = [&](uint4 v, uint32_t mu) { mask_keys(v, mu); return fold(v); };
-        uint32_t best2 = 0x80008000u, folded[kArgmax && kRows == 1 ? kHeld : 1];   // kArgmax, one row: the lane's best keys, the best of each of its groups (two halves)
+        // kArgmax, one row to a unit: the lane's best keys and those of each of its groups, in the halves of a register
+        uint32_t best2 = 0x80008000u, folded[kArgmax && kRows == 1 ? kHeld : 1];
         const uint8_t *mask_bytes = reinterpret_cast<const uint8_t *>(bits4);     // byte g = bits of group g
         auto masked = [&](int i, uint32_t mu) {
             folded[i] = group_fold(held[i], mu);
@@ -947,7 +954,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
             // Per group: the AND masks of the two halves of the mask byte come from the LDS table, masked halves
             // get the lowest key and three packed maxima fold the group; what is left of it (one register) stays, and
             // one more packed maximum is the lane's best.  The block's best key is found first (step_block_best);
-            // only the lanes that hold it then look for the group, and in the group for the token.
+            // only the waves that hold it then look for the group, and in the group for the token.
             auto mask_byte_of = [&](int g) -> uint32_t {
                 if (by_lane) return (E.dense_rows[(size_t)plan.dense * n_vec * 4 + (g >> 2)] >> ((g & 3) * 8)) & 0xFFu;
                 return mask_bytes[g];
