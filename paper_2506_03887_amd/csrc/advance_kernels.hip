@@ -978,7 +978,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
                 if (!kByLane) masked_from_lds();
                 best = max(half_max(best2), tail_fold);
                 top = step_block_best(best, s_key, tid);
-                unsigned long long holders = __ballot(best == top);
+                const unsigned long long holders = __ballot(best == top);
                 if constexpr (!kByLane) {
                     if (best == top) {
                         // the first of a lane's groups that holds the value (its groups ascend, the partial one is the last)
@@ -997,35 +997,42 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
                     auto has = [&](uint32_t x) {
                         return (int)(int16_t)(x & 0xFFFFu) == top || (int)x >> 16 == top;
                     };
-                    int token = 0x7FFFFFFF;
-                    do {                                // (one lane but for ties)
-                        const int who = __ffsll((long long)holders) - 1;
-                        holders &= holders - 1ull;
+                    int who = __ffsll((long long)holders) - 1, i = -1;                     // the lane, its group (-1: the partial one)
+                    if ((holders & (holders - 1ull)) == 0ull) {
                         __builtin_amdgcn_wave_barrier();
                         if (lane == who) {
 #pragma unroll
-                            for (int i = 0; i < kHeld; ++i) spot[i] = folded[i];
+                            for (int u = 0; u < kHeld; ++u) spot[u] = folded[u];
                         }
                         __builtin_amdgcn_wave_barrier();
                         const uint32_t f = spot[lane < kHeld ? lane : 0];
                         const unsigned long long here = __ballot(lane < kHeld && has(f));
-                        const int i = here != 0ull ? __ffsll((long long)here) - 1 : -1;       // -1: in the partial group
-                        at = i >= 0 ? i * kStepData + wave * 64 + who : whole;
-                        __builtin_amdgcn_wave_barrier();
-                        if (lane == who) {
-                            if (i < 0) {
-                                *reinterpret_cast<uint4 *>(spot) = tail_keys;
-                            } else {
+                        i = here != 0ull ? __ffsll((long long)here) - 1 : -1;
+                    } else {
+                        // Several lanes: ids ascend by group, then by lane, so the first lane of the first group that holds the value
+                        // has it (no lane beside the first one of the row has the partial group).  8 steps of 256 x 128,256 equal logits
+                        // 131 us, 1,218 with one lane after the other (152 with a select over all groups in every lane).
 #pragma unroll
-                                for (int u = 0; u < kHeld; ++u) reinterpret_cast<uint4 *>(spot)[u] = held[u];
-                            }
+                        for (int u = kHeld - 1; u >= 0; --u) {
+                            const unsigned long long in = __ballot(has(folded[u]));
+                            if (in != 0ull) { i = u; who = __ffsll((long long)in) - 1; }
                         }
-                        __builtin_amdgcn_wave_barrier();
-                        const int key = reinterpret_cast<const int16_t *>(spot)[(i > 0 ? i * 8 : 0) + (lane & 7)];
-                        uint32_t hold = (uint32_t)__ballot(lane < 8 && key == top);            // tokens with that key, masked ones among them
-                        if ((hold & (hold - 1u)) != 0u) hold &= i < 0 ? (uint32_t)__builtin_amdgcn_readfirstlane(tail_m) : mask_byte_of(at);
-                        token = min(token, at * 8 + __builtin_ctz(hold | 0x80u));
-                    } while (holders != 0ull);
+                    }
+                    at = i >= 0 ? i * kStepData + wave * 64 + who : whole;
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane == who) {
+                        if (i < 0) {
+                            *reinterpret_cast<uint4 *>(spot) = tail_keys;
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < kHeld; ++u) reinterpret_cast<uint4 *>(spot)[u] = held[u];
+                        }
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    const int key = reinterpret_cast<const int16_t *>(spot)[(i > 0 ? i * 8 : 0) + (lane & 7)];
+                    uint32_t hold = (uint32_t)__ballot(lane < 8 && key == top);            // tokens with that key, masked ones among them
+                    if ((hold & (hold - 1u)) != 0u) hold &= i < 0 ? (uint32_t)__builtin_amdgcn_readfirstlane(tail_m) : mask_byte_of(at);
+                    const int token = at * 8 + __builtin_ctz(hold | 0x80u);
                     if (lane == 0) atomicMin(&s_token, token);
                 }
             } else {

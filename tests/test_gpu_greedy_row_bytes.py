@@ -69,3 +69,65 @@ def test_greedy_step_on_materialised_and_other_rows(V, B, pad, offset, options):
         tokens[rng.random(B) < 0.15] = v.eos_id         # some end (and stay finished), some are refused it
         tok_d.copy_(torch.from_numpy(tokens))
     assert lib.fault_count() == 0
+
+
+@pytest.mark.parametrize("V,B", [(70_000, 128), (128_256, 256)])
+def test_equal_logits(V, B):
+    """Rows of one value (the best token is the first allowed one, every lane holds the best), of a value that half of the allowed
+    tokens have, and of one that only the partial group and another lane's groups have: the oracle's tokens, and a step takes no
+    more than twice as long as on random logits (with the lanes that hold the best looked at one after the other: nine times)."""
+    import torch
+    from paper_2506_03887_amd import Pre3
+    dev, cap, V = torch.device("cuda:0"), 48, V + 3
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the lines of the dispatch are drawn for 256 compute units")
+    v, o = _vocab(V), Oracle(G.JSON)
+    lib = Pre3(G.JSON, v.bytes, v.offsets, v.eos_id, max_token_len=v.max_len, stack_cap=cap)
+    text = o.advance(o.initial_stack(0), b'["a')[1]          # inside a string: most tokens are allowed
+    data = np.zeros((B, cap), np.int32)
+    data[:, : len(text)] = text
+    d_d, l_d = torch.from_numpy(data).to(dev), torch.full((B,), len(text), dtype=torch.int32, device=dev)
+    s_d, err_d = d_d[:, len(text) - 1].contiguous(), torch.zeros(B, dtype=torch.int32, device=dev)
+    lib.bind_state(s_d, d_d, l_d, err_d)
+    mask_d, out_d = torch.zeros((B, v.words), dtype=torch.int32, device=dev), torch.zeros(B, dtype=torch.int32, device=dev)
+    none = torch.full((B,), v.eos_id, dtype=torch.int32, device=dev)       # refused here: the stacks stay as they are
+    mask = o.fill_mask(s_d.cpu().numpy(), data, np.full(B, len(text), np.int32), v)
+    allowed = np.flatnonzero((mask[0, np.arange(V) >> 5] >> (np.arange(V) & 31).astype(np.uint32)) & 1)
+    assert len(allowed) > V // 3
+    rng = np.random.default_rng(V)
+    logits = torch.zeros((B, V + 5), dtype=torch.bfloat16, device=dev)[:, :V]
+    assert lib.step_form(logits, greedy=True) == "one kernel"
+
+    def step():
+        lib.advance_fill_argmax(none, mask_d, logits, out_d)
+
+    def us_per_step():
+        for _ in range(5):
+            step()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        times = []
+        for _ in range(7):
+            a.record()
+            for _ in range(20):
+                step()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 50)
+        return sorted(times)[3]
+
+    took = {}
+    for kind in ("random", "equal", "half", "ends"):
+        host = bf16_logits(rng, B, V)
+        if kind == "equal":
+            host[:] = np.where(np.arange(B) % 2, 0x4000, 0xC000)[:, None]
+        elif kind == "half":
+            host[rng.random(host.shape) < 0.5] = 0x4300
+        elif kind == "ends":
+            host[:, np.append(allowed[-1:], allowed[-1:] - np.arange(1, 4) * 8 * LANES)] = 0x4300
+        logits.copy_(torch.from_numpy(host.view(np.int16)).to(dev).view(torch.bfloat16))
+        step()
+        assert (out_d.cpu().numpy() == oracle_masked_argmax(host, mask, V)).all(), kind
+        assert (mask_d.cpu().numpy().view(np.uint32) == mask).all() and (err_d.cpu().numpy() == 1).all(), kind
+        took[kind] = us_per_step()
+    print(took)
+    assert max(took.values()) < 2 * took["random"], took
