@@ -189,9 +189,9 @@ __device__ __forceinline__ int fold_cycles(int32_t *s, int n, const int32_t *cyc
             if (seg > 0) {
                 if (w != r0 + prev) {                   // all lanes read, then all lanes write: the ranges may overlap
                     const int v = lane < seg ? s[r0 + prev + lane] : 0;
-                    __builtin_amdgcn_wave_barrier();
+                    wave_exchange();
                     if (lane < seg) s[w + lane] = v;
-                    __builtin_amdgcn_wave_barrier();
+                    wave_exchange();
                     moved = w < moved ? w : moved;
                 }
                 w += seg;
@@ -427,7 +427,7 @@ __device__ __forceinline__ void fold_new_stack(Advanced &r, const WaveStack &ws,
             stack[i] = p < 0 ? old : pushed;
         }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_exchange();
     int nl = r.nl, first_moved = nl;                    // (1 after a restart: only the bottom entry stays)
     if (nl >= 2) nl = fold_cycles(stack, nl, cycle_head, cycle_pool, n_states, lane, &first_moved);
     r.from = r.restarted ? nl : (first_moved < r.base ? first_moved : r.base);
@@ -999,12 +999,12 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
                     };
                     int who = __ffsll((long long)holders) - 1, i = -1;                     // the lane, its group (-1: the partial one)
                     if ((holders & (holders - 1ull)) == 0ull) {
-                        __builtin_amdgcn_wave_barrier();
+                        wave_exchange();
                         if (lane == who) {
 #pragma unroll
                             for (int u = 0; u < kHeld; ++u) spot[u] = folded[u];
                         }
-                        __builtin_amdgcn_wave_barrier();
+                        wave_exchange();
                         const uint32_t f = spot[lane < kHeld ? lane : 0];
                         const unsigned long long here = __ballot(lane < kHeld && has(f));
                         i = here != 0ull ? __ffsll((long long)here) - 1 : -1;
@@ -1019,17 +1019,18 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
                         }
                     }
                     at = i >= 0 ? i * kStepData + wave * 64 + who : whole;
-                    __builtin_amdgcn_wave_barrier();
+                    wave_exchange();
                     if (lane == who) {
                         if (i < 0) {
-                            *reinterpret_cast<uint4 *>(spot) = tail_keys;
+                            __builtin_memcpy(__builtin_assume_aligned(spot, 16), &tail_keys, 16);
                         } else {
 #pragma unroll
-                            for (int u = 0; u < kHeld; ++u) reinterpret_cast<uint4 *>(spot)[u] = held[u];
+                            for (int u = 0; u < kHeld; ++u) __builtin_memcpy(__builtin_assume_aligned(spot + u * 4, 16), &held[u], 16);
                         }
                     }
-                    __builtin_amdgcn_wave_barrier();
-                    const int key = reinterpret_cast<const int16_t *>(spot)[(i > 0 ? i * 8 : 0) + (lane & 7)];
+                    wave_exchange();
+                    const uint32_t pair = spot[(i > 0 ? i * 4 : 0) + ((lane & 7) >> 1)];
+                    const int key = (int16_t)(pair >> (16 * (lane & 1)));
                     uint32_t hold = (uint32_t)__ballot(lane < 8 && key == top);            // tokens with that key, masked ones among them
                     if ((hold & (hold - 1u)) != 0u) hold &= i < 0 ? (uint32_t)__builtin_amdgcn_readfirstlane(tail_m) : mask_byte_of(at);
                     const int token = at * 8 + __builtin_ctz(hold | 0x80u);
@@ -1535,7 +1536,7 @@ __global__ __launch_bounds__(64 * kJfSeqPerBlock) void jump_forward_kernel(
         __threadfence_block();
         int32_t *stack = jf_stage + wave * cap;
         for (int i = lane; i < n; i += 64) stack[i] = row[i];
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         int first_moved = n;
         const int w = fold_cycles(stack, n, cycle_head, cycle_pool, T.n_states, lane, &first_moved);
         if (w != n) {
@@ -1572,7 +1573,7 @@ __global__ __launch_bounds__(256) void compact_stacks_kernel(const int32_t *__re
         any |= (unsigned)x < (unsigned)n_states && cycle_head[x] >= 0;
     }
     if (!__any(any)) return;
-    __builtin_amdgcn_wave_barrier();
+    wave_exchange();
     int first_moved;
     const int w = fold_cycles(s, n, cycle_head, pool, n_states, lane, &first_moved);
     if (w != n) {

@@ -1,12 +1,20 @@
 // The greedy choice among allowed bf16 logits: order keys, the candidate word that lanes, waves and
 // blocks are combined through, and the exact float-compare pass for the rows the keys cannot decide.
-// Shared by the sampler kernel and the one-launch greedy step kernel.
+// Shared by the sampler kernel and the one-launch greedy step kernel, with the exchange between lanes of a wave through LDS.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
 namespace pre3 {
+
+// Between what lanes of a wave lay in LDS and what other lanes of it read there (or write over it).  The lanes run together and
+// the wave's LDS accesses are served in order, so this is no instruction; the fences keep the compiler from moving the accesses.
+__device__ __forceinline__ void wave_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
 namespace {
 

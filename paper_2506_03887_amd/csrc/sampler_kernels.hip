@@ -277,11 +277,11 @@ __device__ __noinline__ uint32_t topk_cut_list(unsigned long long *list, int n, 
         const unsigned long long w = r0 + lane < n ? list[r0 + lane] : 0ull;
         const bool take = w >= thr;
         const unsigned long long mm = __ballot(take);
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         if (take) list[base + __popcll(mm & ((1ull << lane) - 1ull))] = w;
         base += __popcll(mm);
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_exchange();
     return (uint32_t)(thr >> kTopkIdBits);
 }
 
@@ -796,7 +796,7 @@ __device__ __forceinline__ void topk_segment(
         if (w * 4 < whole && w * 4 + 4 > whole) x = mw[i] & ((1u << ((whole & 3) * 8)) - 1u);
         s_mask[wave * (kG * 16) + i * 64 + lane] = x;
     }
-    __builtin_amdgcn_wave_barrier();                          // (written and read by the same wave)
+    wave_exchange();                          // (written and read by the same wave)
     const uint8_t *mask_bytes = reinterpret_cast<const uint8_t *>(s_mask) + wave * (kG * 64);
     uint32_t kp[kG * 4], mu[kG];
     int gmax[kG], best_i = 0;                                 // the largest pattern of a group, of the thread (as signed numbers)

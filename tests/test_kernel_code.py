@@ -182,3 +182,15 @@ def test_the_flow_of_input_addresses_sees_a_late_load():
     f = flow("s_cbranch_scc1 3", "s_mov_b64 s[4:5], 0", "s_nop 0", "s_load_dword s20, s[4:5], 0x0", "s_endpgm")     # tainted on one way
     assert f.loads == {3}
     assert flow("s_mov_b64 s[4:5], 0", "s_load_dword s20, s[4:5], 0x0", "s_endpgm").loads == set()
+
+
+def test_lanes_exchange_words_through_lds_behind_a_fence():
+    """What a lane lays in LDS for other lanes of its wave is read behind wave_exchange, whose fences hold the compiler (the wave
+    barrier alone does not), and as the words or bytes it was written as: a read through a pointer to 16-bit values need
+    not see stores of words."""
+    from paper_2506_03887_amd.build import CSRC
+    text = {os.path.basename(f): open(f).read() for f in glob.glob(os.path.join(CSRC, "*.h*"))}
+    assert {f: t.count("__builtin_amdgcn_wave_barrier") for f, t in text.items() if "__builtin_amdgcn_wave_barrier" in t} == {"argmax.hpp": 1}
+    fenced = r"ATOMIC_RELEASE, \"wavefront\", \"local\"\);\s+__builtin_amdgcn_wave_barrier\(\);\s+\S+ATOMIC_ACQUIRE, \"wavefront\", \"local\""
+    assert re.search(fenced, text["argmax.hpp"])
+    assert text["advance_kernels.hip"].count("wave_exchange()") >= 7 and "reinterpret_cast<const int16_t *>(s" not in text["advance_kernels.hip"]
