@@ -706,12 +706,14 @@ __device__ __forceinline__ bool order_undecided(int key) { return key > kOrderPo
 // largest value, first of equal values, +0 = -0, NaN never), the block combines the lanes, and out_tokens[b]
 // is the sequence's next token (-1 if nothing is allowed).  out_tokens may be the tokens buffer: block b
 // reads tokens[b] before anything else and writes out_tokens[b] last.
-// With one row to a unit and up to seventeen groups per lane (kByLane) the waves do not meet before the mask: a block's row loads
+// With one row to a unit and ten to seventeen groups per lane (kByLane) the waves do not meet before the mask: a block's row loads
 // are served one wave after the other (the first wave has its groups at 5,800 cycles, the last at 20,100), and a wave that has
 // issued all of its loads waits for nothing but the plan, a flag in LDS.  Where the plan is a materialised row, every lane then
 // fetches the mask bytes of its own groups and folds, and the wave that advances copies the mask row out; other rows are put
-// together in LDS.  15.9 -> 14.4 us per launch at 256 x 128,256, 8 greedy steps 127.4 -> 122.7 us.  (The masking step loses by it:
-// stores that begin while other waves fetch, 191 against 215 us per 8 steps.)
+// together in LDS.  8 greedy steps of 256 x 128,256 126.3 -> 118.1 us on JSON, 136.6 -> 130.9 with cycle-aware stacks.  Twenty groups
+// leave no registers for the mask words.  Up to nine, the logits are there before the plan is, and waves that look for it one by one
+// gain nothing on what meets once: 256 x 52,000 97.1 and 99.9 us, cycle-aware 111.4 and 115.8, 256 x 69,000 115.2 and 117.6.  (The
+// masking step loses too: stores that begin while other waves fetch, 191 against 215 us per 8 steps.)
 // kRows = 2 (greedy, batches of more rows than compute units): two blocks share a unit, so a lane has half the registers; a block
 // holds the first kHeld groups per lane, fetched under the advance, and streams what follows once it knows the mask,
 // reading nothing that is masked as a whole.  Neither the advance as a launch of its own nor the second round of a grid of
@@ -747,8 +749,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
     const bool vector_ok = (T.n_words & 3) == 0 && (reinterpret_cast<uintptr_t>(bitmask) & 15) == 0;
     uint16_t *lrow = logits + (size_t)b * row_stride;
     int top = -32768;                                  // kArgmax: the block's best order key
-    // (not with twenty groups per lane, which leave no registers for the mask words)
-    constexpr bool kByLane = kArgmax && kRows == 1 && kHeld <= 17;
+    constexpr bool kByLane = kArgmax && kRows == 1 && kHeld > 9 && kHeld <= 17;
     bool by_lane = false;                              // kByLane: every lane fetches the mask bytes of its groups, the row is not in LDS
     __shared__ int s_key[kArgmax ? kStepBlock / 64 : 1], s_token;
     if (kArgmax && tid == 0) s_token = 0x7FFFFFFF;     // (read behind three barriers)

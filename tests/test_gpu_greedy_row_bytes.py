@@ -1,5 +1,6 @@
 """The greedy step with one row to a unit, whose waves go on by themselves when the plan is there and mask what they hold with the
-materialised row's bytes: lockstep with the oracle at the edges of both variants' rows, the best token alone, twice in a lane, in
+materialised row's bytes (ten to seventeen groups of logits per lane; shorter rows meet first): lockstep with the oracle at the edges
+of the variants' rows, the best token alone, twice in a lane, in
 two lanes, in two waves and beside masked tokens of the same value, and on rows that are put together in LDS after all (id lists,
 open rows, finished sequences, all in one batch)."""
 import numpy as np

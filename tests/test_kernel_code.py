@@ -194,3 +194,11 @@ def test_lanes_exchange_words_through_lds_behind_a_fence():
     fenced = r"ATOMIC_RELEASE, \"wavefront\", \"local\"\);\s+__builtin_amdgcn_wave_barrier\(\);\s+\S+ATOMIC_ACQUIRE, \"wavefront\", \"local\""
     assert re.search(fenced, text["argmax.hpp"])
     assert text["advance_kernels.hip"].count("wave_exchange()") >= 7 and "reinterpret_cast<const int16_t *>(s" not in text["advance_kernels.hip"]
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no llvm-objdump")
+def test_which_steps_look_for_the_plan_by_themselves(kernels):
+    """The waves of the greedy step poll for the plan where the row's logits take longer than the advance (ten to seventeen groups
+    per lane); shorter rows, which lose by it, the longest and every other form meet at a barrier."""
+    polls = {n for n, code in kernels.items() if "advance_fill_apply_kernel" in n and any(x.startswith("s_sleep") for x in code)}
+    assert {re.search(r"kernelILb[01]ELi(\d+)ELb(\d)ELi(\d)E", n).groups() for n in polls} == {("17", "1", "1")} and len(polls) == 2
