@@ -280,7 +280,10 @@ __device__ __forceinline__ StepInputs read_inputs(const int32_t *tokens, const i
 // rounds, five in the spread step): 1 x 128,256 54.2 -> 52.8 us, 64 x 32,000 67.9 -> 67.1, fill + mask + advance of 96 x 100,003
 // 153.1 -> 151.4, advance + fill before a top-k of 256 x 128,256 179.4 -> 178.2.  The wave that keeps to scalar loads is not held
 // to that order: it has not the registers for all of them at once (greedy 320 x 128,256, cycle-aware, 202.4 us and 203.7 held to it).
-template <bool kScalar, class Meet>
+// kWindowFirst: the window is in its lanes before the token's line is asked for (sixteen and thirty-two scalar registers together pass
+// what the wave has where the block's other waves need the registers most: two rows to a unit, 368 scalars in lanes against 188;
+// cycle-aware stacks on 256 x 150,000 161.5 against 159.1 us; the other forms lose by it: 256 x 128,256 130.7 against 134.5).
+template <bool kScalar, bool kWindowFirst, class Meet>
 __device__ __forceinline__ Advanced advance_stack(const DevTables &T, const DevTokenEdges &E, const StepInputs &in, int cap,
                                                   int restart_on_eos, WaveStack &ws, int lane, Meet meet) {
     const int32_t *row = ws.row;
@@ -308,14 +311,19 @@ __device__ __forceinline__ Advanced advance_stack(const DevTables &T, const DevT
     int32_t line;
     if (kScalar) {
         const int32_t *rec = T.tok_info + (size_t)tc * 32;
+        if (kWindowFirst) {
+            if (cap >= 16) ws.win = deal_window(row, scalar_load16(row + window_chunk(nc, cap, 0)), nc, cap, lane);
+            else ws.win = nc - 1 - lane >= 0 ? row[nc - 1 - lane] : -1;
+            __builtin_amdgcn_sched_barrier(0);
+        }
         const NativeInt16 line0 = scalar_load16(rec), line1 = scalar_load16(rec + 16);
-        if (cap >= 16) {
+        if (!kWindowFirst && cap >= 16) {
             const NativeInt16 first = scalar_load16(row + window_chunk(nc, cap, 0));
             line = deal_token_line(line0, line1);
             ws.win = deal_window(row, first, nc, cap, lane);
         } else {
             line = deal_token_line(line0, line1);
-            ws.win = nc - 1 - lane >= 0 ? row[nc - 1 - lane] : -1;
+            if (!kWindowFirst) ws.win = nc - 1 - lane >= 0 ? row[nc - 1 - lane] : -1;
         }
     } else {
         const int at = nc - 1 - lane;
@@ -488,7 +496,7 @@ __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
     }
     int32_t *row = data + (size_t)b * cap, *stack = adv_stage + wave * cap;
     WaveStack ws{row, scratch + b, (size_t)batch, 0, 0, 0};
-    Advanced r = advance_stack<false>(T, E, in, cap, restart_on_eos, ws, lane,
+    Advanced r = advance_stack<false, false>(T, E, in, cap, restart_on_eos, ws, lane,
                                       [&] { if (kCompact && stage_cycles) __syncthreads(); });
     if (kCompact && r.shape_ok) fold_new_stack(r, ws, stack, cycle_head, cycle_pool, T.n_states, lane);
     commit_advance<kCompact>(r, ws, stack, states, row, len, err, cap, b, lane);
@@ -501,12 +509,12 @@ __global__ __launch_bounds__(64 * kAdvSeqPerBlock) void advance_kernel(
 // after_row + cap meanwhile and meet this wave at one block barrier.
 // The tree is descended BEFORE anything is stored: a wave that has stores in flight waits for them wherever it next waits
 // for a load, and in the one-launch step kernel they complete only behind the row loads of the block's other waves.
-template <bool kCompact, bool kScalar = false>
+template <bool kCompact, bool kScalar = false, bool kWindowFirst = false>
 __device__ __forceinline__ Advanced advance_and_plan(const DevTables &T, const DevTokenEdges &E, const StepInputs &in, int cap,
                                                  int restart_on_eos, WaveStack &ws, const int32_t *cycle_head,
                                                  const int32_t *cycle_pool, int stage_cycles, int32_t *after_row, RowPlan &plan,
                                                  int lane) {
-    Advanced r = advance_stack<kScalar>(T, E, in, cap, restart_on_eos, ws, lane, [&] {
+    Advanced r = advance_stack<kScalar, kWindowFirst>(T, E, in, cap, restart_on_eos, ws, lane, [&] {
         if (kCompact && stage_cycles) {                 // the other waves have copied the cycle tables meanwhile
             __syncthreads();
             int32_t *cycle_lds = after_row + cap;
@@ -750,6 +758,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
     uint16_t *lrow = logits + (size_t)b * row_stride;
     int top = -32768;                                  // kArgmax: the block's best order key
     constexpr bool kByLane = kArgmax && kRows == 1 && kHeld > 9 && kHeld <= 17;
+    constexpr bool kWindowFirst = kArgmax && (kRows == 2 || kHeld > 17);
     bool by_lane = false;                              // kByLane: every lane fetches the mask bytes of its groups, the row is not in LDS
     __shared__ int s_key[kArgmax ? kStepBlock / 64 : 1], s_token;
     if (kArgmax && tid == 0) s_token = 0x7FFFFFFF;     // (read behind three barriers)
@@ -787,7 +796,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
         if (tokens) {
             WaveStack ws{row, adv_scratch + b, (size_t)batch, 0, 0, 0};
             int32_t *after_row = reinterpret_cast<int32_t *>(bits4 + n_vec);
-            const Advanced r = advance_and_plan<kCompact, true>(T, E, in, cap, restart_on_eos, ws, cycle_head, cycle_pool,
+            const Advanced r = advance_and_plan<kCompact, true, kWindowFirst>(T, E, in, cap, restart_on_eos, ws, cycle_head, cycle_pool,
                                                                 stage_cycles, after_row, plan, lane);
             if (kArgmax) plan_ready();
             commit_advance<kCompact>(r, ws, after_row, states, row, len, err, cap, b, lane);

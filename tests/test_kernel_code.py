@@ -8,7 +8,7 @@ import subprocess
 
 import pytest
 
-OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+OBJDUMP, READELF = "/opt/rocm/llvm/bin/llvm-objdump", "/opt/rocm/llvm/bin/llvm-readelf"
 
 
 @pytest.fixture(scope="module")
@@ -35,6 +35,20 @@ def listing(tmp_path_factory):
                 out[name].append((int(m.group(2), 16), m.group(1), target))
     assert out
     return out
+
+
+@pytest.fixture(scope="module")
+def spilled_scalars(tmp_path_factory):
+    """name -> scalar registers kept in lanes of vector registers, by the code object's own notes."""
+    from paper_2506_03887_amd.binding import LIB_PATH
+    at = tmp_path_factory.mktemp("notes")
+    shutil.copy(LIB_PATH, at / "lib.so")
+    subprocess.run([OBJDUMP, "--offloading", str(at / "lib.so")], check=True, capture_output=True)
+    text = "".join(subprocess.run([READELF, "--notes", f], check=True, capture_output=True, text=True).stdout
+                   for f in glob.glob(str(at / "lib.so.*gfx950")))
+    names, counts = re.findall(r"^ {4}\.name: +(\S+)$", text, re.M), re.findall(r"^ {4}\.sgpr_spill_count: +(\d+)$", text, re.M)
+    assert names and len(names) == len(counts)
+    return dict(zip(names, map(int, counts)))
 
 
 @pytest.fixture(scope="module")
@@ -202,3 +216,11 @@ def test_which_steps_look_for_the_plan_by_themselves(kernels):
     per lane); shorter rows, which lose by it, the longest and every other form meet at a barrier."""
     polls = {n for n, code in kernels.items() if "advance_fill_apply_kernel" in n and any(x.startswith("s_sleep") for x in code)}
     assert {re.search(r"kernelILb[01]ELi(\d+)ELb(\d)ELi(\d)E", n).groups() for n in polls} == {("17", "1", "1")} and len(polls) == 2
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
+def test_scalars_that_the_greedy_step_of_two_rows_keeps_in_lanes(spilled_scalars):
+    """Half the registers of a unit for each of two blocks: no more scalars in lanes than the form was measured with (231; the window
+    and the token's line in flight together took 368)."""
+    found = {n: c for n, c in spilled_scalars.items() if re.search(r"advance_fill_apply_kernelILb[01]ELi\d+ELb1ELi2E", n)}
+    assert len(found) == 2 and max(found.values()) <= 231, found
