@@ -1050,39 +1050,39 @@ size_t masked_topk_workspace_bytes(int batch, int vocab) {
 
 // Groups of eight logits per thread of the blocks that a row is cut into (4: the narrow block, 16,384 tokens; else the wide
 // one).  A row that fits the registers of a block is one block's, the smallest that holds it (128,256 tokens, k = 50: 8.0 us
-// for one row, 10.7 for 64, 15.4 for 256, against 9.9 and 14.1 us for 1 and 64 rows in segments of 16,384 tokens and a second
-// launch).  Beyond sixteen groups that depends (us, one block of twenty groups and the other form):
-//   * rows on 16-byte boundaries: from four rows on, and below seven eighths of the twenty groups, where it is even (64 x 152,064
-//     11.8 and 12.6, 200 14.5 and 21.7, 512 31.8 and 42.0, 16 on a schema 11.1 and 11.9; but 1 x 152,064 10.5 and 9.9, 2 x 156,000
-//     11.0 and 10.2, 3 x 163,840 10.8 and 10.4);
-//   * other rows, whose loads a block gets through more slowly: only where two blocks a row are more than one round of the chip
-//     (160,003 tokens: 200 rows 20.8 and 28.3, 300 38.0 and 39.9; but 128 19.8 and 17.8, 32 18.3 and 16.1, and, against segments,
-//     16 17.8 and 12.4, 2 16.9 and 10.9).
+// for one row, 10.7 for 64, 15.4 for 256), except
+//   * small batches of the rows that one block streams longest, which go over narrow blocks that hand over in one launch.  That costs
+//     the exchange (a store, a count and a load past the L2s, about 2.5 us) and saves the stream of one compute unit and, where few
+//     tokens are allowed, the ranking of all of them by one block.  us, narrow blocks and one block, k = 50 (64; k = 50 with 1 in 1,024 tokens
+//     allowed): 24 x 131,073 9.2 and 11.2 (11.1 and 11.5; 10.4 and 15.1), 17 x 139,264 9.0 and 10.4 (11.1 and 10.7), 8 x 152,064 8.5 and 10.7
+//     (10.6 and 11.0; 9.8 and 12.6), 24 x 152,064 9.4 and 11.1 (11.5 and 11.4; 10.6 and 14.9), 25 x 163,840 9.7 and 11.2 (11.8 and 11.4; 11.1 and
+//     14.0); 4 x 128,256 8.2 and 9.3 (10.5 and 9.6; 9.7 and 11.9), 16 x 128,256 8.8 and 9.7 (11.0 and 10.0; 10.1 and 13.2), 24 x 128,256 9.4 and
+//     9.8; 8 x 114,689 8.2 and 9.6.  Rows of more than sixteen groups take them while their blocks fit the compute units once (beyond, 31 x
+//     163,840 10.7 and 11.4, 12.8 and 11.7 with k = 64), rows of more than fourteen for half of the units; a block lists a quarter more than k
+//     tokens, and where that passes the words it hands over it ranks them first: then for an eighth.  On shorter rows they lose (16 x
+//     65,000 10.0 and 7.8);
+//   * rows of more than sixteen groups off 16-byte boundaries, whose loads a block gets through more slowly: twenty groups only where
+//     two blocks a row are more than one round of the chip (160,003 tokens: 200 rows 20.8 and 28.3, 300 38.0 and 39.9; but 128 19.8 and
+//     17.8, 32 18.3 and 16.1, and, against narrow blocks, 16 17.8 and 12.4, 2 16.9 and 10.9); on 16-byte boundaries they win (64 x
+//     152,064 11.8 and 12.6, 200 14.5 and 21.7, 512 31.8 and 42.0).
 // A longer row is cut into wide blocks unless the batch is too small to fill the chip with them (at the line, 31 rows
-// of 200,000 tokens take 13.8 to 14.4 us in segments of 16,384 and 13.7 in blocks), of twenty groups where those come to
+// of 200,000 tokens take 13.8 to 14.4 us in narrow blocks and 13.7 in wide ones), of twenty groups where those come to
 // fewer rounds (280,000 tokens: 128 rows 19.4 us, 27.3 in blocks of sixteen; 256 33.5 and 40.6; but 500,000 x 32 15.9 and 14.3,
-// 400,000 x 64 16.3 and 15.4).  (The forms in several blocks were measured with a second launch that merged their lists; merged by
+// 400,000 x 64 16.3 and 15.4).  (This and the line before: measured with a second launch that merged the blocks' lists; merged by
 // the last of the blocks they take 0.6 to 1.9 us less: 2 x 160,003 10.6 -> 9.4, 31 x 160,003 13.0 -> 11.9, 16 x 200,000 11.2 -> 10.3,
-// 40 x 200,000 13.6 -> 13.0, 16 x 131,075 11.2 -> 10.3, with few allowed tokens 12.6 -> 10.8.)
-int masked_topk_groups(int vocab, int batch, bool aligned, int n_compute_units) {
+// 40 x 200,000 13.6 -> 13.0.)
+int masked_topk_groups(int vocab, int batch, bool aligned, int k, int n_compute_units) {
     constexpr int kPerGroup = 8 * kTopkBlockWide;
     if (vocab <= kTopkChunk) return 4;
+    const int most = vocab > 8 * kTopkChunk ? n_compute_units : vocab > 7 * kTopkChunk ? n_compute_units / (k * 5 / 4 <= kTopkMax ? 2 : 8) : 0;
+    if (batch * masked_topk_chunks(vocab) <= most) return 4;
     for (int g : {8, 12, 16})
         if (vocab <= g * kPerGroup) return g;
-    if (vocab <= kTopkRowTokens && aligned && (batch > 3 || vocab < kTopkRowTokens / 8 * 7)) return 20;
+    if (vocab <= kTopkRowTokens && aligned) return 20;
     if (batch * 8 < n_compute_units) return 4;
     const int shorter = vocab <= 24 * kPerGroup ? 12 : 16;
     auto rounds = [&](int g) { return (batch * masked_topk_chunks(vocab, g * kPerGroup) + n_compute_units - 1) / n_compute_units; };
     return rounds(20) < rounds(shorter) ? 20 : shorter;
-}
-
-// Small batches of rows that one block streams longest: cut into blocks of 16,384 tokens, which hand over in one launch.  What that
-// costs is the exchange (a store, a count and a load past the L2s, about 2.5 us); what it saves is the stream of one compute unit.
-// us per call, spread and not: 1 x 152,064 7.9 and 9.3, 4 x 152,064 8.8 and 10.7, 16 x 152,064 9.9 and 11.1 (few allowed: 10.5 and 10.7),
-// 24 x 152,064 10.4 and 11.2 (11.2 and 11.2); 1 x 128,256 8.2 and 8.8, 4 x 128,256 8.9 and 9.6, but 8 x 128,256 9.0 and 9.3 (10.3 and 9.8),
-// 32 x 128,256 10.2 and 10.1, 16 x 65,000 10.0 and 7.8.
-bool masked_topk_spread(int vocab, int batch, int n_compute_units) {
-    return vocab > 7 * kTopkChunk && batch * masked_topk_chunks(vocab) <= (vocab > 8 * kTopkChunk ? n_compute_units * 5 / 8 : n_compute_units / 8);
 }
 
 hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,
@@ -1100,9 +1100,9 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS, SEVERAL>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, \
                        vocab, row_stride, n_words, k, workspace, out_ids, out_vals, arrivals)
     int n_seg = 1;
-    switch (masked_topk_spread(vocab, batch, n_compute_units) ? 4 : masked_topk_groups(vocab, batch, aligned, n_compute_units)) {
+    switch (masked_topk_groups(vocab, batch, aligned, k, n_compute_units)) {
         case 4: PRE3_TOPK_ROW(kTopkBlock, 4); break;
-        case 8: PRE3_TOPK_ROW(kTopkBlockWide, 8); break;
+        case 8: PRE3_TOPK_BLOCKS(kTopkBlockWide, 8, false); break;          // (always one block)
         case 12: PRE3_TOPK_ROW(kTopkBlockWide, 12); break;
         case 16: PRE3_TOPK_ROW(kTopkBlockWide, 16); break;
         default: PRE3_TOPK_ROW(kTopkBlockWide, 20);

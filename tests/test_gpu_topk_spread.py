@@ -8,20 +8,10 @@ from oracle import masked_topk
 from workloads.vocab import Vocab, bf16_logits
 
 
-def test_lines_of_the_rule():
-    import ctypes
-    from paper_2506_03887_amd import load
-    rule = load()["_ZN4pre318masked_topk_spreadEiii"]
-    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_int] * 3
-    spread = lambda V, batch: bool(rule(V, batch, 256))
-    assert not spread(16_384, 1) and not spread(114_688, 1)
-    assert spread(114_689, 4) and not spread(114_689, 5) and spread(131_072, 4)
-    assert spread(131_073, 17) and not spread(131_073, 18) and spread(152_064, 16) and not spread(163_841, 15)
-
-
 @pytest.mark.gpu
-@pytest.mark.parametrize("V,B,pad,offset", [(114_689, 4, 7, 0), (128_256, 1, 0, 0), (131_073, 17, 0, 1), (152_064, 16, 0, 0), (163_840, 16, 3, 3),
-                                            (180_225, 14, 0, 0), (262_149, 40, 0, 0)])
+@pytest.mark.parametrize("V,B,pad,offset", [(114_689, 4, 7, 0), (128_256, 1, 0, 0), (131_072, 16, 0, 5), (131_073, 17, 0, 1), (131_073, 28, 7, 0),
+                                            (152_064, 16, 0, 0), (152_064, 25, 0, 0), (163_840, 16, 3, 3), (180_225, 14, 0, 0),
+                                            (262_149, 40, 0, 0)])
 def test_blocks_that_hand_over(V, B, pad, offset):
     import torch
     from test_gpu_argmax import _bound_lib

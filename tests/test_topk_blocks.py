@@ -5,17 +5,20 @@ import ctypes
 import pytest
 
 
-def _groups(V, batch, aligned):
+def _groups(V, batch, aligned, k):
     from paper_2506_03887_amd import load
-    rule = load()["_ZN4pre318masked_topk_groupsEiibi"]
-    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.c_int]
-    return rule(V, batch, aligned, 256)
+    rule = load()["_ZN4pre318masked_topk_groupsEiibii"]
+    rule.restype, rule.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.c_int, ctypes.c_int]
+    return rule(V, batch, aligned, k, 256)
 
 
 @pytest.mark.parametrize("V,batch,aligned,groups", [
-    (1, 1, True, 4), (16_384, 300, False, 4), (16_385, 1, False, 8), (65_537, 1, True, 12), (98_305, 256, False, 16), (131_072, 1, False, 16),
-    # one block of twenty groups: aligned rows, except one to three of the longest
-    (131_073, 1, True, 20), (143_359, 3, True, 20), (143_360, 3, True, 4), (143_360, 4, True, 20), (163_840, 1, True, 4), (163_840, 512, True, 20),
+    (1, 1, True, 4), (16_384, 300, False, 4), (16_385, 1, False, 8), (65_537, 1, True, 12), (98_305, 256, False, 16), (131_072, 256, False, 16),
+    # small batches of the rows that one block streams longest: narrow blocks that hand over
+    (114_688, 1, True, 16), (114_689, 16, True, 4), (114_689, 17, False, 16), (131_072, 16, False, 4), (131_072, 17, True, 16), (131_073, 1, True, 4),
+    (131_073, 28, True, 4), (131_073, 29, True, 20), (147_456, 28, False, 4), (147_457, 25, True, 4), (147_457, 26, True, 20), (152_064, 24, True, 4),
+    # one block of twenty groups: aligned rows
+    (143_360, 40, True, 20), (163_840, 25, True, 4), (163_840, 26, True, 20), (163_840, 512, True, 20),
     # other rows: segments, two blocks a row, and twenty groups where two blocks a row do not fit the chip at once
     (131_073, 1, False, 4), (160_003, 31, False, 4), (131_075, 32, False, 12), (160_003, 128, False, 12), (160_003, 129, False, 20),
     (163_840, 256, False, 20), (163_840, 512, False, 20),
@@ -23,7 +26,13 @@ def _groups(V, batch, aligned):
     (163_841, 31, True, 4), (163_841, 300, True, 12), (196_609, 300, True, 16), (262_144, 300, False, 16), (262_145, 64, True, 16),
     (262_145, 85, True, 16), (262_145, 86, True, 20), (280_000, 128, False, 20), (280_000, 256, True, 20), (400_000, 100, True, 16), (500_000, 64, True, 16)])
 def test_lines_of_the_rule(V, batch, aligned, groups):
-    assert _groups(V, batch, aligned) == groups
+    assert _groups(V, batch, aligned, 50) == groups
+
+
+@pytest.mark.parametrize("V,batch,groups", [(114_689, 4, 4), (114_689, 5, 16), (131_072, 5, 16), (131_073, 28, 4), (131_073, 29, 20), (163_840, 25, 4)])
+def test_lines_of_the_rule_for_the_longest_lists(V, batch, groups):
+    assert _groups(V, batch, True, 52) == _groups(V, batch, True, 64) == groups
+    assert _groups(V, min(batch, 16), True, 51) == 4
 
 
 @pytest.mark.gpu
