@@ -954,9 +954,14 @@ __device__ __forceinline__ void topk_merge(const unsigned long long *__restrict_
     unsigned long long c[kPer], top = 0ull;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        // neighbouring threads take words of different blocks: a block's words may be ranked, and four of those under one maximum
-        // left four times k words to rank (16 x 200,000, k = 64: 15.9 us, so 11.3; k = 50, where they come as they were found, 10.3 and 9.3)
-        const int at = i * kBlock + tid, nth = at / n_seg, from = at - nth * n_seg;
+        // The threads of one maximum take words far apart in a block's list (a wave one block's 512 bytes), or of different blocks: where a
+        // block has ranked its words first, neighbours under one maximum left four times k words to rank (16 x 200,000, k = 64: 15.9 us,
+        // 11.3 with neighbours of different blocks, so 9.6; k = 50 10.3, 9.3, 9.1; 40 and fewer lose 2 % by it).
+        constexpr int kLanes = kBlock / kTopkMaxima;
+        const int at = i * kBlock + tid;
+        int from = at / kTopkMax, nth = at % kTopkMax;
+        if (k > kTopkMax * 3 / 4) nth = nth % kLanes * (kTopkMax / kLanes) + nth / kLanes;
+        if (width != kTopkMax) { nth = at / n_seg; from = at - nth * n_seg; }
         c[i] = 0ull;
         if (at < n_cand)
             c[i] = __hip_atomic_load(workspace + ((size_t)b * n_seg + from) * kTopkMax + nth, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -60,7 +60,7 @@ def test_blocks_that_hand_over(V, B, pad, offset):
 
 @pytest.mark.gpu
 def test_time_of_the_longest_lists():
-    """16 x 200,000: the 64 best take no more than 1.38 times as long as the 50 best (1.22; 1.54 where the words that blocks rank
+    """16 x 200,000: the 64 best take no more than 1.15 times as long as the 50 best (1.05; 1.24 and 1.54 where the words that blocks rank
     first lay side by side before the block that merges them)."""
     import torch
     from test_gpu_argmax import _bound_lib
@@ -88,4 +88,4 @@ def test_time_of_the_longest_lists():
             times.append(a.elapsed_time(b) * 1e3 / (8 * len(logits)))
         took[k] = sorted(times)[4]
     print(took)
-    assert took[64] < 1.38 * took[50], took
+    assert took[64] < 1.15 * took[50], took
