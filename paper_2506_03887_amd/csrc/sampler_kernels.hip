@@ -1059,12 +1059,11 @@ size_t masked_topk_workspace_bytes(int batch, int vocab) {
 //   * small batches of the rows that one block streams longest, which go over narrow blocks that hand over in one launch.  That costs
 //     the exchange (a store, a count and a load past the L2s, about 2.5 us) and saves the stream of one compute unit and, where few
 //     tokens are allowed, the ranking of all of them by one block.  us, narrow blocks and one block, k = 50 (64; k = 50 with 1 in 1,024 tokens
-//     allowed): 24 x 131,073 9.2 and 11.2 (11.1 and 11.5; 10.4 and 15.1), 17 x 139,264 9.0 and 10.4 (11.1 and 10.7), 8 x 152,064 8.5 and 10.7
-//     (10.6 and 11.0; 9.8 and 12.6), 24 x 152,064 9.4 and 11.1 (11.5 and 11.4; 10.6 and 14.9), 25 x 163,840 9.7 and 11.2 (11.8 and 11.4; 11.1 and
-//     14.0); 4 x 128,256 8.2 and 9.3 (10.5 and 9.6; 9.7 and 11.9), 16 x 128,256 8.8 and 9.7 (11.0 and 10.0; 10.1 and 13.2), 24 x 128,256 9.4 and
-//     9.8; 8 x 114,689 8.2 and 9.6.  Rows of more than sixteen groups take them while their blocks fit the compute units once (beyond, 31 x
-//     163,840 10.7 and 11.4, 12.8 and 11.7 with k = 64), rows of more than fourteen for half of the units; a block lists a quarter more than k
-//     tokens, and where that passes the words it hands over it ranks them first: then for an eighth.  On shorter rows they lose (16 x
+//     allowed): 8 x 131,073 8.1 and 10.7 (8.5 and 11.0; 8.3 and 14.5), 28 x 131,073 9.0 and 11.3 (9.2 and 11.6; 9.2 and 15.2), 1 x 152,064 7.9
+//     and 9.4 (8.3 and 12.6; 8.1 and 9.7), 25 x 152,064 9.3 and 11.1 (9.6 and 11.4; 9.5 and 14.9), 25 x 163,840 9.3 and 11.3 (9.8 and 11.6; 9.5
+//     and 14.1); 1 x 128,256 7.6 and 8.9 (8.0 and 9.2; 7.9 and 9.0), 16 x 128,256 8.4 and 9.8 (8.7 and 10.0; 8.6 and 13.3), 16 x 114,689 8.4 and 9.9.
+//     Rows of more than sixteen groups take them while their blocks fit the compute units once (with a few more, 31 x 163,840 with k = 64,
+//     12.8 and 11.7), rows of more than fourteen for half of the units (24 x 128,256 9.4 and 9.8).  On shorter rows they lose (16 x
 //     65,000 10.0 and 7.8);
 //   * rows of more than sixteen groups off 16-byte boundaries, whose loads a block gets through more slowly: twenty groups only where
 //     two blocks a row are more than one round of the chip (160,003 tokens: 200 rows 20.8 and 28.3, 300 38.0 and 39.9; but 128 19.8 and
@@ -1076,10 +1075,10 @@ size_t masked_topk_workspace_bytes(int batch, int vocab) {
 // 400,000 x 64 16.3 and 15.4).  (This and the line before: measured with a second launch that merged the blocks' lists; merged by
 // the last of the blocks they take 0.6 to 1.9 us less: 2 x 160,003 10.6 -> 9.4, 31 x 160,003 13.0 -> 11.9, 16 x 200,000 11.2 -> 10.3,
 // 40 x 200,000 13.6 -> 13.0.)
-int masked_topk_groups(int vocab, int batch, bool aligned, int k, int n_compute_units) {
+int masked_topk_groups(int vocab, int batch, bool aligned, int n_compute_units) {
     constexpr int kPerGroup = 8 * kTopkBlockWide;
     if (vocab <= kTopkChunk) return 4;
-    const int most = vocab > 8 * kTopkChunk ? n_compute_units : vocab > 7 * kTopkChunk ? n_compute_units / (k * 5 / 4 <= kTopkMax ? 2 : 8) : 0;
+    const int most = vocab > 8 * kTopkChunk ? n_compute_units : vocab > 7 * kTopkChunk ? n_compute_units / 2 : 0;
     if (batch * masked_topk_chunks(vocab) <= most) return 4;
     for (int g : {8, 12, 16})
         if (vocab <= g * kPerGroup) return g;
@@ -1105,7 +1104,7 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS, SEVERAL>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, \
                        vocab, row_stride, n_words, k, workspace, out_ids, out_vals, arrivals)
     int n_seg = 1;
-    switch (masked_topk_groups(vocab, batch, aligned, k, n_compute_units)) {
+    switch (masked_topk_groups(vocab, batch, aligned, n_compute_units)) {
         case 4: PRE3_TOPK_ROW(kTopkBlock, 4); break;
         case 8: PRE3_TOPK_BLOCKS(kTopkBlockWide, 8, false); break;          // (always one block)
         case 12: PRE3_TOPK_ROW(kTopkBlockWide, 12); break;
