@@ -63,7 +63,7 @@ _lib = None
 
 def load():
     """Loads the built library; raises if it has not been built (no fallback exists)."""
-    global _lib, _torch, _current_device, _current_stream
+    global _lib, _torch, _current_device, _current_stream, _in_bad_fork
     if _lib is not None:
         return _lib
     # PyTorch ships its own HIP runtime: it must be in the process before libpre3.so is
@@ -117,19 +117,23 @@ def load():
                   u8=(torch.uint8,))
     if hasattr(torch._C, "_cuda_getDevice"):
         _current_device, _current_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+        _in_bad_fork = torch._C._cuda_isInBadFork
     _torch, _lib = torch, lib
     return lib
 
 
-_torch = _current_device = _current_stream = None          # set by load(), with the dtypes each kind of buffer may have
+_torch = _current_device = _current_stream = _in_bad_fork = None          # set by load(), with the dtypes each kind of buffer may have
 _KINDS = {}
 
 
 def _stream_ptr(stream):
     """Handle of `stream` (a torch stream or a plain handle), by default the current stream of the current device.
     The handle is asked for directly: building a torch.cuda.Stream object for it took 3.0 of the 13 us of a call.  (Where the
-    tensors are, the GPU has been initialised, which is what torch.cuda.current_device looks for first.)"""
+    tensors are, the GPU has been initialised, which is what torch.cuda.current_device looks for first -- unless by the
+    process that this one was forked from.)"""
     if stream is None:
+        if _in_bad_fork():
+            _torch.cuda.current_device()                # raises, and says why
         return _current_stream(_current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
