@@ -358,9 +358,9 @@ class Pre3:
     def advance_fill_apply_mask(self, tokens, bitmask, logits, restart_on_eos=False, one_kernel=False, stream=None):
         """The whole decode step: advance, next mask rows, and those rows applied to `logits` in place.
         one_kernel: ask for the one-kernel form at any batch size (the library chooses by itself otherwise)."""
-        rows, words = bitmask.shape[:2]
-        assert tokens.is_contiguous() and bitmask.is_contiguous() and words == self.words
-        assert logits.dim() == 2 and logits.shape[0] == rows
+        shape = bitmask.shape
+        assert tokens.is_contiguous() and bitmask.is_contiguous() and shape[1] == self.words
+        assert logits.dim() == 2 and logits.shape[0] == shape[0]
         stride, one = logits.stride()
         assert one == 1
         # (a small batch's step takes the GPU 6 us, about what a call takes here: nothing is asked of torch twice)
@@ -373,9 +373,9 @@ class Pre3:
     def advance_fill_argmax(self, tokens, bitmask, logits, out_tokens, restart_on_eos=False, one_kernel=False, stream=None):
         """The whole greedy step: advance, next mask rows, and out_tokens[b] = arg max of the allowed logits of
         row b (the logits are only read; out_tokens may be `tokens`)."""
-        rows, words = bitmask.shape[:2]
-        assert tokens.is_contiguous() and bitmask.is_contiguous() and words == self.words and out_tokens.is_contiguous()
-        assert logits.dim() == 2 and logits.shape[0] == rows == out_tokens.numel()
+        shape = bitmask.shape
+        assert tokens.is_contiguous() and bitmask.is_contiguous() and shape[1] == self.words and out_tokens.is_contiguous()
+        assert logits.dim() == 2 and logits.shape[0] == shape[0] == out_tokens.numel()
         stride, one = logits.stride()
         assert one == 1
         rc = self._lib.pre3_advance_fill_argmax(self._h, _dev(tokens, "i32"), _dev(bitmask, "u32"), _dev(logits, "u16"), stride,
