@@ -67,7 +67,8 @@ def test_plain_c_program_matches_the_oracle(tmp_path):
 
 def test_device_timestamps_follow_stream_order_and_time_a_kernel():
     """pre3_debug_timestamp: stamps recorded around a masking launch, eagerly and inside a captured graph,
-    increase in stream order, and the launch they bracket takes a plausible time (the clock runs at 100 MHz)."""
+    increase in stream order, and inside the graph the launch they bracket takes a plausible time (the clock runs at 100 MHz).
+    Eager stamps are as far apart as the host launches them: the first two of a process 40 us, more than stamp, launch, stamp."""
     import torch
     from paper_2506_03887_amd import apply_mask
     from paper_2506_03887_amd.binding import Pre3Error, device_timestamp, load
@@ -93,7 +94,6 @@ def test_device_timestamps_follow_stream_order_and_time_a_kernel():
     torch.cuda.synchronize()
     t = stamps.cpu().numpy()
     assert (np.diff(t[:3]) > 0).all() and (np.diff(t[3:]) > 0).all() and t[3] > t[2], t
-    for first in (0, 3):
-        launch_us = ((t[first + 2] - t[first + 1]) - (t[first + 1] - t[first])) * 0.01
-        assert -2.0 < launch_us < 200.0, (first, launch_us, t)
+    launch_us = ((t[5] - t[4]) - (t[4] - t[3])) * 0.01
+    assert -2.0 < launch_us < 200.0, (launch_us, t)
     assert load().pre3_debug_timestamp(None, None) < 0          # a null pointer is refused, nothing is launched
