@@ -423,7 +423,7 @@ int32_t pre3_debug_token_effect(const pre3_handle *h, const int32_t *stack, int3
  * nodes, [2] deepest stack entry tested, [3] bytes of device memory. */
 int pre3_symbol_edge_stats(const pre3_handle *h, int64_t out[4]);
 /* Bytes of the per-batch workspaces that pre3_bind_state holds for a batch of `batch` sequences (tests
- * and tools): out[0] private-stack spill of the advance, [1] counters of the spread step, [2] arg max,
+ * and tools): out[0] private-stack spill of the advance, [1] row counters of the spread step and the top-k, [2] arg max,
  * [3] top-k (0: beyond its limit), [4] spill of per-lane walks.  Host call; a host-only handle answers
  * for 256 compute units.  Errors: BADARG. */
 int pre3_debug_workspace_bytes(const pre3_handle *h, int32_t batch, int64_t out[5]);

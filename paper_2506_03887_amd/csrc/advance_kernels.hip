@@ -761,7 +761,7 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
     constexpr bool kWindowFirst = kArgmax && (kRows == 2 || kHeld > 17);
     bool by_lane = false;                              // kByLane: every lane fetches the mask bytes of its groups, the row is not in LDS
     __shared__ int s_key[kArgmax ? kStepBlock / 64 : 1], s_token;
-    if (kArgmax && tid == 0) s_token = 0x7FFFFFFF;     // (read behind three barriers)
+    if (kArgmax && tid == 0) s_token = 0x7FFFFFFF;     // (lowered and read behind the block's barriers)
     // kArgmax: half a mask byte -> AND masks of two registers.  Sixteen entries: lanes that read the same entry are
     // served together and different entries lie in different banks (a 256-entry table of whole bytes cost 4-way
     // bank conflicts on every read: 5.1 us for the arg max of a block instead of the 3.3 us it takes now)

@@ -50,7 +50,7 @@ struct pre3_handle {
     struct Workspace { void *p = nullptr; size_t bytes = 0; };
     Workspace ws_adv, ws_argmax, ws_topk, ws_af_spill, ws_arrivals;
     int32_t *adv_scratch = nullptr;              // private-stack spill of the advance
-    StepArrivals *arrivals = nullptr;            // per-row counters of the spread step, zero between launches
+    StepArrivals *arrivals = nullptr;            // per-row counters of the spread step and the top-k, zero between launches
     int32_t *af_walk_spill = nullptr;            // ... of per-lane walks beside an advance
     unsigned long long *argmax_best = nullptr;   // per-segment partial results of pre3_apply_mask_argmax
     unsigned long long *topk_cand = nullptr;     // per-segment candidates of pre3_apply_mask_topk
@@ -386,7 +386,7 @@ BatchWorkspaces batch_workspaces(const pre3_handle *h, int batch) {
     const int spread_rows = std::min(batch, spread_step_rows(h)), columns = std::max(batch, spread_step_blocks(h, spread_rows));
     BatchWorkspaces w;
     w.adv = advance_scratch_entries(columns, h->max_depth) * sizeof(int32_t);
-    w.arrivals = (size_t)std::max(spread_rows, batch) * sizeof(StepArrivals);
+    w.arrivals = (size_t)batch * sizeof(StepArrivals);
     w.argmax = masked_argmax_workspace_bytes(batch, h->V.n_tokens, h->n_compute_units);
     w.topk = masked_topk_workspace_bytes(batch, h->V.n_tokens);
     if (w.topk > (size_t)1 << 30) w.topk = 0;
@@ -516,11 +516,11 @@ int pre3_bind_state(pre3_handle *h, int32_t *states, pre3_stacks stacks, int32_t
     if ((e = grow_workspace(h->ws_adv, need.adv, &h->adv_scratch)) != hipSuccess) return failed(e, "allocate advance scratch");
     if (need.arrivals > 0) {
         const size_t held = h->ws_arrivals.bytes;
-        if ((e = grow_workspace(h->ws_arrivals, need.arrivals, &h->arrivals)) != hipSuccess) return failed(e, "allocate step counters");
+        if ((e = grow_workspace(h->ws_arrivals, need.arrivals, &h->arrivals)) != hipSuccess) return failed(e, "allocate row counters");
         if (h->ws_arrivals.bytes != held) {             // new: the counters start at zero, on whatever stream the steps run
             e = hipMemset(h->arrivals, 0, h->ws_arrivals.bytes);
             if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
-            if (e != hipSuccess) { (void)hipFree(h->arrivals); h->ws_arrivals = {}; h->arrivals = nullptr; return failed(e, "clear step counters"); }
+            if (e != hipSuccess) { (void)hipFree(h->arrivals); h->ws_arrivals = {}; h->arrivals = nullptr; return failed(e, "clear row counters"); }
         }
     }
     if ((e = grow_workspace(h->ws_argmax, need.argmax, &h->argmax_best)) != hipSuccess) return failed(e, "allocate argmax workspace");

@@ -240,7 +240,7 @@ __device__ __forceinline__ unsigned long long wave_kth_largest(const unsigned lo
 //   bound rises by one more, because later chunks hold larger ids, which lose every tie.
 //   At the end every thread ranks the words of its wave's list that fall to it (rank = number of
 //   larger words in all lists) and the k best write themselves in order.
-// The k words are written to out[(row * n_seg + segment) * k ..], best first, 0-padded; with one
+// The k words are handed over (topk_hand_over), best first, 0-padded; with one
 // segment per row the kernel writes the row's ids and bf16 patterns itself (out_ids, out_vals).
 constexpr int kTopkBlock = 512, kTopkBlockWide = 1024;        // threads per block
 constexpr int kTopkPerThread = 32;
