@@ -131,9 +131,11 @@ def test_topk_of_rows_kept_in_registers(V, B):
         assert len(bad) == 0, (k, bad[:4].tolist())
 
 
-@pytest.mark.parametrize("V,B", [(131_080, 300), (147_457, 4), (163_839, 40), (163_840, 4), (163_841, 17), (163_848, 48), (262_147, 33)])
+@pytest.mark.parametrize("V,B", [(131_080, 300), (147_457, 4), (163_839, 40), (163_840, 4), (163_841, 17), (163_848, 48), (262_147, 33),
+                                  (131_080, 29), (163_840, 26), (163_840, 300)])
 def test_topk_of_rows_at_the_longest_variant(V, B):
-    """One block of twenty groups per row (an aligned row, four rows or more), or several blocks."""
+    """One block of twenty groups per row (aligned rows of more than 131,072 tokens whose narrow blocks would pass the compute units),
+    or several blocks."""
     test_topk_of_rows_kept_in_registers(V, B)
 
 

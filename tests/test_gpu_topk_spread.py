@@ -11,13 +11,14 @@ from workloads.vocab import Vocab, bf16_logits
 @pytest.mark.gpu
 @pytest.mark.parametrize("V,B,pad,offset", [(114_689, 4, 7, 0), (128_256, 1, 0, 0), (131_072, 16, 0, 5), (131_073, 17, 0, 1), (131_073, 28, 7, 0),
                                             (152_064, 16, 0, 0), (152_064, 25, 0, 0), (163_840, 16, 3, 3), (180_225, 14, 0, 0),
-                                            (262_149, 40, 0, 0)])
+                                            (262_149, 40, 0, 0), (262_149, 4, 3, 0), (262_145, 15, 0, 0), (400_000, 3, 0, 0), (600_000, 2, 0, 0)])
 def test_blocks_that_hand_over(V, B, pad, offset):
     import torch
     from test_gpu_argmax import _bound_lib
     dev, rng, W, stride = torch.device("cuda:0"), np.random.default_rng(V + B), (V + 31) // 32, V + pad
     lib = _bound_lib(Vocab([bytes([97 + i % 5]) for i in range(V - 1)] + [b""], V - 1), B)
     graph, static = None, None
+    longest = min(64 if B % 2 else 50, 1024 // -(-V // 16_384))             # (more than 16 blocks hand over k words each, others 64)
     for turn in range(4):
         host = bf16_logits(rng, B, stride)
         mask = rng.integers(0, 2 ** 32, size=(B, W), dtype=np.uint64).astype(np.uint32)
@@ -43,12 +44,12 @@ def test_blocks_that_hand_over(V, B, pad, offset):
             static = flat[offset:].view(B, stride), torch.zeros((B, W), dtype=torch.int32, device=dev)
         static[0].copy_(torch.from_numpy(host.view(np.int16)).to(dev))
         static[1].copy_(torch.from_numpy(mask.view(np.int32)).to(dev))
-        for k in (1, 50):
+        for k in (1, longest):
             ids, vals = torch.empty((B, k), dtype=torch.int32, device=dev), torch.empty((B, k), dtype=torch.int16, device=dev)
             lib.apply_mask_topk(static[0].view(torch.bfloat16), static[1], ids, vals)
             want_ids, want_vals = masked_topk(host, mask, V, k)
             assert (ids.cpu().numpy() == want_ids).all() and (vals.cpu().numpy().view(np.uint16) == want_vals).all(), (turn, k)
-        if graph is None:                               # k = 50, recorded once and replayed on the later turns' inputs
+        if graph is None:                               # the longest list, recorded once and replayed on the later turns' inputs
             g_ids, g_vals = torch.empty_like(ids), torch.empty_like(vals)
             graph = torch.cuda.CUDAGraph()
             with torch.cuda.graph(graph):

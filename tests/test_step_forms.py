@@ -92,7 +92,7 @@ def test_a_smaller_batch_never_needs_a_larger_workspace(V, compact):
     for b, h in zip(sizes, held):                       # enough for the batch in whichever form it runs
         blocks = b * seg if b * seg <= 1024 else 0
         assert h["advance_spill"] >= 4 * deep * max(b, blocks) and h["walk_spill"] >= 4 * deep * 64 * max(b, blocks)
-        assert h["step_counters"] >= 16 * (b if blocks else 0) and h["argmax"] >= 8 * b
+        assert h["step_counters"] >= 24 * b and h["argmax"] >= 8 * b         # (the top-k counts the blocks of every bound row)
 
 
 @pytest.mark.gpu
