@@ -59,6 +59,7 @@ constexpr int kTopkMax = 64;
 bool masked_topk_fits(int vocab, int k);      // (chunks of 16,384 tokens) x k <= 1,024 candidates per row
 size_t masked_topk_workspace_bytes(int batch, int vocab);
 int masked_topk_groups(int vocab, int batch, bool aligned, int n_compute_units);   // groups of 8 logits per thread of its blocks
+bool masked_topk_merged_apart(int batch, int n_seg, int n_compute_units);
 hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,
                               int k, int n_compute_units, unsigned long long *workspace, StepArrivals *arrivals /* batch, all zero */,
                               int32_t *out_ids, uint16_t *out_vals, hipStream_t stream);

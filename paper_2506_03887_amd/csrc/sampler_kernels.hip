@@ -987,18 +987,21 @@ __device__ __forceinline__ void topk_merge(const unsigned long long *__restrict_
     topk_rank<kBlock>(s_words, n, k, tid, put);
 }
 
+__device__ __forceinline__ int topk_width(int n_seg, int k) { return n_seg * kTopkMax <= kTopkMergeMax ? kTopkMax : k; }
+
 // A row per blockIdx.x, a segment per blockIdx.y (kSeveral: of more than one).  The blocks of a row that has several count
 // themselves in when what they hand over has arrived; the last one merges, and sets the count back to zero for the next
-// launch.  No block waits for another.
+// launch.  No block waits for another.  (arrivals null: masked_topk_merge_kernel merges, in a launch of its own.)
 template <int kBlock, int kG, bool kSeveral>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void masked_topk_row_kernel(
     const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
     int n_words, int k, unsigned long long *__restrict__ workspace, int32_t *__restrict__ out_ids,
     uint16_t *__restrict__ out_vals, StepArrivals *__restrict__ arrivals) {
     const int b = blockIdx.x, seg = kSeveral ? blockIdx.y : 0, n_seg = kSeveral ? gridDim.y : 1, tid = threadIdx.x;
-    const int width = n_seg * kTopkMax <= kTopkMergeMax ? kTopkMax : k;
+    const int width = topk_width(n_seg, k);
     topk_segment<kBlock, kG, kSeveral>(logits, bitmask, vocab, row_stride, n_words, k, workspace, out_ids, out_vals, b, seg, n_seg, width, tid);
     if constexpr (kSeveral) {
+        if (arrivals == nullptr) return;
         __shared__ int s_last;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this wave's candidates are where the other XCDs see them ...
         __syncthreads();                                           // ... and those of the block's other waves
@@ -1008,6 +1011,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         if (tid == 0) atomicExch(&arrivals[b].listed, 0u);
         topk_merge<kBlock>(workspace, n_seg, width, k, logits + (size_t)b * row_stride, out_ids, out_vals, b, tid);
     }
+}
+__global__ __launch_bounds__(kTopkBlock) void masked_topk_merge_kernel(
+    const unsigned long long *__restrict__ workspace, int n_seg, int k, const uint16_t *__restrict__ logits, int64_t row_stride,
+    int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_vals) {
+    const int b = blockIdx.x;
+    topk_merge<kTopkBlock>(workspace, n_seg, topk_width(n_seg, k), k, logits + (size_t)b * row_stride, out_ids, out_vals, b, threadIdx.x);
 }
 
 }  // namespace
@@ -1089,6 +1098,12 @@ int masked_topk_groups(int vocab, int batch, bool aligned, int n_compute_units) 
     return rounds(20) < rounds(shorter) ? 20 : shorter;
 }
 
+// A row's blocks are merged by a launch of their own where they are more than two rounds of the chip: the exchange is paid with every
+// round, a launch (2 to 3 us) once.  us per call, k = 50, merged by the last block and apart: 128 x 200,000 18.8 and 19.5, 256 x 200,000 32.3
+// and 32.6, 256 x 300,000 39.3 and 40.0, but 300 x 200,000 41.5 and 40.5, 400 x 200,000 51.7 and 49.6, 640 x 200,000 68.6 and 64.5, 400 x 300,000
+// 65.2 and 63.0, 300 x 500,000 71.7 and 67.8 (k = 33); 16 x 900,000 in narrow blocks 16.0 and 15.7, 16 x 500,000 10.8 and 11.2.
+bool masked_topk_merged_apart(int batch, int n_seg, int n_compute_units) { return batch * n_seg > 2 * n_compute_units; }
+
 hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, int batch, int vocab, int64_t row_stride,
                               int k, int n_compute_units, unsigned long long *workspace, StepArrivals *arrivals, int32_t *out_ids,
                               uint16_t *out_vals, hipStream_t stream) {
@@ -1098,12 +1113,14 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     const bool aligned = (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && (row_stride & 7) == 0;
 #define PRE3_TOPK_ROW(BLOCK, GROUPS)                                                                                         \
     n_seg = masked_topk_chunks(vocab, BLOCK * GROUPS * 8);                                                                   \
+    apart = n_seg > 1 && masked_topk_merged_apart(batch, n_seg, n_compute_units);                                              \
     if (n_seg > 1) PRE3_TOPK_BLOCKS(BLOCK, GROUPS, true);                                                                    \
     else PRE3_TOPK_BLOCKS(BLOCK, GROUPS, false)
 #define PRE3_TOPK_BLOCKS(BLOCK, GROUPS, SEVERAL)                                                                             \
     hipLaunchKernelGGL((masked_topk_row_kernel<BLOCK, GROUPS, SEVERAL>), dim3(batch, n_seg), dim3(BLOCK), 0, stream, logits, bitmask, \
-                       vocab, row_stride, n_words, k, workspace, out_ids, out_vals, arrivals)
+                       vocab, row_stride, n_words, k, workspace, out_ids, out_vals, apart ? nullptr : arrivals)
     int n_seg = 1;
+    bool apart = false;
     switch (masked_topk_groups(vocab, batch, aligned, n_compute_units)) {
         case 4: PRE3_TOPK_ROW(kTopkBlock, 4); break;
         case 8: PRE3_TOPK_BLOCKS(kTopkBlockWide, 8, false); break;          // (always one block)
@@ -1113,6 +1130,9 @@ hipError_t launch_masked_topk(const uint16_t *logits, const uint32_t *bitmask, i
     }
 #undef PRE3_TOPK_BLOCKS
 #undef PRE3_TOPK_ROW
+    if (apart)
+        hipLaunchKernelGGL(masked_topk_merge_kernel, dim3(batch), dim3(kTopkBlock), 0, stream, workspace, n_seg, k, logits, row_stride, out_ids,
+                           out_vals);
     return hipGetLastError();
 }
 

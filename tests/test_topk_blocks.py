@@ -29,8 +29,16 @@ def test_lines_of_the_rule(V, batch, aligned, groups):
     assert _groups(V, batch, aligned) == groups
 
 
+def test_which_rows_are_merged_by_a_launch_of_their_own():
+    from paper_2506_03887_amd import load
+    rule = load()["_ZN4pre324masked_topk_merged_apartEiii"]
+    rule.restype, rule.argtypes = ctypes.c_bool, [ctypes.c_int] * 3
+    assert not rule(256, 2, 256) and rule(257, 2, 256) and not rule(31, 16, 256) and rule(31, 17, 256) and not rule(1, 62, 256)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("V,B,pad,offset", [(143_360, 3, 0, 0), (163_840, 3, 8, 0), (143_363, 5, 0, 1), (163_839, 33, 0, 0), (131_073, 129, 0, 3),
+@pytest.mark.parametrize("V,B,pad,offset", [(163_849, 256, 0, 0), (163_849, 257, 7, 0), (400_000, 31, 0, 0), (500_003, 130, 0, 1),
+                                            (143_360, 3, 0, 0), (163_840, 3, 8, 0), (143_363, 5, 0, 1), (163_839, 33, 0, 0), (131_073, 129, 0, 3),
                                             (262_149, 86, 3, 0), (262_149, 33, 0, 0)])
 def test_rows_of_either_form(V, B, pad, offset):
     """Rows with ties at the bound, few allowed tokens, the best in the last group of a block or in the rest of the row."""
@@ -55,7 +63,7 @@ def test_rows_of_either_form(V, B, pad, offset):
     view = flat[offset:].view(B, stride)
     view.copy_(torch.from_numpy(host.view(np.int16)).to(dev))
     mask_d = torch.from_numpy(mask.view(np.int32)).to(dev)
-    for k in (1, 50):
+    for k in (1, min(50, 1024 // -(-V // 16_384))):
         ids, vals = torch.empty((B, k), dtype=torch.int32, device=dev), torch.empty((B, k), dtype=torch.int16, device=dev)
         lib.apply_mask_topk(view.view(torch.bfloat16), mask_d, ids, vals)
         want_ids, want_vals = masked_topk(host, mask, V, k)
