@@ -1136,11 +1136,14 @@ __global__ __launch_bounds__(kStepBlock) __attribute__((amdgpu_waves_per_eu(4 * 
         } else if (!order_undecided(top)) {
             if (tid == 0) out_tokens[b] = s_token;
         } else {
+            if (by_lane) {                             // (the row a second time, in order: its mask from LDS: 8 steps of 256 x 128,256 zeros 625 us, 687 from memory)
+                const uint4 *src = reinterpret_cast<const uint4 *>(E.dense_rows) + (size_t)plan.dense * n_vec;
+                for (int w = tid; w < n_vec; w += kStepBlock) bits4[w] = src[w];
+                lds_barrier();
+            }
             const unsigned long long mine = argmax_block_max(
-                argmax_by_compare<kArgBlock>(lrow, [&](int g) {
-                    if (by_lane) return (E.dense_rows[(size_t)plan.dense * n_vec * 4 + (g >> 2)] >> ((g & 3) * 8)) & 0xFFu;
-                    return (uint32_t)reinterpret_cast<const uint8_t *>(bits4)[g];
-                }, 0, (T.n_tokens + 7) >> 3, T.n_tokens, tid), s_part, tid);
+                argmax_by_compare<kArgBlock>(lrow, [&](int g) { return (uint32_t)reinterpret_cast<const uint8_t *>(bits4)[g]; }, 0,
+                                          (T.n_tokens + 7) >> 3, T.n_tokens, tid), s_part, tid);
             if (tid == 0) out_tokens[b] = mine != 0ull ? (int32_t)(0xFFFFFFFFu - (uint32_t)mine) : -1;
         }
     }
