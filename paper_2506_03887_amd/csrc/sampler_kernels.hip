@@ -167,85 +167,13 @@ __device__ __forceinline__ uint32_t packed_min_u16(uint32_t a, uint32_t b) {
 // A candidate travels between the stages as the word  key << 21 | (0x1FFFFF - id)  (id < 2^21):
 // distinct words, larger = better value, then smaller id; 0 = no candidate.
 constexpr int kTopkIdBits = 21;
-constexpr int kTopkWordBits = 16 + kTopkIdBits;
 constexpr uint32_t kTopkIdMask = (1u << kTopkIdBits) - 1u;
 __device__ __forceinline__ unsigned long long topk_word(uint32_t key, uint32_t id) {
     return ((unsigned long long)key << kTopkIdBits) | (unsigned long long)(kTopkIdMask - id);
 }
 
-// Number of (lane, element) pairs for which pred(i) holds, by ballots (scalar population counts: no
-// LDS, no cross-lane data movement).
-template <int kPer, class Pred>
-__device__ __forceinline__ int wave_count(Pred pred) {
-    int c = 0;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) c += __popcll(__ballot(pred(i)));
-    return c;
-}
-
-// The largest threshold t (16 bits, found bit by bit from the top) that at least `want` of the
-// wave's keys reach; *reached = how many do.  want >= 1 and at least `want` keys are non-zero.
-template <int kPer, class KeyAt>
-__device__ __forceinline__ uint32_t wave_key_threshold(KeyAt key_at, int n_nonzero, int want, int *reached) {
-    uint32_t T = 0u;
-    int at_T = n_nonzero;
-    for (int bit = 15; bit >= 0 && at_T != want; --bit) {
-        const uint32_t t = T | (1u << bit);
-        const int c = wave_count<kPer>([&](int i) { return key_at(i) >= t; });
-        if (c >= want) { T = t; at_T = c; }
-    }
-    *reached = at_T;
-    return T == 0u ? 1u : T;                                  // want == n_nonzero: every candidate
-}
-
-// The kk-th largest of the S distinct non-zero words of an LDS list (1 <= kk <= S), found bit by bit
-// from the top by one wave; lane l looks at the words l, l + 64, ... (kept in registers when there
-// are at most 512 of them).  Words >= the result are the kk largest.
-__device__ __forceinline__ unsigned long long wave_kth_largest(const unsigned long long *list, int S, int kk, int lane) {
-    if (kk >= S) return 1ull;
-    constexpr int kRegs = 8;
-    unsigned long long r[kRegs];
-#pragma unroll
-    for (int i = 0; i < kRegs; ++i) r[i] = i * 64 + lane < S ? list[i * 64 + lane] : 0ull;
-    const bool in_regs = S <= 64 * kRegs;
-    unsigned long long prefix = 0ull;
-    for (int bit = kTopkWordBits - 1; bit >= 0; --bit) {
-        const unsigned long long t = prefix | (1ull << bit);
-        int c = 0;
-        if (in_regs) {
-#pragma unroll
-            for (int i = 0; i < kRegs; ++i)
-                if (i * 64 < S) c += __popcll(__ballot(r[i] >= t));
-        } else {
-            for (int r0 = 0; r0 < S; r0 += 64) c += __popcll(__ballot(r0 + lane < S && list[r0 + lane] >= t));
-        }
-        if (c >= kk) {
-            prefix = t;
-            if (c == kk) break;
-        }
-    }
-    return prefix;
-}
-
-// The k best candidates of one segment of one row (blockIdx.x = row, blockIdx.y = segment: a run of
-// chunks_per_seg chunks of kTopkChunk tokens, taken in order).  Of each chunk every thread keeps the
-// 16-bit keys of its 32 tokens in registers, two per register (0 = masked, NaN or beyond the
-// vocabulary), so the logits are read once; the loads of the next chunk are in flight meanwhile.
-//   From the per-thread maxima of the first chunk that holds candidates the block derives a lower
-//   bound M of the k-th largest key (at least k threads hold a key >= M), so only keys >= M can be
-//   among the k best: of every chunk a little more than k.  From then on the waves do not meet again
-//   until the end: each appends its keys >= M to a list of its own (kTopkRegion words of LDS).  A wave
-//   whose list runs full cuts it to its k best and from then on uses the key of its k-th as its bound
-//   (a wave's k-th best is a lower bound of the block's); after a chunk in which that happened the
-//   bound rises by one more, because later chunks hold larger ids, which lose every tie.
-//   At the end every thread ranks the words of its wave's list that fall to it (rank = number of
-//   larger words in all lists) and the k best write themselves in order.
-// The k words are handed over (topk_hand_over), best first, 0-padded; with one
-// segment per row the kernel writes the row's ids and bf16 patterns itself (out_ids, out_vals).
 constexpr int kTopkBlock = 512, kTopkBlockWide = 1024;        // threads per block
-constexpr int kTopkPerThread = 32;
-constexpr int kTopkChunk = kTopkPerThread * kTopkBlock;   // tokens per chunk (twice as many for the wide block)
-constexpr int kTopkRegion = 256;
+constexpr int kTopkChunk = 4 * 8 * kTopkBlock;                // tokens of a narrow block
 
 // Eight logits from t0 on, one 2-byte load each (the group that straddles the end of the vocabulary);
 // tokens beyond the vocabulary read as NaN.  A loop that
@@ -269,361 +197,10 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Cuts a wave's list (n > k words) to its k best, moved to the front; returns the key of the k-th.
-__device__ __noinline__ uint32_t topk_cut_list(unsigned long long *list, int n, int k, int lane) {
-    const unsigned long long thr = wave_kth_largest(list, n, k, lane);
-    int base = 0;
-    for (int r0 = 0; r0 < n; r0 += 64) {                      // all lanes read, then write: the ranges may overlap
-        const unsigned long long w = r0 + lane < n ? list[r0 + lane] : 0ull;
-        const bool take = w >= thr;
-        const unsigned long long mm = __ballot(take);
-        wave_exchange();
-        if (take) list[base + __popcll(mm & ((1ull << lane) - 1ull))] = w;
-        base += __popcll(mm);
-    }
-    wave_exchange();
-    return (uint32_t)(thr >> kTopkIdBits);
-}
-
 // What the blocks of a row hand to the one that merges them: kTopkMax words a block (512 bytes, lines of its own), of which those
 // behind its last candidate are zero.  Stored and loaded past the L2s: the blocks run on different XCDs.
 __device__ __forceinline__ void topk_hand_over(unsigned long long *workspace, int b, int seg, int n_seg, int i, unsigned long long word) {
     __hip_atomic_store(workspace + ((size_t)b * n_seg + seg) * kTopkMax + i, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <int kBlock>
-__device__ __forceinline__ void masked_topk_chunked(
-    const uint16_t *__restrict__ logits, const uint32_t *__restrict__ bitmask, int vocab, int64_t row_stride,
-    int n_words, int k, int chunks_per_seg, unsigned long long *__restrict__ out,
-    int32_t *__restrict__ out_ids, uint16_t *__restrict__ out_vals, int b, int seg, int n_seg) {
-    constexpr int kWaves = kBlock / 64, kChunk = kTopkPerThread * kBlock;
-    __shared__ unsigned long long s_list[kWaves * kTopkRegion];
-    __shared__ int s_nz[kWaves];
-    __shared__ uint32_t s_wbound[kWaves];
-    __shared__ int s_n[kWaves];
-    __shared__ uint2 s_expand[16];                            // half a mask byte -> AND masks of two of the group's registers
-    __shared__ unsigned long long s_short[kBlock];        // the few words left at the end, one per thread
-    __shared__ int s_total;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    mask_nibble_table_init(s_expand, tid);
-    const uint8_t *mrow = reinterpret_cast<const uint8_t *>(bitmask + (size_t)b * n_words);
-    const uint16_t *lrow = logits + (size_t)b * row_stride;
-    const int n_mask_bytes = n_words * 4;
-    // with one segment per row (out_ids given) the ranked words are the row's result and go out as ids and patterns
-    auto emit = [&](int rank, unsigned long long word) {
-        if (out_ids == nullptr) {
-            topk_hand_over(out, b, seg, n_seg, rank, word);
-        } else if (word != 0ull) {
-            const uint32_t id = kTopkIdMask - ((uint32_t)word & kTopkIdMask);
-            out_ids[(size_t)b * k + rank] = (int32_t)id;
-            if (out_vals) out_vals[(size_t)b * k + rank] = lrow[id];
-        } else {
-            out_ids[(size_t)b * k + rank] = -1;
-            if (out_vals) out_vals[(size_t)b * k + rank] = 0xFF80u;
-        }
-    };
-    const int n_chunks = (vocab + kChunk - 1) / kChunk;
-    const int c_begin = seg * chunks_per_seg;
-    const int c_end = c_begin + chunks_per_seg < n_chunks ? c_begin + chunks_per_seg : n_chunks;
-    // element e of a thread (0 .. 31) is token  chunk * kChunk + rel(e); its key is half (e & 1) of kp[e >> 1]
-    auto rel = [&](int e) { return (tid + (e >> 3) * kBlock) * 8 + (e & 7); };
-    unsigned long long *mylist = s_list + wave * kTopkRegion;
-    const unsigned long long lanes_below = (1ull << lane) - 1ull;
-    int n_mine = 0;                                           // length of the wave's list
-    uint32_t block_bound = 0u;                                // 0: no candidate seen yet; 1: every candidate (same in all waves)
-    uint32_t wave_bound = 0u;                                 // what the wave's own list has proved since
-    // The loads run ahead of the selection: while a chunk is worked on, the logits of the next one and
-    // the mask bytes of the one after it are in flight (a group's logits are only read when its mask
-    // byte is not 0, so the mask has to arrive one stage earlier).
-    auto load_mask = [&](int chunk, uint32_t (&m)[kTopkPerThread / 8]) {
-#pragma unroll
-        for (int g = 0; g < kTopkPerThread / 8; ++g) {
-            const int t0 = chunk * kChunk + (tid + g * kBlock) * 8;
-            m[g] = (chunk < c_end && t0 < vocab && (t0 >> 3) < n_mask_bytes) ? mrow[t0 >> 3] : 0u;
-        }
-    };
-    auto load_logits = [&](int chunk, const uint32_t (&m)[kTopkPerThread / 8], uint4 (&v)[kTopkPerThread / 8]) {
-        const uint16_t *p = lrow + (size_t)chunk * kChunk + (size_t)tid * 8;
-        if ((chunk + 1) * kChunk <= vocab) {                 // a whole chunk
-#pragma unroll
-            for (int g = 0; g < kTopkPerThread / 8; ++g) {
-                v[g] = make_uint4(0u, 0u, 0u, 0u);               // its mask zeroes the keys anyway
-                if (m[g] != 0u) v[g] = stream_load(p + g * kBlock * 8);
-            }
-            return;
-        }
-#pragma unroll
-        for (int g = 0; g < kTopkPerThread / 8; ++g) {
-            const int t0 = chunk * kChunk + (tid + g * kBlock) * 8;
-            v[g] = make_uint4(0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u, 0x7FC07FC0u);   // NaN: no candidate
-            if (m[g] != 0u) {
-                if (t0 + 8 <= vocab) v[g] = stream_load(lrow + (size_t)t0);
-                else v[g] = topk_load_last_group(lrow, t0, vocab);
-            }
-        }
-    };
-    uint32_t m[kTopkPerThread / 8], m_ahead[kTopkPerThread / 8];
-    uint4 v[kTopkPerThread / 8];
-    load_mask(c_begin, m);
-    load_mask(c_begin + 1, m_ahead);
-    load_logits(c_begin, m, v);
-    lds_barrier();                                            // s_expand
-    for (int chunk = c_begin; chunk < c_end; ++chunk) {
-        uint32_t kp[kTopkPerThread / 2];
-        // two keys per register with packed 16-bit arithmetic; the mask byte of a group expands to the
-        // four AND masks of its registers through a table in LDS
-        uint32_t best2 = 0u;
-#pragma unroll
-        for (int g = 0; g < kTopkPerThread / 8; ++g) {
-            const uint4 allow = expand_mask_byte(s_expand, m[g]);
-            const uint32_t x[4] = {v[g].x, v[g].y, v[g].z, v[g].w}, a[4] = {allow.x, allow.y, allow.z, allow.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                kp[g * 4 + j] = bf16_key_pair(x[j]) & a[j];
-                best2 = packed_max_u16(best2, kp[g * 4 + j]);
-            }
-        }
-        if ((best2 & 0xFFFFu) > kTopkKeyMax || (best2 >> 16) > kTopkKeyMax) {      // an allowed NaN: one half at a time
-            best2 = 0u;
-#pragma unroll
-            for (int g = 0; g < kTopkPerThread / 8; ++g) {
-                const uint32_t x[4] = {v[g].x, v[g].y, v[g].z, v[g].w};
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t lo = x[j] & 0xFFFFu, hi = x[j] >> 16;
-                    const bool ok_lo = ((m[g] >> (2 * j)) & 1u) && (lo & 0x7FFFu) <= 0x7F80u;
-                    const bool ok_hi = ((m[g] >> (2 * j + 1)) & 1u) && (hi & 0x7FFFu) <= 0x7F80u;
-                    kp[g * 4 + j] = (ok_lo ? bf16_key(lo) : 0u) | ((ok_hi ? bf16_key(hi) : 0u) << 16);
-                    best2 = packed_max_u16(best2, kp[g * 4 + j]);
-                }
-            }
-        }
-        const uint32_t best = (best2 & 0xFFFFu) > (best2 >> 16) ? (best2 & 0xFFFFu) : (best2 >> 16);
-#pragma unroll
-        for (int g = 0; g < kTopkPerThread / 8; ++g) m[g] = m_ahead[g];
-        if (chunk + 1 < c_end) load_logits(chunk + 1, m, v);
-        load_mask(chunk + 2, m_ahead);
-        if (block_bound <= 1u) {
-            // A lower bound of the k-th largest key from the threads' maxima: wave w takes the q_w-th
-            // largest of its 64 maxima, q_w = min(j, threads of w that hold a candidate), with the
-            // smallest j for which the q_w add up to k; the smallest of these is reached by at least k keys.
-            const int nz_wave = __popcll(__ballot(best != 0u));
-            if (lane == 0) s_nz[wave] = nz_wave;
-            lds_barrier();
-            int quota = 0, holders = 0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) holders += s_nz[w];
-            if (holders >= k) {
-                for (quota = 1; quota < 64; ++quota) {
-                    int sum = 0;
-#pragma unroll
-                    for (int w = 0; w < kWaves; ++w) sum += s_nz[w] < quota ? s_nz[w] : quota;
-                    if (sum >= k) break;
-                }
-            }
-            uint32_t mine = 0x10000u;                         // no candidate in this wave
-            if (nz_wave > 0) {
-                mine = 1u;                                    // fewer than k holders in the block: every candidate
-                if (quota > 0) {
-                    int reached;
-                    mine = wave_key_threshold<1>([&](int) { return best; }, nz_wave, nz_wave < quota ? nz_wave : quota, &reached);
-                }
-            }
-            if (lane == 0) s_wbound[wave] = mine;
-            lds_barrier();
-            uint32_t cb = 0x10000u;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) cb = s_wbound[w] < cb ? s_wbound[w] : cb;
-            if (cb != 0x10000u && cb > block_bound) block_bound = cb;
-        }
-        uint32_t bound = block_bound > wave_bound ? block_bound : wave_bound;
-        if (bound == 0u || !__any(best >= bound)) continue;
-        // The keys that reach the bound (few): every thread counts its own -- a saturating packed
-        // subtraction leaves a non-zero half where a key reaches it -- and notes in which register.
-        const uint32_t below = (bound - 1u) * 0x10001u;
-        uint32_t count2 = 0u, where2 = 0u;                    // per half: how many reach it, and the sum of their register numbers
-#pragma unroll
-        for (int i = 0; i < kTopkPerThread / 2; ++i) {
-            const uint32_t one = packed_min_u16(packed_sub_sat_u16(kp[i], below), 0x00010001u);
-            count2 += one;
-            where2 += one * (uint32_t)i;
-        }
-        const int mine = (int)((count2 & 0xFFFFu) + (count2 >> 16));      // 0 .. 32
-        const unsigned long long holders = __ballot(mine > 0);
-        int before = __popcll(holders & lanes_below), total = __popcll(holders);   // right when no thread holds several
-        if (__ballot(mine > 1) != 0ull) {
-            before = 0;
-            total = 0;
-#pragma unroll
-            for (int bit = 0; bit < 6; ++bit) {
-                const unsigned long long has = __ballot((mine >> bit) & 1);
-                before += __popcll(has & lanes_below) << bit;
-                total += __popcll(has) << bit;
-            }
-        }
-        if (n_mine + total <= kTopkRegion) {
-            int slot = n_mine + before;
-            if (mine == 1) {
-                // the usual case: the key is the thread's maximum, and the sum is its register
-                const int e = (count2 & 0xFFFFu) ? 2 * (int)(where2 & 0xFFFFu) : 2 * (int)(where2 >> 16) + 1;
-                mylist[slot] = topk_word(best, (uint32_t)(chunk * kChunk + rel(e)));
-            } else if (mine > 1) {
-#pragma unroll
-                for (int i = 0; i < kTopkPerThread / 2; ++i) {
-                    const uint32_t reach = packed_sub_sat_u16(kp[i], below);
-                    if (reach & 0xFFFFu) mylist[slot++] = topk_word(kp[i] & 0xFFFFu, (uint32_t)(chunk * kChunk + rel(2 * i)));
-                    if (reach >> 16) mylist[slot++] = topk_word(kp[i] >> 16, (uint32_t)(chunk * kChunk + rel(2 * i + 1)));
-                }
-            }
-            n_mine += total;
-            continue;
-        }
-        // the list may run full: element by element, with room made when it is needed
-        bool cut = false;
-        uint32_t last_kth = 0u;                               // key of the k-th word after the latest cut
-#pragma unroll
-        for (int e = 0; e < kTopkPerThread; ++e) {
-            const uint32_t key = (kp[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu;
-            bool take = key >= bound;
-            unsigned long long mm = __ballot(take);
-            if (mm == 0ull) continue;
-            if (n_mine + __popcll(mm) > kTopkRegion) {        // n_mine > k here: the cut leaves k words
-                last_kth = topk_cut_list(mylist, n_mine, k, lane);
-                n_mine = k;
-                wave_bound = last_kth > wave_bound ? last_kth : wave_bound;
-                bound = block_bound > wave_bound ? block_bound : wave_bound;
-                cut = true;
-                take = key >= bound;
-                mm = __ballot(take);
-            }
-            if (take) mylist[n_mine + __popcll(mm & lanes_below)] = topk_word(key, (uint32_t)(chunk * kChunk + rel(e)));
-            n_mine += __popcll(mm);
-        }
-        if (cut) {                                            // from the next chunk on ties with the k-th can be left out
-            if (n_mine > k) {
-                last_kth = topk_cut_list(mylist, n_mine, k, lane);
-                n_mine = k;
-            }
-            wave_bound = last_kth + 1u > wave_bound ? last_kth + 1u : wave_bound;
-        }
-    }
-    // The lists are complete.  If they hold many words, the same bound as above -- now from the
-    // maxima of the listed words each thread holds -- leaves little more than k of them, and every
-    // wave drops the rest of its list.  Then every thread ranks the words of its wave's list that fall
-    // to it against all lists (rank = number of larger words) and the k best write themselves in order.
-    if (lane == 0) s_n[wave] = n_mine;
-    lds_barrier();
-    int S = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) S += s_n[w];
-    if (tid >= S && tid < k) emit(tid, 0ull);
-    unsigned long long w[kTopkRegion / 64];
-#pragma unroll
-    for (int r = 0; r < kTopkRegion / 64; ++r) w[r] = r * 64 + lane < n_mine ? mylist[r * 64 + lane] : 0ull;
-    uint32_t cb = 1u;                                         // every listed word
-    if (S > 2 * k + 32) {                                     // the same in every thread
-        unsigned long long top = 0ull;
-#pragma unroll
-        for (int r = 0; r < kTopkRegion / 64; ++r) top = w[r] > top ? w[r] : top;
-        const uint32_t best = (uint32_t)(top >> kTopkIdBits);
-        const int nz_wave = __popcll(__ballot(best != 0u));
-        if (lane == 0) s_nz[wave] = nz_wave;
-        lds_barrier();
-        int quota = 0, holders = 0;
-#pragma unroll
-        for (int ww = 0; ww < kWaves; ++ww) holders += s_nz[ww];
-        if (holders >= k) {
-            for (quota = 1; quota < 64; ++quota) {
-                int sum = 0;
-#pragma unroll
-                for (int ww = 0; ww < kWaves; ++ww) sum += s_nz[ww] < quota ? s_nz[ww] : quota;
-                if (sum >= k) break;
-            }
-        }
-        uint32_t mine = 0x10000u;
-        if (nz_wave > 0) {
-            mine = 1u;
-            if (quota > 0) {
-                int reached;
-                mine = wave_key_threshold<1>([&](int) { return best; }, nz_wave, nz_wave < quota ? nz_wave : quota, &reached);
-            }
-        }
-        if (lane == 0) s_wbound[wave] = mine;
-        lds_barrier();
-        cb = 0x10000u;
-#pragma unroll
-        for (int ww = 0; ww < kWaves; ++ww) cb = s_wbound[ww] < cb ? s_wbound[ww] : cb;
-    }
-    {
-        // the words that reach it: counted, and if there are few, gathered in one short list, one word per thread
-        bool keep[kTopkRegion / 64];
-        int kept = 0;
-#pragma unroll
-        for (int r = 0; r < kTopkRegion / 64; ++r) {
-            keep[r] = w[r] != 0ull && (uint32_t)(w[r] >> kTopkIdBits) >= cb;
-            kept += __popcll(__ballot(keep[r]));
-        }
-        if (tid == 0) s_total = 0;
-        if (lane == 0) s_nz[wave] = kept;                     // (every wave has read the old values before the last barrier)
-        lds_barrier();
-        int S2 = 0;
-#pragma unroll
-        for (int ww = 0; ww < kWaves; ++ww) S2 += s_nz[ww];
-        if (S2 <= kBlock) {
-            int at = 0;
-            if (lane == 0 && kept > 0) at = atomicAdd(&s_total, kept);
-            at = __builtin_amdgcn_readfirstlane(at);
-#pragma unroll
-            for (int r = 0; r < kTopkRegion / 64; ++r) {
-                const unsigned long long mm = __ballot(keep[r]);
-                if (keep[r]) s_short[at + __popcll(mm & lanes_below)] = w[r];
-                at += __popcll(mm);
-            }
-            lds_barrier();
-            if (wave * 64 >= S2) return;
-            const unsigned long long mine = tid < S2 ? s_short[tid] : ~0ull;
-            int rank = 0;
-#pragma unroll 8
-            for (int j = 0; j < S2; ++j) rank += s_short[j] > mine ? 1 : 0;
-            if (tid < S2 && rank < k) emit(rank, mine);
-            return;
-        }
-        // many ties with the bound: the words stay where they are, every wave drops the others from its list
-        kept = 0;
-#pragma unroll
-        for (int r = 0; r < kTopkRegion / 64; ++r) {
-            const unsigned long long mm = __ballot(keep[r]);
-            if (keep[r]) mylist[kept + __popcll(mm & lanes_below)] = w[r];   // every word of the list is in a register by now
-            kept += __popcll(mm);
-        }
-        n_mine = kept;
-        if (lane == 0) s_n[wave] = n_mine;
-        lds_barrier();
-#pragma unroll
-        for (int r = 0; r < kTopkRegion / 64; ++r) w[r] = r * 64 + lane < n_mine ? mylist[r * 64 + lane] : 0ull;
-    }
-    if (n_mine == 0) return;
-    int rank[kTopkRegion / 64];
-#pragma unroll
-    for (int r = 0; r < kTopkRegion / 64; ++r) rank[r] = 0;
-    for (int ww = 0; ww < kWaves; ++ww) {
-        const unsigned long long *other = s_list + ww * kTopkRegion;
-        const int n_other = s_n[ww];
-        if (n_mine <= 64) {
-#pragma unroll 8
-            for (int j = 0; j < n_other; ++j) rank[0] += other[j] > w[0] ? 1 : 0;
-        } else {
-#pragma unroll 2
-            for (int j = 0; j < n_other; ++j) {
-                const unsigned long long o = other[j];
-#pragma unroll
-                for (int r = 0; r < kTopkRegion / 64; ++r) rank[r] += o > w[r] ? 1 : 0;
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kTopkRegion / 64; ++r)
-        if (r * 64 + lane < n_mine && rank[r] < k) emit(rank[r], w[r]);
 }
 
 // The stored bf16 pattern behind a key of bf16_key, or -1 for the key of zero, which -0 and +0 share.
@@ -651,8 +228,7 @@ __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
 // positive sign takes the maxima and (1) again on the keys of bf16_key (0xFFFF, the pattern of a negative NaN, becomes
 // 0 = no candidate) of the groups that have an allowed token; the registers keep the patterns.
 // Lists that would run full (hundreds of ties with the bound, or a dense row where the threads' maxima do not
-// say enough) are given up: the block then takes the row chunk by chunk with masked_topk_chunked, which has no
-// such limit.
+// say enough) are given up: the block then counts (topk_by_counts), which has no such limit.
 // Twenty groups per thread (163,840 tokens) is what the 128 vector registers hold without spills.
 // (14.6 us per launch at 256 x 128,256, k = 50, 4.8 TB/s; 15.4 us per call in a graph: 9.4 us until the row has arrived and is worked on, 0.8 for
 // the bound, 1.4 for the list, 0.7 for the ranks.  24.9 us before, with keys computed for every token, all sixteen
@@ -665,13 +241,6 @@ __device__ __forceinline__ int bf16_pattern_of_key(uint32_t key) {
 // microseconds apart, so the barrier gains nothing, and the looser bound doubles the list.)
 __device__ __forceinline__ uint32_t packed_max_i16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(PackedI16, a), __builtin_bit_cast(PackedI16, b)));
-}
-// The segment chunk by chunk, as a call (its registers stay apart from the row kernel's).
-template <int kBlock>
-__device__ __noinline__ void topk_in_chunks(const uint16_t *logits, const uint32_t *bitmask, int vocab, int64_t row_stride,
-                                            int n_words, int k, int chunks_per_seg, unsigned long long *workspace, int32_t *out_ids,
-                                            uint16_t *out_vals, int b, int seg, int n_seg) {
-    masked_topk_chunked<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, chunks_per_seg, workspace, out_ids, out_vals, b, seg, n_seg);
 }
 constexpr int kTopkRowTokens = 20 * 8 * kTopkBlockWide;        // longest row that one block keeps in registers
 constexpr int kTopkRowList = 512, kTopkRowGroupList = 256;
@@ -745,6 +314,227 @@ __device__ __forceinline__ void topk_put(int rank, unsigned long long word, int 
     if (out_vals) out_vals[(size_t)b * k + rank] = value;
 }
 
+// Of the threads' words (distinct, 0: none) those that reach the k-th largest of 128 maxima of neighbouring threads, to s_words;
+// returns how many.  The bound of topk_bound, of whole words, ids among them, for what that left: hundreds of words that tie
+// take longer to rank (a block's 365, 6 us) than to bound again.  s_words may be where the words came from.  Three barriers.
+template <int kBlock, int kPer>
+__device__ __forceinline__ int topk_cut(const unsigned long long (&c)[kPer], int k, unsigned long long *s_words, int tid) {
+    constexpr int kLanes = kBlock / kTopkMaxima;
+    __shared__ unsigned long long s_top[kTopkMaxima], s_least;
+    __shared__ int s_few;
+    const int lane = tid & 63, at = tid / kLanes, part = tid % kLanes;
+    unsigned long long top = 0ull;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) top = c[i] > top ? c[i] : top;
+#pragma unroll
+    for (int step = 1; step < kLanes; step *= 2) {
+        const unsigned long long other = shfl_xor_u64(top, step);
+        top = other > top ? other : top;
+    }
+    if (part == 0) s_top[at] = top;
+    if (tid == 0) { s_least = 0ull; s_few = 0; }
+    lds_barrier();
+    int larger = 0;
+#pragma unroll 4
+    for (int i = part; i < kTopkMaxima; i += kLanes) larger += s_top[i] > top ? 1 : 0;
+    larger = lanes_reduce<kLanes>(larger, [](int x, int y) { return x + y; });
+    if (part == 0 && larger == k - 1 && top != 0ull) s_least = top;      // (fewer than k maxima: every word stays)
+    lds_barrier();
+    const unsigned long long least = s_least;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const bool keep = c[i] != 0ull && c[i] >= least;
+        const unsigned long long m = __ballot(keep);
+        if (m == 0ull) continue;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&s_few, __popcll(m));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (keep) s_words[base + __popcll(m & ((1ull << lane) - 1ull))] = c[i];
+    }
+    lds_barrier();
+    return s_few;
+}
+
+// A segment's n listed words, the k best among them (behind a barrier): ranked to out_ids and out_vals, or, where the row has
+// several segments, to the workspace (topk_hand_over), unranked where they fit there; the block that merges ranks them.
+template <int kBlock, bool kSeveral>
+__device__ __forceinline__ void topk_hand_out(unsigned long long *s_cand, int n, int k, const uint16_t *__restrict__ row,
+                                              unsigned long long *__restrict__ workspace, int32_t *__restrict__ out_ids,
+                                              uint16_t *__restrict__ out_vals, int b, int seg, int n_seg, int width, int tid) {
+    auto emit = [&](int rank, unsigned long long word) {
+        if (kSeveral) topk_hand_over(workspace, b, seg, n_seg, rank, word);
+        else topk_put(rank, word, k, b, row, out_ids, out_vals);
+    };
+    auto nothing_behind = [&](int at) {                       // no candidates beyond those that are handed over
+        if (kSeveral && tid >= at && tid < width) topk_hand_over(workspace, b, seg, n_seg, tid, 0ull);
+    };
+    if (n > 2 * kTopkMaxima) {                                // (below that the ranking is the shorter: 200 words of 128,256 tokens 13.0 us, 14.2 cut first)
+        constexpr int kApart = kBlock / kTopkRowList;
+        const unsigned long long c[1] = {tid % kApart == 0 && tid / kApart < n ? s_cand[tid / kApart] : 0ull};
+        n = topk_cut<kBlock, 1>(c, k, s_cand, tid);
+    }
+    if (kSeveral && n <= width) {
+        if (tid < n) topk_hand_over(workspace, b, seg, n_seg, tid, s_cand[tid]);
+        nothing_behind(n);
+        return;
+    }
+    if (tid >= n && tid < k) emit(tid, 0ull);
+    topk_rank<kBlock>(s_cand, n, k, tid, emit);
+    nothing_behind(k);
+}
+
+// The k best of a segment in which more tokens reach `bound` (a key of bf16_key, 1 or more) than the lists hold: nearly always
+// ties with the bound, because a row has few values, or few that are not -inf.  The segment is read again, its keys stay in
+// registers, and the block counts how many reach a key: the bound, the next key, and by bisection from there, until they are
+// few enough to list or the k-th largest key is found.  Then the larger ones are listed and, because ids ascend by group, then by
+// thread, the first of its ties.  A call of its own: its registers stay apart from the row kernel's
+// (one to each kernel, which then knows where its LDS lies).
+// Bound by the latency of its rounds: the loads, two counts and one round of ties for the rows above.  It replaces a pass with lists
+// per wave that were cut to their k best whenever they ran full, a cut being 37 counts.  us per call, that pass and this: 16 x
+// 152,064 equal logits, k = 50, in narrow blocks 111 and 15.1 (in one block a row 100), k = 1 89 and 11.8; 20 tokens finite and the rest -inf, k = 1,
+// which one block a row need not come here for and takes 10.1, 86 and 12.8; 64 x 128,256 equal, one block a row, k = 50, 100 and
+// 29.4; 200 x 152,064 111 and 46.7.  Also the way of vocabularies below eight tokens.
+template <int kBlock, int kG, bool kSeveral>
+__device__ __noinline__ void topk_by_counts(const uint16_t *logits, const uint32_t *bitmask, int vocab, int64_t row_stride, int n_words, int k,
+                                            uint32_t bound, unsigned long long *workspace, int32_t *out_ids,
+                                            uint16_t *out_vals, int b, int seg, int n_seg, int width) {
+    constexpr int kWaves = kBlock / 64, kSegTokens = kBlock * kG * 8, kAhead = kG < 8 ? kG : 8;
+    constexpr int kCounts = 18;                               // the bound, the next key, sixteen halvings
+    __shared__ uint2 s_expand[16];
+    __shared__ int s_reach[kCounts], s_tied[kG][kWaves], s_n;
+    __shared__ unsigned long long s_cand[kTopkRowList];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned long long lanes_below = (1ull << lane) - 1ull;
+    const uint16_t *whole_row = logits + (size_t)b * row_stride;
+    const int first_token = seg * kSegTokens, n_tokens = min(vocab - first_token, kSegTokens), whole = n_tokens >> 3;
+    const uint8_t *mask_bytes = reinterpret_cast<const uint8_t *>(bitmask + (size_t)b * n_words + first_token / 32);
+    // (as in topk_segment; a row below eight tokens: sixteen bytes that are there, none of them looked at)
+    const uint16_t *lrow = vocab < 8 ? reinterpret_cast<const uint16_t *>(workspace) : whole_row + (whole > 0 ? first_token : max(first_token - 8, 0));
+    const uint32_t last_group = (uint32_t)max(whole - 1, 0) * 16u;
+    mask_nibble_table_init(s_expand, tid);
+    if (tid < kCounts) s_reach[tid] = 0;
+    if (tid == 0) s_n = 0;
+    lds_barrier();
+    // the keys, two to a register; 0: masked, NaN, behind the row
+    uint32_t kp[kG * 4], m[kG], packed[kG / 4];
+    auto keys = [](uint32_t x, uint32_t allow) {
+        const uint32_t key = bf16_key_pair(x), nan = packed_min_u16(packed_sub_sat_u16(key, kTopkKeyMax * 0x10001u), 0x00010001u);
+        return allow & packed_sub_sat_u16(key, nan * 0xFFFFu);                                             // (a positive NaN's key goes)
+    };
+#pragma unroll
+    for (int u = 0; u < kG; ++u) m[u] = mask_bytes[min(u * kBlock + tid, max(whole - 1, 0))];
+#pragma unroll
+    for (int i = 0; i < kG / 4; ++i) {
+        packed[i] = m[i * 4] | m[i * 4 + 1] << 8 | m[i * 4 + 2] << 16 | m[i * 4 + 3] << 24;
+        asm volatile("" : "+v"(packed[i]));
+    }
+    uint4 v[kG];
+    auto load_group = [&](int u) { v[u] = stream_load_at(lrow, min((uint32_t)tid * 16u + (uint32_t)(u * kBlock * 16), last_group)); };
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) load_group(u);
+#pragma unroll
+    for (int u = 0; u < kG; ++u) {
+        if (u + kAhead < kG) load_group(u + kAhead);
+        __builtin_amdgcn_sched_barrier(0);
+        const uint4 allow = expand_mask_byte(s_expand, u * kBlock + tid < whole ? (packed[u / 4] >> (8 * (u & 3))) & 0xFFu : 0u);
+        kp[u * 4] = keys(v[u].x, allow.x);
+        kp[u * 4 + 1] = keys(v[u].y, allow.y);
+        kp[u * 4 + 2] = keys(v[u].z, allow.z);
+        kp[u * 4 + 3] = keys(v[u].w, allow.w);
+        asm volatile("" : "+v"(kp[u * 4]), "+v"(kp[u * 4 + 1]), "+v"(kp[u * 4 + 2]), "+v"(kp[u * 4 + 3]));
+    }
+    if ((n_tokens & 7) != 0 && whole % kBlock == tid) {         // the last, partial group
+        const uint4 x = topk_load_last_group(whole_row, first_token + whole * 8, vocab), allow = expand_mask_byte(s_expand, mask_bytes[whole]);
+#pragma unroll
+        for (int u = 0; u < kG; ++u) {
+            if (u != whole / kBlock) continue;
+            kp[u * 4] = keys(x.x, allow.x);
+            kp[u * 4 + 1] = keys(x.y, allow.y);
+            kp[u * 4 + 2] = keys(x.z, allow.z);
+            kp[u * 4 + 3] = keys(x.w, allow.w);
+        }
+    }
+    auto count = [&](uint32_t key, int at) {                  // the segment's keys of at least `key`
+        const uint32_t below = (key - 1u) * 0x10001u;
+        uint32_t two = 0u;
+#pragma unroll
+        for (int i = 0; i < kG * 4; ++i) two += packed_min_u16(packed_sub_sat_u16(kp[i], below), 0x00010001u);
+        int sum = (int)((two & 0xFFFFu) + (two >> 16));
+        for (int step = 32; step > 0; step >>= 1) sum += __shfl_xor(sum, step);
+        if (lane == 0) atomicAdd(&s_reach[at], sum);
+        lds_barrier();
+        return __builtin_amdgcn_readfirstlane(s_reach[at]);
+    };
+    // lo: reached by `few` or more (unknown before the first count), hi: by n_hi, fewer than k
+    constexpr int kUnknown = 0x7FFFFFFF;
+    uint32_t lo = bound - 1u, hi = kTopkKeyMax + 1u, mid = bound;
+    int n_lo = kUnknown, n_hi = 0;
+    for (int at = 0; at < kCounts && n_lo > kTopkRowList && hi - lo > 1u; ++at) {
+        const int c = count(mid, at);
+        if (c >= k) { lo = mid; n_lo = c; }
+        else { hi = mid; n_hi = c; }
+        mid = at == 0 ? lo + 1u : lo + (hi - lo) / 2u;
+    }
+    const bool fits = n_lo <= kTopkRowList;
+    // (one token of a group at a time, in a loop: the code is fetched for the one call)
+    auto four = [&](int at) { return (unsigned long long)kp[at + 1] << 32 | kp[at]; };
+    const uint32_t least = fits ? lo : hi, below = (least - 1u) * 0x10001u;
+#pragma unroll
+    for (int u = 0; u < kG; ++u) {
+        uint32_t any = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) any |= packed_sub_sat_u16(kp[u * 4 + j], below);
+        if (any != 0u) {
+            const unsigned long long low = four(u * 4), high = four(u * 4 + 2);
+#pragma unroll 1
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t key = (uint32_t)((e < 4 ? low : high) >> (16 * (e & 3))) & 0xFFFFu;
+                if (key >= least) s_cand[atomicAdd(&s_n, 1)] = topk_word(key, (uint32_t)(first_token + (u * kBlock + tid) * 8 + e));
+            }
+        }
+    }
+    int n = fits ? n_lo : n_hi;
+    if (!fits && n_lo != kUnknown) {                           // ties of the k-th, group by group of all threads
+        const int want = k - n_hi;
+        int taken = 0;
+#pragma unroll
+        for (int u = 0; u < kG; ++u) {
+            if (taken >= want) continue;                       // (the same in every thread)
+            uint32_t others = 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) others += packed_min_u16(kp[u * 4 + j] ^ (lo * 0x10001u), 0x00010001u);
+            const int mine = 8 - (int)((others & 0xFFFFu) + (others >> 16));
+            int slot = taken, sum = 0;                         // ties of the lanes before, of the wave
+#pragma unroll
+            for (int bit = 0; bit < 4; ++bit) {
+                const unsigned long long has = __ballot((mine >> bit) & 1);
+                slot += __popcll(has & lanes_below) << bit;
+                sum += __popcll(has) << bit;
+            }
+            if (lane == 0) s_tied[u][wave] = sum;
+            lds_barrier();
+            int upto = lane < kWaves ? s_tied[u][lane] : 0;       // lane w: ties of the waves 0 .. w
+            upto += __builtin_amdgcn_mov_dpp(upto, 0x111, 0xF, 0xF, true);       // (row shifts by 1, 2, 4, 8)
+            upto += __builtin_amdgcn_mov_dpp(upto, 0x112, 0xF, 0xF, true);
+            upto += __builtin_amdgcn_mov_dpp(upto, 0x114, 0xF, 0xF, true);
+            upto += __builtin_amdgcn_mov_dpp(upto, 0x118, 0xF, 0xF, true);
+            if (wave > 0) slot += __builtin_amdgcn_readlane(upto, wave - 1);
+            taken += __builtin_amdgcn_readlane(upto, kWaves - 1);
+            if (mine != 0 && slot < want) {
+                const unsigned long long low = four(u * 4), high = four(u * 4 + 2);
+#pragma unroll 1
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t key = (uint32_t)((e < 4 ? low : high) >> (16 * (e & 3))) & 0xFFFFu;
+                    if (key == lo && slot < want) s_cand[n_hi + slot++] = topk_word(lo, (uint32_t)(first_token + (u * kBlock + tid) * 8 + e));
+                }
+            }
+        }
+        n = k;
+    }
+    lds_barrier();
+    topk_hand_out<kBlock, kSeveral>(s_cand, n, k, whole_row, workspace, out_ids, out_vals, b, seg, n_seg, width, tid);
+}
+
 // A row's segment: its k best to out_ids and out_vals, or, where the row has several, its candidates to the workspace
 // (topk_hand_over: `width` words, the k best of the segment among them).
 template <int kBlock, int kG, bool kSeveral>
@@ -754,7 +544,7 @@ __device__ __forceinline__ void topk_segment(
     uint16_t *__restrict__ out_vals, int b, int seg, int n_seg, int width, int tid) {
     constexpr int kWaves = kBlock / 64, kSegTokens = kBlock * kG * 8;
     constexpr int kAhead = kG < 8 ? kG : 8;                   // groups a thread has in flight
-    static_assert(kG % 4 == 0 && kSegTokens % (kTopkPerThread * kBlock) == 0, "mask words of four rounds at a time, whole chunks");
+    static_assert(kG % 4 == 0, "mask words of four rounds at a time");
     __shared__ uint32_t s_mask[kBlock * kG / 4];              // the mask row, for every wave the bytes of its groups
     __shared__ uint2 s_expand[16];                            // half a mask byte -> AND masks of two of the group's registers
     __shared__ __align__(16) uint32_t s_pub[2][kTopkMaxima];
@@ -765,7 +555,7 @@ __device__ __forceinline__ void topk_segment(
     __shared__ int s_count, s_groups;
     const int lane = tid & 63, wave = tid >> 6;
     if (kBlock == kTopkBlock && vocab < 8) {                  // not one group of eight logits that the loads below could take
-        topk_in_chunks<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, 1, workspace, out_ids, out_vals, b, 0, 1);
+        topk_by_counts<kBlock, kG, kSeveral>(logits, bitmask, vocab, row_stride, n_words, k, 1u, workspace, out_ids, out_vals, b, 0, 1, width);
         return;
     }
     const unsigned long long lanes_below = (1ull << lane) - 1ull;
@@ -856,16 +646,8 @@ __device__ __forceinline__ void topk_segment(
         if ((int)(int16_t)tail < 0) tail = 0u;
     }
     const uint32_t bound = kth != 0u ? kth : first != 0u ? 1u : 0u;      // fewer than k: every candidate
-    auto emit = [&](int rank, unsigned long long word) {
-        if (kSeveral) topk_hand_over(workspace, b, seg, n_seg, rank, word);
-        else topk_put(rank, word, k, b, whole_row, out_ids, out_vals);
-    };
-    auto nothing_behind = [&](int n) {                        // no candidates beyond the n that are handed over
-        if (kSeveral && tid >= n && tid < width) topk_hand_over(workspace, b, seg, n_seg, tid, 0ull);
-    };
     if (bound == 0u) {                                        // nothing is allowed (or only NaN)
-        if (kSeveral) nothing_behind(0);
-        else if (tid < k) emit(tid, 0ull);
+        topk_hand_out<kBlock, kSeveral>(s_cand, 0, k, whole_row, workspace, out_ids, out_vals, b, seg, n_seg, width, tid);
         return;
     }
     // (2) the groups that hold a value of at least `bound`, then the tokens
@@ -921,21 +703,12 @@ __device__ __forceinline__ void topk_segment(
     lds_barrier();
     const int n = s_count;
     if (n > kTopkRowList || n_groups > kTopkRowGroupList) {   // same in every thread
-        constexpr int kChunks = kSegTokens / (kTopkPerThread * kBlock);
-        topk_in_chunks<kBlock>(logits, bitmask, vocab, row_stride, n_words, k, kChunks, workspace, kSeveral ? nullptr : out_ids,
-                               out_vals, b, seg, n_seg);
-        nothing_behind(k);
-        return;
-    }
-    if (kSeveral && n <= width) {                             // the block that merges ranks them
-        if (tid < n) topk_hand_over(workspace, b, seg, n_seg, tid, s_cand[tid]);
-        nothing_behind(n);
+        topk_by_counts<kBlock, kG, kSeveral>(logits, bitmask, vocab, row_stride, n_words, k, bound + to_key, workspace, out_ids, out_vals, b, seg,
+                                             n_seg, width);
         return;
     }
     // (3) ranks
-    if (tid >= n && tid < k) emit(tid, 0ull);
-    topk_rank<kBlock>(s_cand, n, k, tid, emit);
-    nothing_behind(k);
+    topk_hand_out<kBlock, kSeveral>(s_cand, n, k, whole_row, workspace, out_ids, out_vals, b, seg, n_seg, width, tid);
 }
 
 // The k best of a row out of what its blocks handed over (n_cand <= kTopkMergeMax words, 0 = empty), by the last of them.  As
@@ -981,7 +754,8 @@ __device__ __forceinline__ void topk_merge(const unsigned long long *__restrict_
         if (keep) s_words[base + __popcll(m & ((1ull << lane) - 1ull))] = c[i];
     }
     lds_barrier();
-    const int n = s_count;
+    int n = s_count;
+    if (n > kTopkMaxima) n = topk_cut<kBlock, kPer>(c, k, s_words, tid);
     auto put = [&](int rank, unsigned long long word) { topk_put(rank, word, k, b, row, out_ids, out_vals); };
     if (tid >= n && tid < k) put(tid, 0ull);
     topk_rank<kBlock>(s_words, n, k, tid, put);

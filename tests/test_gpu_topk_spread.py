@@ -59,6 +59,27 @@ def test_blocks_that_hand_over(V, B, pad, offset):
         assert (g_ids.cpu().numpy() == want_ids).all() and (g_vals.cpu().numpy().view(np.uint16) == want_vals).all(), turn
 
 
+def _us_per_call(lib, logits, mask, k):
+    """Of apply_mask_topk on each of `logits` in turn, captured and replayed."""
+    import torch
+    ids, vals = (torch.empty((logits.shape[1], k), dtype=t, device=logits.device) for t in (torch.int32, torch.int16))
+    lib.apply_mask_topk(logits[0], mask, ids, vals)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for x in logits:
+            lib.apply_mask_topk(x, mask, ids, vals)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    times = []
+    for _ in range(9):
+        a.record()
+        for _ in range(8):
+            graph.replay()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / (8 * len(logits)))
+    return sorted(times)[4]
+
+
 @pytest.mark.gpu
 def test_time_of_the_longest_lists():
     """16 x 200,000: the 64 best take no more than 1.15 times as long as the 50 best (1.05; 1.24 and 1.54 where the words that blocks rank
@@ -70,23 +91,71 @@ def test_time_of_the_longest_lists():
     rng = torch.Generator(device=dev).manual_seed(1)
     logits = torch.randn((16, B, V), generator=rng, device=dev).to(torch.bfloat16)
     mask = torch.randint(-2 ** 31, 2 ** 31 - 1, (B, (V + 31) // 32), generator=rng, dtype=torch.int32, device=dev)
-    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    took = {}
-    for k in (50, 64):
-        ids, vals = torch.empty((B, k), dtype=torch.int32, device=dev), torch.empty((B, k), dtype=torch.int16, device=dev)
-        lib.apply_mask_topk(logits[0], mask, ids, vals)
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph):
-            for x in logits:
-                lib.apply_mask_topk(x, mask, ids, vals)
-        times = []
-        for _ in range(9):
-            a.record()
-            for _ in range(8):
-                graph.replay()
-            b.record()
-            b.synchronize()
-            times.append(a.elapsed_time(b) * 1e3 / (8 * len(logits)))
-        took[k] = sorted(times)[4]
+    took = {k: _us_per_call(lib, logits, mask, k) for k in (50, 64)}
     print(took)
     assert took[64] < 1.15 * took[50], took
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V,B", [(152_064, 16), (128_256, 16), (128_256, 64)])
+def test_time_of_rows_of_few_values(V, B):
+    """Twenty finite logits and the rest -inf, and equal logits: no more than six times as long as random ones (3.5 at most; 7 to 13 times
+    where blocks cut their full lists again and again)."""
+    import torch
+    from test_gpu_argmax import _bound_lib
+    dev = torch.device("cuda:0")
+    lib = _bound_lib(Vocab([bytes([97 + i % 5]) for i in range(V - 1)] + [b""], V - 1), B)
+    rng = torch.Generator(device=dev).manual_seed(1)
+    x = torch.randn((8, B, V), generator=rng, device=dev).to(torch.bfloat16)
+    mask = torch.randint(-2 ** 31, 2 ** 31 - 1, (B, (V + 31) // 32), generator=rng, dtype=torch.int32, device=dev)
+    few = torch.where(torch.rand(x.shape, generator=rng, device=dev) < 40 / V, x, torch.full_like(x, float("-inf")))
+    for k in (1, 50):
+        took = {name: _us_per_call(lib, y, mask, k) for name, y in (("random", x), ("few", few), ("equal", torch.ones_like(x)))}
+        print(k, took)
+        assert max(took.values()) < 6 * took["random"], (k, took)
+
+
+def _rows_of_few_values(rng, B, V):
+    """kind -> bf16 patterns [B, V]: more tokens reach the bound of a block than it lists."""
+    x = bf16_logits(rng, B, V)
+    kinds = {"random": x, "equal": np.full((B, V), 0x3F80, np.uint16), "zeros of both signs": np.where(rng.random((B, V)) < 0.5, 0, 0x8000).astype(np.uint16),
+             "two values": np.where(rng.random((B, V)) < 0.5, 0x3F80, 0xBF80).astype(np.uint16)}
+    filtered = np.full((B, V), 0xFF80, np.uint16)                    # a top-p filter's row: few finite values, the rest -inf
+    for b in range(B):
+        at = rng.choice(V, size=min(V, int(rng.integers(0, 40))), replace=False)
+        filtered[b, at] = x[b, at]
+    kinds["few finite"] = filtered
+    levels = np.array([0xC000, 0xBF80, 0x8000, 0x0000, 0x3F80, 0x4000, 0x4040], np.uint16)
+    kinds["levels"] = levels[np.clip(np.round(rng.normal(size=(B, V)) * 0.8 + 3), 0, 6).astype(np.int64)]
+    kinds["rising"] = np.broadcast_to((0x3F00 + np.arange(V) // 700).astype(np.uint16), (B, V)).copy()
+    nan = kinds["levels"].copy()                                     # NaN of both signs among them, and +inf
+    nan[:, ::5], nan[:, 1::7], nan[:, 3::911] = 0x7FC0, 0xFFC0, 0x7F80
+    kinds["levels and NaN"] = nan
+    return kinds
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V,B,offset", [(3, 5, 0), (9, 3, 1), (1_003, 4, 0), (16_384, 3, 0), (16_391, 40, 5), (65_536, 30, 0), (98_301, 70, 0),
+                                        (128_256, 16, 0), (128_256, 40, 3), (152_064, 25, 0), (152_064, 60, 0), (163_840, 26, 0), (163_845, 33, 1),
+                                        (262_149, 4, 0), (400_000, 40, 0)])
+def test_rows_of_few_values(V, B, offset):
+    """The lists of every form run full (blocks of four to twenty groups, one or several to a row): the oracle's tokens."""
+    import torch
+    from test_gpu_argmax import _bound_lib
+    dev, rng, W = torch.device("cuda:0"), np.random.default_rng(V + B), (V + 31) // 32
+    lib = _bound_lib(Vocab([bytes([97 + i % 5]) for i in range(V - 1)] + [b""], V - 1), B)
+    longest = min(64, 1024 // -(-V // 16_384))
+    for kind, host in _rows_of_few_values(rng, B, V).items():
+        mask = rng.integers(0, 2 ** 32, size=(B, W), dtype=np.uint64).astype(np.uint32)
+        mask[::3] |= rng.integers(0, 2 ** 32, size=(len(mask[::3]), W), dtype=np.uint64).astype(np.uint32)
+        mask[1::5] = 0xFFFFFFFF
+        mask[2, : W // 2] = 0
+        flat = torch.zeros(B * V + 8, dtype=torch.int16, device=dev)
+        view = flat[offset: offset + B * V].view(B, V)
+        view.copy_(torch.from_numpy(host.view(np.int16)).to(dev))
+        mask_d = torch.from_numpy(mask.view(np.int32)).to(dev)
+        for k in {1, min(50, longest), longest}:
+            ids, vals = torch.empty((B, k), dtype=torch.int32, device=dev), torch.empty((B, k), dtype=torch.int16, device=dev)
+            lib.apply_mask_topk(view.view(torch.bfloat16), mask_d, ids, vals)
+            want_ids, want_vals = masked_topk(np.ascontiguousarray(host), mask, V, k)
+            assert (ids.cpu().numpy() == want_ids).all() and (vals.cpu().numpy().view(np.uint16) == want_vals).all(), (kind, k)
