@@ -243,7 +243,7 @@ __device__ __forceinline__ uint32_t packed_max_i16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(PackedI16, a), __builtin_bit_cast(PackedI16, b)));
 }
 constexpr int kTopkRowTokens = 20 * 8 * kTopkBlockWide;        // longest row that one block keeps in registers
-constexpr int kTopkRowList = 512, kTopkRowGroupList = 256;
+constexpr int kTopkRowList = 512;
 constexpr int kTopkMaxima = 128;                   // thread maxima that give the bound
 static_assert(kTopkMax <= kTopkMaxima, "the k-th of them has to exist");
 
@@ -545,12 +545,16 @@ __device__ __forceinline__ void topk_segment(
     constexpr int kWaves = kBlock / 64, kSegTokens = kBlock * kG * 8;
     constexpr int kAhead = kG < 8 ? kG : 8;                   // groups a thread has in flight
     static_assert(kG % 4 == 0, "mask words of four rounds at a time");
+    // Groups listed.  A narrow block, whose part of a row holds fewer different values, lists as many as tokens: with 256, half-integers
+    // on 16 x 128,256, k = 64, were counted although the list holds them (19.2 us, 13.8).  The wide ones lose 0.3 % by it (top-50 steps
+    // of 256 x 128,256).
+    constexpr int kGroupList = kBlock == kTopkBlock ? kTopkRowList : kTopkRowList / 2;
     __shared__ uint32_t s_mask[kBlock * kG / 4];              // the mask row, for every wave the bytes of its groups
     __shared__ uint2 s_expand[16];                            // half a mask byte -> AND masks of two of the group's registers
     __shared__ __align__(16) uint32_t s_pub[2][kTopkMaxima];
     __shared__ uint32_t s_bound[2][2];
-    __shared__ uint4 s_group[kTopkRowGroupList];
-    __shared__ int s_group_at[kTopkRowGroupList];
+    __shared__ uint4 s_group[kGroupList];
+    __shared__ int s_group_at[kGroupList];
     __shared__ unsigned long long s_cand[kTopkRowList];
     __shared__ int s_count, s_groups;
     const int lane = tid & 63, wave = tid >> 6;
@@ -667,7 +671,7 @@ __device__ __forceinline__ void topk_segment(
         for (int u = 0; u < kG; ++u) {
             if (reach[u] == 0ull) continue;
             const int slot = slot0 + __popcll(reach[u] & lanes_below);
-            if (gmax[u] >= (int)bound && slot < kTopkRowGroupList) {
+            if (gmax[u] >= (int)bound && slot < kGroupList) {
                 s_group[slot] = make_uint4(kp[u * 4], kp[u * 4 + 1], kp[u * 4 + 2], kp[u * 4 + 3]);
                 s_group_at[slot] = tid + u * kBlock;
             }
@@ -680,7 +684,7 @@ __device__ __forceinline__ void topk_segment(
     }
     lds_barrier();
     const int n_groups = s_groups;                            // the same in every thread
-    if (n_groups <= kTopkRowGroupList) {
+    if (n_groups <= kGroupList) {
         const uint16_t *halves = reinterpret_cast<const uint16_t *>(s_group);
         for (int at0 = wave * 64; at0 < n_groups * 8; at0 += kBlock) {
             const int at = at0 + lane;
@@ -702,7 +706,7 @@ __device__ __forceinline__ void topk_segment(
     }
     lds_barrier();
     const int n = s_count;
-    if (n > kTopkRowList || n_groups > kTopkRowGroupList) {   // same in every thread
+    if (n > kTopkRowList || n_groups > kGroupList) {   // same in every thread
         topk_by_counts<kBlock, kG, kSeveral>(logits, bitmask, vocab, row_stride, n_words, k, bound + to_key, workspace, out_ids, out_vals, b, seg,
                                              n_seg, width);
         return;

@@ -127,6 +127,14 @@ def _rows_of_few_values(rng, B, V):
     kinds["few finite"] = filtered
     levels = np.array([0xC000, 0xBF80, 0x8000, 0x0000, 0x3F80, 0x4000, 0x4040], np.uint16)
     kinds["levels"] = levels[np.clip(np.round(rng.normal(size=(B, V)) * 0.8 + 3), 0, 6).astype(np.int64)]
+    halves = (np.round(rng.standard_normal((B, V)) * 2) / 2).astype(np.float32)      # a few hundred tie, each in a group of its own
+    kinds["half-integers"] = (halves.view(np.uint32) >> 16).astype(np.uint16)
+    if V >= 16_384:                                                  # as many ties as the lists of a block hold, one more, half as many
+        full = np.minimum(x | 0x8000, 0xBFFF).astype(np.uint16)
+        for b in range(B):
+            n = (512, 513, 256, 257, 511)[b % 5]
+            full[b, np.arange(n) * (16_384 // n)] = 0x4000
+        kinds["full lists"] = full
     kinds["rising"] = np.broadcast_to((0x3F00 + np.arange(V) // 700).astype(np.uint16), (B, V)).copy()
     nan = kinds["levels"].copy()                                     # NaN of both signs among them, and +inf
     nan[:, ::5], nan[:, 1::7], nan[:, 3::911] = 0x7FC0, 0xFFC0, 0x7F80
@@ -150,6 +158,8 @@ def test_rows_of_few_values(V, B, offset):
         mask[::3] |= rng.integers(0, 2 ** 32, size=(len(mask[::3]), W), dtype=np.uint64).astype(np.uint32)
         mask[1::5] = 0xFFFFFFFF
         mask[2, : W // 2] = 0
+        if kind == "full lists":
+            mask[:] = 0xFFFFFFFF
         flat = torch.zeros(B * V + 8, dtype=torch.int16, device=dev)
         view = flat[offset: offset + B * V].view(B, V)
         view.copy_(torch.from_numpy(host.view(np.int16)).to(dev))
